@@ -959,11 +959,17 @@ ps_status ps_debug_last_batch(ps_ctx* c, int32_t i, uint8_t* pool1_host, uint8_t
     }
     PS_HIP(c, hipStreamSynchronize(s));
     if (pool1_host) {
-        // pool1 window bytes are kept as (winner's offset in a 30-wide image, gate in bit 7); the caller gets
-        // the documented form: bits 0-1 winner dy*2+dx, bit 2 gate
-        for (size_t i = 0; i < B * P1_SIZE; ++i) {
-            const uint8_t b = pool1_host[i], off = b & 0x7f;
-            pool1_host[i] = (uint8_t)((off & 1) | (off >= 30 ? 2 : 0) | ((b & AM1_GATE) ? 4 : 0));
+        // pool1 window bytes are kept [position][channel] as (winner's offset in a 30-wide image, gate in bit 7);
+        // the caller gets the documented form: [channel][position], bits 0-1 winner dy*2+dx, bit 2 gate
+        std::vector<uint8_t> image(P1_SIZE);
+        for (size_t s = 0; s < B; ++s) {
+            uint8_t* out = pool1_host + s * P1_SIZE;
+            std::copy(out, out + P1_SIZE, image.begin());
+            for (int p = 0; p < P1_POS; ++p)
+                for (int c = 0; c < C1; ++c) {
+                    const uint8_t b = image[p * C1 + c], off = b & 0x7f;
+                    out[c * P1_POS + p] = (uint8_t)((off & 1) | (off >= 30 ? 2 : 0) | ((b & AM1_GATE) ? 4 : 0));
+                }
         }
     }
     return PS_OK;

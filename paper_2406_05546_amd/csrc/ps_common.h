@@ -42,7 +42,7 @@ struct WorkerBuffers {
     const float* x;      // [n*B][784]
     const int32_t* y;    // [n*B]
     float* p1;           // [n*B][16][196]  conv1 -> ReLU -> pool
-    uint8_t* am1;        // [n*B][16][196]  bits 0-6 the window winner's offset dy*30 + dx in a 30-wide padded input
+    uint8_t* am1;        // [n*B][196][16]  bits 0-6 the window winner's offset dy*30 + dx in a 30-wide padded input
                          //                 image (0, 1, 30, 31), bit 7 winner > 0: what conv1's weight gradient needs
     float* p2;           // [n*B][32][49]
     uint8_t* am2;        // [n*B][32][49]
@@ -88,7 +88,7 @@ __device__ __forceinline__ float pool_first_max(float v0, float v1, float v2, fl
 constexpr int FC2_PART_B4 = NCLS * FC1, FC2_PART_B3 = FC2_PART_B4 + NCLS, FC2_PART_LOSS = FC2_PART_B3 + FC1,
               FC2_PART = 5648;
 int fc2_split(int n);  // blocks per worker of the fc2 kernel (one partial slot each)
-int conv1_part_slots(int batch);  // conv1 partial slots per worker (one per wavefront of conv2's input-gradient kernel)
+int conv1_part_slots(int batch);  // conv1 partial slots per worker (one per image, written by conv2's input-gradient kernel)
 
 void launch_conv1_fwd(const WorkerBuffers& wb, hipStream_t s);
 void launch_fc1_fwd(const WorkerBuffers& wb, hipStream_t s);

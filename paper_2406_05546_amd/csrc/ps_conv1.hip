@@ -7,9 +7,10 @@ namespace ps {
 
 namespace {
 
-// One (pooled position, output channel) pair: four 3x3 sums over the 4x4 input patch, pool, store.
-__device__ __forceinline__ void conv1_pair(const WorkerBuffers& wb, const float* __restrict__ ws, const float (&patch)[4][4],
-                                           size_t g, int pos, int o)
+// One (pooled position, output channel) pair: four 3x3 sums over the 4x4 input patch, pool, store; returns the
+// window byte.
+__device__ __forceinline__ uint32_t conv1_pair(const WorkerBuffers& wb, const float* __restrict__ ws, const float (&patch)[4][4],
+                                               size_t g, int pos, int o)
 {
     float k[9];
 #pragma unroll
@@ -33,9 +34,8 @@ __device__ __forceinline__ void conv1_pair(const WorkerBuffers& wb, const float*
     if (v[1] > best) { best = v[1]; off = 1; }
     if (v[2] > best) { best = v[2]; off = 30; }
     if (v[3] > best) { best = v[3]; off = 31; }
-    const size_t out = g * P1_SIZE + o * P1_POS + pos;
-    wb.p1[out] = fmaxf(best, 0.f);
-    wb.am1[out] = (uint8_t)(off | (best > 0.f ? AM1_GATE : 0));
+    wb.p1[g * P1_SIZE + o * P1_POS + pos] = fmaxf(best, 0.f);
+    return (uint32_t)(off | (best > 0.f ? AM1_GATE : 0));
 }
 
 // conv1 (1 -> 16, 3x3, pad 1) + ReLU + 2x2 max pool.  The kernel is bound by vector-ALU issue, and 196
@@ -86,10 +86,12 @@ __global__ __launch_bounds__(256) void conv1_fwd_kernel(WorkerBuffers wb, int bl
 #pragma unroll
             for (int b = 0; b < 4; ++b) patch[a][b] = xcur[(2 * py + a) * 30 + 2 * px + b];
         if (t < 192) {
+            uint32_t bytes[4] = {0u, 0u, 0u, 0u};  // the position's 16 window bytes, channel by channel
 #pragma unroll
-            for (int o = 0; o < C1; ++o) conv1_pair(wb, ws, patch, g, pos, o);
+            for (int o = 0; o < C1; ++o) bytes[o / 4] |= conv1_pair(wb, ws, patch, g, pos, o) << (8 * (o % 4));
+            *reinterpret_cast<uint4*>(wb.am1 + g * P1_SIZE + pos * C1) = make_uint4(bytes[0], bytes[1], bytes[2], bytes[3]);
         } else {
-            conv1_pair(wb, ws, patch, g, pos, t & 15);
+            wb.am1[g * P1_SIZE + pos * C1 + (t & 15)] = (uint8_t)conv1_pair(wb, ws, patch, g, pos, t & 15);
         }
     }
 }

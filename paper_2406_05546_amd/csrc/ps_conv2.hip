@@ -6,19 +6,18 @@
 // The 32x16x9 filter bank lives in registers for the whole block (72 VGPRs per lane) in exactly the
 // layout the MFMA B operand wants; it is read from the worker's ring slot once per block.
 #include "ps_common.h"
+#include "ps_split.h"
 
 namespace ps {
 
 namespace {
-
-typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 // LDS pitch (floats) of one padded 16x16 plane, chosen per kernel so that the 32 lanes an LDS read
 // serves per cycle fall into 32 different banks: the lane quarters of the forward A operand are four
 // channels over 8+8 window columns (pitch = 8 mod 32), those of the input-gradient A operand two
 // channels over 16 consecutive positions (pitch = 16 mod 32), and the weight-gradient operands put 16
 // channels on 16 lanes at 2 neighbouring positions (pitch = 2 mod 32).
-constexpr int CHS_FWD = 264, CHS_DX = 272, CHS_DW = 258;
+constexpr int CHS_FWD = 264, CHS_DW = 258;
 
 __device__ __forceinline__ floatx4 mfma16(float a, float b, floatx4 c)
 {
@@ -237,208 +236,192 @@ __global__ __launch_bounds__(FWD_NT, 512 / FWD_NT) void conv2_fwd_kernel(WorkerB
 
 // ---------------------------------------------------------------------------------------------
 // Input gradient of conv2 fused with the weight gradient of conv1.
-//   d pool1[c][y][x] = sum_{o,dy,dx} d2pad[o][y+2-dy][x+2-dx] * W2[o][c][dy][dx], zeroed where pool1 == 0.
-// GEMM rows are the 196 positions of an image (16 per tile), columns the 16 input channels,
-// K = (flipped tap, output channel) = 288.  The result never goes to memory: conv1 has no input
-// gradient, so each value is routed to its pool1 window's winner and multiplied right away with the
-// 3x3 neighbourhood of input pixels there,
+//   d pool1[c][Y][X] = sum_{o,dy,dx} d2pad[o][Y+2-dy][X+2-dx] * W2[o][c][dy][dx], zeroed where pool1 == 0.
+// On the bf16 matrix cores (ps_split.h, 16x16x32): GEMM rows are the 16 columns of a padded row of the 14x14
+// map, columns the 16 input channels, one k-step the 32 output channels of one tap.  A row of d2 is put
+// together in registers from the pooled gradients and the window winners, split once and used for all nine
+// taps: the three dx are the same operand moved by 0, 1, 2 lanes, the three dy go to the accumulators of
+// three output rows, which rotate.  The 9 x 3 operands of the filter bank stay in 108 registers.
+// The result never goes to memory: conv1 has no input gradient, so each value is routed to its pool1
+// window's winner and multiplied right away with the 3x3 neighbourhood of input pixels there,
 //   d W1[c][dy][dx] += d pool1[c][p] * xpad[winner(c,p) + (dy,dx)],   d b1[c] += d pool1[c][p],
-// on the vector ALU, which is idle while the matrix cores run.  A block owns up to DX_IPB images of
-// one worker and walks them DX_G at a time; each wavefront's conv1 sums go to its own partial slot.
-// DX_G images per group (between two block barriers), DX_NW wavefronts per block
-constexpr int DX_G = 1, DX_NW = 2, DX_NT = 64 * DX_NW, DX_IPB = 32;
-// The conv1 sums leave the registers every DX_FLUSH images, one partial slot per (DX_FLUSH images, wavefront),
-// whatever number of images a block owns (a multiple of DX_FLUSH): the order in which a worker's partial sums
-// are formed and added up then never depends on how the launch was cut into blocks.
-constexpr int DX_FLUSH = 8;
+// on the vector ALU.  A wavefront works on whole images by itself (no block barrier anywhere) and writes
+// one partial slot of conv1 sums per image, so that nothing depends on how a launch is cut up.
+// 65,536 images: 1.146 -> 0.600 ms against the fp32 MFMA kernel in two-wavefront blocks it replaced; two
+// workers of 32 images: 87 -> 17 us (a wavefront walked eight images there, now one).
+constexpr int DX_NW = 4, DX_NT = 64 * DX_NW, DX_IPW = 8;  // wavefronts per block, most images per wavefront
+constexpr int DX_XW = 30, DX_XS = 30 * DX_XW + 16;        // padded input image (and what lanes 14, 15 read past it)
 
-__global__ __launch_bounds__(DX_NT, 512 / DX_NT) void conv2_dx_kernel(WorkerBuffers wb, int blocks_per_worker, int ipb)
+struct DxImage {  // one wavefront's image
+    float dp2[P2_SIZE];            // gated pool2 gradient
+    uint32_t code[P2_SIZE / 4];    // window winners 0..3, bytes
+    uint8_t am1[P1_SIZE + 32];     // pool1 window bytes, [position][channel]
+    float xs[DX_XS];
+};
+
+// d pool1 of channel c at (Y, X) with fp32 FMAs: for sums the split cannot hold (see ps_split.h).
+__device__ __forceinline__ float conv2_dx_plain(const DxImage& im, const float* __restrict__ W2, int c, int Y, int X)
 {
-    constexpr int CHS = CHS_DX, D2_IMS = C2 * CHS;
-    __shared__ __attribute__((aligned(16))) float tile[DX_G * D2_IMS];  // 69,632 B
-    __shared__ __attribute__((aligned(16))) float xs[DX_G * 900];       // zero-padded 30x30 input images
-    // position of the group -> offset in the d2 planes; pooled position -> offset of its 2x2 window in
-    // the padded input image (looked up rather than computed: see the forward kernel)
-    __shared__ int a_off[DX_G * P1_POS];
-    __shared__ __attribute__((aligned(16))) int x_off[P1_POS];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, q = lane >> 4, l16 = lane & 15;
+    const uint8_t* code = reinterpret_cast<const uint8_t*>(im.code);
+    float sum = 0.f;
+#pragma unroll 1
+    for (int o = 0; o < C2; ++o)
+#pragma unroll 1
+        for (int t = 0; t < 9; ++t) {
+            const int y = Y + 1 - t / 3, x = X + 1 - t % 3;
+            float v = 0.f;
+            if (y >= 0 && y < P1_W && x >= 0 && x < P1_W) {
+                const int p = o * P2_POS + (y >> 1) * P2_W + (x >> 1);
+                v = code[p] == 2 * (y & 1) + (x & 1) ? im.dp2[p] : 0.f;
+            }
+            sum = fmaf(v, W2[(o * C1 + c) * 9 + t], sum);
+        }
+    return sum;
+}
+
+__global__ __launch_bounds__(DX_NT, 2) void conv2_dx_kernel(WorkerBuffers wb, int blocks_per_worker, int ipw)
+{
+    __shared__ __attribute__((aligned(16))) DxImage images[DX_NW];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, q = lane >> 4, l16 = lane & 15;
     const int w = blockIdx.x / blocks_per_worker, chunk = blockIdx.x % blocks_per_worker;
-    const int B = wb.B, s_begin = chunk * ipb, s_end = min(B, s_begin + ipb);
+    const int B = wb.B, s_begin = (chunk * DX_NW + wave) * ipw, s_end = min(B, s_begin + ipw);
+    if (s_begin >= s_end) return;
+    DxImage& im = images[wave];
     const float* __restrict__ W2 = worker_theta(wb, w) + OFF_W2;
 
-    // K = (output channel o, flipped tap t') = 288, four per MFMA step, one per lane quarter q.  A step's four
-    // are chosen so that its LDS reads need no address arithmetic and few bank conflicts: the 32 lanes an LDS
-    // read serves per cycle are two quarters, and two quarters that read the same plane in the same row (taps
-    // next to each other) touch 17 neighbouring addresses, which is conflict-free, whereas two different planes
-    // or two different rows always collide somewhere (16 positions of 14-wide rows in 16-wide planes span up
-    // to 20 banks).  Per output channel o:
-    //   step X_o: taps (0,0) (0,1) | (1,0) (1,1)     both halves conflict-free
-    //   step Y_o: taps (2,0) (2,1) | (0,2) (1,2)     first half conflict-free
-    // and per four channels one step Z with tap (2,2) of channels 4g .. 4g+3.  Every read is then
-    // lane base + o * plane pitch, an immediate offset, from one of three lane bases per tile.
-    // B operand: lane (q, l16) holds W2[o][c = l16][8 - t'] for its quarter's tap t'.
-    const int tx = q == 0 ? 0 : q == 1 ? 1 : q == 2 ? 3 : 4;   // flipped taps of step X
-    const int ty = q == 0 ? 6 : q == 1 ? 7 : q == 2 ? 2 : 5;   // and of step Y
-    float wx[32], wy[32], wz[8];
+    Split8 wt[9];  // lane (q, l16): W2[o = 8q + j][c = l16][tap]
 #pragma unroll
-    for (int o = 0; o < 32; ++o) {
-        wx[o] = W2[(o * C1 + l16) * 9 + 8 - tx];
-        wy[o] = W2[(o * C1 + l16) * 9 + 8 - ty];
+    for (int t = 0; t < 9; ++t) {
+        float v[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = W2[((8 * q + j) * C1 + l16) * 9 + t];
+        wt[t] = split8(v);
     }
-#pragma unroll
-    for (int g = 0; g < 8; ++g) wz[g] = W2[((4 * g + q) * C1 + l16) * 9];
+    for (int i = lane; i < DX_XS; i += 64) im.xs[i] = 0.f;  // the border stays zero
+    if (lane < 32) im.am1[P1_SIZE + lane] = 0;
 
-    for (int i = tid; i < DX_G * D2_IMS / 4; i += DX_NT)
-        reinterpret_cast<float4*>(tile)[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int i = tid; i < DX_G * 900; i += DX_NT) xs[i] = 0.f;
-    for (int i = tid; i < DX_G * P1_POS; i += DX_NT) {
-        const int img = i / P1_POS, pos = i % P1_POS;
-        a_off[i] = img * D2_IMS + (pos / P1_W) * 16 + pos % P1_W;
-        if (img == 0) x_off[pos] = 2 * (pos / P1_W) * 30 + 2 * (pos % P1_W);
-    }
-    __syncthreads();
+    // column l16 of the padded map is x = l16 - 1; columns 0 and 15 are border
+    const int x = l16 - 1;
+    const uint32_t want0 = (x >= 0 && x < P1_W) ? (uint32_t)(x & 1) : 0x100u;  // winner code of an even row at x; never for the border
+    const int d2_at = 8 * q * P2_POS + min(max(x >> 1, 0), P2_W - 1);
+    const uint32_t real = q == 3 ? 0u : ~0u;  // positions X = 4q + 2, 4q + 3 exist
 
-    // input pixels of a group: DX_G * 196 float4
-    constexpr int NX4 = DX_G * (IMG_PIX / 4), NXV = (NX4 + DX_NT - 1) / DX_NT;
-    float4 xv[NXV];
-    auto prefetch_x = [&](size_t g0, int valid) {
+    for (int s = s_begin; s < s_end; ++s) {
+        const size_t g = (size_t)w * B + s;
+        // pooled gradients and winners: 392 float4 and 98 uint4; pool1 window bytes and pixels: 196 of either
+        // (lanes past the end repeat the last one).  The other wavefront of the SIMD works meanwhile.
+        floatx4 pv[7], xv[4];
+        uintx4 pc[2], bv[4];
 #pragma unroll
-        for (int k = 0; k < NXV; ++k) {
-            const int i4 = tid + DX_NT * k;
-            xv[k] = (i4 < NX4 && i4 / (IMG_PIX / 4) < valid)
-                        ? *reinterpret_cast<const float4*>(wb.x + g0 * IMG_PIX + (size_t)i4 * 4)
-                        : make_float4(0.f, 0.f, 0.f, 0.f);
-        }
-    };
-    auto commit_x = [&]() {
+        for (int k = 0; k < 7; ++k)
+            pv[k] = reinterpret_cast<const floatx4*>(wb.dp2g + g * P2_SIZE)[min(lane + 64 * k, P2_SIZE / 4 - 1)];
 #pragma unroll
-        for (int k = 0; k < NXV; ++k) {
-            const int i4 = tid + DX_NT * k;
-            if (i4 >= NX4) break;
-            const int img = i4 / (IMG_PIX / 4), r = (i4 % (IMG_PIX / 4)) * 4;  // 28 % 4 == 0: one image row
-            float* dst = xs + img * 900 + (r / IMG_W + 1) * 30 + r % IMG_W + 1;
-            dst[0] = xv[k].x; dst[1] = xv[k].y; dst[2] = xv[k].z; dst[3] = xv[k].w;
+        for (int k = 0; k < 2; ++k)
+            pc[k] = reinterpret_cast<const uintx4*>(wb.am2 + g * P2_SIZE)[min(lane + 64 * k, P2_SIZE / 16 - 1)];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int i = min(lane + 64 * k, IMG_PIX / 4 - 1);
+            xv[k] = reinterpret_cast<const floatx4*>(wb.x + g * IMG_PIX)[i];
+            bv[k] = reinterpret_cast<const uintx4*>(wb.am1 + g * P1_SIZE)[i];
         }
-    };
+        wave_lds_fence();  // the last image has been read
+#pragma unroll
+        for (int k = 0; k < 7; ++k)
+            if (64 * (k + 1) <= P2_SIZE / 4 || lane + 64 * k < P2_SIZE / 4) reinterpret_cast<floatx4*>(im.dp2)[lane + 64 * k] = pv[k];
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+            if (64 * (k + 1) <= P2_SIZE / 16 || lane + 64 * k < P2_SIZE / 16)
+                reinterpret_cast<uintx4*>(im.code)[lane + 64 * k] = pc[k] & 0x03030303u;
+        wave_lds_fence();
 
-    float g1[9], gb1 = 0.f;  // this lane's share of d W1[l16][.] and d b1[l16]
+        float g1[9], gb1 = 0.f;  // this lane's share of d W1[l16][.] and d b1[l16]
 #pragma unroll
-    for (int i = 0; i < 9; ++i) g1[i] = 0.f;
+        for (int i = 0; i < 9; ++i) g1[i] = 0.f;
 
-    // lane parts of the three A-operand bases: tap offset (row * 16 + column) of the lane's quarter
-    const float* ax_lane = tile + (tx / 3) * 16 + tx % 3;
-    const float* ay_lane = tile + (ty / 3) * 16 + ty % 3;
-    const float* az_lane = tile + q * CHS + 2 * 16 + 2;
-    D2Stage<DX_G, CHS, DX_NT> stage;
-    stage.init(tid);
-    stage.prefetch(wb, (size_t)w * B + s_begin, min(DX_G, s_end - s_begin), tid);
-    prefetch_x((size_t)w * B + s_begin, min(DX_G, s_end - s_begin));
-    for (int s0 = s_begin; s0 < s_end; s0 += DX_G) {
-        const size_t g0 = (size_t)w * B + s0;
-        const int valid = min(DX_G, s_end - s0);
-        const int rot = s0 / DX_G;  // which wavefront takes the odd tile depends on the images, not on the block
-        stage.commit(tile, tid);
-        commit_x();
-        __syncthreads();
-        if (s0 + DX_G < s_end) {
-            stage.prefetch(wb, g0 + DX_G, min(DX_G, s_end - s0 - DX_G), tid);
-            prefetch_x(g0 + DX_G, min(DX_G, s_end - s0 - DX_G));
-        }
-        // Lane (q, l16) of tile t will hold channel l16 at positions 16t + 4q .. +3 (never straddling an image).
-        // Their pool1 window bytes (winner's offset in the padded input image, gate) are fetched one tile ahead;
-        // a position beyond the images of the group gets zero bytes, whose gate is shut, so the tile needs no
-        // branch.  The 36 input pixels of conv1's weight gradient are read in front of the matrix work and used
-        // behind it; the first A-operand values of the next tile are read during the current one, so that the
-        // matrix cores do not wait behind those 36 reads at the start of a tile (LDS reads return in order).
-        static_assert(DX_G <= 2, "image of a position is found with one comparison");
-        constexpr int N_TILES = (DX_G * P1_POS + 15) / 16, AHEAD = 4;  // A values of channels 0 .. AHEAD-1 read ahead
-        const uint8_t* am1_lane = wb.am1 + g0 * P1_SIZE + l16 * P1_POS + 4 * q;
-        auto window_bytes = [&](int t) -> uint32_t {
-            const int mo = 16 * t + 4 * q;  // position in the group; the second image starts P1_SIZE bytes after the first
-            return (t < N_TILES && mo < valid * P1_POS)
-                       ? *reinterpret_cast<const uint32_t*>(am1_lane + 16 * t + (mo >= P1_POS ? P1_SIZE - P1_POS : 0))
-                       : 0u;
-        };
-        auto a_base = [&](int t) -> int {
-            const int m = 16 * t + l16;  // lane row l16 = position 16t + l16 of the group (rows beyond it read position 0)
-            return a_off[m < DX_G * P1_POS ? m : 0];
-        };
-        const int t_first = (wave + rot) % DX_NW;
-        uint32_t win_next = window_bytes(t_first);
-        int at = a_base(t_first);
-        float ax_next[AHEAD], ay_next[AHEAD];
+        // conv1's gradient from d pool1 row Y: lane (q, l16) holds channel l16 at X = 4q .. 4q + 3
+        auto finish_row = [&](int Y, floatx4 acc) {
+            if (__any(__builtin_isunordered(acc[0], acc[1]) || __builtin_isunordered(acc[2], acc[3])))
 #pragma unroll
-        for (int o = 0; o < AHEAD; ++o) {
-            ax_next[o] = ax_lane[at + o * CHS];
-            ay_next[o] = ay_lane[at + o * CHS];
-        }
-        for (int t = t_first; t < N_TILES; t += DX_NW) {
-            const uint32_t win = win_next;
-            // the 3x3 input neighbourhoods at the four winners
-            const int mo = min(16 * t + 4 * q, DX_G * P1_POS - 4), img_o = mo >= P1_POS ? 1 : 0, pos_o = mo - img_o * P1_POS;
-            const float* ximg = xs + img_o * 900;
-            const int4 xo = *reinterpret_cast<const int4*>(x_off + pos_o);  // pos_o is a multiple of 4
-            const float* px[4] = {ximg + xo.x + (win & 0x7fu), ximg + xo.y + ((win >> 8) & 0x7fu),
-                                  ximg + xo.z + ((win >> 16) & 0x7fu), ximg + xo.w + ((win >> 24) & 0x7fu)};
-            float xr[36];
-#pragma unroll
-            for (int r = 0; r < 36; ++r) xr[r] = px[r / 9][((r % 9) / 3) * 30 + (r % 9) % 3];
-            win_next = window_bytes(t + DX_NW);
-            const float* ax = ax_lane + at;
-            const float* ay = ay_lane + at;
-            const float* az = az_lane + at;
-            const int at_next = a_base(min(t + DX_NW, N_TILES - 1));
-            floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int g = 0; g < 8; ++g) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int o = 4 * g + j;
-                    acc = mfma16(o < AHEAD ? ax_next[o] : ax[o * CHS], wx[o], acc);
-                    acc = mfma16(o < AHEAD ? ay_next[o] : ay[o * CHS], wy[o], acc);
-                }
-                acc = mfma16(az[4 * g * CHS], wz[g], acc);
-                if (g == 6) {  // the next tile's first reads: their operands above are consumed by now
-#pragma unroll
-                    for (int o = 0; o < AHEAD; ++o) {
-                        ax_next[o] = ax_lane[at_next + o * CHS];
-                        ay_next[o] = ay_lane[at_next + o * CHS];
-                    }
-                }
-            }
-            at = at_next;
+                for (int i = 0; i < 4; ++i) acc[i] = conv2_dx_plain(im, W2, l16, Y, 4 * q + i);
+            const uint8_t* bytes = im.am1 + (P1_W * Y + 4 * q) * C1 + l16;
+            const float* row = im.xs + 2 * Y * DX_XW + 8 * q;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                // gate bit -> all ones or zero
-                const uint32_t keep = (uint32_t)((int32_t)(win << (24 - 8 * i)) >> 31);
+                uint32_t b = bytes[C1 * i];
+                if (i >= 2) b &= real;
+                const float* px = row + 2 * i + (b & 0x7fu);
+                const uint32_t keep = (uint32_t)((int32_t)(b << 24) >> 31);  // gate bit -> all ones or zero
                 const float v = __uint_as_float(__float_as_uint(acc[i]) & keep);
                 gb1 += v;
 #pragma unroll
-                for (int k = 0; k < 9; ++k) g1[k] = fmaf(v, xr[9 * i + k], g1[k]);
+                for (int k = 0; k < 9; ++k) g1[k] = fmaf(v, px[(k / 3) * DX_XW + k % 3], g1[k]);
+            }
+        };
+
+        floatx4 acc[3];  // d pool1 rows y - 1, y, y + 1
+#pragma unroll
+        for (int i = 0; i < 3; ++i) acc[i] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+        for (int py = 0; py < P2_W; ++py) {
+            float v[8];
+            uint32_t code[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                v[j] = im.dp2[d2_at + j * P2_POS + py * P2_W];
+                code[j] = reinterpret_cast<const uint8_t*>(im.code)[d2_at + j * P2_POS + py * P2_W];
+            }
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {
+                const int y = 2 * py + r;
+                float d[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) d[j] = code[j] == want0 + 2 * r ? v[j] : 0.f;
+                const Split8 a0 = split8(d), a1 = lanes_up<1>(a0), a2 = lanes_up<2>(a0);
+                // row y of d2 is tap row dy of row y - 1 + dy of the result (row -1 does not exist)
+                const Split8* const moved[3] = {&a2, &a1, &a0};
+#pragma unroll
+                for (int dx = 0; dx < 3; ++dx) {
+                    if (r == 1 || py > 0)
+                        mfma_split<3>(*moved[dx], {&wt[dx], &wt[3 + dx], &wt[6 + dx]}, {&acc[0], &acc[1], &acc[2]});
+                    else
+                        mfma_split<2>(*moved[dx], {&wt[3 + dx], &wt[6 + dx]}, {&acc[1], &acc[2]});
+                }
+                if (y == 0) {  // the rest of the image, which row 0 of the result needs first
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        const int i = lane + 64 * k;
+                        if (64 * (k + 1) <= IMG_PIX / 4 || i < IMG_PIX / 4) {
+                            float* dst = im.xs + (4 * i / IMG_W + 1) * DX_XW + 4 * i % IMG_W + 1;  // 28 % 4 == 0: one image row
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) dst[e] = xv[k][e];
+                            reinterpret_cast<uintx4*>(im.am1)[i] = bv[k];
+                        }
+                    }
+                    wave_lds_fence();
+                } else {
+                    finish_row(y - 1, acc[0]);
+                }
+                acc[0] = acc[1];
+                acc[1] = acc[2];
+                acc[2] = floatx4{0.f, 0.f, 0.f, 0.f};
             }
         }
-        __syncthreads();
-        stage.clear(tile, tid);
-        if ((s0 + DX_G) % DX_FLUSH == 0 || s0 + DX_G >= s_end) {
-            // fold the four lane quarters; lanes of quarter 0 hold the wavefront's sums for channel l16
+        finish_row(P1_W - 1, acc[0]);
+
+        // fold the four lane quarters; lanes of quarter 0 hold the image's sums for channel l16
 #pragma unroll
-            for (int i = 0; i < 9; ++i) {
-                g1[i] += __shfl_xor(g1[i], 16, 64);
-                g1[i] += __shfl_xor(g1[i], 32, 64);
-            }
-            gb1 += __shfl_xor(gb1, 16, 64);
-            gb1 += __shfl_xor(gb1, 32, 64);
-            if (q == 0) {
-                float* part = wb.part1 + ((size_t)w * (DX_NW * ((B + DX_FLUSH - 1) / DX_FLUSH)) + (s0 / DX_FLUSH) * DX_NW + wave) * OFF_W2;
-#pragma unroll
-                for (int i = 0; i < 9; ++i) part[OFF_W1 + l16 * 9 + i] = g1[i];
-                part[OFF_B1 + l16] = gb1;
-            }
-#pragma unroll
-            for (int i = 0; i < 9; ++i) g1[i] = 0.f;
-            gb1 = 0.f;
+        for (int i = 0; i < 9; ++i) {
+            g1[i] += __shfl_xor(g1[i], 16, 64);
+            g1[i] += __shfl_xor(g1[i], 32, 64);
         }
-        __syncthreads();  // the planes are cleared by all threads, the next commit scatters into them
+        gb1 += __shfl_xor(gb1, 16, 64);
+        gb1 += __shfl_xor(gb1, 32, 64);
+        if (q == 0) {
+            float* part = wb.part1 + g * OFF_W2;
+#pragma unroll
+            for (int i = 0; i < 9; ++i) part[OFF_W1 + l16 * 9 + i] = g1[i];
+            part[OFF_B1 + l16] = gb1;
+        }
     }
 }
 
@@ -533,9 +516,7 @@ __global__ __launch_bounds__(256, 2) void conv2_dw_kernel(WorkerBuffers wb)
 
 }  // namespace
 
-// Images per block: as many as FWD_IPB / DX_IPB when the launch still gives every compute unit as many blocks
-// as fit it, else fewer (16, 8), so that a small launch does not leave part of the chip idle.
-static int images_per_block(int n, int batch, int most, int blocks_per_cu)
+static int compute_units()
 {
     static int cus = 0;
     if (cus == 0) {
@@ -543,8 +524,15 @@ static int images_per_block(int n, int batch, int most, int blocks_per_cu)
         if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
             cus = 256;
     }
+    return cus;
+}
+
+// Images per block: as many as FWD_IPB when the launch still gives every compute unit as many blocks as fit
+// it, else fewer (16, 8), so that a small launch does not leave part of the chip idle.
+static int images_per_block(int n, int batch, int most, int blocks_per_cu)
+{
     int ipb = most;
-    while (ipb > DX_FLUSH && n * ((batch + ipb - 1) / ipb) < blocks_per_cu * cus) ipb /= 2;
+    while (ipb > 8 && n * ((batch + ipb - 1) / ipb) < blocks_per_cu * compute_units()) ipb /= 2;
     return ipb;
 }
 
@@ -554,12 +542,16 @@ void launch_conv2_fwd(const WorkerBuffers& wb, hipStream_t s)
     hipLaunchKernelGGL(conv2_fwd_kernel, dim3(wb.n * bpw), dim3(FWD_NT), 0, s, wb, bpw, ipb);
 }
 
-int conv1_part_slots(int batch) { return DX_NW * ((batch + DX_FLUSH - 1) / DX_FLUSH); }
+int conv1_part_slots(int batch) { return batch; }
 
+// A wavefront walks as many images (up to DX_IPW) as leave two wavefronts for every SIMD: reading and
+// splitting the filter bank, once per wavefront, takes about a quarter of an image's time.
 void launch_conv2_dx(const WorkerBuffers& wb, hipStream_t s)
 {
-    const int ipb = images_per_block(wb.n, wb.B, DX_IPB, 512 / DX_NT), bpw = (wb.B + ipb - 1) / ipb;
-    hipLaunchKernelGGL(conv2_dx_kernel, dim3(wb.n * bpw), dim3(DX_NT), 0, s, wb, bpw, ipb);
+    int ipw = DX_IPW;
+    while (ipw > 1 && wb.n * ((wb.B + ipw - 1) / ipw) < 2 * 4 * compute_units()) ipw /= 2;
+    const int bpw = (wb.B + DX_NW * ipw - 1) / (DX_NW * ipw);
+    hipLaunchKernelGGL(conv2_dx_kernel, dim3(wb.n * bpw), dim3(DX_NT), 0, s, wb, bpw, ipw);
 }
 
 void launch_conv2_dw(const WorkerBuffers& wb, hipStream_t s)
