@@ -51,7 +51,7 @@ struct Carve {
 };
 
 struct Layout {
-    uint64_t theta, ring, queue, ada_g2, ada_dx2, meta, idx, slotq, st_state, st_stamp, st_entry, st_ringver, st_log, st_range, st_idx, st_wid, p1, am1, p2, am2, ht, z, pred, d3, dp2g, part, part1, fpart, normpart, scale, eval_loss, eval_ok, keep, total;
+    uint64_t theta, ring, queue, ada_g2, ada_dx2, meta, idx, slotq, st_state, st_stamp, st_entry, st_ringver, st_log, st_range, st_idx, st_wid, p1, am1, p2, am2, am2t, ht, z, pred, d3, dp2g, part, part1, fpart, normpart, scale, eval_loss, eval_ok, keep, total;
 };
 
 bool config_ok(const ps_config* c)
@@ -84,13 +84,14 @@ Layout make_layout(const ps_config& c)
     l.p1 = k.take(n * P1_SIZE * 4);
     l.am1 = k.take(n * P1_SIZE);
     l.p2 = k.take(n * P2_SIZE * 4);
-    l.am2 = k.take(n * P2_SIZE);
+    l.am2 = k.take(n * AM2_SIZE);
+    l.am2t = k.take(n * P2_SIZE);
     l.ht = k.take(n * FC1 * 4);
     l.z = k.take(n * NCLS * 4);
     l.pred = k.take(n * 4);
     l.d3 = k.take(n * FC1 * 4);
-    l.dp2g = k.take(n * P2_SIZE * 4);
-    l.part = k.take((uint64_t)c.max_workers * N_PART * CONV_PART * 4);
+    l.dp2g = k.take(n * P2_SIZE * 4 + 16);  // conv2's weight gradient reads rows of 7 in pieces of 4
+    l.part = k.take((uint64_t)c.max_workers * conv2_part_slots(c.batch) * CONV2_PART * 4);
     l.part1 = k.take((uint64_t)c.max_workers * conv1_part_slots(c.batch) * OFF_W2 * 4);
     l.fpart = k.take((uint64_t)(512 + c.max_workers) * FC2_PART * 4);  // >= n * fc2_split(n) slots
     l.normpart = k.take((uint64_t)c.queue_capacity * norm_slices() * 4);
@@ -217,6 +218,7 @@ WorkerBuffers buffers(const ps_ctx* c, int n, const float* x, const int32_t* y, 
     wb.am1 = c->at<uint8_t>(c->lay.am1);
     wb.p2 = c->at<float>(c->lay.p2);
     wb.am2 = c->at<uint8_t>(c->lay.am2);
+    wb.am2t = c->at<uint8_t>(c->lay.am2t);
     wb.ht = c->at<float>(c->lay.ht);
     wb.z = c->at<float>(c->lay.z);
     wb.pred = c->at<int32_t>(c->lay.pred);
@@ -938,6 +940,13 @@ ps_status ps_version(ps_ctx* c, uint64_t* version_host)
     return PS_OK;
 }
 
+// where the window byte of pooled output i (images back to back) is kept
+static size_t pool2_byte(size_t i)
+{
+    const size_t img = i / P2_SIZE, o = i % P2_SIZE / P2_POS, p = i % P2_POS;
+    return img * AM2_SIZE + (o * P2_W + p / P2_W) * AM2_PITCH + p % P2_W;
+}
+
 ps_status ps_debug_last_batch(ps_ctx* c, int32_t i, uint8_t* pool1_host, uint8_t* pool2_host, uint8_t* keep_host,
                               float* hdrop_host, float* z_host, int32_t* pred_host)
 {
@@ -946,7 +955,8 @@ ps_status ps_debug_last_batch(ps_ctx* c, int32_t i, uint8_t* pool1_host, uint8_t
     const size_t B = c->cfg.batch, g0 = (size_t)i * B;
     hipStream_t s = c->stream;
     if (pool1_host) PS_HIP(c, hipMemcpyAsync(pool1_host, c->at<uint8_t>(c->lay.am1) + g0 * P1_SIZE, B * P1_SIZE, hipMemcpyDeviceToHost, s));
-    if (pool2_host) PS_HIP(c, hipMemcpyAsync(pool2_host, c->at<uint8_t>(c->lay.am2) + g0 * P2_SIZE, B * P2_SIZE, hipMemcpyDeviceToHost, s));
+    std::vector<uint8_t> am2(pool2_host ? B * AM2_SIZE : 0);
+    if (pool2_host) PS_HIP(c, hipMemcpyAsync(am2.data(), c->at<uint8_t>(c->lay.am2) + g0 * AM2_SIZE, am2.size(), hipMemcpyDeviceToHost, s));
     if (hdrop_host) PS_HIP(c, hipMemcpyAsync(hdrop_host, c->at<float>(c->lay.ht) + g0 * FC1, B * FC1 * 4, hipMemcpyDeviceToHost, s));
     if (z_host) PS_HIP(c, hipMemcpyAsync(z_host, c->at<float>(c->lay.z) + g0 * NCLS, B * NCLS * 4, hipMemcpyDeviceToHost, s));
     if (pred_host) PS_HIP(c, hipMemcpyAsync(pred_host, c->at<int32_t>(c->lay.pred) + g0, B * 4, hipMemcpyDeviceToHost, s));
@@ -972,6 +982,11 @@ ps_status ps_debug_last_batch(ps_ctx* c, int32_t i, uint8_t* pool1_host, uint8_t
                 }
         }
     }
+    if (pool2_host)
+        for (size_t i = 0; i < B * P2_SIZE; ++i) {
+            const uint8_t b = am2[pool2_byte(i)];
+            pool2_host[i] = (uint8_t)((b >> 4) | ((b & 15) ? 4 : 0));
+        }
     return PS_OK;
 }
 
@@ -983,11 +998,24 @@ ps_status ps_debug_last_activations(ps_ctx* c, int32_t i, float* pool1_val_host,
         return fail(c, PS_EINVAL, "ps_debug_last_activations: no such worker in the last call");
     const size_t B = c->cfg.batch, g0 = (size_t)i * B;
     hipStream_t s = c->stream;
-    if (pool1_val_host) PS_HIP(c, hipMemcpyAsync(pool1_val_host, c->at<float>(c->lay.p1) + g0 * P1_SIZE, B * P1_SIZE * 4, hipMemcpyDeviceToHost, s));
     if (pool2_val_host) PS_HIP(c, hipMemcpyAsync(pool2_val_host, c->at<float>(c->lay.p2) + g0 * P2_SIZE, B * P2_SIZE * 4, hipMemcpyDeviceToHost, s));
     if (d3_host) PS_HIP(c, hipMemcpyAsync(d3_host, c->at<float>(c->lay.d3) + g0 * FC1, B * FC1 * 4, hipMemcpyDeviceToHost, s));
-    if (dpool2_host) PS_HIP(c, hipMemcpyAsync(dpool2_host, c->at<float>(c->lay.dp2g) + g0 * P2_SIZE, B * P2_SIZE * 4, hipMemcpyDeviceToHost, s));
+    std::vector<uint8_t> am2(dpool2_host ? B * AM2_SIZE : 0);
+    std::vector<float> p1(pool1_val_host ? B * P1_SIZE : 0);
+    if (dpool2_host) {
+        PS_HIP(c, hipMemcpyAsync(dpool2_host, c->at<float>(c->lay.dp2g) + g0 * P2_SIZE, B * P2_SIZE * 4, hipMemcpyDeviceToHost, s));
+        PS_HIP(c, hipMemcpyAsync(am2.data(), c->at<uint8_t>(c->lay.am2) + g0 * AM2_SIZE, am2.size(), hipMemcpyDeviceToHost, s));
+    }
+    if (pool1_val_host) PS_HIP(c, hipMemcpyAsync(p1.data(), c->at<float>(c->lay.p1) + g0 * P1_SIZE, B * P1_SIZE * 4, hipMemcpyDeviceToHost, s));
     PS_HIP(c, hipStreamSynchronize(s));
+    if (pool1_val_host)  // kept [position][channel]
+        for (size_t i = 0; i < B * P1_SIZE; ++i) {
+            const size_t r = i % P1_SIZE;
+            pool1_val_host[i] = p1[i - r + r % P1_POS * C1 + r / P1_POS];
+        }
+    if (dpool2_host)  // the gate is applied by the kernels that read the buffer
+        for (size_t i = 0; i < B * P2_SIZE; ++i)
+            if (!(am2[pool2_byte(i)] & 15)) dpool2_host[i] = 0.f;
     return PS_OK;
 }
 

@@ -14,15 +14,15 @@ constexpr int IMG_W = 28, IMG_PIX = 784;
 constexpr int C1 = 16, C2 = 32;
 constexpr int P1_W = 14, P1_POS = 196, P1_SIZE = C1 * P1_POS;  // 3136
 constexpr int P2_W = 7, P2_POS = 49, P2_SIZE = C2 * P2_POS;    // 1568
+constexpr int AM2_PITCH = 8, AM2_SIZE = C2 * P2_W * AM2_PITCH;  // pool2 window bytes of an image, rows of 7 padded to 8
 constexpr int FC1 = 512, NCLS = 10;
 
 constexpr int OFF_W1 = 0, OFF_B1 = 144, OFF_W2 = 160, OFF_B2 = 4768, OFF_W3 = 4800, OFF_B3 = 807616,
               OFF_W4 = 808128, OFF_B4 = 813248, P = 813258;
 // Row pitch of every P-vector in HBM (weights, ring slots, queue entries): P rounded up to 256 B.
 constexpr int PSTRIDE = 813312;
-constexpr int CONV_PART = OFF_W3;  // conv1 + conv2 gradient floats (4800), reduced from chunk partials
-constexpr int N_CHUNK = 8;         // image chunks per worker in the conv weight-gradient reductions
-constexpr int N_PART = 4 * N_CHUNK;  // partial slots per worker: one per (chunk, wavefront) of conv2's kernel
+// Partial slots of the conv2 weight gradient: d W2 as conv2_dw_kernel's registers hold it, then d b2.
+constexpr int CONV2_PART_B2 = C2 * C1 * 9, CONV2_PART = CONV2_PART_B2 + C2;
 
 constexpr int AM1_GATE = 0x80;  // pool1 window byte: winner's pre-activation > 0
 
@@ -41,17 +41,18 @@ struct WorkerBuffers {
     const WorkerMeta* meta;  // [n]
     const float* x;      // [n*B][784]
     const int32_t* y;    // [n*B]
-    float* p1;           // [n*B][16][196]  conv1 -> ReLU -> pool
+    float* p1;           // [n*B][196][16]  conv1 -> ReLU -> pool
     uint8_t* am1;        // [n*B][196][16]  bits 0-6 the window winner's offset dy*30 + dx in a 30-wide padded input
                          //                 image (0, 1, 30, 31), bit 7 winner > 0: what conv1's weight gradient needs
     float* p2;           // [n*B][32][49]
-    uint8_t* am2;        // [n*B][32][49]
+    uint8_t* am2;        // [n*B][32][7][8] bits 0-3 one-hot winner (0 where the activation is 0), bits 4-5 the winner; byte 7 of a row is 0
+    uint8_t* am2t;       // [n*B][49][32]   bits 0-3 of am2, position by position
     float* ht;           // [n*B][512]      fc1 -> ReLU -> dropout
     float* z;            // [n*B][10]       logits
     int32_t* pred;       // [n*B]
     float* d3;           // [n*B][512]      d loss / d fc1 pre-activation
-    float* dp2g;         // [n*B][1568]     d loss / d pool2, zero where pool2 == 0
-    float* part;         // [n][N_PART][4800] partial sums of the conv2 weight gradient (conv1 region unused)
+    float* dp2g;         // [n*B][1568]     d loss / d pool2 (its readers apply the ReLU gate of the window bytes)
+    float* part;         // [n][conv2_part_slots(B)][CONV2_PART] partial sums of the conv2 weight gradient
     float* part1;        // [n][conv1_part_slots(B)][160] partial sums of the conv1 weight gradient
     float* fpart;        // [n][split][FC2_PART] partial sums of the fc2 kernel's blocks
     float* loss;         // [n] or nullptr
@@ -88,7 +89,11 @@ __device__ __forceinline__ float pool_first_max(float v0, float v1, float v2, fl
 constexpr int FC2_PART_B4 = NCLS * FC1, FC2_PART_B3 = FC2_PART_B4 + NCLS, FC2_PART_LOSS = FC2_PART_B3 + FC1,
               FC2_PART = 5648;
 int fc2_split(int n);  // blocks per worker of the fc2 kernel (one partial slot each)
+int conv2_part_slots(int batch);  // conv2 partial slots per worker (one per block of its weight-gradient kernel)
 int conv1_part_slots(int batch);  // conv1 partial slots per worker (one per image, written by conv2's input-gradient kernel)
+
+int compute_units();  // of the current GPU
+int images_per_wavefront(int n, int batch, int most);  // for the kernels in which a wavefront works on whole images
 
 void launch_conv1_fwd(const WorkerBuffers& wb, hipStream_t s);
 void launch_fc1_fwd(const WorkerBuffers& wb, hipStream_t s);

@@ -1,10 +1,8 @@
-// conv2 (16 -> 32 channels, 3x3, pad 1, on 14x14 maps) as implicit GEMMs on the gfx950 matrix cores
-// (v_mfma_f32_16x16x4_f32): forward with fused ReLU + 2x2 max pool, input gradient, and per-worker
-// weight gradient.  Zero-padded feature maps are staged in LDS as [channel][16][16] planes (plane
-// pitch a little above 256 floats), so that a 3x3 tap is a compile-time address offset (dy*16 + dx)
-// from a lane's base address.
-// The 32x16x9 filter bank lives in registers for the whole block (72 VGPRs per lane) in exactly the
-// layout the MFMA B operand wants; it is read from the worker's ring slot once per block.
+// conv2 (16 -> 32 channels, 3x3, pad 1, on 14x14 maps) on the gfx950 bf16 matrix cores with operands split in
+// three (ps_split.h): forward with fused ReLU + 2x2 max pool, input gradient fused with conv1's weight
+// gradient, and per-worker weight gradient.  In all three a wavefront works on whole images by itself, its
+// operands go from memory to registers, are split there once and reused for several taps, and what a
+// wavefront needs to turn round inside an image goes through LDS of its own: no block barrier in any loop.
 #include "ps_common.h"
 #include "ps_split.h"
 
@@ -12,257 +10,188 @@ namespace ps {
 
 namespace {
 
-// LDS pitch (floats) of one padded 16x16 plane, chosen per kernel so that the 32 lanes an LDS read
-// serves per cycle fall into 32 different banks: the lane quarters of the forward A operand are four
-// channels over 8+8 window columns (pitch = 8 mod 32), those of the input-gradient A operand two
-// channels over 16 consecutive positions (pitch = 16 mod 32), and the weight-gradient operands put 16
-// channels on 16 lanes at 2 neighbouring positions (pitch = 2 mod 32).
-constexpr int CHS_FWD = 264, CHS_DW = 258;
+// Pool2 window bytes of an image: [channel][7 rows][AM2_PITCH], the byte past a row's seven is 0.
+// Bits 0-3: bit (2 dy + dx) of the winner, set only where the winner's activation is > 0; bits 4-5: the winner.
+// The input gradient reads bits 0-3 from a second copy, [window][channel].
 
-__device__ __forceinline__ floatx4 mfma16(float a, float b, floatx4 c)
-{
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-
-// Staging is split in two so that the global loads of the next group of images are in flight while
-// the matrix cores work on the current one: prefetch_* issues the loads into registers, commit_*
-// writes the registers into the padded LDS planes after the barrier that ends the current group.
-
-// pool1 planes of COUNT images (16 channels, 14x14 interiors); NV float4 per thread of a block of NT.
-template <int COUNT, int CHS, int NT = 256>
-struct Pool1Stage {
-    static constexpr int P1_IMS = C1 * CHS;
-    static constexpr int N4 = COUNT * (P1_SIZE / 4), NV = (N4 + NT - 1) / NT;
-    floatx4 v[NV];
-    uint32_t src[NV];  // float offset of this thread's k-th float4 inside a group of COUNT images
-    __device__ __forceinline__ void init(int tid)
-    {
-#pragma unroll
-        for (int k = 0; k < NV; ++k) src[k] = (uint32_t)min(tid + NT * k, N4 - 1) * 4;  // threads without an element repeat the last one
-    }
-    // images [g0, g0 + valid) exist; the rest of the group repeats the last existing image (its
-    // results are never stored), so the loads need no branches
-    __device__ __forceinline__ void prefetch(const float* __restrict__ p1, size_t g0, int valid, int tid)
-    {
-        const float* group = p1 + g0 * P1_SIZE;
-        if (valid >= COUNT) {  // uniform over the block
-#pragma unroll
-            for (int k = 0; k < NV; ++k) v[k] = *reinterpret_cast<const floatx4*>(group + src[k]);
-        } else {
-#pragma unroll
-            for (int k = 0; k < NV; ++k) {
-                const uint32_t img = min(src[k] / P1_SIZE, (uint32_t)(valid - 1));
-                v[k] = *reinterpret_cast<const floatx4*>(group + img * P1_SIZE + src[k] % P1_SIZE);
-            }
-        }
-    }
-    // Where the float4s land does not change from group to group: a table (bits 0-14 the offset of
-    // the first element, bit 15 set when the four positions run over the end of a 14-wide row after two
-    // elements) replaces that arithmetic by one 2-byte LDS read per float4.
-    static __device__ __forceinline__ void build_table(uint16_t* __restrict__ tab, int tid)
-    {
-        static_assert(COUNT * P1_IMS < (1 << 15), "offsets must fit 15 bits");
-        for (int i4 = tid; i4 < N4; i4 += NT) {
-            const int img = i4 / (P1_SIZE / 4), r = (i4 % (P1_SIZE / 4)) * 4, c = r / P1_POS, pos = r % P1_POS;
-            const int base = img * P1_IMS + c * CHS + 17 + (pos / P1_W) * 16 + pos % P1_W;  // interior starts at (1,1)
-            tab[i4] = (uint16_t)(base | (pos % P1_W == P1_W - 2 ? 0x8000 : 0));
-        }
-    }
-    __device__ __forceinline__ void commit(float* __restrict__ tile, const uint16_t* __restrict__ tab, int tid) const
-    {
-#pragma unroll
-        for (int k = 0; k < NV; ++k) {
-            const int i4 = tid + NT * k;
-            if (NT * (k + 1) <= N4 || i4 < N4) {
-                const uint32_t e = tab[i4];
-                float* dst = tile + (e & 0x7fffu);
-                const uint32_t hop = (e >> 15) * 2;  // the next row starts 16 - 14 further on
-                dst[0] = v[k][0];
-                dst[1] = v[k][1];
-                dst[2 + hop] = v[k][2];
-                dst[3 + hop] = v[k][3];
-            }
-        }
-    }
-};
-
-// Gated pool2 gradient of COUNT images, routed to the window winners of padded planes
-// d2[o][16][16] (interior at (1,1)).  A thread moves four consecutive values at a time (one 16-byte load
-// of gradients, one 4-byte load of window bytes); where a value lands apart from its winner's place in
-// the window never changes, so those offsets are computed once per block (two 16-bit offsets per
-// register) and a commit costs a handful of vector instructions per value instead of the divisions by 49
-// and 7.  Before the next commit the planes are cleared as a whole with 16-byte stores.
-template <int COUNT, int CHS, int NT = 256>
-struct D2Stage {
-    static constexpr int D2_IMS = C2 * CHS;
-    static constexpr int N4 = COUNT * (P2_SIZE / 4), NV = (N4 + NT - 1) / NT;
-    static_assert(P2_SIZE % 4 == 0, "a group of four values never straddles two images");
-    static_assert(COUNT * D2_IMS < (1 << 16), "offsets must fit 16 bits");
-    floatx4 v[NV];
-    uint32_t code[NV];
-    uint32_t base[NV][2];  // offsets of the four values' windows (winner (0,0)), 16 bits each
-    __device__ __forceinline__ void init(int tid)
-    {
-#pragma unroll
-        for (int k = 0; k < NV; ++k) {
-            uint32_t b[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int e = min(4 * (tid + NT * k), COUNT * P2_SIZE - 4) + j;
-                const int img = e / P2_SIZE, r = e % P2_SIZE, o = r / P2_POS, p = r % P2_POS;
-                b[j] = (uint32_t)(img * D2_IMS + o * CHS + (2 * (p / P2_W) + 1) * 16 + 2 * (p % P2_W) + 1);
-            }
-            base[k][0] = b[0] | (b[1] << 16);
-            base[k][1] = b[2] | (b[3] << 16);
-        }
-    }
-    __device__ __forceinline__ void prefetch(const WorkerBuffers& wb, size_t g0, int valid, int tid)
-    {
-#pragma unroll
-        for (int k = 0; k < NV; ++k) {
-            const int i4 = tid + NT * k;
-            const bool ok = (NT * (k + 1) <= N4 || i4 < N4) && (4 * i4) / P2_SIZE < valid;
-            v[k] = ok ? *reinterpret_cast<const floatx4*>(wb.dp2g + g0 * P2_SIZE + (size_t)i4 * 4) : floatx4{0.f, 0.f, 0.f, 0.f};
-            code[k] = ok ? *reinterpret_cast<const uint32_t*>(wb.am2 + g0 * P2_SIZE + (size_t)i4 * 4) : 0u;
-        }
-    }
-    __device__ __forceinline__ void commit(float* __restrict__ d2, int tid) const
-    {
-#pragma unroll
-        for (int k = 0; k < NV; ++k) {
-            if (!(NT * (k + 1) <= N4 || tid + NT * k < N4)) break;
-            // winner (dy, dx) of every byte -> dy * 16 + dx, four at once
-            const uint32_t off = (code[k] & 0x01010101u) | ((code[k] & 0x02020202u) << 3);
-            d2[(base[k][0] & 0xffffu) + (off & 0xffu)] = v[k][0];
-            d2[(base[k][0] >> 16) + ((off >> 8) & 0xffu)] = v[k][1];
-            d2[(base[k][1] & 0xffffu) + ((off >> 16) & 0xffu)] = v[k][2];
-            d2[(base[k][1] >> 16) + (off >> 24)] = v[k][3];
-        }
-    }
-    // zeroes all COUNT * D2_IMS floats of the planes
-    static __device__ __forceinline__ void clear(float* __restrict__ d2, int tid)
-    {
-        static_assert(COUNT * D2_IMS % 4 == 0, "16-byte stores");
-        constexpr int T4 = COUNT * D2_IMS / 4;
-#pragma unroll
-        for (int i = 0; i < (T4 + NT - 1) / NT; ++i)
-            if (NT * (i + 1) <= T4 || tid + NT * i < T4)
-                reinterpret_cast<floatx4*>(d2)[tid + NT * i] = floatx4{0.f, 0.f, 0.f, 0.f};
-    }
-};
+__device__ __forceinline__ bool any_nan(const floatx4& a) { return __builtin_isunordered(a[0], a[1]) || __builtin_isunordered(a[2], a[3]); }
 
 // ---------------------------------------------------------------------------------------------
-// Forward.  GEMM rows are conv outputs ordered (pooled position, window element) so that the four
-// accumulators of a lane are one 2x2 pool window; columns are the 32 output channels (two 16-wide
-// MFMA tiles sharing the A operand); K = (tap, channel).  A block owns up to FWD_IPB images of one
-// worker and walks them FWD_G at a time (FWD_G * 49 pooled positions, four per row tile), FWD_NW wavefronts
-// per block.
-constexpr int FWD_G = 4, FWD_NW = 4, FWD_NT = 64 * FWD_NW, FWD_IPB = 32;
-constexpr int FWD_TILES = (FWD_G * P2_POS + 3) / 4;
+// Forward (32x32x16).  GEMM rows are two rows of the map, 16 padded columns each; columns the 32 output
+// channels; one k-step the 16 input channels of one tap.  Lane (h, e, column) of the A operand holds eight
+// channels of one position of row R + e, which is 32 consecutive bytes of pool1.  The rows read for tap row
+// dy are R = 2t - 1 + dy for pooled row t; each pair of rows is split once per tap row, the three dx are the
+// same operand moved by 0, 1, 2 lanes, and the pair of dy = 2 is that of dy = 0 one pooled row further on.
+// A lane ends up with both rows of four windows of one output channel, so pooling stays in its registers;
+// the pooled image is turned to [channel][position] in LDS and leaves in 16-byte stores.
+// 14 of 16 columns are real: 378 MFMAs per image, 12,100 cycles of a SIMD's matrix pipe.
+// 65,536 images: 1.005 -> 0.61 ms against the fp32 MFMA kernel that staged padded planes in LDS (matrix pipe busy
+// 68 % of the cycles at the 2.0 GHz the chip then runs at; a loop of nothing but these MFMAs on random operands
+// sustains 1.8 PFLOP/s, this kernel 1.3); two workers of 32 images: 41 -> 13 us.
+constexpr int FWD_NW = 4, FWD_NT = 64 * FWD_NW, FWD_IPW = 8;  // wavefronts per block, most images per wavefront
 
-__global__ __launch_bounds__(FWD_NT, 512 / FWD_NT) void conv2_fwd_kernel(WorkerBuffers wb, int blocks_per_worker, int ipb)
+struct FwdImage {  // one wavefront's pooled image
+    float p2[P2_SIZE];
+    uint8_t am2[AM2_SIZE];
+    uint8_t am2t[P2_SIZE];
+};
+
+// Pre-activation (without bias) of output channel o at (y, x) with fp32 FMAs (see ps_split.h).
+__device__ __forceinline__ float conv2_fwd_plain(const float* __restrict__ p1, const float* __restrict__ W2, int o, int y, int x)
 {
-    constexpr int CHS = CHS_FWD, P1_IMS = C1 * CHS;
-    __shared__ __attribute__((aligned(16))) float tile[FWD_G * P1_IMS];  // 16,896 B per image
-    // pooled position of the group -> offset of its window in the planes / of its output.  On this chip
-    // fp32 MFMAs and vector-ALU instructions do not overlap, so index arithmetic inside the tile loop
-    // is paid for in matrix time: look it up.
-    // (entries past the group's last position, in a last tile that is not full, point at position 0: read, never stored)
-    __shared__ int win_off[4 * FWD_TILES], out_off[4 * FWD_TILES];
-    __shared__ uint16_t stage_tab[Pool1Stage<FWD_G, CHS_FWD, FWD_NT>::N4];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, q = lane >> 4, l16 = lane & 15;
-    const int w = blockIdx.x / blocks_per_worker, chunk = blockIdx.x % blocks_per_worker;
-    const int B = wb.B, s_begin = chunk * ipb, s_end = min(B, s_begin + ipb);
-    const float* __restrict__ W2 = worker_theta(wb, w) + OFF_W2;
-    for (int i = tid; i < 4 * FWD_TILES; i += FWD_NT) {
-        const int e = i < FWD_G * P2_POS ? i : 0, img = e / P2_POS, pos = e % P2_POS;
-        win_off[i] = img * P1_IMS + 2 * (pos / P2_W) * 16 + 2 * (pos % P2_W);
-        out_off[i] = img * P2_SIZE + pos;
+    float sum = 0.f;
+#pragma unroll 1
+    for (int t = 0; t < 9; ++t) {
+        const int yy = y + t / 3 - 1, xx = x + t % 3 - 1;
+        const bool inside = yy >= 0 && yy < P1_W && xx >= 0 && xx < P1_W;
+        const float* p = p1 + (inside ? yy * P1_W + xx : 0) * C1;
+#pragma unroll 1
+        for (int c = 0; c < C1; ++c) sum = fmaf(inside ? p[c] : 0.f, W2[(o * C1 + c) * 9 + t], sum);
     }
-    Pool1Stage<FWD_G, CHS, FWD_NT>::build_table(stage_tab, tid);
+    return sum;
+}
 
-    // B operand of k-step s (channels 4*(s/9) .. +3, tap = s%9): lane (q, l16) holds W2[o][4*(s/9)+q][tap].
-    // Taps innermost: the nine A reads of a channel group then share one LDS base address.
-    float wreg[36][2];
-#pragma unroll
-    for (int s = 0; s < 36; ++s)
-#pragma unroll
-        for (int hf = 0; hf < 2; ++hf) wreg[s][hf] = W2[((l16 + 16 * hf) * C1 + 4 * (s / 9) + q) * 9 + s % 9];
-    const float bias0 = W2[C2 * C1 * 9 + l16], bias1 = W2[C2 * C1 * 9 + 16 + l16];
+__global__ __launch_bounds__(FWD_NT, 2) void conv2_fwd_kernel(WorkerBuffers wb, int blocks_per_worker, int ipw)
+{
+    __shared__ __attribute__((aligned(16))) FwdImage images[FWD_NW];
+    const int lane = threadIdx.x & 63, wave = uniform(threadIdx.x >> 6);
+    const int h = lane >> 5, l32 = lane & 31, e = l32 >> 4, x = (lane & 15) - 1;
+    const int w = blockIdx.x / blocks_per_worker, chunk = blockIdx.x % blocks_per_worker;
+    const int B = wb.B, s_begin = (chunk * FWD_NW + wave) * ipw, s_end = min(B, s_begin + ipw);
+    if (s_begin >= s_end) return;
+    FwdImage& im = images[wave];
+    const float* __restrict__ W2 = worker_theta(wb, w) + OFF_W2;
 
-    for (int i = tid; i < FWD_G * P1_IMS / 4; i += FWD_NT)
-        reinterpret_cast<float4*>(tile)[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-    __syncthreads();
-
-    // this lane's part of the A operand address: channel quarter, window element
-    const float* a_lane = tile + q * CHS + ((l16 >> 1) & 1) * 16 + (l16 & 1);
-    Pool1Stage<FWD_G, CHS, FWD_NT> stage;
-    stage.init(tid);
-    stage.prefetch(wb.p1, (size_t)w * B + s_begin, min(FWD_G, s_end - s_begin), tid);
-    int rot = 0;
-    for (int s0 = s_begin; s0 < s_end; s0 += FWD_G, ++rot) {
-        const size_t g0 = (size_t)w * B + s0;
-        const int valid = min(FWD_G, s_end - s0);
-        stage.commit(tile, stage_tab, tid);
-        __syncthreads();
-        if (s0 + FWD_G < s_end) stage.prefetch(wb.p1, g0 + FWD_G, min(FWD_G, s_end - s0 - FWD_G), tid);
-        for (int t = (wave + rot) % FWD_NW; t < FWD_TILES; t += FWD_NW) {  // which wavefront takes the odd tile rotates
-            // A operand: lane row l16 = (pooled position 4t + l16/4, window element l16%4)
-            const float* a = a_lane + win_off[4 * t + (l16 >> 2)];
-            floatx4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
+    constexpr uint32_t ROW_BYTES = P1_W * C1 * 4, IMAGE_BYTES = P1_SIZE * 4;
+    const uint32_t at = (x >= 0 && x < P1_W) ? (uint32_t)e * ROW_BYTES + (uint32_t)(x * C1 + 8 * h) * 4 : BUFFER_NOWHERE;
+    floatx4 raw[2][2];  // rows (R, R + 1) of the next pooled row: R = 2t and R = 2t + 1
+    auto prefetch = [&](size_t g, int t) {
+        const Buffer b = buffer_of(wb.p1 + g * P1_SIZE, IMAGE_BYTES);
 #pragma unroll
-            for (int s = 0; s < 36; ++s) {
-                const float av = a[4 * (s / 9) * CHS + ((s % 9) / 3) * 16 + (s % 9) % 3];
-                acc0 = mfma16(av, wreg[s][0], acc0);
-                acc1 = mfma16(av, wreg[s][1], acc1);
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int k = 0; k < 2; ++k) raw[i][k] = buffer_float4(b, at + (uint32_t)(2 * t + i) * ROW_BYTES + 16 * k);
+    };
+    auto split_raw = [&](int i) {
+        const float v[8] = {raw[i][0][0], raw[i][0][1], raw[i][0][2], raw[i][0][3], raw[i][1][0], raw[i][1][1], raw[i][1][2], raw[i][1][3]};
+        return split8(v);
+    };
+    prefetch((size_t)w * B + s_begin, 0);
+
+    Split8 wt[9];  // lane (h, l32): W2[o = l32][c = 8h + j][tap]
+#pragma unroll
+    for (int t = 0; t < 9; ++t) {
+        float v[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = W2[(l32 * C1 + 8 * h + j) * 9 + t];
+        wt[t] = split8(v);
+    }
+    const float bias = W2[C2 * C1 * 9 + l32];
+
+    for (int s = s_begin; s < s_end; ++s) {
+        const size_t g = (size_t)w * B + s;
+        wave_lds_fence();  // the last image has been stored
+        Split8 up;  // rows 2t - 1 and 2t
+#pragma unroll 1
+        for (int t = 0; t < P2_W; ++t) {
+            const Split8 mid = split_raw(0), low = split_raw(1);  // rows 2t, 2t + 1 and 2t + 1, 2t + 2
+            if (t == 0) {  // rows -1 (zero) and 0: the odd groups of 16 lanes take what the even ones of `mid` hold
+#pragma unroll
+                for (int i = 0; i < 3; ++i)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) up.p[i][j] = __builtin_amdgcn_permlane16_swap(0u, mid.p[i][j], false, false)[0];
             }
-            // lane (q, l16) now holds the 2x2 window of pooled position 4t + q for channels l16, l16+16
-            const int ppo = 4 * t + q;
-            if (ppo < valid * P2_POS) {
-                const size_t out = g0 * P2_SIZE + out_off[ppo];
-                // the four values of a window share their channel's bias: it is added to the winner only
-                int code;
-                float best = pool_first_max(acc0[0], acc0[1], acc0[2], acc0[3], code) + bias0;
-                wb.p2[out + l16 * P2_POS] = fmaxf(best, 0.f);
-                wb.am2[out + l16 * P2_POS] = (uint8_t)(code | (best > 0.f ? 4 : 0));
-                best = pool_first_max(acc1[0], acc1[1], acc1[2], acc1[3], code) + bias1;
-                wb.p2[out + (l16 + 16) * P2_POS] = fmaxf(best, 0.f);
-                wb.am2[out + (l16 + 16) * P2_POS] = (uint8_t)(code | (best > 0.f ? 4 : 0));
+            if (t + 1 < P2_W)
+                prefetch(g, t + 1);
+            else if (s + 1 < s_end)
+                prefetch(g + 1, 0);
+            SplitSum<floatx16> sum;
+            sum.clear();
+            const Split8* const rows[3] = {&up, &mid, &low};
+#pragma unroll
+            for (int dy = 0; dy < 3; ++dy) {
+                sum.add(*rows[dy], wt[3 * dy]);
+                sum.add(lanes_up<1>(*rows[dy]), wt[3 * dy + 1]);
+                sum.add(lanes_up<2>(*rows[dy]), wt[3 * dy + 2]);
+            }
+            up = low;
+            floatx16 acc = sum.value();
+            // register i of lane (h, l32): channel l32 at row 2t + i / 8, column 8 (i / 4 % 2) + 4h + i % 4
+            bool nan = false;
+#pragma unroll
+            for (int i = 0; i < 16; i += 2) nan |= __builtin_isunordered(acc[i], acc[i + 1]);
+            if (__any(nan)) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i) acc[i] = conv2_fwd_plain(wb.p1 + g * P1_SIZE, W2, l32, 2 * t + i / 8, 8 * (i / 4 % 2) + 4 * h + i % 4);
+            }
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+                uint32_t bytes = 0;
+#pragma unroll
+                for (int m = 0; m < 2; ++m) {
+                    const int px = 4 * half + 2 * h + m, i = 4 * half + 2 * m;
+                    int code;
+                    // the four values of a window share their channel's bias: it is added to the winner only
+                    const float best = pool_first_max(acc[i], acc[i + 1], acc[i + 8], acc[i + 9], code) + bias;
+                    const uint32_t b = (uint32_t)(code << 4) | (best > 0.f ? 1u << code : 0u);
+                    if (half == 0 || m == 0 || h == 0) {  // px = 7 does not exist
+                        im.p2[l32 * P2_POS + t * P2_W + px] = fmaxf(best, 0.f);
+                        im.am2t[(t * P2_W + px) * C2 + l32] = (uint8_t)(b & 15u);
+                        bytes |= b << (8 * m);
+                    }
+                }
+                *reinterpret_cast<uint16_t*>(im.am2 + (l32 * P2_W + t) * AM2_PITCH + 4 * half + 2 * h) = (uint16_t)bytes;
             }
         }
-        __syncthreads();
+        wave_lds_fence();
+#pragma unroll
+        for (int k = 0; k < 7; ++k)
+            if (64 * (k + 1) <= P2_SIZE / 4 || lane + 64 * k < P2_SIZE / 4)
+                reinterpret_cast<floatx4*>(wb.p2 + g * P2_SIZE)[lane + 64 * k] = reinterpret_cast<const floatx4*>(im.p2)[lane + 64 * k];
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+            if (64 * (k + 1) <= AM2_SIZE / 16 || lane + 64 * k < AM2_SIZE / 16)
+                reinterpret_cast<uintx4*>(wb.am2 + g * AM2_SIZE)[lane + 64 * k] = reinterpret_cast<const uintx4*>(im.am2)[lane + 64 * k];
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+            if (64 * (k + 1) <= P2_SIZE / 16 || lane + 64 * k < P2_SIZE / 16)
+                reinterpret_cast<uintx4*>(wb.am2t + g * P2_SIZE)[lane + 64 * k] = reinterpret_cast<const uintx4*>(im.am2t)[lane + 64 * k];
     }
 }
 
 // ---------------------------------------------------------------------------------------------
 // Input gradient of conv2 fused with the weight gradient of conv1.
 //   d pool1[c][Y][X] = sum_{o,dy,dx} d2pad[o][Y+2-dy][X+2-dx] * W2[o][c][dy][dx], zeroed where pool1 == 0.
-// On the bf16 matrix cores (ps_split.h, 16x16x32): GEMM rows are the 16 columns of a padded row of the 14x14
-// map, columns the 16 input channels, one k-step the 32 output channels of one tap.  A row of d2 is put
-// together in registers from the pooled gradients and the window winners, split once and used for all nine
-// taps: the three dx are the same operand moved by 0, 1, 2 lanes, the three dy go to the accumulators of
-// three output rows, which rotate.  The 9 x 3 operands of the filter bank stay in 108 registers.
+// 16x16x32: GEMM rows are the 16 columns of a padded row of the 14x14 map, columns the 16 input channels, one
+// k-step the 32 output channels of one tap.  The pooled gradients are split once per image, on their way into
+// LDS; a row of d2 is those parts masked by the window bytes and serves all nine taps: the three dx are the
+// same operand moved by 0, 1, 2 lanes, the three dy go to the accumulators of three output rows, which rotate.
+// The 9 x 3 operands of the filter bank stay in 108 registers.
 // The result never goes to memory: conv1 has no input gradient, so each value is routed to its pool1
 // window's winner and multiplied right away with the 3x3 neighbourhood of input pixels there,
 //   d W1[c][dy][dx] += d pool1[c][p] * xpad[winner(c,p) + (dy,dx)],   d b1[c] += d pool1[c][p],
 // on the vector ALU.  A wavefront works on whole images by itself (no block barrier anywhere) and writes
 // one partial slot of conv1 sums per image, so that nothing depends on how a launch is cut up.
-// 65,536 images: 1.146 -> 0.600 ms against the fp32 MFMA kernel in two-wavefront blocks it replaced; two
-// workers of 32 images: 87 -> 17 us (a wavefront walked eight images there, now one).
+// 65,536 images: 1.146 -> 0.65 ms against the fp32 MFMA kernel in two-wavefront blocks; two workers of 32
+// images: 87 -> 16 us (a wavefront walked eight images there, now one).  Matrix pipe busy 58 % of the cycles.
 constexpr int DX_NW = 4, DX_NT = 64 * DX_NW, DX_IPW = 8;  // wavefronts per block, most images per wavefront
 constexpr int DX_XW = 30, DX_XS = 30 * DX_XW + 16;        // padded input image (and what lanes 14, 15 read past it)
+// A d2 operand lane holds eight output channels 8q + DX_CHANNEL(i); the order is the one in which a word of
+// window bytes turns into 16-bit masks.
+constexpr int DX_WIN = 40;  // pitch of a window in the planes of parts, in values: 80 bytes, eight windows in different banks
+__device__ __forceinline__ constexpr int dx_channel(int i) { return i < 4 ? 2 * i : 2 * i - 7; }   // 0 2 4 6 1 3 5 7
+__device__ __forceinline__ int dx_place(int o) { return (o & ~7) + (o & 1) * 4 + (o & 7) / 2; }    // its inverse over all channels
 
 struct DxImage {  // one wavefront's image
-    float dp2[P2_SIZE];            // gated pool2 gradient
-    uint32_t code[P2_SIZE / 4];    // window winners 0..3, bytes
-    uint8_t am1[P1_SIZE + 32];     // pool1 window bytes, [position][channel]
+    uint16_t dp2[3][P2_POS * DX_WIN];  // pool2 gradient, its three parts, [window][place of channel]
+    uint8_t am2t[P2_SIZE];             // pool2 window bytes, [window][channel]
+    uint8_t am1[P1_SIZE + 32];         // pool1 window bytes, [position][channel]
     float xs[DX_XS];
 };
 
-// d pool1 of channel c at (Y, X) with fp32 FMAs: for sums the split cannot hold (see ps_split.h).
-__device__ __forceinline__ float conv2_dx_plain(const DxImage& im, const float* __restrict__ W2, int c, int Y, int X)
+// d pool1 of channel c at (Y, X) of image g with fp32 FMAs: for sums the split cannot hold (see ps_split.h).
+__device__ __forceinline__ float conv2_dx_plain(const WorkerBuffers& wb, size_t g, const float* __restrict__ W2, int c, int Y, int X)
 {
-    const uint8_t* code = reinterpret_cast<const uint8_t*>(im.code);
     float sum = 0.f;
 #pragma unroll 1
     for (int o = 0; o < C2; ++o)
@@ -271,8 +200,8 @@ __device__ __forceinline__ float conv2_dx_plain(const DxImage& im, const float* 
             const int y = Y + 1 - t / 3, x = X + 1 - t % 3;
             float v = 0.f;
             if (y >= 0 && y < P1_W && x >= 0 && x < P1_W) {
-                const int p = o * P2_POS + (y >> 1) * P2_W + (x >> 1);
-                v = code[p] == 2 * (y & 1) + (x & 1) ? im.dp2[p] : 0.f;
+                const int p = (y >> 1) * P2_W + (x >> 1);
+                v = wb.am2t[g * P2_SIZE + p * C2 + o] >> (2 * (y & 1) + (x & 1)) & 1 ? wb.dp2g[g * P2_SIZE + o * P2_POS + p] : 0.f;
             }
             sum = fmaf(v, W2[(o * C1 + c) * 9 + t], sum);
         }
@@ -282,42 +211,46 @@ __device__ __forceinline__ float conv2_dx_plain(const DxImage& im, const float* 
 __global__ __launch_bounds__(DX_NT, 2) void conv2_dx_kernel(WorkerBuffers wb, int blocks_per_worker, int ipw)
 {
     __shared__ __attribute__((aligned(16))) DxImage images[DX_NW];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, q = lane >> 4, l16 = lane & 15;
+    const int lane = threadIdx.x & 63, wave = uniform(threadIdx.x >> 6), q = lane >> 4, l16 = lane & 15;
     const int w = blockIdx.x / blocks_per_worker, chunk = blockIdx.x % blocks_per_worker;
     const int B = wb.B, s_begin = (chunk * DX_NW + wave) * ipw, s_end = min(B, s_begin + ipw);
     if (s_begin >= s_end) return;
     DxImage& im = images[wave];
     const float* __restrict__ W2 = worker_theta(wb, w) + OFF_W2;
 
-    Split8 wt[9];  // lane (q, l16): W2[o = 8q + j][c = l16][tap]
+    Split8 wt[9];  // lane (q, l16): W2[o = 8q + dx_channel(i)][c = l16][tap]
 #pragma unroll
     for (int t = 0; t < 9; ++t) {
         float v[8];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) v[j] = W2[((8 * q + j) * C1 + l16) * 9 + t];
+        for (int i = 0; i < 8; ++i) v[i] = W2[((8 * q + dx_channel(i)) * C1 + l16) * 9 + t];
         wt[t] = split8(v);
     }
     for (int i = lane; i < DX_XS; i += 64) im.xs[i] = 0.f;  // the border stays zero
     if (lane < 32) im.am1[P1_SIZE + lane] = 0;
 
-    // column l16 of the padded map is x = l16 - 1; columns 0 and 15 are border
-    const int x = l16 - 1;
-    const uint32_t want0 = (x >= 0 && x < P1_W) ? (uint32_t)(x & 1) : 0x100u;  // winner code of an even row at x; never for the border
-    const int d2_at = 8 * q * P2_POS + min(max(x >> 1, 0), P2_W - 1);
+    // column l16 of the padded map is x = l16 - 1; columns 0 and 15 are border, whose shift finds a bit that is never set
+    const int x = l16 - 1, px = min(max(x >> 1, 0), P2_W - 1);
+    const bool border = x < 0 || x >= P1_W;
+    const uint32_t shift[2] = {border ? 0u : 7u - (x & 1), border ? 0u : 5u - (x & 1)};  // bit of (row, x) -> bit 7 of its byte
     const uint32_t real = q == 3 ? 0u : ~0u;  // positions X = 4q + 2, 4q + 3 exist
+    // lane (o, half) = (lane / 2, lane % 2) brings in windows 25 half .. of channel o: 25 or 24 of them
+    const int o_in = lane >> 1, win_in = 25 * (lane & 1), last_in = o_in * P2_POS + (lane & 1 ? P2_POS - 1 : 24);
 
     for (int s = s_begin; s < s_end; ++s) {
         const size_t g = (size_t)w * B + s;
-        // pooled gradients and winners: 392 float4 and 98 uint4; pool1 window bytes and pixels: 196 of either
-        // (lanes past the end repeat the last one).  The other wavefront of the SIMD works meanwhile.
-        floatx4 pv[7], xv[4];
+        // the image's pooled gradients, window bytes (98 uint4), pool1 window bytes and pixels (196 of either;
+        // lanes past the end repeat the last one).  The other wavefront of the SIMD works meanwhile.
+        float pv[26];
+        floatx4 xv[4];
         uintx4 pc[2], bv[4];
+        const float* dp = wb.dp2g + g * P2_SIZE;
 #pragma unroll
-        for (int k = 0; k < 7; ++k)
-            pv[k] = reinterpret_cast<const floatx4*>(wb.dp2g + g * P2_SIZE)[min(lane + 64 * k, P2_SIZE / 4 - 1)];
+        for (int k = 0; k < 6; ++k) __builtin_memcpy(&pv[4 * k], dp + o_in * P2_POS + win_in + 4 * k, 16);
+        pv[24] = pv[25] = dp[last_in];
 #pragma unroll
         for (int k = 0; k < 2; ++k)
-            pc[k] = reinterpret_cast<const uintx4*>(wb.am2 + g * P2_SIZE)[min(lane + 64 * k, P2_SIZE / 16 - 1)];
+            pc[k] = reinterpret_cast<const uintx4*>(wb.am2t + g * P2_SIZE)[min(lane + 64 * k, P2_SIZE / 16 - 1)];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const int i = min(lane + 64 * k, IMG_PIX / 4 - 1);
@@ -325,13 +258,20 @@ __global__ __launch_bounds__(DX_NT, 2) void conv2_dx_kernel(WorkerBuffers wb, in
             bv[k] = reinterpret_cast<const uintx4*>(wb.am1 + g * P1_SIZE)[i];
         }
         wave_lds_fence();  // the last image has been read
+        const int at = win_in * DX_WIN + dx_place(o_in);
 #pragma unroll
-        for (int k = 0; k < 7; ++k)
-            if (64 * (k + 1) <= P2_SIZE / 4 || lane + 64 * k < P2_SIZE / 4) reinterpret_cast<floatx4*>(im.dp2)[lane + 64 * k] = pv[k];
+        for (int m = 0; m < 26; m += 2) {
+            uint32_t part[3];
+            split2(pv[m], pv[m + 1], part[0], part[1], part[2]);
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                if (m < 24 || !(lane & 1)) im.dp2[i][at + m * DX_WIN] = (uint16_t)part[i];
+                if (m < 24) im.dp2[i][at + (m + 1) * DX_WIN] = (uint16_t)(part[i] >> 16);
+            }
+        }
 #pragma unroll
         for (int k = 0; k < 2; ++k)
-            if (64 * (k + 1) <= P2_SIZE / 16 || lane + 64 * k < P2_SIZE / 16)
-                reinterpret_cast<uintx4*>(im.code)[lane + 64 * k] = pc[k] & 0x03030303u;
+            if (64 * (k + 1) <= P2_SIZE / 16 || lane + 64 * k < P2_SIZE / 16) reinterpret_cast<uintx4*>(im.am2t)[lane + 64 * k] = pc[k];
         wave_lds_fence();
 
         float g1[9], gb1 = 0.f;  // this lane's share of d W1[l16][.] and d b1[l16]
@@ -340,51 +280,56 @@ __global__ __launch_bounds__(DX_NT, 2) void conv2_dx_kernel(WorkerBuffers wb, in
 
         // conv1's gradient from d pool1 row Y: lane (q, l16) holds channel l16 at X = 4q .. 4q + 3
         auto finish_row = [&](int Y, floatx4 acc) {
-            if (__any(__builtin_isunordered(acc[0], acc[1]) || __builtin_isunordered(acc[2], acc[3])))
+            if (__any(any_nan(acc))) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) acc[i] = conv2_dx_plain(im, W2, l16, Y, 4 * q + i);
+                for (int i = 0; i < 4; ++i) acc[i] = conv2_dx_plain(wb, g, W2, l16, Y, 4 * q + i);
+            }
             const uint8_t* bytes = im.am1 + (P1_W * Y + 4 * q) * C1 + l16;
             const float* row = im.xs + 2 * Y * DX_XW + 8 * q;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 uint32_t b = bytes[C1 * i];
                 if (i >= 2) b &= real;
-                const float* px = row + 2 * i + (b & 0x7fu);
-                const uint32_t keep = (uint32_t)((int32_t)(b << 24) >> 31);  // gate bit -> all ones or zero
+                const float* p = row + 2 * i + (b & 0x7fu);
+                const uint32_t keep = (uint32_t)__builtin_amdgcn_sbfe((int)b, 7, 1);  // gate bit -> all ones or zero
                 const float v = __uint_as_float(__float_as_uint(acc[i]) & keep);
                 gb1 += v;
 #pragma unroll
-                for (int k = 0; k < 9; ++k) g1[k] = fmaf(v, px[(k / 3) * DX_XW + k % 3], g1[k]);
+                for (int k = 0; k < 9; ++k) g1[k] = fmaf(v, p[(k / 3) * DX_XW + k % 3], g1[k]);
             }
         };
 
-        floatx4 acc[3];  // d pool1 rows y - 1, y, y + 1
+        SplitSum<floatx4> acc[3];  // d pool1 rows y - 1, y, y + 1
 #pragma unroll
-        for (int i = 0; i < 3; ++i) acc[i] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int i = 0; i < 3; ++i) acc[i].clear();
 #pragma unroll 1
         for (int py = 0; py < P2_W; ++py) {
-            float v[8];
-            uint32_t code[8];
+            const int win = py * P2_W + px;
+            uintx4 part[3];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                v[j] = im.dp2[d2_at + j * P2_POS + py * P2_W];
-                code[j] = reinterpret_cast<const uint8_t*>(im.code)[d2_at + j * P2_POS + py * P2_W];
-            }
+            for (int i = 0; i < 3; ++i) part[i] = *reinterpret_cast<const uintx4*>(&im.dp2[i][win * DX_WIN + 8 * q]);
+            const uint32_t* code = reinterpret_cast<const uint32_t*>(im.am2t + win * C2 + 8 * q);
+            const uint32_t code0 = code[0], code1 = code[1];
 #pragma unroll
             for (int r = 0; r < 2; ++r) {
                 const int y = 2 * py + r;
-                float d[8];
+                // the window's bit of this row and column in bit 7 of every byte; bits 15 and 31 fill half words
+                const uint32_t c0 = code0 << shift[r], c1 = code1 << shift[r];
+                const uintx4 mask = {__builtin_amdgcn_perm(0u, c0 << 8, 0x09090808u), __builtin_amdgcn_perm(0u, c1 << 8, 0x09090808u),
+                                     __builtin_amdgcn_perm(0u, c0, 0x09090808u), __builtin_amdgcn_perm(0u, c1, 0x09090808u)};
+                Split8 a0;
 #pragma unroll
-                for (int j = 0; j < 8; ++j) d[j] = code[j] == want0 + 2 * r ? v[j] : 0.f;
-                const Split8 a0 = split8(d), a1 = lanes_up<1>(a0), a2 = lanes_up<2>(a0);
+                for (int i = 0; i < 3; ++i) a0.p[i] = part[i] & mask;
                 // row y of d2 is tap row dy of row y - 1 + dy of the result (row -1 does not exist)
-                const Split8* const moved[3] = {&a2, &a1, &a0};
 #pragma unroll
-                for (int dx = 0; dx < 3; ++dx) {
-                    if (r == 1 || py > 0)
-                        mfma_split<3>(*moved[dx], {&wt[dx], &wt[3 + dx], &wt[6 + dx]}, {&acc[0], &acc[1], &acc[2]});
-                    else
-                        mfma_split<2>(*moved[dx], {&wt[3 + dx], &wt[6 + dx]}, {&acc[1], &acc[2]});
+                for (int dx = 2; dx >= 0; --dx) {
+                    const Split8 a = dx == 2 ? a0 : dx == 1 ? lanes_up<1>(a0) : lanes_up<2>(a0);
+#pragma unroll
+                    for (int t = 0; t <= SPLIT_SMALL; ++t) {
+                        if (r == 1 || py > 0) acc[0].add(t, a, wt[dx]);
+                        acc[1].add(t, a, wt[3 + dx]);
+                        acc[2].add(t, a, wt[6 + dx]);
+                    }
                 }
                 if (y == 0) {  // the rest of the image, which row 0 of the result needs first
 #pragma unroll
@@ -399,14 +344,14 @@ __global__ __launch_bounds__(DX_NT, 2) void conv2_dx_kernel(WorkerBuffers wb, in
                     }
                     wave_lds_fence();
                 } else {
-                    finish_row(y - 1, acc[0]);
+                    finish_row(y - 1, acc[0].value());
                 }
                 acc[0] = acc[1];
                 acc[1] = acc[2];
-                acc[2] = floatx4{0.f, 0.f, 0.f, 0.f};
+                acc[2].clear();
             }
         }
-        finish_row(P1_W - 1, acc[0]);
+        finish_row(P1_W - 1, acc[0].value());
 
         // fold the four lane quarters; lanes of quarter 0 hold the image's sums for channel l16
 #pragma unroll
@@ -426,137 +371,225 @@ __global__ __launch_bounds__(DX_NT, 2) void conv2_dx_kernel(WorkerBuffers wb, in
 }
 
 // ---------------------------------------------------------------------------------------------
-// Weight gradient: d W2[o][c][dy][dx] = sum over the worker's images and positions of
-// d2[o][y][x] * pool1pad[c][y+dy][x+dx];  d b2[o] = sum d2[o].  GEMM rows are the 32 output channels
-// (two tiles), columns (tap, input channel) (nine tiles), K = positions, four per MFMA step.  A block
-// owns one chunk of a worker's images; its four wavefronts split every image's 49 k-steps and keep
-// their 18 accumulator tiles across images; each wavefront's sum goes to its own partial slot.
-__global__ __launch_bounds__(256, 2) void conv2_dw_kernel(WorkerBuffers wb)
-{
-    constexpr int CHS = CHS_DW, D2_IMS = C2 * CHS, P1_IMS = C1 * CHS;
-    __shared__ __attribute__((aligned(16))) float d2[D2_IMS];   // 33,024 B
-    __shared__ __attribute__((aligned(16))) float p1t[P1_IMS];  // 16,512 B
-    // position -> offset inside a padded plane.  On this chip fp32 MFMAs and vector-ALU instructions do
-    // not overlap, so index arithmetic inside the MFMA loops is paid for in matrix time: look it up.
-    __shared__ int plane_off[P1_POS];
-    __shared__ uint16_t stage_tab[Pool1Stage<1, CHS_DW>::N4];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, q = lane >> 4, l16 = lane & 15;
-    const int w = blockIdx.x, chunk = blockIdx.y, B = wb.B;
-    const int per = (B + N_CHUNK - 1) / N_CHUNK;
-    const int s_begin = chunk * per, s_end = min(B, s_begin + per);
+// Weight gradient (16x16x32): d W2[o][c][dy][dx] = sum over the worker's images and positions of
+// d2[o][y][x] * pool1pad[c][y+dy][x+dx];  d b2[o] = sum d2[o].  GEMM rows are the output channels (two
+// tiles), columns the 16 input channels of one tap (nine tiles), one k-step the two map rows of a pooled
+// row, 16 columns each: lane (q = 2e + xh, l16) holds columns 8xh .. 8xh + 7 of row 2py + e.  A d2 operand is
+// four pooled values, each split once into both halves of a register and masked by the window's bits; a
+// pool1 operand is ten values of a row, split once: columns from -1 (dx = 0) and +1 (dx = 2) on are the same
+// pairs, those from 0 on the pairs shifted by one value.  d b2 is the product with a column of ones.
+// A block's four wavefronts take DW_IPW images each at most, meet in LDS once, and write one partial slot;
+// the slots depend on the batch alone, so that the order of a worker's sums does not depend on the launch.
+// All six terms share one accumulator here: the 72 more of a second one do not fit next to the operands.  The
+// sums are final results, so the cut-off bits of ps_split.h are not added up any further: d W2 is off by 1.2e-7
+// to 3.6e-7, as it was with fp32 MFMAs.
+// 65,536 images: 0.93 -> 0.63 ms against the fp32 MFMA kernel; one worker of 256 images 162 -> 45 us, two of 32
+// 24 -> 14 us (more, smaller shares).
+constexpr int DW_NW = 4, DW_NT = 64 * DW_NW, DW_MAX_SLOTS = 16;
+constexpr int DW_REGS = 2 * 9 * 4;  // sums per lane without the bias
 
-    floatx4 acc[2][9];
+// eight columns of a pool1 row from each of the three starting columns
+struct ShiftedRow {
+    uint32_t pair[3][5], odd[3][4];
+    __device__ __forceinline__ Split8 columns(int dx) const
+    {
+        Split8 s;
 #pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) s.p[i][j] = dx == 0 ? pair[i][j] : dx == 1 ? odd[i][j] : pair[i][j + 1];
+        return s;
+    }
+};
+
+__device__ __forceinline__ ShiftedRow shifted_row(const float (&v)[10])
+{
+    ShiftedRow r;
+#pragma unroll
+    for (int j = 0; j < 5; ++j) split2(v[2 * j], v[2 * j + 1], r.pair[0][j], r.pair[1][j], r.pair[2][j]);
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) r.odd[i][j] = __builtin_amdgcn_alignbit(r.pair[i][j + 1], r.pair[i][j], 16);
+    return r;
+}
+
+// One sum over images [s_begin, s_end) of worker w with fp32 FMAs (see ps_split.h): tap 0..8, or 9 for the bias.
+__device__ __forceinline__ float conv2_dw_plain(const WorkerBuffers& wb, int w, int s_begin, int s_end, int o, int c, int tap)
+{
+    float sum = 0.f;
+#pragma unroll 1
+    for (int s = s_begin; s < s_end; ++s) {
+        const size_t g = (size_t)w * wb.B + s;
+#pragma unroll 1
+        for (int p = 0; p < P1_POS; ++p) {
+            const int y = p / P1_W, x = p % P1_W, r = o * P2_W + (y >> 1);
+            const float d = wb.am2[g * AM2_SIZE + r * AM2_PITCH + (x >> 1)] >> (2 * (y & 1) + (x & 1)) & 1
+                                ? wb.dp2g[g * P2_SIZE + r * P2_W + (x >> 1)] : 0.f;
+            const int yy = y + tap / 3 - 1, xx = x + tap % 3 - 1;
+            const bool inside = yy >= 0 && yy < P1_W && xx >= 0 && xx < P1_W;
+            sum = tap == 9 ? sum + d : fmaf(d, inside ? wb.p1[g * P1_SIZE + (yy * P1_W + xx) * C1 + c] : 0.f, sum);
+        }
+    }
+    return sum;
+}
+
+__global__ __launch_bounds__(DW_NT, 2) void conv2_dw_kernel(WorkerBuffers wb, int slots, int ipw)
+{
+    __shared__ __attribute__((aligned(16))) float red[DW_NW][DW_REGS + 2][64];  // 75,776 B
+    const int lane = threadIdx.x & 63, wave = uniform(threadIdx.x >> 6), q = lane >> 4, l16 = lane & 15, e = q >> 1, xh = q & 1;
+    const int w = blockIdx.x / slots, slot = blockIdx.x % slots;
+    const int B = wb.B, s_begin = min(B, (slot * DW_NW + wave) * ipw), s_end = min(B, s_begin + ipw);
+
+    floatx4 acc[2][9], acc_b[2];
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt) {
+        acc_b[mt] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int j = 0; j < 9; ++j) acc[mt][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-    float sum0 = 0.f, sum1 = 0.f;
-
-    for (int i = tid; i < D2_IMS / 4; i += 256) reinterpret_cast<float4*>(d2)[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int i = tid; i < P1_IMS / 4; i += 256) reinterpret_cast<float4*>(p1t)[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (tid < P1_POS) plane_off[tid] = (tid / P1_W) * 16 + tid % P1_W;
-    Pool1Stage<1, CHS>::build_table(stage_tab, tid);
-    __syncthreads();
-    const float* d2_lane = d2 + l16 * CHS + 17;
-    const float* p1_lane = p1t + l16 * CHS;
-
-    D2Stage<1, CHS> sd;
-    sd.init(tid);
-    Pool1Stage<1, CHS> sp;
-    sp.init(tid);
-    if (s_begin < s_end) {
-        sd.prefetch(wb, (size_t)w * B + s_begin, 1, tid);
-        sp.prefetch(wb.p1, (size_t)w * B + s_begin, 1, tid);
     }
-    int rot = 0;
-    for (int s = s_begin; s < s_end; ++s, ++rot) {
+
+    constexpr uint32_t POS_BYTES = C1 * 4, ROW_BYTES = P1_W * POS_BYTES;
+    // columns 8xh - 1 .. 8xh + 8 of row e; of those outside the map only -1 and 14 ever meet a d2 value
+    const uint32_t at = (uint32_t)e * ROW_BYTES + (uint32_t)(8 * xh) * POS_BYTES + 4 * l16;  // column 8xh
+    const uint32_t at_first = xh == 0 ? BUFFER_NOWHERE : at - POS_BYTES, at_col14 = xh == 1 ? BUFFER_NOWHERE : at + 6 * POS_BYTES;
+    float raw[2][10];   // rows R + e of the next pooled row: R = 2py and R = 2py + 1
+    floatx4 pooled[2];  // pool2 gradients of windows px = 4xh .. 4xh + 3 (px = 7: whatever follows, masked) and their bytes
+    uint32_t bytes[2];
+    auto prefetch = [&](size_t g, int py) {
+        const Buffer b = buffer_of(wb.p1 + g * P1_SIZE, P1_SIZE * 4);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const uint32_t row = (uint32_t)(2 * py + i) * ROW_BYTES;
+#pragma unroll
+            for (int k = 0; k < 10; ++k)
+                raw[i][k] = buffer_float(b, k == 0 ? at_first + row : k == 7 ? at_col14 + row : at + row + (k - 1) * POS_BYTES);
+        }
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt) {
+            const int r = (16 * mt + l16) * P2_W + py;
+            __builtin_memcpy(&pooled[mt], wb.dp2g + g * P2_SIZE + r * P2_W + 4 * xh, 16);
+            bytes[mt] = *reinterpret_cast<const uint32_t*>(wb.am2 + g * AM2_SIZE + r * AM2_PITCH + 4 * xh);
+        }
+    };
+    if (s_begin < s_end) prefetch((size_t)w * B + s_begin, 0);
+
+    for (int s = s_begin; s < s_end; ++s) {
         const size_t g = (size_t)w * B + s;
-        sd.commit(d2, tid);
-        sp.commit(p1t, stage_tab, tid);
-        __syncthreads();
-        if (s + 1 < s_end) {
-            sd.prefetch(wb, g + 1, 1, tid);
-            sp.prefetch(wb.p1, g + 1, 1, tid);
-        }
-        for (int pos = 4 * ((wave + rot) & 3) + q; pos < P1_POS; pos += 16) {
-            const int off = plane_off[pos];
-            const float a0 = d2_lane[off], a1 = d2_lane[16 * CHS + off];
-            sum0 += a0;
-            sum1 += a1;
-            const float* b = p1_lane + off;
+        ShiftedRow up;  // rows 2py - 1 + e
+#pragma unroll 1
+        for (int py = 0; py < P2_W; ++py) {
+            Split8 d2[2];
 #pragma unroll
-            for (int j = 0; j < 9; ++j) {
-                const float bv = b[(j / 3) * 16 + j % 3];
-                acc[0][j] = mfma16(a0, bv, acc[0][j]);
-                acc[1][j] = mfma16(a1, bv, acc[1][j]);
+            for (int mt = 0; mt < 2; ++mt) {
+                const uint32_t bits = bytes[mt] >> (2 * e);  // bits 0, 1 of every byte: winner in this row, left or right
+#pragma unroll
+                for (int m = 0; m < 4; ++m) {
+                    const uint32_t left = (uint32_t)__builtin_amdgcn_sbfe((int)bits, 8 * m, 1), right = (uint32_t)__builtin_amdgcn_sbfe((int)bits, 8 * m + 1, 1);
+                    const uint32_t mask = (left & 0xffffu) | (right & 0xffff0000u);
+                    uint32_t p0, p1, p2;
+                    split2(pooled[mt][m], pooled[mt][m], p0, p1, p2);
+                    d2[mt].p[0][m] = p0 & mask;
+                    d2[mt].p[1][m] = p1 & mask;
+                    d2[mt].p[2][m] = p2 & mask;
+                }
             }
+            const ShiftedRow mid = shifted_row(raw[0]);
+            if (py == 0) {  // rows -1 (zero) and 0: lanes 32..63 take what lanes 0..31 of `mid` hold
+#pragma unroll
+                for (int i = 0; i < 3; ++i) {
+#pragma unroll
+                    for (int j = 0; j < 5; ++j) up.pair[i][j] = __builtin_amdgcn_permlane32_swap(0u, mid.pair[i][j], false, false)[0];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) up.odd[i][j] = __builtin_amdgcn_permlane32_swap(0u, mid.odd[i][j], false, false)[0];
+                }
+            }
+            const ShiftedRow low = shifted_row(raw[1]);
+            if (py + 1 < P2_W)
+                prefetch(g, py + 1);
+            else if (s + 1 < s_end)
+                prefetch(g + 1, 0);
+            const ShiftedRow* const rows[3] = {&up, &mid, &low};
+#pragma unroll
+            for (int dy = 0; dy < 3; ++dy)
+#pragma unroll
+                for (int dx = 0; dx < 3; ++dx) {
+                    const Split8 b = rows[dy]->columns(dx);
+#pragma unroll
+                    for (int t = 0; t <= SPLIT_SMALL; ++t)
+#pragma unroll
+                        for (int mt = 0; mt < 2; ++mt)
+                            acc[mt][3 * dy + dx] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(d2[mt].part(TERM_A[t]), b.part(TERM_B[t]), acc[mt][3 * dy + dx], 0, 0, 0);
+                }
+            const bf16x8 ones = __builtin_bit_cast(bf16x8, uintx4{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u});
+#pragma unroll
+            for (int i = 2; i >= 0; --i)
+#pragma unroll
+                for (int mt = 0; mt < 2; ++mt) acc_b[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(d2[mt].part(i), ones, acc_b[mt], 0, 0, 0);
+            up = low;
         }
-        __syncthreads();
-        sd.clear(d2, tid);
-        __syncthreads();  // cleared by all threads before the next commit scatters into the planes
     }
 
-    // accumulator i of tile (mt, j): output channel 16*mt + 4q + i, input channel l16, tap j
-    float* part = wb.part + ((size_t)w * N_PART + chunk * 4 + wave) * CONV_PART;
+    // register i of tile (mt, j): output channel 16 mt + 4q + i, input channel l16, tap j (every column of the bias tile alike)
+    bool nan = false;
 #pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
+    for (int mt = 0; mt < 2; ++mt) {
+        nan |= any_nan(acc_b[mt]);
 #pragma unroll
-        for (int j = 0; j < 9; ++j)
+        for (int j = 0; j < 9; ++j) {
+            nan |= any_nan(acc[mt][j]);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) part[OFF_W2 + ((16 * mt + 4 * q + i) * C1 + l16) * 9 + j] = acc[mt][j][i];
-    sum0 += __shfl_xor(sum0, 16, 64);
-    sum0 += __shfl_xor(sum0, 32, 64);
-    sum1 += __shfl_xor(sum1, 16, 64);
-    sum1 += __shfl_xor(sum1, 32, 64);
-    if (q == 0) {
-        part[OFF_B2 + l16] = sum0;
-        part[OFF_B2 + 16 + l16] = sum1;
+            for (int i = 0; i < 4; ++i) red[wave][(mt * 9 + j) * 4 + i][lane] = acc[mt][j][i];
+        }
+        if (l16 == 0) *reinterpret_cast<floatx4*>(&red[wave][DW_REGS + mt][4 * q]) = acc_b[mt];
+    }
+    if (__any(nan)) {
+#pragma unroll 1
+        for (int r = 0; r < DW_REGS; ++r)
+            red[wave][r][lane] = conv2_dw_plain(wb, w, s_begin, s_end, 16 * (r / 36) + 4 * q + r % 4, l16, r % 36 / 4);
+        if (lane < 32) red[wave][DW_REGS + lane / 16][lane % 16] = conv2_dw_plain(wb, w, s_begin, s_end, lane, 0, 9);
+    }
+    __syncthreads();
+    float* part = wb.part + ((size_t)w * slots + slot) * CONV2_PART;
+#pragma unroll
+    for (int i = 0; i < CONV2_PART_B2 / DW_NT; ++i) {
+        const int r = (threadIdx.x >> 6) + DW_NW * i;
+        part[r * 64 + lane] = (red[0][r][lane] + red[1][r][lane]) + (red[2][r][lane] + red[3][r][lane]);
+    }
+    if (threadIdx.x < C2) {
+        const int r = DW_REGS + threadIdx.x / 16, j = threadIdx.x % 16;
+        part[CONV2_PART_B2 + threadIdx.x] = (red[0][r][j] + red[1][r][j]) + (red[2][r][j] + red[3][r][j]);
     }
 }
 
 }  // namespace
 
-static int compute_units()
-{
-    static int cus = 0;
-    if (cus == 0) {
-        int dev = 0;
-        if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
-            cus = 256;
-    }
-    return cus;
-}
-
-// Images per block: as many as FWD_IPB when the launch still gives every compute unit as many blocks as fit
-// it, else fewer (16, 8), so that a small launch does not leave part of the chip idle.
-static int images_per_block(int n, int batch, int most, int blocks_per_cu)
-{
-    int ipb = most;
-    while (ipb > 8 && n * ((batch + ipb - 1) / ipb) < blocks_per_cu * compute_units()) ipb /= 2;
-    return ipb;
-}
-
 void launch_conv2_fwd(const WorkerBuffers& wb, hipStream_t s)
 {
-    const int ipb = images_per_block(wb.n, wb.B, FWD_IPB, 512 / FWD_NT), bpw = (wb.B + ipb - 1) / ipb;
-    hipLaunchKernelGGL(conv2_fwd_kernel, dim3(wb.n * bpw), dim3(FWD_NT), 0, s, wb, bpw, ipb);
+    const int ipw = images_per_wavefront(wb.n, wb.B, FWD_IPW), bpw = (wb.B + FWD_NW * ipw - 1) / (FWD_NW * ipw);
+    hipLaunchKernelGGL(conv2_fwd_kernel, dim3(wb.n * bpw), dim3(FWD_NT), 0, s, wb, bpw, ipw);
 }
 
 int conv1_part_slots(int batch) { return batch; }
 
-// A wavefront walks as many images (up to DX_IPW) as leave two wavefronts for every SIMD: reading and
-// splitting the filter bank, once per wavefront, takes about a quarter of an image's time.
 void launch_conv2_dx(const WorkerBuffers& wb, hipStream_t s)
 {
-    int ipw = DX_IPW;
-    while (ipw > 1 && wb.n * ((wb.B + ipw - 1) / ipw) < 2 * 4 * compute_units()) ipw /= 2;
-    const int bpw = (wb.B + DX_NW * ipw - 1) / (DX_NW * ipw);
+    const int ipw = images_per_wavefront(wb.n, wb.B, DX_IPW), bpw = (wb.B + DX_NW * ipw - 1) / (DX_NW * ipw);
     hipLaunchKernelGGL(conv2_dx_kernel, dim3(wb.n * bpw), dim3(DX_NT), 0, s, wb, bpw, ipw);
+}
+
+static int conv2_dw_ipw(int batch) { return (batch + DW_NW * DW_MAX_SLOTS - 1) / (DW_NW * DW_MAX_SLOTS); }
+
+int conv2_part_slots(int batch)
+{
+    const int per_slot = DW_NW * conv2_dw_ipw(batch);
+    return (batch + per_slot - 1) / per_slot;
 }
 
 void launch_conv2_dw(const WorkerBuffers& wb, hipStream_t s)
 {
-    hipLaunchKernelGGL(conv2_dw_kernel, dim3(wb.n, N_CHUNK), dim3(256), 0, s, wb);
+    const int slots = conv2_part_slots(wb.B);
+    hipLaunchKernelGGL(conv2_dw_kernel, dim3(wb.n * slots), dim3(DW_NT), 0, s, wb, slots, conv2_dw_ipw(wb.B));
 }
 
 }  // namespace ps

@@ -1,6 +1,5 @@
 // The three contractions of the 1568 -> 512 fully connected layer on the matrix cores: forward with
-// fused bias + ReLU + dropout, input gradient with the conv2 ReLU gate, and the per-worker weight
-// gradient written straight into the worker's queue entry.
+// fused bias + ReLU + dropout, input gradient, and the per-worker weight gradient written straight into the worker's queue entry.
 #include "ps_common.h"
 #include "ps_gemm.h"
 #include "ps_philox.h"
@@ -33,27 +32,17 @@ struct Fc1FwdEpi {
     }
 };
 
-// d pool2 = d3 . W3, zeroed where the pooled activation is zero (ReLU gate of conv2).
-// Rows m are pool2 features, columns n samples, contraction over the 512 units.  The gate is bit 2 of
-// the pool2 window bytes (winner > 0, which is the same as pooled activation > 0): four bytes per
-// epilogue call, fetched before the contraction starts.
+// d pool2 = d3 . W3 (the conv2 kernels that read it apply the ReLU gate).
+// Rows m are pool2 features, columns n samples, contraction over the 512 units.
 struct Fc1DxEpi {
     WorkerBuffers wb;
     __device__ const float* a_ptr(int z) const { return worker_theta(wb, z) + OFF_W3; }
     __device__ const float* b_ptr(int z) const { return wb.d3 + (size_t)z * wb.B * FC1; }
-    typedef uint32_t Pre;
-    __device__ Pre prefetch(int z, int m, int n) const
+    struct Pre {};
+    __device__ Pre prefetch(int, int, int) const { return Pre{}; }
+    __device__ void operator()(int z, int m, int n, float4 acc, Pre) const
     {
-        return *reinterpret_cast<const uint32_t*>(wb.am2 + ((size_t)z * wb.B + n) * P2_SIZE + m);  // m % 4 == 0
-    }
-    __device__ void operator()(int z, int m, int n, float4 acc, Pre gate) const
-    {
-        float4 o;
-        o.x = (gate & 0x00000004u) ? acc.x : 0.f;
-        o.y = (gate & 0x00000400u) ? acc.y : 0.f;
-        o.z = (gate & 0x00040000u) ? acc.z : 0.f;
-        o.w = (gate & 0x04000000u) ? acc.w : 0.f;
-        *reinterpret_cast<float4*>(wb.dp2g + ((size_t)z * wb.B + n) * P2_SIZE + m) = o;
+        *reinterpret_cast<float4*>(wb.dp2g + ((size_t)z * wb.B + n) * P2_SIZE + m) = acc;
     }
 };
 
@@ -88,14 +77,8 @@ constexpr int FEAT_WIDE = P2_SIZE / 128 * 128;  // 1536
 // order in which a value's products are added up does not depend on the tile shape).
 void launch_fc1_fwd(const WorkerBuffers& wb, hipStream_t s)
 {
-    static int cus = 0;
-    if (cus == 0) {
-        int dev = 0;
-        if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
-            cus = 256;
-    }
     const int wide_tiles = (FC1 / 128) * ((wb.B + 127) / 128) * wb.n;
-    if (wide_tiles >= 2 * cus)
+    if (wide_tiles >= 2 * compute_units())
         gemm_launch<GemmCfg<true, true, 2, 2, 2, 2, 16>, 1>(FC1, wb.B, P2_SIZE, P2_SIZE, P2_SIZE, wb.n, Fc1FwdEpi{wb}, s);
     else
         gemm_launch<GemmCfg<true, true, 1, 2, 2, 2, 16>, 1>(FC1, wb.B, P2_SIZE, P2_SIZE, P2_SIZE, wb.n, Fc1FwdEpi{wb}, s);

@@ -2,12 +2,17 @@
 //   x = x0 + x1 + x2 (+ at most 2^-27 |x|),  x0 = bf16(x), x1 = bf16(x - x0), x2 = bf16(x - x0 - x1),
 // every difference exact, and a product a*b is taken as the six terms a0b0 + a0b1 + a1b0 + a0b2 + a2b0 +
 // a1b1; what is left out is below 2^-25 |a*b|, of either sign.  Products of two bf16 values are exact in
-// fp32 and the matrix cores add 16 or 32 of them per instruction in fp32, so that a sum of K products is
-// rounded K/16 or K/32 times instead of K/2 or K/4 times: measured against 64 bits the six-term sums are
-// off by 0.6-0.9 times what v_mfma_f32_32x32x2_f32 is, for K = 64 .. 12,544 on signed and on positive
-// operands.  Six bf16 MFMAs take 3/8 of the time of the fp32 MFMAs they replace (16 x the rate), and unlike
-// those they leave the vector ALU free: eight v_fma_f32 behind every 32x32x16 MFMA of two wavefronts cost
-// 19.2 ns per MFMA instead of 16.6 ns, where the fp32 MFMA pays their full time (27.1 -> 44.2 ns).
+// fp32, and the matrix cores add 16 or 32 of them per instruction to an fp32 accumulator, but cut off (towards
+// minus infinity) what a small addend has below the large one's last bit.  So a0b0 and the five small terms
+// are summed in accumulators of their own and meet at the end: measured against 64 bits such sums are off by
+// 0.25-0.4 times what v_mfma_f32_32x32x2_f32 is (K = 64 .. 12,544; signed, positive and mostly zero operands;
+// mean error below 2e-9 of the mean result).  With all six terms in one accumulator it is 0.6-0.9 times, 1.4 to
+// 1.8 times where most operands are zero, and the mean error is -1e-8 (K = 144) to -3e-8 (K = 512), which a later
+// sum over many such results does not average out.
+// Six bf16 MFMAs take 3/8 of the time of the fp32 MFMAs they replace (16 x the rate), and unlike those they
+// leave the vector ALU free: per 32x32x16 MFMA of two wavefronts (14.2 ns alone) four v_fma_f32 make 16.1 ns and
+// eight 19.0 ns, per 16x16x32 MFMA (6.9 ns) one, two and three make 7.1, 7.8 and 9.2 ns; next to the fp32
+// 32x32x2 MFMA (27.1 ns) eight take their full time (44.2 ns).
 // What the split cannot hold: an infinity, or a value that rounds to one (above 3.39e38), leaves NaN in x1
 // and so in every sum it enters; the kernels look for NaN in their sums and redo such a sum with fp32 FMAs.
 // Parts below 2^-126 are flushed to zero: operands under 2^-110 keep their leading 16 bits.
@@ -57,20 +62,34 @@ __device__ __forceinline__ Split8 split8(const float (&x)[8])
     return s;
 }
 
-// The six terms in the order in which they are added up, the small ones first: part of A, part of B.
-constexpr int SPLIT_TERMS = 6, TERM_A[SPLIT_TERMS] = {1, 0, 2, 0, 1, 0}, TERM_B[SPLIT_TERMS] = {1, 2, 0, 1, 0, 0};
+// The terms: five small ones, then a0b0.
+constexpr int SPLIT_SMALL = 5, TERM_A[SPLIT_SMALL + 1] = {1, 0, 2, 0, 1, 0}, TERM_B[SPLIT_SMALL + 1] = {1, 2, 0, 1, 0, 0};
 
-// acc[i] += A . B[i] over one k-step for N products that share A: term by term, so that consecutive MFMAs
-// belong to different sums.
-template <int N>
-__device__ __forceinline__ void mfma_split(const Split8& a, const Split8* const (&b)[N], floatx4* const (&acc)[N])
-{
+// A sum in its two accumulators.
+template <class V>
+struct SplitSum {
+    V big, small;
+    __device__ __forceinline__ void clear()
+    {
 #pragma unroll
-    for (int t = 0; t < SPLIT_TERMS; ++t)
+        for (unsigned i = 0; i < sizeof(V) / 4; ++i) big[i] = small[i] = 0.f;
+    }
+    __device__ __forceinline__ V value() const { return big + small; }
+    // one term of A . B over one k-step
+    __device__ __forceinline__ void add(int t, const Split8& a, const Split8& b)
+    {
+        V& acc = t < SPLIT_SMALL ? small : big;
+        if constexpr (sizeof(V) == sizeof(floatx4))
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.part(TERM_A[t]), b.part(TERM_B[t]), acc, 0, 0, 0);
+        else
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.part(TERM_A[t]), b.part(TERM_B[t]), acc, 0, 0, 0);
+    }
+    __device__ __forceinline__ void add(const Split8& a, const Split8& b)
+    {
 #pragma unroll
-        for (int i = 0; i < N; ++i)
-            *acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.part(TERM_A[t]), b[i]->part(TERM_B[t]), *acc[i], 0, 0, 0);
-}
+        for (int t = 0; t <= SPLIT_SMALL; ++t) add(t, a, b);
+    }
+};
 
 // The same operand with every lane taking the value S lanes further on in its row of 16 (zero past the end).
 template <int S>
@@ -83,6 +102,27 @@ __device__ __forceinline__ Split8 lanes_up(const Split8& a)
         for (int j = 0; j < 4; ++j)
             r.p[i][j] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)a.p[i][j], 0x100 + S, 0xF, 0xF, true);  // row_shl:S
     return r;
+}
+
+// A wave-uniform value the compiler cannot prove to be one, as a scalar.
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
+// Loads through a buffer descriptor (its base must be uniform): offsets at or beyond `bytes`, negative ones
+// and BUFFER_NOWHERE among them, read as zero, which is how the kernels get the zero border of a feature map.
+typedef __amdgpu_buffer_rsrc_t Buffer;
+constexpr uint32_t BUFFER_NOWHERE = 0x40000000u;  // stays out of range with any offset inside a map added
+
+__device__ __forceinline__ Buffer buffer_of(const float* base, uint32_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), 0, (int)bytes, 0x00020000);
+}
+__device__ __forceinline__ float buffer_float(Buffer b, uint32_t offset)
+{
+    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(b, (int)offset, 0, 0));
+}
+__device__ __forceinline__ floatx4 buffer_float4(Buffer b, uint32_t offset)
+{
+    return __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(b, (int)offset, 0, 0));
 }
 
 // LDS written by some lanes of a wavefront and read by others of the same wavefront.

@@ -12,15 +12,14 @@ namespace ps {
 namespace {
 
 // Sums the partial slots in fixed order into the worker's queue entry: conv1 tensors have one partial
-// per (8 images, wavefront) of conv2's input-gradient kernel, conv2 tensors one per (chunk, wavefront) of its
-// weight-gradient kernel, fc2 tensors, fc1 bias and the loss one per block of the fc2 kernel.
-// Grid (workers, REDUCE_Y) x 256 threads.  The 160 conv1 values have many slots each (128 at 256 images), so
+// per image (of conv2's input-gradient kernel), conv2 tensors one per block of its weight-gradient kernel, fc2 tensors, fc1 bias and the loss one per block of the fc2 kernel.
+// Grid (workers, REDUCE_Y) x 256 threads.  The 160 conv1 values have many slots each (one per image), so
 // a block takes 20 of them with 12 threads per value (thread j adds slots j, j + 12, ... in order, thread 0
 // then adds the 12 sums in order); everything else is one thread per value over the few slots it has.
 constexpr int REDUCE_Y = 8, C1_PER_BLOCK = OFF_W2 / REDUCE_Y, C1_LANES = 12;
 static_assert(C1_PER_BLOCK * REDUCE_Y == OFF_W2 && C1_PER_BLOCK * C1_LANES <= 256, "conv1 values over the blocks");
 
-__global__ __launch_bounds__(256) void grad_reduce_kernel(WorkerBuffers wb, int fc2_slots, int c1_slots)
+__global__ __launch_bounds__(256) void grad_reduce_kernel(WorkerBuffers wb, int fc2_slots, int c1_slots, int c2_slots)
 {
     __shared__ float c1_sum[C1_PER_BLOCK][C1_LANES + 1];
     const int w = blockIdx.x;
@@ -41,13 +40,14 @@ __global__ __launch_bounds__(256) void grad_reduce_kernel(WorkerBuffers wb, int 
             grad[blockIdx.y * C1_PER_BLOCK + threadIdx.x] = sum;
         }
     }
-    const float* part = wb.part + (size_t)w * N_PART * CONV_PART;
+    const float* part = wb.part + (size_t)w * c2_slots * CONV2_PART;
     const int tid = blockIdx.y * 256 + threadIdx.x, stride = REDUCE_Y * 256;
-    for (int i = OFF_W2 + tid; i < CONV_PART; i += stride) {
+    for (int i = tid; i < CONV2_PART; i += stride) {
         float sum = 0.f;
-#pragma unroll
-        for (int c = 0; c < N_PART; ++c) sum += part[(size_t)c * CONV_PART + i];
-        grad[i] = sum;
+        for (int c = 0; c < c2_slots; ++c) sum += part[(size_t)c * CONV2_PART + i];
+        // register r = i / 64 of lane i % 64 of that kernel: tile row mt = r / 36, tap r % 36 / 4
+        const int r = i / 64, o = 16 * (r / 36) + 4 * (i % 64 / 16) + r % 4;
+        grad[i < CONV2_PART_B2 ? OFF_W2 + (o * C1 + i % 16) * 9 + r % 36 / 4 : OFF_B2 + i - CONV2_PART_B2] = sum;
     }
     const float* fpart = wb.fpart + (size_t)w * fc2_slots * FC2_PART;
     for (int i = tid; i <= FC2_PART_LOSS; i += stride) {
@@ -80,6 +80,26 @@ __global__ __launch_bounds__(256) void keep_mask_kernel(uint8_t* keep, int B, ui
 
 }  // namespace
 
+int compute_units()
+{
+    static int cus = 0;
+    if (cus == 0) {
+        int dev = 0;
+        if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
+            cus = 256;
+    }
+    return cus;
+}
+
+// As many (up to `most`) as leave two wavefronts for every SIMD: what a wavefront does once per launch, reading
+// and splitting a filter bank above all, takes up to a quarter of an image's time.
+int images_per_wavefront(int n, int batch, int most)
+{
+    int ipw = most;
+    while (ipw > 1 && n * ((batch + ipw - 1) / ipw) < 2 * 4 * compute_units()) ipw /= 2;
+    return ipw;
+}
+
 #define PS_TIMED(id, ...)      \
     do {                       \
         prof.begin(id, s);     \
@@ -105,7 +125,7 @@ hipError_t launch_worker_backward(const WorkerBuffers& wb, hipStream_t s, Profil
     PS_TIMED(K_CONV2_DW, launch_conv2_dw(wb, s));
     PS_TIMED(K_CONV2_DX, launch_conv2_dx(wb, s));
     PS_TIMED(K_GRAD_REDUCE, hipLaunchKernelGGL(grad_reduce_kernel, dim3(wb.n, REDUCE_Y), dim3(256), 0, s, wb, fc2_split(wb.n),
-                                                conv1_part_slots(wb.B)));
+                                                conv1_part_slots(wb.B), conv2_part_slots(wb.B)));
     return hipGetLastError();
 }
 
