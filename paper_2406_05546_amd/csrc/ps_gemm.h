@@ -1,261 +1,385 @@
-// Batched fp32 GEMM on the gfx950 matrix cores (v_mfma_f32_32x32x2_f32), used for the three
-// contractions of the 1568 -> 512 fully connected layer (forward, input gradient, per-worker
-// weight gradient).
+// Batched fp32 GEMM on the gfx950 bf16 matrix cores with operands split in three (ps_split.h), used for the
+// three contractions of the 1568 -> 512 fully connected layer (forward, input gradient, per-worker weight
+// gradient).
 //
 //   C[m][n] = sum_k A(m,k) * B(n,k)        one problem per batch index z (= worker)
 //
-// Either operand may be stored k-contiguous ("KC": element (r,k) at base[r*ld + k]) or
-// row-contiguous ("RC": element (r,k) at base[k*ld + r]).  A 256-thread block (4 wavefronts arranged
-// WM x WN) owns a (WM*TM*32) x (WN*TN*32) tile of C; each wavefront owns TM x TN MFMA tiles of 32x32.
-// K advances KS at a time through double-buffered LDS, with the global loads running two stages
-// ahead and everything inside the loop straight-line code, so that loads, LDS writes and address
-// updates issue in the shadow of the 64-cycle MFMAs.  Within a stage the contraction index is
-// consumed in the order that lets a lane fetch four consecutive k of a KC operand with one 16-byte
-// LDS read: MFMA step (j,i), j < KS/8, i < 4, pairs lane half h with k = 8j + 4h + i for both
-// operands.
+// Either operand may be stored k-contiguous ("KC": element (r,k) at base[r*ld + k]) or row-contiguous ("RC":
+// element (r,k) at base[k*ld + r]).  A 256-thread block (4 wavefronts arranged WM x WN) owns a (WM*TM*32) x
+// (WN*TN*32) tile of C; each wavefront owns TM x TN MFMA tiles of 32x32.  K advances 16 at a time through
+// double-buffered LDS: a thread loads eight consecutive values (AHEAD + 1 stages ahead), splits them once and
+// writes the three parts with 16-byte stores, so that splitting costs 88 vector instructions per thread and
+// stage next to the wavefront's 24 MFMAs.  The parts of a KC operand lie as [k / 8][row][8 k] and a lane's
+// operand is one 16-byte LDS read; those of an RC operand lie as [k][row], and the transposing LDS read
+// (ds_read_b64_tr_b16: 16 lanes read four k of 16 rows and each gets the four k of its row) turns them.
 //
 // Blocks are numbered so that the blocks of one batch index run next to each other on one XCD (work
 // groups are handed to the 8 XCDs round-robin, each XCD has its own L2): the operand that belongs to
 // the batch index is then fetched from HBM once and re-used out of that L2.
 //
-// The epilogue functor receives four consecutive rows m..m+3 of one column n:
-//   epi(z, m, n, float4 acc, pre)   with m % 4 == 0,
-// where pre = epi.prefetch(z, m, n) was fetched before the K loop (type Epi::Pre; an empty struct if the
-// epilogue needs nothing from memory), so that its latency hides under the whole contraction.
+// The epilogue functor names the operands (a_ptr(z), b_ptr(z)) and receives four consecutive rows m..m+3 of
+// one column n: epi(z, m, n, float4 sums)   with m % 4 == 0.
 #pragma once
 #include "ps_common.h"
+#include "ps_split.h"
 
 namespace ps {
 
-typedef float floatx16 __attribute__((ext_vector_type(16)));
-typedef float floatx4v __attribute__((ext_vector_type(4)));  // first-class vector: stays in registers
-
 constexpr int GEMM_XCDS = 8;
+constexpr int GEMM_KS = 16;  // contraction indices per stage
 
 struct GemmShape {
-    int M, N, K;     // M % 4 == 0; K % 4 == 0 when an operand is KC
+    int M, N, K;     // rows of an RC operand: a multiple of 8; K % 16 == 0 when an operand is KC
     int lda, ldb;
     int gx, gy, gz;  // tiles along M, along N, batch size
     int m_base, n_base;  // origin of the tile grid inside C (a launch may cover only part of C)
 };
 
-// Operand tiles are read with unconditional loads from addresses that are clamped into the operand,
-// so the loop carries no branches and no 64-bit address arithmetic (uniform base + 32-bit offset):
-//   KC operand [nrows][ld]: a row >= nrows reads the last row instead.  It only reaches rows/columns
-//                           of C that are never stored.  K must be a multiple of KS.
-//   RC operand [K][ld]:     four-row groups >= nrows read the last group instead.  If K is not a
-//                           multiple of KS (RAGGED), a k >= K reads k = K-1 and is then replaced by
-//                           zeros, because it is part of the contraction.
-template <int ROWS, int KS, bool KC, bool RAGGED>
+// Operand tiles are read with unconditional loads from addresses that are clamped into the operand, so the
+// loop carries no branches and no 64-bit address arithmetic (uniform base + 32-bit offset): rows past the end
+// repeat the last ones (they only reach rows or columns of C that are never stored); if K is not a multiple
+// of 16 (RAGGED, RC operands only), a k past the end reads k = K-1 and is replaced by zeros.
+template <int ROWS, bool KC, bool RAGGED>
 struct GemmOperand {
-    static constexpr int LD = KC ? KS + 4 : ROWS;           // LDS pitch: padded k-row, or one k-plane of ROWS
-    static constexpr int FLOATS = KC ? ROWS * LD : KS * LD;
-    static constexpr int N4 = ROWS * KS / 4, NV = (N4 + 255) / 256;  // float4 per stage, per thread
+    static_assert(KC ? !RAGGED : true, "KC operands come in whole stages");
+    static constexpr int PIECES = ROWS * GEMM_KS / 8;  // of eight values each; at most one per thread
+    static_assert(PIECES <= 256, "one piece per thread");
+    // KC: the second k / 8 plane starts 64 bytes on, so that four rows of both planes fill all banks on a
+    // write.  RC: 32-byte groups of 16 rows are exchanged by k % 4, so that the four k of a transposing
+    // read lie in different banks.
+    static constexpr int PLANE8 = ROWS * 16 + 64;                            // KC: bytes of one k / 8 plane
+    static constexpr int PART = KC ? 2 * PLANE8 : GEMM_KS * ROWS * 2, BYTES = 3 * PART;
+    static constexpr int SWAP = ROWS / 16 - 1 < 3 ? ROWS / 16 - 1 : 3;
 
     const float* base;
-    uint32_t off[NV];     // float offset of this thread's float4 i in stage 0
-    uint32_t last[NV];    // RC only: the same element at k = K-1
-    uint32_t stage_step;  // float distance between consecutive stages
+    uint32_t off, stage_step;  // float offset of this thread's piece in stage 0; floats between stages
+    int k0, k_last, ld;        // RC: k of the piece in stage 0
 
-    __device__ __forceinline__ void init(const float* b, int ld, int row0, int nrows, int K, int tid)
+    __device__ __forceinline__ void init(const float* b, int ld_, int row0, int nrows, int K, int tid)
     {
+        const int f = min(tid, PIECES - 1);
         base = b;
-        stage_step = KC ? KS : KS * ld;
-#pragma unroll
-        for (int i = 0; i < NV; ++i) {
-            const int f = min(tid + 256 * i, N4 - 1);  // threads without an element repeat the last one
-            if (KC) {
-                off[i] = (uint32_t)min(row0 + f / (KS / 4), nrows - 1) * ld + (f % (KS / 4)) * 4;
-                last[i] = 0;
-            } else {
-                const uint32_t row = min(row0 + (f % (ROWS / 4)) * 4, nrows - 4);
-                off[i] = (uint32_t)(f / (ROWS / 4)) * ld + row;
-                last[i] = (uint32_t)(K - 1) * ld + row;
-            }
+        ld = ld_;
+        k_last = K - 1;
+        stage_step = KC ? GEMM_KS : GEMM_KS * ld;
+        if (KC) {
+            k0 = 0;
+            off = (uint32_t)min(row0 + f / 2, nrows - 1) * ld + (f & 1) * 8;
+        } else {
+            k0 = f / (ROWS / 8);
+            off = (uint32_t)min(row0 + f % (ROWS / 8) * 8, nrows - 8);
+            if (!RAGGED) off += (uint32_t)k0 * ld;
         }
     }
 
     // Global -> registers for stage kt.
-    __device__ __forceinline__ void load(int kt, floatx4v (&r)[NV]) const
+    __device__ __forceinline__ void load(int kt, floatx4 (&r)[2]) const
     {
-        const uint32_t so = (uint32_t)kt * stage_step;
+        uint32_t o = off;
+        bool inside = true;
+        if (RAGGED) {
+            const int k = kt * GEMM_KS + k0;
+            inside = k <= k_last;
+            o += (uint32_t)min(k, k_last) * ld;
+        } else {
+            o += (uint32_t)kt * stage_step;
+        }
 #pragma unroll
-        for (int i = 0; i < NV; ++i) {
-            if (KC || !RAGGED) {
-                r[i] = *reinterpret_cast<const floatx4v*>(base + so + off[i]);
-            } else {
-                const uint32_t o = off[i] + so;
-                const floatx4v v = *reinterpret_cast<const floatx4v*>(base + min(o, last[i]));
-                r[i] = o > last[i] ? floatx4v{0.f, 0.f, 0.f, 0.f} : v;
-            }
+        for (int i = 0; i < 2; ++i) {
+            r[i] = *reinterpret_cast<const floatx4*>(base + o + 4 * i);
+            if (RAGGED) r[i] = inside ? r[i] : floatx4{0.f, 0.f, 0.f, 0.f};
         }
     }
 
-    static __device__ __forceinline__ void store(float* __restrict__ tile, int tid, const floatx4v (&r)[NV])
+    static __device__ __forceinline__ void store(char* __restrict__ tile, int tid, const floatx4 (&r)[2])
     {
+        const float v[8] = {r[0][0], r[0][1], r[0][2], r[0][3], r[1][0], r[1][1], r[1][2], r[1][3]};
+        const Split8 s = split8(v);
+        int at;
+        if (KC) {
+            at = (tid & 1) * PLANE8 + tid / 2 * 16;
+        } else {
+            const int k = tid / (ROWS / 8), r8 = tid % (ROWS / 8);
+            at = k * ROWS * 2 + ((r8 / 2) ^ (k & SWAP)) * 32 + r8 % 2 * 16;
+        }
+        if (PIECES == 256 || tid < PIECES) {
 #pragma unroll
-        for (int i = 0; i < NV; ++i) {
-            const int f = tid + 256 * i;
-            const int at = KC ? (f / (KS / 4)) * LD + (f % (KS / 4)) * 4 : (f / (ROWS / 4)) * LD + (f % (ROWS / 4)) * 4;
-            if (256 * (i + 1) <= N4 || f < N4) *reinterpret_cast<floatx4v*>(tile + at) = r[i];
+            for (int i = 0; i < 3; ++i) *reinterpret_cast<uintx4*>(tile + i * PART + at) = s.p[i];
         }
     }
 
-    // The four operand values (i = 0..3) a lane feeds to MFMA steps (j, 0..3) for tile row `row`.
-    static __device__ __forceinline__ floatx4v fetch(const float* __restrict__ tile, int row, int j, int h)
+    // The operand of rows 32 * rt .. +31: lane (h, l32) gets k = 8h .. 8h + 7 of row l32.
+    static __device__ __forceinline__ Split8 fetch(const char* __restrict__ tile, int rt, int lane)
     {
-        if (KC) return *reinterpret_cast<const floatx4v*>(tile + row * LD + 8 * j + 4 * h);
-        const float* p = tile + (8 * j + 4 * h) * LD + row;
-        return floatx4v{p[0], p[LD], p[2 * LD], p[3 * LD]};
+        Split8 s;
+        if (KC) {
+            const char* p = tile + (lane >> 5) * PLANE8 + (32 * rt + (lane & 31)) * 16;
+#pragma unroll
+            for (int i = 0; i < 3; ++i) s.p[i] = *reinterpret_cast<const uintx4*>(p + i * PART);
+        } else {
+            typedef short shortx4 __attribute__((ext_vector_type(4)));
+            typedef uint32_t uintx2 __attribute__((ext_vector_type(2)));
+            const int t = lane & 15, k = 8 * (lane >> 5) + (t >> 2), group = (2 * rt + (lane >> 4 & 1)) ^ ((t >> 2) & SWAP);
+            const char* p = tile + k * ROWS * 2 + group * 32 + (t & 3) * 8;
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {  // k and k + 4
+                    typedef __attribute__((address_space(3))) shortx4* LdsPtr;
+                    const shortx4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LdsPtr)(shortx4*)(p + i * PART + j * 4 * ROWS * 2));
+                    const uintx2 d = __builtin_bit_cast(uintx2, v);
+                    s.p[i][2 * j] = d[0];
+                    s.p[i][2 * j + 1] = d[1];
+                }
+        }
+        return s;
     }
 };
+
+// One element of C with fp32 FMAs (see ps_split.h).
+template <bool A_KC, bool B_KC>
+__device__ __forceinline__ float gemm_plain(const GemmShape& sh, const float* __restrict__ A, const float* __restrict__ B, int m, int n)
+{
+    float sum = 0.f;
+#pragma unroll 1
+    for (int k = 0; k < sh.K; ++k)
+        sum = fmaf(A[A_KC ? (size_t)m * sh.lda + k : (size_t)k * sh.lda + m], B[B_KC ? (size_t)n * sh.ldb + k : (size_t)k * sh.ldb + n], sum);
+    return sum;
+}
+
+// Hands rows m .. m + 3 of column n to the epilogue.
+template <bool A_KC, bool B_KC, class Epi>
+__device__ __forceinline__ void gemm_store(const GemmShape& sh, const Epi& epi, int z, int m, int n, float v0, float v1, float v2, float v3)
+{
+    if (m >= sh.M || n >= sh.N) return;
+    float4 v = make_float4(v0, v1, v2, v3);
+    if (__builtin_isunordered(v0, v1) || __builtin_isunordered(v2, v3)) {
+        const float* A = epi.a_ptr(z);
+        const float* B = epi.b_ptr(z);
+        v = make_float4(gemm_plain<A_KC, B_KC>(sh, A, B, m, n), gemm_plain<A_KC, B_KC>(sh, A, B, m + 1, n),
+                        gemm_plain<A_KC, B_KC>(sh, A, B, m + 2, n), gemm_plain<A_KC, B_KC>(sh, A, B, m + 3, n));
+    }
+    epi(z, m, n, v);
+}
+
+// Stores one 32x32 tile of sums at (m0, n0): register i of lane (h, l32) is row 8*(i/4) + 4*h + i%4, column l32.
+template <bool A_KC, bool B_KC, class Epi>
+__device__ __forceinline__ void gemm_finish(const GemmShape& sh, const Epi& epi, int z, int m0, int n0, int lane, const floatx16& acc)
+{
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+        gemm_store<A_KC, B_KC>(sh, epi, z, m0 + 8 * g + 4 * (lane >> 5), n0 + (lane & 31), acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]);
+}
 
 // Tile configuration of one launch.
-template <bool A_KC_, bool B_KC_, int TM_, int TN_, int WM_, int WN_, int KS_>
+template <bool A_KC_, bool B_KC_, int TM_, int TN_, int WM_, int WN_, int AHEAD_>
 struct GemmCfg {
     static constexpr bool A_KC = A_KC_, B_KC = B_KC_;
-    static constexpr int TM = TM_, TN = TN_, WM = WM_, WN = WN_, KS = KS_;
+    static constexpr int TM = TM_, TN = TN_, WM = WM_, WN = WN_, AHEAD = AHEAD_;
     static constexpr int BM = WM * TM * 32, BN = WN * TN * 32;
     static_assert(WM * WN == 4, "four wavefronts per block");
-    template <bool RAGGED>
-    static constexpr int lds_floats()  // one of the two stage buffers
-    {
-        return GemmOperand<BM, KS, A_KC, RAGGED>::FLOATS + GemmOperand<BN, KS, B_KC, RAGGED>::FLOATS;
-    }
+    static constexpr int STAGE = GemmOperand<BM, A_KC, false>::BYTES + GemmOperand<BN, B_KC, false>::BYTES;  // one of the two stage buffers
 };
 
-// One block's tile: `block` of `sh.gx * sh.gy * sh.gz` (rounded up to the XCD count), stage buffers in lds.
-template <class Cfg, bool RAGGED, class Epi>
-__device__ __forceinline__ void gemm_block(const GemmShape& sh, const Epi& epi, int block, float* __restrict__ lds)
+// Where block `block` of a launch over `total` tiles works: XCD x (= block number mod 8) walks a contiguous
+// range of (z, y, x) triples.
+__device__ __forceinline__ int gemm_tile(int block, int total)
 {
-    constexpr bool A_KC = Cfg::A_KC, B_KC = Cfg::B_KC;
-    constexpr int TM = Cfg::TM, TN = Cfg::TN, WM = Cfg::WM, KS = Cfg::KS, BM = Cfg::BM, BN = Cfg::BN;
-    using OpA = GemmOperand<BM, KS, A_KC, RAGGED>;
-    using OpB = GemmOperand<BN, KS, B_KC, RAGGED>;
-    constexpr int STAGE = OpA::FLOATS + OpB::FLOATS;
+    const int per_xcd = (total + GEMM_XCDS - 1) / GEMM_XCDS;
+    return block % GEMM_XCDS * per_xcd + block / GEMM_XCDS;
+}
 
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
-    const int h = lane >> 5, l32 = lane & 31;
+// One block's tile: `block` of `sh.gx * sh.gy * sh.gz` (rounded up to the XCD count), stage buffers in lds.
+// CHUNK > 0: the sum is formed as the sum, in order, of the sums over CHUNK stages each.  The order in which a
+// value's products are added up depends on CHUNK alone, not on the tile shape.
+template <class Cfg, bool RAGGED, int CHUNK, class Epi>
+__device__ __forceinline__ void gemm_block(const GemmShape& sh, const Epi& epi, int block, char* __restrict__ lds)
+{
+    constexpr int TM = Cfg::TM, TN = Cfg::TN, WM = Cfg::WM, BM = Cfg::BM, BN = Cfg::BN;
+    using OpA = GemmOperand<BM, Cfg::A_KC, RAGGED>;
+    using OpB = GemmOperand<BN, Cfg::B_KC, RAGGED>;
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
     const int wm = wave % WM, wn = wave / WM;
-
-    // XCD-aware numbering: XCD x (= linear id mod 8) walks a contiguous range of (z, y, x) triples.
-    const int total = sh.gx * sh.gy * sh.gz, per_xcd = (total + GEMM_XCDS - 1) / GEMM_XCDS;
-    const int v = (block % GEMM_XCDS) * per_xcd + block / GEMM_XCDS;
-    if (v >= total) return;
+    const int v = gemm_tile(block, sh.gx * sh.gy * sh.gz);
+    if (v >= sh.gx * sh.gy * sh.gz) return;
     const int m0 = sh.m_base + (v % sh.gx) * BM, n0 = sh.n_base + (v / sh.gx % sh.gy) * BN, z = v / (sh.gx * sh.gy);
-    const float* __restrict__ A = epi.a_ptr(z);
-    const float* __restrict__ B = epi.b_ptr(z);
 
-    floatx16 acc[TM][TN];
-    typename Epi::Pre pre[TM][TN][4];
+    SplitSum<floatx16> acc[TM][TN];
+    floatx16 total[TM][TN];
 #pragma unroll
     for (int a = 0; a < TM; ++a)
 #pragma unroll
         for (int b = 0; b < TN; ++b) {
-#pragma unroll
-            for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
-            const int n = n0 + (wn * TN + b) * 32 + l32;
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int m = m0 + (wm * TM + a) * 32 + 8 * g + 4 * h;
-                pre[a][b][g] = (m < sh.M && n < sh.N) ? epi.prefetch(z, m, n) : typename Epi::Pre{};
-            }
+            acc[a][b].clear();
+            total[a][b] = acc[a][b].big;
         }
 
-    // Three-deep pipeline: while the matrix cores consume stage kt out of one LDS buffer, stage kt+1
-    // (loaded from HBM/L2 during the previous iteration) is written into the other buffer half way
-    // through, and the loads of stage kt+2 are issued right behind that write.
-    floatx4v ra[OpA::NV], rb[OpB::NV];
-    const int nk = (sh.K + KS - 1) / KS;
+    // Pipeline: while the matrix cores consume stage kt out of one LDS buffer, stage kt + 1 is split and written
+    // into the other, out of one of AHEAD register sets, which then takes the loads of stage kt + 1 + AHEAD.
+    constexpr int AHEAD = Cfg::AHEAD;
+    floatx4 ra[AHEAD][2], rb[AHEAD][2];
+    const int nk = (sh.K + GEMM_KS - 1) / GEMM_KS;
     OpA opa;
     OpB opb;
-    opa.init(A, sh.lda, m0, sh.M, sh.K, tid);
-    opb.init(B, sh.ldb, n0, sh.N, sh.K, tid);
+    opa.init(epi.a_ptr(z), sh.lda, m0, sh.M, sh.K, tid);
+    opb.init(epi.b_ptr(z), sh.ldb, n0, sh.N, sh.K, tid);
     {
-        floatx4v ra0[OpA::NV], rb0[OpB::NV];  // stages 0 and 1 are in flight together
+        floatx4 ra0[2], rb0[2];
         opa.load(0, ra0);
         opb.load(0, rb0);
-        opa.load(min(1, nk - 1), ra);
-        opb.load(min(1, nk - 1), rb);
+#pragma unroll
+        for (int i = 0; i < AHEAD; ++i) {
+            opa.load(min(1 + i, nk - 1), ra[i]);
+            opb.load(min(1 + i, nk - 1), rb[i]);
+        }
         OpA::store(lds, tid, ra0);
-        OpB::store(lds + OpA::FLOATS, tid, rb0);
+        OpB::store(lds + OpA::BYTES, tid, rb0);
     }
     __syncthreads();
 
-    for (int kt = 0; kt < nk; ++kt) {
-        const int cur = kt & 1;
-        const float* ta = lds + cur * STAGE;
-        const float* tb = ta + OpA::FLOATS;
-        float* na = lds + (cur ^ 1) * STAGE;
+    static_assert(AHEAD % 2 == 0, "the LDS buffer of an unrolled stage is fixed");
+    for (int kt0 = 0; kt0 < nk; kt0 += AHEAD) {
 #pragma unroll
-        for (int j = 0; j < KS / 8; ++j) {
-            floatx4v fa[TM], fb[TN];
+        for (int u = 0; u < AHEAD; ++u) {
+            const int kt = kt0 + u;
+            if (u > 0 && kt >= nk) break;
+            const char* ta = lds + (u & 1) * Cfg::STAGE;
+            char* na = lds + (~u & 1) * Cfg::STAGE;
+            Split8 fa[TM], fb[TN];
 #pragma unroll
-            for (int a = 0; a < TM; ++a) fa[a] = OpA::fetch(ta, (wm * TM + a) * 32 + l32, j, h);
+            for (int a = 0; a < TM; ++a) fa[a] = OpA::fetch(ta, wm * TM + a, lane);
 #pragma unroll
-            for (int b = 0; b < TN; ++b) fb[b] = OpB::fetch(tb, (wn * TN + b) * 32 + l32, j, h);
+            for (int b = 0; b < TN; ++b) fb[b] = OpB::fetch(ta + OpA::BYTES, wn * TN + b, lane);
+            // unconditional on purpose (straight-line code): past the end the last stage is simply loaded and
+            // stored again where nobody reads it
+            OpA::store(na, tid, ra[u]);
+            OpB::store(na + OpA::BYTES, tid, rb[u]);
+            opa.load(min(kt + 1 + AHEAD, nk - 1), ra[u]);
+            opb.load(min(kt + 1 + AHEAD, nk - 1), rb[u]);
 #pragma unroll
-            for (int a = 0; a < TM; ++a)
+            for (int t = 0; t <= SPLIT_SMALL; ++t)
 #pragma unroll
-                for (int b = 0; b < TN; ++b) {
-                    acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[a].x, fb[b].x, acc[a][b], 0, 0, 0);
-                    acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[a].y, fb[b].y, acc[a][b], 0, 0, 0);
-                    acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[a].z, fb[b].z, acc[a][b], 0, 0, 0);
-                    acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[a].w, fb[b].w, acc[a][b], 0, 0, 0);
-                }
-            if (j == KS / 16 - 1) {
-                // unconditional on purpose (straight-line code schedules under the MFMAs): past the
-                // end the last stage is simply loaded and stored again where nobody reads it
-                OpA::store(na, tid, ra);
-                OpB::store(na + OpA::FLOATS, tid, rb);
-                opa.load(min(kt + 2, nk - 1), ra);
-                opb.load(min(kt + 2, nk - 1), rb);
+                for (int a = 0; a < TM; ++a)
+#pragma unroll
+                    for (int b = 0; b < TN; ++b) acc[a][b].add(t, fa[a], fb[b]);
+            if (CHUNK > 0 && (kt + 1) % (CHUNK > 0 ? CHUNK : 1) == 0) {
+#pragma unroll
+                for (int a = 0; a < TM; ++a)
+#pragma unroll
+                    for (int b = 0; b < TN; ++b) {
+                        total[a][b] += acc[a][b].value();
+                        acc[a][b].clear();
+                    }
             }
+            __syncthreads();
         }
-        __syncthreads();
     }
-
-    // Accumulator register i of lane (h, l32) holds C[8*(i/4) + 4*h + i%4][l32] of its 32x32 tile.
 #pragma unroll
     for (int a = 0; a < TM; ++a)
 #pragma unroll
-        for (int b = 0; b < TN; ++b) {
-            const int n = n0 + (wn * TN + b) * 32 + l32;
+        for (int b = 0; b < TN; ++b)
+            gemm_finish<Cfg::A_KC, Cfg::B_KC>(sh, epi, z, m0 + (wm * TM + a) * 32, n0 + (wn * TN + b) * 32, lane, CHUNK > 0 ? total[a][b] : acc[a][b].value());
+}
+
+// The same sums for a launch with too few tiles to fill the chip: a block owns one 32x32 tile and its wavefronts
+// one CHUNK of stages each, every wavefront with its operands straight from memory; the chunks' sums meet in
+// LDS and are added up in order, so that a value is bit for bit what gemm_block<..., CHUNK> makes of it.
+template <bool KC>
+struct GemmLane {  // the operand rows of one lane
+    const float* p;
+    int ld;
+    __device__ __forceinline__ void init(const float* b, int ld_, int row, int nrows, int lane)
+    {
+        ld = ld_;
+        row = min(row, nrows - 1);
+        p = KC ? b + (size_t)row * ld + 8 * (lane >> 5) : b + (size_t)(8 * (lane >> 5)) * ld + row;
+    }
+    __device__ __forceinline__ void load(int kt, float (&v)[8]) const
+    {
+        if (KC) {
+            const floatx4* q = reinterpret_cast<const floatx4*>(p + (size_t)kt * GEMM_KS);
+            const floatx4 a = q[0], b = q[1];
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int m = m0 + (wm * TM + a) * 32 + 8 * g + 4 * h;
-                if (m < sh.M && n < sh.N)
-                    epi(z, m, n,
-                        make_float4(acc[a][b][4 * g], acc[a][b][4 * g + 1], acc[a][b][4 * g + 2], acc[a][b][4 * g + 3]),
-                        pre[a][b][g]);
+            for (int j = 0; j < 4; ++j) {
+                v[j] = a[j];
+                v[4 + j] = b[j];
             }
+        } else {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] = p[((size_t)kt * GEMM_KS + j) * ld];
         }
+    }
+};
+
+template <bool A_KC, bool B_KC, int CHUNKS, int CHUNK, class Epi>
+__global__ __launch_bounds__(64 * CHUNKS) void gemm_split_chunks(GemmShape sh, Epi epi)
+{
+    static_assert(CHUNKS >= 4, "four wavefronts store the tile");
+    __shared__ float part[CHUNKS][16][64];
+    const int lane = threadIdx.x & 63, wave = uniform(threadIdx.x >> 6);
+    const int t = gemm_tile(blockIdx.x, sh.gx * sh.gy * sh.gz);
+    if (t >= sh.gx * sh.gy * sh.gz) return;
+    const int m0 = t % sh.gx * 32, n0 = t / sh.gx % sh.gy * 32, z = t / (sh.gx * sh.gy);
+    GemmLane<A_KC> la;
+    GemmLane<B_KC> lb;
+    la.init(epi.a_ptr(z), sh.lda, m0 + (lane & 31), sh.M, lane);
+    lb.init(epi.b_ptr(z), sh.ldb, n0 + (lane & 31), sh.N, lane);
+    SplitSum<floatx16> sum;
+    sum.clear();
+    const int k0 = wave * CHUNK;
+    constexpr int AHEAD = 2;  // stages in flight
+    float a[AHEAD][8], b[AHEAD][8];
+#pragma unroll
+    for (int i = 0; i < AHEAD; ++i) {
+        la.load(k0 + i, a[i]);
+        lb.load(k0 + i, b[i]);
+    }
+#pragma unroll
+    for (int kt = 0; kt < CHUNK; ++kt) {
+        const Split8 sa = split8(a[kt % AHEAD]), sb = split8(b[kt % AHEAD]);
+        if (kt + AHEAD < CHUNK) {
+            la.load(k0 + kt + AHEAD, a[kt % AHEAD]);
+            lb.load(k0 + kt + AHEAD, b[kt % AHEAD]);
+        }
+        sum.add(sa, sb);
+    }
+    const floatx16 acc = sum.value();
+#pragma unroll
+    for (int i = 0; i < 16; ++i) part[wave][i][lane] = acc[i];
+    __syncthreads();
+    if (wave >= 4) return;
+    float v[4];  // wavefront g stores rows 8g + 4h .. +3
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        v[i] = part[0][4 * wave + i][lane];
+#pragma unroll
+        for (int c = 1; c < CHUNKS; ++c) v[i] += part[c][4 * wave + i][lane];
+    }
+    gemm_store<A_KC, B_KC>(sh, epi, z, m0 + 8 * wave + 4 * (lane >> 5), n0 + (lane & 31), v[0], v[1], v[2], v[3]);
 }
 
 constexpr int gemm_grid(const GemmShape& sh) { return (sh.gx * sh.gy * sh.gz + GEMM_XCDS - 1) / GEMM_XCDS * GEMM_XCDS; }
 
-template <class Cfg, bool RAGGED, int MINW, class Epi>
-__global__ __launch_bounds__(256, MINW) void gemm_f32_mfma(GemmShape sh, Epi epi)
+template <class Cfg, bool RAGGED, int CHUNK, int MINW, class Epi>
+__global__ __launch_bounds__(256, MINW) void gemm_split(GemmShape sh, Epi epi)
 {
-    __shared__ __attribute__((aligned(16))) float lds[2 * Cfg::template lds_floats<RAGGED>()];
-    gemm_block<Cfg, RAGGED>(sh, epi, blockIdx.x, lds);
+    __shared__ __attribute__((aligned(16))) char lds[2 * Cfg::STAGE];
+    gemm_block<Cfg, RAGGED, CHUNK>(sh, epi, blockIdx.x, lds);
 }
 
 // Two tile shapes in one launch: the first `main_blocks` blocks cover the main part of C with Main tiles,
 // the rest cover an edge strip with Edge tiles.  The edge blocks are dispatched last and run next to the
 // last main blocks instead of as a launch of their own behind them.
-template <class Main, class Edge, bool RAGGED, int MINW, class Epi>
-__global__ __launch_bounds__(256, MINW) void gemm_f32_mfma_edge(GemmShape sh_main, GemmShape sh_edge, int main_blocks, Epi epi)
+template <class Main, class Edge, bool RAGGED, int CHUNK, int MINW, class Epi>
+__global__ __launch_bounds__(256, MINW) void gemm_split_edge(GemmShape sh_main, GemmShape sh_edge, int main_blocks, Epi epi)
 {
-    constexpr int LDS = Main::template lds_floats<RAGGED>() > Edge::template lds_floats<RAGGED>()
-                            ? Main::template lds_floats<RAGGED>()
-                            : Edge::template lds_floats<RAGGED>();
-    __shared__ __attribute__((aligned(16))) float lds[2 * LDS];
+    constexpr int STAGE = Main::STAGE > Edge::STAGE ? Main::STAGE : Edge::STAGE;
+    __shared__ __attribute__((aligned(16))) char lds[2 * STAGE];
     if ((int)blockIdx.x < main_blocks)  // uniform over the block
-        gemm_block<Main, RAGGED>(sh_main, epi, blockIdx.x, lds);
+        gemm_block<Main, RAGGED, CHUNK>(sh_main, epi, blockIdx.x, lds);
     else
-        gemm_block<Edge, RAGGED>(sh_edge, epi, blockIdx.x - main_blocks, lds);
+        gemm_block<Edge, RAGGED, CHUNK>(sh_edge, epi, blockIdx.x - main_blocks, lds);
 }
 
 template <class Cfg>
@@ -267,35 +391,43 @@ GemmShape gemm_shape(int M, int N, int K, int lda, int ldb, int batch, int m_beg
 
 // One problem per batch index, all of C covered with Cfg tiles over a 1-D grid padded to a multiple of
 // the XCD count.
-template <class Cfg, int MINW, class Epi>
+template <class Cfg, int CHUNK, int MINW, class Epi>
 void gemm_launch(int M, int N, int K, int lda, int ldb, int batch, const Epi& epi, hipStream_t s)
 {
     if (M <= 0 || N <= 0 || batch <= 0) return;
     const GemmShape sh = gemm_shape<Cfg>(M, N, K, lda, ldb, batch, 0, M, 0, N);
-    if (K % Cfg::KS == 0)
-        hipLaunchKernelGGL((gemm_f32_mfma<Cfg, false, MINW, Epi>), dim3(gemm_grid(sh)), dim3(256), 0, s, sh, epi);
+    constexpr bool CAN_BE_RAGGED = !Cfg::A_KC && !Cfg::B_KC;
+    if (!CAN_BE_RAGGED || K % GEMM_KS == 0)
+        hipLaunchKernelGGL((gemm_split<Cfg, false, CHUNK, MINW, Epi>), dim3(gemm_grid(sh)), dim3(256), 0, s, sh, epi);
     else
-        hipLaunchKernelGGL((gemm_f32_mfma<Cfg, true, MINW, Epi>), dim3(gemm_grid(sh)), dim3(256), 0, s, sh, epi);
+        hipLaunchKernelGGL((gemm_split<Cfg, CAN_BE_RAGGED, CHUNK, MINW, Epi>), dim3(gemm_grid(sh)), dim3(256), 0, s, sh, epi);
+}
+
+// One problem per batch index in 32x32 tiles, K = CHUNKS * CHUNK stages.
+template <bool A_KC, bool B_KC, int CHUNKS, int CHUNK, class Epi>
+void gemm_launch_chunks(int M, int N, int lda, int ldb, int batch, const Epi& epi, hipStream_t s)
+{
+    if (M <= 0 || N <= 0 || batch <= 0) return;
+    const GemmShape sh{M, N, CHUNKS * CHUNK * GEMM_KS, lda, ldb, (M + 31) / 32, (N + 31) / 32, batch, 0, 0};
+    hipLaunchKernelGGL((gemm_split_chunks<A_KC, B_KC, CHUNKS, CHUNK, Epi>), dim3(gemm_grid(sh)), dim3(64 * CHUNKS), 0, s, sh, epi);
 }
 
 // Rows [0, m_split) x columns [0, n_split) of C with Main tiles and the rest with Edge tiles, where exactly
 // one of the splits is inside C (the other equals M or N) and is a multiple of Main's tile: covering a
 // ragged edge with narrow tiles avoids a mostly empty wide tile.
-template <class Main, class Edge, int MINW, class Epi>
+template <class Main, class Edge, int CHUNK, int MINW, class Epi>
 void gemm_launch_edge(int M, int N, int K, int lda, int ldb, int batch, int m_split, int n_split, const Epi& epi, hipStream_t s)
 {
-    static_assert(Main::KS == Edge::KS, "one K step for both tile shapes");
     if (M <= 0 || N <= 0 || batch <= 0) return;
     const GemmShape sh_main = gemm_shape<Main>(M, N, K, lda, ldb, batch, 0, m_split, 0, n_split);
     const GemmShape sh_edge = m_split < M ? gemm_shape<Edge>(M, N, K, lda, ldb, batch, m_split, M, 0, N)
                                           : gemm_shape<Edge>(M, N, K, lda, ldb, batch, 0, M, n_split, N);
     const int main_blocks = gemm_grid(sh_main), grid = main_blocks + gemm_grid(sh_edge);
-    if (K % Main::KS == 0)
-        hipLaunchKernelGGL((gemm_f32_mfma_edge<Main, Edge, false, MINW, Epi>), dim3(grid), dim3(256), 0, s, sh_main, sh_edge,
-                           main_blocks, epi);
+    constexpr bool CAN_BE_RAGGED = !Main::A_KC && !Main::B_KC;
+    if (!CAN_BE_RAGGED || K % GEMM_KS == 0)
+        hipLaunchKernelGGL((gemm_split_edge<Main, Edge, false, CHUNK, MINW, Epi>), dim3(grid), dim3(256), 0, s, sh_main, sh_edge, main_blocks, epi);
     else
-        hipLaunchKernelGGL((gemm_f32_mfma_edge<Main, Edge, true, MINW, Epi>), dim3(grid), dim3(256), 0, s, sh_main, sh_edge,
-                           main_blocks, epi);
+        hipLaunchKernelGGL((gemm_split_edge<Main, Edge, CAN_BE_RAGGED, CHUNK, MINW, Epi>), dim3(grid), dim3(256), 0, s, sh_main, sh_edge, main_blocks, epi);
 }
 
 }  // namespace ps
