@@ -12,55 +12,67 @@ namespace ps {
 namespace {
 
 // Sums the partial slots in fixed order into the worker's queue entry: conv1 tensors have one partial
-// per image (of conv2's input-gradient kernel), conv2 tensors one per block of its weight-gradient kernel, fc2 tensors, fc1 bias and the loss one per block of the fc2 kernel.
-// Grid (workers, REDUCE_Y) x 256 threads.  The 160 conv1 values have many slots each (one per image), so
-// a block takes 20 of them with 12 threads per value (thread j adds slots j, j + 12, ... in order, thread 0
-// then adds the 12 sums in order); everything else is one thread per value over the few slots it has.
-constexpr int REDUCE_Y = 8, C1_PER_BLOCK = OFF_W2 / REDUCE_Y, C1_LANES = 12;
-static_assert(C1_PER_BLOCK * REDUCE_Y == OFF_W2 && C1_PER_BLOCK * C1_LANES <= 256, "conv1 values over the blocks");
+// per image (of conv2's input-gradient kernel), conv2 tensors one per block of its weight-gradient kernel, fc2
+// tensors, fc1 bias and the loss one per block of the fc2 kernel.  Nothing but memory latency at few workers:
+// the up to 16 slots of a conv2 or fc2 value are loaded together by one thread; the 160 conv1 values have a slot
+// per image and get C1_LANES threads each (thread j adds slots j, j + 8, ... in order, 16 loads in flight, and
+// the 8 sums are added in order), 32 values to each of the first 5 blocks of a worker.  How many blocks a worker
+// gets does not change any sum.
+constexpr int REDUCE_SLOTS = 16, C1_LANES = 8, C1_VALUES = 32, C1_BLOCKS = OFF_W2 / C1_VALUES;
+static_assert(C1_VALUES * C1_BLOCKS == OFF_W2 && C1_VALUES * C1_LANES == 256, "conv1 values over the first blocks");
+constexpr int REDUCE_ITEMS = CONV2_PART + FC2_PART_LOSS + 1;  // conv2 values, then fc2's
+
+// p[0] + p[step] + ... in order, `count` values
+__device__ __forceinline__ float ordered_sum(const float* __restrict__ p, size_t step, int count)
+{
+    float sum = 0.f;
+    for (int c0 = 0; c0 < count; c0 += REDUCE_SLOTS) {
+        float v[REDUCE_SLOTS];
+#pragma unroll
+        for (int c = 0; c < REDUCE_SLOTS; ++c) v[c] = p[(size_t)min(c0 + c, count - 1) * step];
+#pragma unroll
+        for (int c = 0; c < REDUCE_SLOTS; ++c)
+            if (c0 + c < count) sum += v[c];
+    }
+    return sum;
+}
 
 __global__ __launch_bounds__(256) void grad_reduce_kernel(WorkerBuffers wb, int fc2_slots, int c1_slots, int c2_slots)
 {
-    __shared__ float c1_sum[C1_PER_BLOCK][C1_LANES + 1];
+    __shared__ float c1_sum[C1_LANES][C1_VALUES];
     const int w = blockIdx.x;
     float* grad = worker_grad(wb, w);
-    {
-        const int e = threadIdx.x / C1_LANES, j = threadIdx.x % C1_LANES;
-        if (e < C1_PER_BLOCK) {
-            const float* p1 = wb.part1 + (size_t)w * c1_slots * OFF_W2 + blockIdx.y * C1_PER_BLOCK + e;
-            float sum = 0.f;
-            for (int c = j; c < c1_slots; c += C1_LANES) sum += p1[(size_t)c * OFF_W2];
-            c1_sum[e][j] = sum;
-        }
+    if (blockIdx.y < C1_BLOCKS) {
+        const int e = threadIdx.x % C1_VALUES, j = threadIdx.x / C1_VALUES, v = blockIdx.y * C1_VALUES + e;
+        c1_sum[j][e] = ordered_sum(wb.part1 + ((size_t)w * c1_slots + j) * OFF_W2 + v, C1_LANES * OFF_W2, (c1_slots - j + C1_LANES - 1) / C1_LANES);
         __syncthreads();
-        if (threadIdx.x < C1_PER_BLOCK) {
+        if (j == 0) {
             float sum = 0.f;
 #pragma unroll
-            for (int j2 = 0; j2 < C1_LANES; ++j2) sum += c1_sum[threadIdx.x][j2];
-            grad[blockIdx.y * C1_PER_BLOCK + threadIdx.x] = sum;
+            for (int k = 0; k < C1_LANES; ++k) sum += c1_sum[k][e];
+            grad[v] = sum;
         }
     }
     const float* part = wb.part + (size_t)w * c2_slots * CONV2_PART;
-    const int tid = blockIdx.y * 256 + threadIdx.x, stride = REDUCE_Y * 256;
-    for (int i = tid; i < CONV2_PART; i += stride) {
-        float sum = 0.f;
-        for (int c = 0; c < c2_slots; ++c) sum += part[(size_t)c * CONV2_PART + i];
-        // register r = i / 64 of lane i % 64 of that kernel: tile row mt = r / 36, tap r % 36 / 4
-        const int r = i / 64, o = 16 * (r / 36) + 4 * (i % 64 / 16) + r % 4;
-        grad[i < CONV2_PART_B2 ? OFF_W2 + (o * C1 + i % 16) * 9 + r % 36 / 4 : OFF_B2 + i - CONV2_PART_B2] = sum;
-    }
     const float* fpart = wb.fpart + (size_t)w * fc2_slots * FC2_PART;
-    for (int i = tid; i <= FC2_PART_LOSS; i += stride) {
-        float sum = 0.f;
-        for (int c = 0; c < fc2_slots; ++c) sum += fpart[(size_t)c * FC2_PART + i];
-        if (i < FC2_PART_B4)
-            grad[OFF_W4 + i] = sum;
-        else if (i < FC2_PART_B3)
-            grad[OFF_B4 + i - FC2_PART_B4] = sum;
-        else if (i < FC2_PART_LOSS)
-            grad[OFF_B3 + i - FC2_PART_B3] = sum;
-        else if (wb.loss)
-            wb.loss[w] = sum / (float)wb.B;
+    for (int i = blockIdx.y * 256 + threadIdx.x; i < REDUCE_ITEMS; i += gridDim.y * 256) {
+        if (i < CONV2_PART) {
+            const float sum = ordered_sum(part + i, CONV2_PART, c2_slots);
+            // register r = i / 64 of lane i % 64 of that kernel: tile row mt = r / 36, tap r % 36 / 4
+            const int r = i / 64, o = 16 * (r / 36) + 4 * (i % 64 / 16) + r % 4;
+            grad[i < CONV2_PART_B2 ? OFF_W2 + (o * C1 + i % 16) * 9 + r % 36 / 4 : OFF_B2 + i - CONV2_PART_B2] = sum;
+        } else {
+            const int f = i - CONV2_PART;
+            const float sum = ordered_sum(fpart + f, FC2_PART, fc2_slots);
+            if (f < FC2_PART_B4)
+                grad[OFF_W4 + f] = sum;
+            else if (f < FC2_PART_B3)
+                grad[OFF_B4 + f - FC2_PART_B4] = sum;
+            else if (f < FC2_PART_LOSS)
+                grad[OFF_B3 + f - FC2_PART_B3] = sum;
+            else if (wb.loss)
+                wb.loss[w] = sum / (float)wb.B;
+        }
     }
 }
 
@@ -124,7 +136,9 @@ hipError_t launch_worker_backward(const WorkerBuffers& wb, hipStream_t s, Profil
     PS_TIMED(K_FC1_DX, launch_fc1_dx(wb, s));
     PS_TIMED(K_CONV2_DW, launch_conv2_dw(wb, s));
     PS_TIMED(K_CONV2_DX, launch_conv2_dx(wb, s));
-    PS_TIMED(K_GRAD_REDUCE, hipLaunchKernelGGL(grad_reduce_kernel, dim3(wb.n, REDUCE_Y), dim3(256), 0, s, wb, fc2_split(wb.n),
+    // one value per thread while the chip has room, at least the blocks that the conv1 values take
+    const int reduce_y = wb.n * (REDUCE_ITEMS / 256 + 1) <= 8 * compute_units() ? REDUCE_ITEMS / 256 + 1 : 8;
+    PS_TIMED(K_GRAD_REDUCE, hipLaunchKernelGGL(grad_reduce_kernel, dim3(wb.n, reduce_y), dim3(256), 0, s, wb, fc2_split(wb.n),
                                                 conv1_part_slots(wb.B), conv2_part_slots(wb.B)));
     return hipGetLastError();
 }
