@@ -21,6 +21,7 @@ static_assert(PS_PARAM_COUNT == P, "header and kernels disagree on the parameter
 namespace {
 
 constexpr int N_STAGE = 4;  // pinned host staging buffers for per-call index / metadata uploads
+constexpr int EVAL_HOST_IMAGES = 1 << 16;  // largest evaluation whose results have pinned host memory of their own
 constexpr int N_HEADRB = 8;  // read-backs of the store's consumed count in flight
 
 struct Entry {
@@ -121,6 +122,10 @@ struct ps_ctx {
     size_t stage_bytes = 0;
     Profiler prof;
     std::string err;
+    // Pinned host memory that an evaluation's last kernel writes: sums per block, predicted classes.
+    EvalSums* eval_sums = nullptr;
+    int32_t* eval_pred = nullptr;
+    int eval_capacity = 0;  // images
 
     // Lock-free store: the server stream, and what the host knows of the device-side counters.
     hipStream_t server = nullptr;
@@ -170,12 +175,29 @@ ps_status upload(ps_ctx* c, void* dst_dev, const void* src, size_t bytes)
     return PS_OK;
 }
 
+// The rows of `idx` as a launch takes them: consecutive ones by their first, others as an uploaded list.
+ps_status row_list(ps_ctx* c, const std::vector<int32_t>& idx, RowList* rows)
+{
+    bool consecutive = true;
+    for (size_t k = 1; k < idx.size(); ++k) consecutive = consecutive && idx[k] == idx[0] + (int32_t)k;
+    *rows = RowList{consecutive ? nullptr : c->at<int32_t>(c->lay.idx), idx[0]};
+    return consecutive ? PS_OK : upload(c, c->at<int32_t>(c->lay.idx), idx.data(), idx.size() * sizeof(int32_t));
+}
+
 ps_status apply_entries(ps_ctx* c, const std::vector<int32_t>& idx, float lr, int mode)
 {
-    ps_status st = upload(c, c->at<int32_t>(c->lay.idx), idx.data(), idx.size() * sizeof(int32_t));
+    RowList rows;
+    ps_status st = row_list(c, idx, &rows);
     if (st != PS_OK) return st;
-    PS_HIP(c, launch_apply(c->theta(), c->at<float>(c->lay.queue), c->at<int32_t>(c->lay.idx), (int)idx.size(), lr,
-                           mode, c->stream, c->prof));
+    PS_HIP(c, launch_apply(c->theta(), c->at<float>(c->lay.queue), rows, (int)idx.size(), lr, mode, c->stream, c->prof));
+    return PS_OK;
+}
+
+// Metadata of the call to the device: with the first kernel's arguments if they fit, else by upload.
+ps_status send_meta(ps_ctx* c, WorkerBuffers* wb)
+{
+    if (wb->n > META_IN_ARGS) return upload(c, wb->meta, c->last_meta.data(), sizeof(WorkerMeta) * wb->n);
+    wb->meta_host = c->last_meta.data();
     return PS_OK;
 }
 
@@ -212,6 +234,8 @@ WorkerBuffers buffers(const ps_ctx* c, int n, const float* x, const int32_t* y, 
     wb.ring = c->at<float>(c->lay.ring);
     wb.queue = c->at<float>(c->lay.queue);
     wb.meta = c->at<WorkerMeta>(c->lay.meta);
+    wb.meta_host = nullptr;
+    wb.all_slot = PER_WORKER;
     wb.x = x;
     wb.y = y;
     wb.p1 = c->at<float>(c->lay.p1);
@@ -371,6 +395,9 @@ ps_status ps_init(ps_ctx** out, const ps_config* cfg, void* workspace_dev, uint6
         e = hipHostMalloc(&c->stage[i].host, c->stage_bytes, hipHostMallocDefault);
         if (e == hipSuccess) e = hipEventCreateWithFlags(&c->stage[i].done, hipEventDisableTiming);
     }
+    c->eval_capacity = (int)std::min<int64_t>((int64_t)cfg->max_workers * cfg->batch, EVAL_HOST_IMAGES);
+    if (e == hipSuccess) e = hipHostMalloc((void**)&c->eval_sums, sizeof(EvalSums) * eval_blocks(c->eval_capacity), hipHostMallocDefault);
+    if (e == hipSuccess) e = hipHostMalloc((void**)&c->eval_pred, sizeof(int32_t) * c->eval_capacity, hipHostMallocDefault);
     // the drain entry point that allocates nothing finds its scratch array resolved on this device
     if (e == hipSuccess) {
         unsigned char* unused = nullptr;
@@ -401,6 +428,8 @@ ps_status ps_destroy(ps_ctx* c)
     for (HeadReadback& r : c->headrb)
         if (r.done) (void)hipEventDestroy(r.done);
     if (c->headrb_host) (void)hipHostFree(c->headrb_host);
+    if (c->eval_sums) (void)hipHostFree(c->eval_sums);
+    if (c->eval_pred) (void)hipHostFree(c->eval_pred);
     for (hipEvent_t ev : c->ev_slot_read)
         if (ev) (void)hipEventDestroy(ev);
     for (hipEvent_t ev : c->ev_slot_written)
@@ -484,9 +513,9 @@ ps_status worker_grads_batched(ps_ctx* c, int32_t n, const int32_t* worker_id_ho
         queue_index_host[i] = q;
         c->last_meta[i] = WorkerMeta{slot, q, (uint32_t)mb, (uint32_t)(mb >> 32)};
     }
-    ps_status st = upload(c, c->at<WorkerMeta>(c->lay.meta), c->last_meta.data(), sizeof(WorkerMeta) * n);
+    WorkerBuffers wb = buffers(c, n, x_dev, y_dev, loss_dev);
+    const ps_status st = send_meta(c, &wb);
     if (st != PS_OK) return st;
-    const WorkerBuffers wb = buffers(c, n, x_dev, y_dev, loss_dev);
     PS_HIP(c, launch_worker_forward(wb, c->stream, c->prof));
     PS_HIP(c, launch_worker_backward(wb, c->stream, c->prof));
     return PS_OK;
@@ -568,10 +597,10 @@ ps_status ps_drain_buffered_mitigated(ps_ctx* c, int32_t mode, const ps_drain_po
     if (lr_used_host) *lr_used_host = lr;
     if (idx.empty()) return PS_OK;
     if (pol->clip_norm > 0.f) {
-        ps_status st = upload(c, c->at<int32_t>(c->lay.idx), idx.data(), idx.size() * sizeof(int32_t));
+        RowList rows;
+        ps_status st = row_list(c, idx, &rows);
         if (st != PS_OK) return st;
-        PS_HIP(c, launch_apply_clipped(c->theta(), c->at<float>(c->lay.queue), c->at<int32_t>(c->lay.idx), (int)idx.size(),
-                                       lr, mode, pol->clip_norm, c->at<float>(c->lay.normpart), c->at<float>(c->lay.scale),
+        PS_HIP(c, launch_apply_clipped(c->theta(), c->at<float>(c->lay.queue), rows, (int)idx.size(), lr, mode, pol->clip_norm, c->at<float>(c->lay.normpart), c->at<float>(c->lay.scale),
                                        c->stream, c->prof));
     } else {
         ps_status st = apply_entries(c, idx, lr, mode);
@@ -619,16 +648,17 @@ ps_status worker_grads_append(ps_ctx* c, int32_t n, const int32_t* worker_id_hos
         c->last_meta[i] = WorkerMeta{version_slot_host[i], row, (uint32_t)mb, (uint32_t)(mb >> 32)};
     }
     const StoreBuffers sb = store_buffers(c);
-    WorkerMeta* meta_dev = c->at<WorkerMeta>(c->lay.meta);
-    st = upload(c, meta_dev, c->last_meta.data(), sizeof(WorkerMeta) * n);
+    WorkerBuffers wb = buffers(c, n, x_dev, y_dev, loss_dev);
+    st = send_meta(c, &wb);
     if (st != PS_OK) return st;
-    st = upload(c, sb.worker_id, worker_id_host, sizeof(int32_t) * n);
-    if (st != PS_OK) return st;
+    if (n > STORE_IDS_IN_ARGS) {
+        st = upload(c, sb.worker_id, worker_id_host, sizeof(int32_t) * n);
+        if (st != PS_OK) return st;
+    }
     c->store_claimed += (uint64_t)n;
-    const WorkerBuffers wb = buffers(c, n, x_dev, y_dev, loss_dev);
     PS_HIP(c, launch_worker_forward(wb, c->stream, c->prof));
     PS_HIP(c, launch_worker_backward(wb, c->stream, c->prof));
-    PS_HIP(c, launch_store_publish(sb, meta_dev, n, c->stream));
+    PS_HIP(c, launch_store_publish(sb, wb.meta, worker_id_host, n, c->stream));
     for (int32_t s : slots) {
         PS_HIP(c, hipEventRecord(c->ev_slot_read[s], c->stream));
         c->slot_read_valid[s] = 1;
@@ -651,7 +681,7 @@ ps_status ps_store_consume(ps_ctx* c, int32_t mode, float lr, int32_t max_entrie
     }
     const StoreBuffers sb = store_buffers(c);
     PS_HIP(c, launch_store_take(sb, limit, c->server));
-    PS_HIP(c, launch_apply(c->theta(), c->at<float>(c->lay.queue), sb.idx, limit, lr, mode, c->server, c->prof, &sb.range->count));
+    PS_HIP(c, launch_apply(c->theta(), c->at<float>(c->lay.queue), RowList{sb.idx, 0}, limit, lr, mode, c->server, c->prof, &sb.range->count));
     PS_HIP(c, launch_store_release(sb, mode, c->server));
     HeadReadback& r = c->headrb[c->next_headrb];
     unsigned long long* dst = c->headrb_host + c->next_headrb;
@@ -824,10 +854,11 @@ ps_status ps_drain_buffered_adadelta(ps_ctx* c, float lr, float rho, float eps, 
     const std::vector<int32_t> idx = c->pending;
     if (n_applied_host) *n_applied_host = (int32_t)idx.size();
     if (idx.empty()) return PS_OK;
-    ps_status st = upload(c, c->at<int32_t>(c->lay.idx), idx.data(), idx.size() * sizeof(int32_t));
+    RowList rows;
+    ps_status st = row_list(c, idx, &rows);
     if (st != PS_OK) return st;
     PS_HIP(c, launch_apply_adadelta(c->theta(), c->at<float>(c->lay.ada_g2), c->at<float>(c->lay.ada_dx2),
-                                    c->at<float>(c->lay.queue), c->at<int32_t>(c->lay.idx), (int)idx.size(), lr, rho, eps,
+                                    c->at<float>(c->lay.queue), rows, (int)idx.size(), lr, rho, eps,
                                     c->stream, c->prof));
     release_entries(c, idx);
     c->version += idx.size();
@@ -899,11 +930,9 @@ ps_status ps_evaluate(ps_ctx* c, int32_t slot, int32_t n_images, const float* x_
         return fail(c, PS_EINVAL, "ps_evaluate: null or misaligned input");
     const int n = n_images / B;
     PS_HIP(c, hipStreamSynchronize(c->server));
-    std::vector<WorkerMeta> meta(n, WorkerMeta{slot, 0, 0, 0});
     c->last_meta.clear();  // the activations of the last worker call are overwritten
-    ps_status st = upload(c, c->at<WorkerMeta>(c->lay.meta), meta.data(), sizeof(WorkerMeta) * n);
-    if (st != PS_OK) return st;
     WorkerBuffers wb = buffers(c, n, x_dev, y_dev, nullptr);
+    wb.all_slot = slot;
     wb.drop_threshold = 0;  // inference: nothing is dropped, nothing is rescaled
     wb.drop_scale = 1.f;
     launch_conv1_fwd(wb, c->stream);
@@ -911,17 +940,29 @@ ps_status ps_evaluate(ps_ctx* c, int32_t slot, int32_t n_images, const float* x_
     launch_fc1_fwd(wb, c->stream);
     launch_fc2_eval(wb, c->at<float>(c->lay.eval_loss), c->at<int32_t>(c->lay.eval_ok), c->stream);
     PS_HIP(c, hipGetLastError());
-    std::vector<float> loss(n_images);
-    std::vector<int32_t> ok(n_images);
-    PS_HIP(c, hipMemcpyAsync(loss.data(), c->at<float>(c->lay.eval_loss), sizeof(float) * n_images, hipMemcpyDeviceToHost, c->stream));
-    PS_HIP(c, hipMemcpyAsync(ok.data(), c->at<int32_t>(c->lay.eval_ok), sizeof(int32_t) * n_images, hipMemcpyDeviceToHost, c->stream));
-    if (pred_host) PS_HIP(c, hipMemcpyAsync(pred_host, c->at<int32_t>(c->lay.pred), sizeof(int32_t) * n_images, hipMemcpyDeviceToHost, c->stream));
-    PS_HIP(c, hipStreamSynchronize(c->stream));
     double ls = 0.0;
     int64_t hits = 0;
-    for (int i = 0; i < n_images; ++i) {
-        ls += loss[i];
-        hits += ok[i];
+    if (n_images <= c->eval_capacity) {
+        // the results go straight to host memory, from a kernel: copies to memory of the caller's cost 40 us each
+        PS_HIP(c, launch_eval_collect(n_images, c->at<float>(c->lay.eval_loss), c->at<int32_t>(c->lay.eval_ok), wb.pred, c->eval_sums,
+                                      pred_host ? c->eval_pred : nullptr, c->stream));
+        PS_HIP(c, hipStreamSynchronize(c->stream));
+        for (int i = 0; i < eval_blocks(n_images); ++i) {
+            ls += c->eval_sums[i].loss;
+            hits += c->eval_sums[i].correct;
+        }
+        if (pred_host) std::memcpy(pred_host, c->eval_pred, sizeof(int32_t) * n_images);
+    } else {
+        std::vector<float> loss(n_images);
+        std::vector<int32_t> ok(n_images);
+        PS_HIP(c, hipMemcpyAsync(loss.data(), c->at<float>(c->lay.eval_loss), sizeof(float) * n_images, hipMemcpyDeviceToHost, c->stream));
+        PS_HIP(c, hipMemcpyAsync(ok.data(), c->at<int32_t>(c->lay.eval_ok), sizeof(int32_t) * n_images, hipMemcpyDeviceToHost, c->stream));
+        if (pred_host) PS_HIP(c, hipMemcpyAsync(pred_host, c->at<int32_t>(c->lay.pred), sizeof(int32_t) * n_images, hipMemcpyDeviceToHost, c->stream));
+        PS_HIP(c, hipStreamSynchronize(c->stream));
+        for (int i = 0; i < n_images; ++i) {
+            ls += loss[i];
+            hits += ok[i];
+        }
     }
     if (loss_host) *loss_host = ls / n_images;
     if (accuracy_host) *accuracy_host = (double)hits / n_images;

@@ -10,10 +10,9 @@
 static_assert(PS_ROW_FLOATS == ps::PSTRIDE, "header and kernels disagree on the row pitch");
 
 // Fixed scratch memory of the drain entry point that allocates nothing (ps_drain_rows_mitigated, at the
-// end of this file): row list int32 [rows] | clip factors float [rows] | partial sums of the squared
-// norms float [rows][32].  Every GPU the process uses holds its own copy at its own address; in host
+// end of this file): clip factors float [rows] | partial sums of the squared norms float [rows][32].  Every GPU the process uses holds its own copy at its own address; in host
 // code this name is only a handle for hipGetSymbolAddress, never a device address.
-#define PS_STATIC_SCRATCH_BYTES ((size_t)PS_STATIC_DRAIN_MAX_ROWS * (4 + 4 + 4 * 32))  /* 557,056 */
+#define PS_STATIC_SCRATCH_BYTES ((size_t)PS_STATIC_DRAIN_MAX_ROWS * (4 + 4 * 32))  /* 540,672 */
 static __device__ __align__(256) unsigned char scratch[PS_STATIC_SCRATCH_BYTES];
 
 namespace ps {
@@ -43,11 +42,20 @@ __device__ __forceinline__ void st_stream(float4* p, float4 x)
     __builtin_nontemporal_store(v, reinterpret_cast<v4f*>(p));
 }
 
+// Queue rows in the order in which they are applied: listed in device memory, or (LISTED = false, list null)
+// consecutive from `first` on, which is what a queue handed out lowest index first nearly always holds and saves
+// the upload of a list: an asynchronous apply is 4 us of kernel, the copy in front of it another 4 us and 5 us of
+// waiting for it.
+template <bool LISTED>
+__device__ __forceinline__ size_t row_of(const RowList& rows, int k)
+{
+    return (size_t)(LISTED ? rows.list[k] : rows.first + k) * ROW4;
+}
+
 // SCALED: gradient k is multiplied by scale[k] first (norm clipping of stale gradients).
-template <int MODE, bool SCALED>
+template <int MODE, bool SCALED, bool LISTED>
 __global__ __launch_bounds__(APPLY_BLOCK) void apply_kernel(float4* __restrict__ theta, const float4* __restrict__ queue,
-                                                     const int32_t* __restrict__ idx, int K, float lr,
-                                                     const float* __restrict__ scale,
+                                                     RowList rows, int K, float lr, const float* __restrict__ scale,
                                                      const uint32_t* __restrict__ K_dev)
 {
     const int i = blockIdx.x * APPLY_BLOCK + threadIdx.x;
@@ -60,7 +68,7 @@ __global__ __launch_bounds__(APPLY_BLOCK) void apply_kernel(float4* __restrict__
     for (; k + UNROLL <= K; k += UNROLL) {
         float4 g[UNROLL];
 #pragma unroll
-        for (int u = 0; u < UNROLL; ++u) g[u] = ld_stream(col + (size_t)idx[k + u] * ROW4);
+        for (int u = 0; u < UNROLL; ++u) g[u] = ld_stream(col + row_of<LISTED>(rows, k + u));
 #pragma unroll
         for (int u = 0; u < UNROLL; ++u) {
             const float c = SCALED ? scale[k + u] : 1.f;
@@ -79,7 +87,7 @@ __global__ __launch_bounds__(APPLY_BLOCK) void apply_kernel(float4* __restrict__
         }
     }
     for (; k < K; ++k) {
-        float4 g = ld_stream(col + (size_t)idx[k] * ROW4);
+        float4 g = ld_stream(col + row_of<LISTED>(rows, k));
         const float c = SCALED ? scale[k] : 1.f;
         if (MODE == 0) {
             s.x = fmaf(c, g.x, s.x); s.y = fmaf(c, g.y, s.y);
@@ -101,10 +109,10 @@ __global__ __launch_bounds__(APPLY_BLOCK) void apply_kernel(float4* __restrict__
 // plain drain: a lane keeps its four weights and their two accumulators in registers while the rows
 // stream past.  The quotient sqrt(E[dx^2] + eps) / sqrt(E[g^2] + eps) is formed with the hardware's
 // square root and reciprocal square root (about 1 ulp each), which keeps the kernel bandwidth bound.
+template <bool LISTED>
 __global__ __launch_bounds__(APPLY_BLOCK) void apply_adadelta_kernel(float4* __restrict__ theta, float4* __restrict__ acc_g2,
                                                               float4* __restrict__ acc_dx2, const float4* __restrict__ queue,
-                                                              const int32_t* __restrict__ idx, int K, float lr, float rho,
-                                                              float eps)
+                                                              RowList rows, int K, float lr, float rho, float eps)
 {
     const int i = blockIdx.x * APPLY_BLOCK + threadIdx.x;
     if (i >= ROW4) return;
@@ -131,11 +139,11 @@ __global__ __launch_bounds__(APPLY_BLOCK) void apply_adadelta_kernel(float4* __r
     for (; k + UNROLL <= K; k += UNROLL) {
         float4 g[UNROLL];
 #pragma unroll
-        for (int u = 0; u < UNROLL; ++u) g[u] = ld_stream(col + (size_t)idx[k + u] * ROW4);
+        for (int u = 0; u < UNROLL; ++u) g[u] = ld_stream(col + row_of<LISTED>(rows, k + u));
 #pragma unroll
         for (int u = 0; u < UNROLL; ++u) step(g[u]);
     }
-    for (; k < K; ++k) step(ld_stream(col + (size_t)idx[k] * ROW4));
+    for (; k < K; ++k) step(ld_stream(col + row_of<LISTED>(rows, k)));
     theta[i] = make_float4(t[0], t[1], t[2], t[3]);
     acc_g2[i] = make_float4(g2[0], g2[1], g2[2], g2[3]);
     acc_dx2[i] = make_float4(dx2[0], dx2[1], dx2[2], dx2[3]);
@@ -185,13 +193,13 @@ __global__ __launch_bounds__(APPLY_BLOCK) void elastic_average_kernel(float4* __
 // (the row padding is zero) and writes one partial; fixed slices and a fixed tree keep it reproducible.
 constexpr int NORM_SLICES = 32;
 
-__global__ __launch_bounds__(256) void grad_sqnorm_kernel(const float4* __restrict__ queue, const int32_t* __restrict__ idx,
-                                                          float* __restrict__ partial)
+template <bool LISTED>
+__global__ __launch_bounds__(256) void grad_sqnorm_kernel(const float4* __restrict__ queue, RowList rows, float* __restrict__ partial)
 {
     __shared__ float red[4];
     const int k = blockIdx.y, b = blockIdx.x;
     constexpr int PER = (ROW4 + NORM_SLICES - 1) / NORM_SLICES;
-    const float4* row = queue + (size_t)idx[k] * ROW4;
+    const float4* row = queue + row_of<LISTED>(rows, k);
     const int end = min(ROW4, (b + 1) * PER);
     float acc = 0.f;
     for (int i = b * PER + threadIdx.x; i < end; i += 256) {
@@ -219,49 +227,57 @@ __global__ __launch_bounds__(256) void clip_scale_kernel(const float* __restrict
 
 }  // namespace
 
-hipError_t launch_apply(float* theta, const float* queue, const int32_t* idx_dev, int K, float lr, int mode,
-                        hipStream_t s, Profiler& prof, const uint32_t* K_dev)
+namespace {
+
+const dim3 APPLY_GRID((ROW4 + APPLY_BLOCK - 1) / APPLY_BLOCK);
+
+template <int MODE, bool SCALED>
+void start_apply(float* theta, const float* queue, const RowList& rows, int K, float lr, const float* scale, const uint32_t* K_dev, hipStream_t s)
+{
+    auto kernel = rows.list ? apply_kernel<MODE, SCALED, true> : apply_kernel<MODE, SCALED, false>;
+    hipLaunchKernelGGL(kernel, APPLY_GRID, dim3(APPLY_BLOCK), 0, s, (float4*)theta, (const float4*)queue, rows, K, lr, scale, K_dev);
+}
+
+}  // namespace
+
+hipError_t launch_apply(float* theta, const float* queue, const RowList& rows, int K, float lr, int mode, hipStream_t s, Profiler& prof,
+                        const uint32_t* K_dev)
 {
     if (K <= 0) return hipSuccess;
-    dim3 grid((ROW4 + APPLY_BLOCK - 1) / APPLY_BLOCK), block(APPLY_BLOCK);
     prof.begin(mode == 0 ? K_APPLY_SUM : K_APPLY_SEQ, s);
     if (mode == 0)
-        hipLaunchKernelGGL((apply_kernel<0, false>), grid, block, 0, s, (float4*)theta, (const float4*)queue, idx_dev, K, lr,
-                           (const float*)nullptr, K_dev);
+        start_apply<0, false>(theta, queue, rows, K, lr, nullptr, K_dev, s);
     else
-        hipLaunchKernelGGL((apply_kernel<1, false>), grid, block, 0, s, (float4*)theta, (const float4*)queue, idx_dev, K, lr,
-                           (const float*)nullptr, K_dev);
+        start_apply<1, false>(theta, queue, rows, K, lr, nullptr, K_dev, s);
     prof.end(s);
     return hipGetLastError();
 }
 
-hipError_t launch_apply_clipped(float* theta, const float* queue, const int32_t* idx_dev, int K, float lr, int mode,
-                                float clip, float* partial_dev, float* scale_dev, hipStream_t s, Profiler& prof)
+hipError_t launch_apply_clipped(float* theta, const float* queue, const RowList& rows, int K, float lr, int mode, float clip,
+                                float* partial_dev, float* scale_dev, hipStream_t s, Profiler& prof)
 {
     if (K <= 0) return hipSuccess;
     prof.begin(K_GRAD_SQNORM, s);
-    hipLaunchKernelGGL(grad_sqnorm_kernel, dim3(NORM_SLICES, K), dim3(256), 0, s, (const float4*)queue, idx_dev, partial_dev);
+    hipLaunchKernelGGL(rows.list ? grad_sqnorm_kernel<true> : grad_sqnorm_kernel<false>, dim3(NORM_SLICES, K), dim3(256), 0, s,
+                       (const float4*)queue, rows, partial_dev);
     prof.end(s);
     hipLaunchKernelGGL(clip_scale_kernel, dim3((K + 255) / 256), dim3(256), 0, s, partial_dev, scale_dev, K, clip);
-    dim3 grid((ROW4 + APPLY_BLOCK - 1) / APPLY_BLOCK), block(APPLY_BLOCK);
     prof.begin(mode == 0 ? K_APPLY_SUM_CLIP : K_APPLY_SEQ_CLIP, s);
     if (mode == 0)
-        hipLaunchKernelGGL((apply_kernel<0, true>), grid, block, 0, s, (float4*)theta, (const float4*)queue, idx_dev, K, lr,
-                           (const float*)scale_dev, (const uint32_t*)nullptr);
+        start_apply<0, true>(theta, queue, rows, K, lr, scale_dev, nullptr, s);
     else
-        hipLaunchKernelGGL((apply_kernel<1, true>), grid, block, 0, s, (float4*)theta, (const float4*)queue, idx_dev, K, lr,
-                           (const float*)scale_dev, (const uint32_t*)nullptr);
+        start_apply<1, true>(theta, queue, rows, K, lr, scale_dev, nullptr, s);
     prof.end(s);
     return hipGetLastError();
 }
 
-hipError_t launch_apply_adadelta(float* theta, float* acc_g2, float* acc_dx2, const float* queue, const int32_t* idx_dev,
-                                 int K, float lr, float rho, float eps, hipStream_t s, Profiler& prof)
+hipError_t launch_apply_adadelta(float* theta, float* acc_g2, float* acc_dx2, const float* queue, const RowList& rows, int K, float lr,
+                                 float rho, float eps, hipStream_t s, Profiler& prof)
 {
     if (K <= 0) return hipSuccess;
     prof.begin(K_APPLY_ADADELTA, s);
-    hipLaunchKernelGGL(apply_adadelta_kernel, dim3((ROW4 + APPLY_BLOCK - 1) / APPLY_BLOCK), dim3(APPLY_BLOCK), 0, s, (float4*)theta, (float4*)acc_g2,
-                       (float4*)acc_dx2, (const float4*)queue, idx_dev, K, lr, rho, eps);
+    hipLaunchKernelGGL(rows.list ? apply_adadelta_kernel<true> : apply_adadelta_kernel<false>, APPLY_GRID, dim3(APPLY_BLOCK), 0, s, (float4*)theta,
+                       (float4*)acc_g2, (float4*)acc_dx2, (const float4*)queue, rows, K, lr, rho, eps);
     prof.end(s);
     return hipGetLastError();
 }
@@ -292,25 +308,17 @@ int norm_slices() { return NORM_SLICES; }
 
 // ---------------------------------------------------------------------------------------------
 // Drain for callers that cannot allocate.  What the context's workspace holds for the mitigated drain
-// (the row list, the per-slice partial sums of the squared norms, the clip factors) lives here in a
+// (the per-slice partial sums of the squared norms, the clip factors) lives here in a
 // fixed array in device memory instead; every GPU of the process has its own copy at its own address.
 namespace {
 
 constexpr int STATIC_MAX_ROWS = PS_STATIC_DRAIN_MAX_ROWS;
-constexpr size_t STATIC_IDX_OFF = 0;                                                   // int32 [rows]
-constexpr size_t STATIC_SCALE_OFF = STATIC_IDX_OFF + sizeof(int32_t) * STATIC_MAX_ROWS;  // float [rows]
+constexpr size_t STATIC_SCALE_OFF = 0;                                                  // float [rows]
 constexpr size_t STATIC_PART_OFF = STATIC_SCALE_OFF + sizeof(float) * STATIC_MAX_ROWS;   // float [rows][NORM_SLICES]
 static_assert(STATIC_PART_OFF + sizeof(float) * STATIC_MAX_ROWS * NORM_SLICES == PS_STATIC_SCRATCH_BYTES, "scratch array size");
 
 constexpr int MAX_DEVICES = 64;
 unsigned char* scratch_of_device[MAX_DEVICES] = {};  // device address of `scratch` on each GPU, once resolved
-
-// rows are taken in the order they lie in memory: idx[k] = k
-__global__ __launch_bounds__(256) void row_list_kernel(int32_t* __restrict__ idx, int n)
-{
-    const int k = blockIdx.x * 256 + threadIdx.x;
-    if (k < n) idx[k] = k;
-}
 
 thread_local char static_error[160] = "";
 
@@ -363,17 +371,16 @@ extern "C" ps_status ps_drain_rows_mitigated(float* theta_dev, const float* grad
     unsigned char* base = nullptr;
     if (static_scratch(&base) != hipSuccess)
         return static_fail(PS_EDEVICE, "ps_drain_rows_mitigated: the address of the static scratch array could not be resolved");
-    int32_t* idx = reinterpret_cast<int32_t*>(base + STATIC_IDX_OFF);
     float* scale = reinterpret_cast<float*>(base + STATIC_SCALE_OFF);
     float* partial = reinterpret_cast<float*>(base + STATIC_PART_OFF);
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     static Profiler no_timing;  // never enabled
-    // Nothing in the array has to start at zero: the row list, every partial sum and every clip factor of
-    // the rows in use are written before they are read.
-    hipLaunchKernelGGL(row_list_kernel, dim3((n_rows + 255) / 256), dim3(256), 0, s, idx, (int)n_rows);
+    // Nothing in the array has to start at zero: every partial sum and every clip factor of the rows in use
+    // are written before they are read.
+    const RowList rows{nullptr, 0};
     hipError_t e = pol->clip_norm > 0.f
-                       ? launch_apply_clipped(theta_dev, grads_dev, idx, n_rows, lr, mode, pol->clip_norm, partial, scale, s, no_timing)
-                       : launch_apply(theta_dev, grads_dev, idx, n_rows, lr, mode, s, no_timing);
+                       ? launch_apply_clipped(theta_dev, grads_dev, rows, n_rows, lr, mode, pol->clip_norm, partial, scale, s, no_timing)
+                       : launch_apply(theta_dev, grads_dev, rows, n_rows, lr, mode, s, no_timing);
     if (e != hipSuccess) return static_fail(PS_EDEVICE, hipGetErrorString(e));
     return PS_OK;
 }

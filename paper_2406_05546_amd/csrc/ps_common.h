@@ -24,6 +24,8 @@ constexpr int PSTRIDE = 813312;
 // Partial slots of the conv2 weight gradient: d W2 as conv2_dw_kernel's registers hold it, then d b2.
 constexpr int CONV2_PART_B2 = C2 * C1 * 9, CONV2_PART = CONV2_PART_B2 + C2;
 
+constexpr int PER_WORKER = -2;  // WorkerBuffers::all_slot: every worker has a slot of its own
+
 constexpr int AM1_GATE = 0x80;  // pool1 window byte: winner's pre-activation > 0
 
 // One worker of a batched call.
@@ -34,11 +36,21 @@ struct WorkerMeta {
     uint32_t mb_hi;
 };
 
+// The metadata of a call with few workers travels in the kernel arguments: conv1 reads it there and writes it to
+// device memory for the kernels behind it.
+constexpr int META_IN_ARGS = 128;
+template <int N>
+struct MetaArgs {
+    WorkerMeta m[N];
+};
+
 // Device buffers of one batched worker step; activations are indexed by global image g = w*B + s.
 struct WorkerBuffers {
     const float* ring;   // [V][PSTRIDE]
     float* queue;        // [cap][PSTRIDE]
-    const WorkerMeta* meta;  // [n]
+    WorkerMeta* meta;    // [n]
+    const WorkerMeta* meta_host;  // [n] in host memory if meta is still to be filled from it, else null
+    int32_t all_slot;    // ring slot that every worker reads (the metadata is then not used for it), or PER_WORKER
     const float* x;      // [n*B][784]
     const int32_t* y;    // [n*B]
     float* p1;           // [n*B][196][16]  conv1 -> ReLU -> pool
@@ -66,7 +78,7 @@ struct WorkerBuffers {
 __device__ __forceinline__ const float* worker_theta(const WorkerBuffers& wb, int w)
 {
     // slot -1 is the server's current weights, which sit one row before the ring
-    return wb.ring + (ptrdiff_t)wb.meta[w].slot * PSTRIDE;
+    return wb.ring + (ptrdiff_t)(wb.all_slot != PER_WORKER ? wb.all_slot : wb.meta[w].slot) * PSTRIDE;
 }
 __device__ __forceinline__ float* worker_grad(const WorkerBuffers& wb, int w)
 {
@@ -101,6 +113,17 @@ void launch_fc1_dw(const WorkerBuffers& wb, hipStream_t s);
 void launch_fc1_dx(const WorkerBuffers& wb, hipStream_t s);
 void launch_fc2(const WorkerBuffers& wb, hipStream_t s);
 void launch_fc2_eval(const WorkerBuffers& wb, float* loss_i, int32_t* correct, hipStream_t s);
+
+// What 256 images of an evaluation add to its results.
+struct EvalSums {
+    double loss;
+    int64_t correct;
+};
+inline int eval_blocks(int n_images) { return (n_images + 255) / 256; }
+// Per-image results to host memory that the GPU can write: sums[eval_blocks(n_images)], pred_out[n_images] unless null.
+hipError_t launch_eval_collect(int n_images, const float* loss_i, const int32_t* correct, const int32_t* pred, EvalSums* sums,
+                               int32_t* pred_out, hipStream_t s);
+
 void launch_conv2_fwd(const WorkerBuffers& wb, hipStream_t s);
 void launch_conv2_dx(const WorkerBuffers& wb, hipStream_t s);
 void launch_conv2_dw(const WorkerBuffers& wb, hipStream_t s);
@@ -138,14 +161,20 @@ hipError_t launch_worker_backward(const WorkerBuffers& wb, hipStream_t s, Profil
 hipError_t launch_keep_mask(uint8_t* keep_dev, int B, uint32_t mb_lo, uint32_t mb_hi, uint32_t seed_lo,
                             uint32_t seed_hi, uint32_t threshold, hipStream_t s);
 
-// theta -= lr * (sum of the K listed queue rows) [mode 0] or K successive updates [mode 1].
+// Queue rows to apply, in order: list[0 .. K) in device memory, or with list null first, first + 1, ...
+struct RowList {
+    const int32_t* list;
+    int32_t first;
+};
+
+// theta -= lr * (sum of the K rows) [mode 0] or K successive updates [mode 1].
 // With K_dev the number of rows is read from device memory by the kernel (at most K_max).
-hipError_t launch_apply(float* theta, const float* queue, const int32_t* idx_dev, int K, float lr, int mode,
-                        hipStream_t s, Profiler& prof, const uint32_t* K_dev = nullptr);
+hipError_t launch_apply(float* theta, const float* queue, const RowList& rows, int K, float lr, int mode, hipStream_t s, Profiler& prof,
+                        const uint32_t* K_dev = nullptr);
 
 // Same with every gradient first scaled by min(1, clip / ||g||_2): a norm pass, then the apply pass.
-hipError_t launch_apply_clipped(float* theta, const float* queue, const int32_t* idx_dev, int K, float lr, int mode,
-                                float clip, float* partial_dev, float* scale_dev, hipStream_t s, Profiler& prof);
+hipError_t launch_apply_clipped(float* theta, const float* queue, const RowList& rows, int K, float lr, int mode, float clip,
+                                float* partial_dev, float* scale_dev, hipStream_t s, Profiler& prof);
 int norm_slices();
 
 // Device address, on the current GPU, of the library's fixed scratch array (used by the drain entry point
@@ -161,8 +190,8 @@ hipError_t launch_elastic_average(float* theta, float* ring, const int32_t* slot
                                   Profiler& prof);
 
 // K Adadelta steps, one per listed queue row in order; acc_g2 and acc_dx2 are P-vector rows of state.
-hipError_t launch_apply_adadelta(float* theta, float* acc_g2, float* acc_dx2, const float* queue, const int32_t* idx_dev,
-                                 int K, float lr, float rho, float eps, hipStream_t s, Profiler& prof);
+hipError_t launch_apply_adadelta(float* theta, float* acc_g2, float* acc_dx2, const float* queue, const RowList& rows, int K, float lr,
+                                 float rho, float eps, hipStream_t s, Profiler& prof);
 
 // Lock-free gradient store (Section 3.3, last paragraph: a gradient is written once by its worker,
 // read once and then deleted by the server, so the store needs no lock).  Positions count appended
@@ -188,6 +217,7 @@ struct StoreRange {  // what the consumer step in flight has taken
     uint32_t count, pad;
 };
 constexpr int STORE_LOG_CAP = 1024;
+constexpr int STORE_IDS_IN_ARGS = 128;  // appends up to this size bring their worker ids in kernel arguments
 
 struct StoreBuffers {
     StoreState* state;
@@ -197,12 +227,12 @@ struct StoreBuffers {
     StoreLogRec* log;                  // [STORE_LOG_CAP], a ring
     StoreRange* range;
     int32_t* idx;                      // [cap] rows taken by the consumer step in flight
-    int32_t* worker_id;                // [max_workers] of the append in flight
+    int32_t* worker_id;                // [max_workers] of the append in flight, if it is too large for kernel arguments
     int cap;
 };
 
 hipError_t launch_store_reset(const StoreBuffers& sb, unsigned long long version, hipStream_t s);
-hipError_t launch_store_publish(const StoreBuffers& sb, const WorkerMeta* meta, int n, hipStream_t s);
+hipError_t launch_store_publish(const StoreBuffers& sb, const WorkerMeta* meta, const int32_t* worker_id_host, int n, hipStream_t s);
 hipError_t launch_store_take(const StoreBuffers& sb, int max_entries, hipStream_t s);
 hipError_t launch_store_release(const StoreBuffers& sb, int mode, hipStream_t s);
 hipError_t launch_store_stamp_version(const StoreBuffers& sb, int slot, hipStream_t s);

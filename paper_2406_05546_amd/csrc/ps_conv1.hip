@@ -19,15 +19,19 @@ namespace {
 constexpr int CONV1_NW = 4, CONV1_NT = 64 * CONV1_NW, CONV1_IPW = 8;  // wavefronts per block, most images per wavefront
 constexpr int CONV1_XW = 30;
 
-__global__ __launch_bounds__(CONV1_NT) void conv1_fwd_kernel(WorkerBuffers wb, int blocks_per_worker, int ipw)
+// N_META > 0: the workers' metadata are in the arguments, and the first block of a worker puts its own where the
+// later kernels of the call look for it (an upload in front costs 4 us of copy and 5 us until conv1 starts).
+template <int N_META>
+__global__ __launch_bounds__(CONV1_NT) void conv1_fwd_kernel(WorkerBuffers wb, int blocks_per_worker, int ipw, MetaArgs<N_META> args)
 {
     __shared__ __attribute__((aligned(16))) float images[CONV1_NW][CONV1_XW * CONV1_XW];
     const int lane = threadIdx.x & 63, wave = uniform(threadIdx.x >> 6), c0 = 4 * (lane & 3);
     const int w = blockIdx.x / blocks_per_worker, chunk = blockIdx.x % blocks_per_worker;
     const int B = wb.B, s_begin = (chunk * CONV1_NW + wave) * ipw, s_end = min(B, s_begin + ipw);
+    if (N_META > 0 && chunk == 0 && threadIdx.x == 0) wb.meta[w] = args.m[w];
     if (s_begin >= s_end) return;
     float* __restrict__ xs = images[wave];
-    const float* __restrict__ theta = worker_theta(wb, w);
+    const float* __restrict__ theta = N_META > 0 ? wb.ring + (ptrdiff_t)args.m[w].slot * PSTRIDE : worker_theta(wb, w);
 
     floatx4 xv[4];  // 196 float4 of an image (lanes past the end repeat the last one)
     auto prefetch = [&](size_t g) {
@@ -101,10 +105,23 @@ __global__ __launch_bounds__(CONV1_NT) void conv1_fwd_kernel(WorkerBuffers wb, i
 
 }  // namespace
 
-void launch_conv1_fwd(const WorkerBuffers& wb, hipStream_t s)
+template <int N_META>
+static void start_conv1_fwd(const WorkerBuffers& wb, hipStream_t s)
 {
     const int ipw = images_per_wavefront(wb.n, wb.B, CONV1_IPW), bpw = (wb.B + CONV1_NW * ipw - 1) / (CONV1_NW * ipw);
-    hipLaunchKernelGGL(conv1_fwd_kernel, dim3(wb.n * bpw), dim3(CONV1_NT), 0, s, wb, bpw, ipw);
+    MetaArgs<N_META> args;
+    if (N_META > 0) std::copy(wb.meta_host, wb.meta_host + wb.n, args.m);
+    hipLaunchKernelGGL(conv1_fwd_kernel<N_META>, dim3(wb.n * bpw), dim3(CONV1_NT), 0, s, wb, bpw, ipw, args);
+}
+
+void launch_conv1_fwd(const WorkerBuffers& wb, hipStream_t s)
+{
+    if (!wb.meta_host)
+        start_conv1_fwd<0>(wb, s);
+    else if (wb.n <= 16)
+        start_conv1_fwd<16>(wb, s);
+    else
+        start_conv1_fwd<META_IN_ARGS>(wb, s);
 }
 
 }  // namespace ps

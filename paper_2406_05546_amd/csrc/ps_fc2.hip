@@ -249,7 +249,41 @@ __global__ __launch_bounds__(256) void fc2_eval_kernel(WorkerBuffers wb, float* 
     }
 }
 
+// The results of 256 images: predicted classes passed on, loss and hits summed (in 64 bits, fixed order).
+__global__ __launch_bounds__(256) void eval_collect_kernel(int n_images, const float* __restrict__ loss_i, const int32_t* __restrict__ correct,
+                                                           const int32_t* __restrict__ pred, EvalSums* __restrict__ sums, int32_t* __restrict__ pred_out)
+{
+    __shared__ double loss_sum[4];
+    __shared__ int hits[4];
+    const int i = blockIdx.x * 256 + threadIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    double loss = 0.0;
+    int ok = 0;
+    if (i < n_images) {
+        loss = loss_i[i];
+        ok = correct[i];
+        if (pred_out) pred_out[i] = pred[i];
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        loss += __shfl_xor(loss, off, 64);
+        ok += __shfl_xor(ok, off, 64);
+    }
+    if (lane == 0) {
+        loss_sum[wave] = loss;
+        hits[wave] = ok;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) sums[blockIdx.x] = EvalSums{(loss_sum[0] + loss_sum[1]) + (loss_sum[2] + loss_sum[3]), hits[0] + hits[1] + hits[2] + hits[3]};
+}
+
 }  // namespace
+
+hipError_t launch_eval_collect(int n_images, const float* loss_i, const int32_t* correct, const int32_t* pred, EvalSums* sums,
+                               int32_t* pred_out, hipStream_t s)
+{
+    hipLaunchKernelGGL(eval_collect_kernel, dim3(eval_blocks(n_images)), dim3(256), 0, s, n_images, loss_i, correct, pred, sums, pred_out);
+    return hipGetLastError();
+}
 
 void launch_fc2_eval(const WorkerBuffers& wb, float* loss_i, int32_t* correct, hipStream_t s)
 {

@@ -21,7 +21,11 @@ typedef unsigned long long u64;
 
 __global__ void store_reset_kernel(StoreState* st, u64 version) { st->version = version; }
 
-__global__ __launch_bounds__(256) void store_publish_kernel(StoreBuffers sb, const WorkerMeta* meta, int n)
+struct WorkerIds {  // of a small append, in the kernel arguments instead of uploaded
+    int32_t id[STORE_IDS_IN_ARGS];
+};
+
+__global__ __launch_bounds__(256) void store_publish_kernel(StoreBuffers sb, const WorkerMeta* meta, int n, WorkerIds ids)
 {
     __shared__ u64 base;
     // everything the worker kernels wrote to the rows precedes this launch in stream order
@@ -38,7 +42,7 @@ __global__ __launch_bounds__(256) void store_publish_kernel(StoreBuffers sb, con
         e.pos = pos;
         e.version = sb.ring_version[m.slot];
         e.mb = ((u64)m.mb_hi << 32) | m.mb_lo;
-        e.worker = sb.worker_id[i];
+        e.worker = n <= STORE_IDS_IN_ARGS ? ids.id[i] : sb.worker_id[i];
         e.pad = 0;
         sb.entry[m.q] = e;
         // the release makes row and metadata visible to whoever reads the stamp with acquire
@@ -98,9 +102,11 @@ hipError_t launch_store_reset(const StoreBuffers& sb, unsigned long long version
     return hipGetLastError();
 }
 
-hipError_t launch_store_publish(const StoreBuffers& sb, const WorkerMeta* meta, int n, hipStream_t s)
+hipError_t launch_store_publish(const StoreBuffers& sb, const WorkerMeta* meta, const int32_t* worker_id_host, int n, hipStream_t s)
 {
-    hipLaunchKernelGGL(store_publish_kernel, dim3(1), dim3(256), 0, s, sb, meta, n);
+    WorkerIds ids{};
+    if (n <= STORE_IDS_IN_ARGS) std::copy(worker_id_host, worker_id_host + n, ids.id);
+    hipLaunchKernelGGL(store_publish_kernel, dim3(1), dim3(256), 0, s, sb, meta, n, ids);
     return hipGetLastError();
 }
 

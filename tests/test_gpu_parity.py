@@ -803,3 +803,28 @@ def test_edges_and_error_codes(ps):
         assert ps.ps_drain_buffered(ctx, ps.DRAIN_SUM, 0.1) == 3 and ps.ps_version(ctx) == 2
     finally:
         ps.ps_destroy(ctx)
+
+
+@pytest.mark.parametrize("order", [[2, 3, 4], [4, 3, 2], [0, 2, 3, 7], [6]])
+def test_applies_over_consecutive_and_listed_rows(ps, order):
+    """Entries that follow each other in the queue travel as their first row, others as a list: the same update."""
+    g = np.random.default_rng(5).uniform(-1e-2, 1e-2, (8, 813258)).astype(np.float32)
+    theta = synth.he_uniform_theta(3)
+    ctx = ps.ps_init(ps.make_config(1, 1, 1, 8, DROP_SEED, P_DROP))
+    try:
+        ps.ps_set_weights(ctx, theta)
+        for k in range(8):
+            assert ps.ps_queue_push_host(ctx, g[k], 0, 0, k) == k
+        ps.ps_apply_sync(ctx, order, 0.5)
+        want = orc.apply_sync(theta.astype(np.float64), [g[k].astype(np.float64) for k in order], 0.5)
+        # the drain takes what was left, in arrival order, then two gradients in entries that came free
+        rows = [k for k in range(8) if k not in order]
+        for k in range(min(2, len(order))):
+            ps.ps_queue_push_host(ctx, g[k], 0, 0, k)
+            rows.append(k)
+        assert ps.ps_drain_buffered(ctx, ps.DRAIN_SEQ, 0.5) == len(rows)
+        want = orc.drain(want, [g[k].astype(np.float64) for k in rows], 0.5, orc.DRAIN_SEQ)
+        # one fp32 rounding per row and update, of sums and weights below 1
+        assert np.abs(ps.ps_get_weights(ctx) - want).max() <= 12 * 2.0 ** -24
+    finally:
+        ps.ps_destroy(ctx)
