@@ -105,11 +105,13 @@ int conv2_part_slots(int batch);  // conv2 partial slots per worker (one per blo
 int conv1_part_slots(int batch);  // conv1 partial slots per worker (one per image, written by conv2's input-gradient kernel)
 
 int compute_units();  // of the current GPU
-int images_per_wavefront(int n, int batch, int most);  // for the kernels in which a wavefront works on whole images
+// For the kernels in which a wavefront works on whole images, or several share one in small launches.
+int images_per_wavefront(int n, int batch, int most);
+int wavefronts_per_image(int n, int batch, int most);
+int blocks_per_worker(int batch, int images_per_wavefront, int wavefronts_per_image, int wavefronts);
 
 void launch_conv1_fwd(const WorkerBuffers& wb, hipStream_t s);
 void launch_fc1_fwd(const WorkerBuffers& wb, hipStream_t s);
-void launch_fc1_dw(const WorkerBuffers& wb, hipStream_t s);
 void launch_fc1_dx(const WorkerBuffers& wb, hipStream_t s);
 void launch_fc2(const WorkerBuffers& wb, hipStream_t s);
 void launch_fc2_eval(const WorkerBuffers& wb, float* loss_i, int32_t* correct, hipStream_t s);
@@ -125,8 +127,10 @@ hipError_t launch_eval_collect(int n_images, const float* loss_i, const int32_t*
                                int32_t* pred_out, hipStream_t s);
 
 void launch_conv2_fwd(const WorkerBuffers& wb, hipStream_t s);
-void launch_conv2_dx(const WorkerBuffers& wb, hipStream_t s);
-void launch_conv2_dw(const WorkerBuffers& wb, hipStream_t s);
+void launch_fc1_dw(const WorkerBuffers& wb, hipStream_t s);
+bool fc1_dw_is_few(int n);  // whether fc1's weight gradient runs in launch_backward's launch, next to conv2's gradients
+enum { BWD_CONV2_DX = 1, BWD_CONV2_DW = 2, BWD_FC1_DW = 4 };
+void launch_backward(const WorkerBuffers& wb, hipStream_t s, int which);
 
 // Kernels of the path, in launch order; ids index the per-kernel timing table.
 enum KernelId {

@@ -12,7 +12,8 @@ namespace {
 // wavefront works on whole images by itself (no block barrier); lane (p, j) = (lane / 4, lane % 4) computes
 // channels 4j .. 4j + 3 of positions p, p + 16, ..., 13 passes of which the last has 16 lanes: the 40 weights
 // of its channels stay in registers, the 4x4 input patch is read for four channels at once, and what a
-// wavefront stores in a pass is one contiguous KB of pool1 ([position][channel], as conv2 reads it).
+// wavefront stores in a pass is one contiguous KB of pool1 ([position][channel], as conv2 reads it).  In launches
+// that would leave SIMDs idle, `parts` wavefronts share an image, each with every parts-th pass.
 // 65,536 images: 0.313 -> 0.265 ms against a lane per position that walked all channels with weights from LDS
 // and stored [channel][position] (0.37 ms when that kernel stored [position][channel], 16 bytes at a time 64
 // bytes apart); two workers of 32 images: 11 -> 8 us.
@@ -22,12 +23,13 @@ constexpr int CONV1_XW = 30;
 // N_META > 0: the workers' metadata are in the arguments, and the first block of a worker puts its own where the
 // later kernels of the call look for it (an upload in front costs 4 us of copy and 5 us until conv1 starts).
 template <int N_META>
-__global__ __launch_bounds__(CONV1_NT) void conv1_fwd_kernel(WorkerBuffers wb, int blocks_per_worker, int ipw, MetaArgs<N_META> args)
+__global__ __launch_bounds__(CONV1_NT) void conv1_fwd_kernel(WorkerBuffers wb, int blocks_per_worker, int ipw, int parts, MetaArgs<N_META> args)
 {
     __shared__ __attribute__((aligned(16))) float images[CONV1_NW][CONV1_XW * CONV1_XW];
     const int lane = threadIdx.x & 63, wave = uniform(threadIdx.x >> 6), c0 = 4 * (lane & 3);
     const int w = blockIdx.x / blocks_per_worker, chunk = blockIdx.x % blocks_per_worker;
-    const int B = wb.B, s_begin = (chunk * CONV1_NW + wave) * ipw, s_end = min(B, s_begin + ipw);
+    const int unit = chunk * CONV1_NW + wave, part = unit % parts;
+    const int B = wb.B, s_begin = unit / parts * ipw, s_end = min(B, s_begin + ipw);
     if (N_META > 0 && chunk == 0 && threadIdx.x == 0) wb.meta[w] = args.m[w];
     if (s_begin >= s_end) return;
     float* __restrict__ xs = images[wave];
@@ -62,14 +64,14 @@ __global__ __launch_bounds__(CONV1_NT) void conv1_fwd_kernel(WorkerBuffers wb, i
         }
         wave_lds_fence();
         if (s + 1 < s_end) prefetch(g + 1);
-        int px = lane / 4 % P1_W, at = lane / 4 / P1_W * 2 * CONV1_XW + 2 * px;  // of position lane / 4
 #pragma unroll 1
-        for (int pos = lane / 4; pos < P1_POS; pos += 16) {
+        for (int pos = lane / 4 + 16 * part; pos < P1_POS; pos += 16 * parts) {
+            const float* window = xs + (pos / P1_W * CONV1_XW + pos % P1_W) * 2;
             float patch[4][4];
 #pragma unroll
             for (int a = 0; a < 4; ++a)
 #pragma unroll
-                for (int b = 0; b < 4; ++b) patch[a][b] = xs[at + a * CONV1_XW + b];
+                for (int b = 0; b < 4; ++b) patch[a][b] = window[a * CONV1_XW + b];
             floatx4 out;
             uint32_t bytes = 0;
 #pragma unroll
@@ -92,13 +94,6 @@ __global__ __launch_bounds__(CONV1_NT) void conv1_fwd_kernel(WorkerBuffers wb, i
             }
             *reinterpret_cast<floatx4*>(wb.p1 + g * P1_SIZE + pos * C1 + c0) = out;
             *reinterpret_cast<uint32_t*>(wb.am1 + g * P1_SIZE + pos * C1 + c0) = bytes;
-            // 16 positions on: one row of 14 and two columns
-            px += 2;
-            at += 2 * CONV1_XW + 4;
-            if (px >= P1_W) {
-                px -= P1_W;
-                at += 2 * CONV1_XW - 2 * P1_W;
-            }
         }
     }
 }
@@ -108,10 +103,11 @@ __global__ __launch_bounds__(CONV1_NT) void conv1_fwd_kernel(WorkerBuffers wb, i
 template <int N_META>
 static void start_conv1_fwd(const WorkerBuffers& wb, hipStream_t s)
 {
-    const int ipw = images_per_wavefront(wb.n, wb.B, CONV1_IPW), bpw = (wb.B + CONV1_NW * ipw - 1) / (CONV1_NW * ipw);
+    const int ipw = images_per_wavefront(wb.n, wb.B, CONV1_IPW), parts = wavefronts_per_image(wb.n, wb.B, 4);
+    const int bpw = blocks_per_worker(wb.B, ipw, parts, CONV1_NW);
     MetaArgs<N_META> args;
     if (N_META > 0) std::copy(wb.meta_host, wb.meta_host + wb.n, args.m);
-    hipLaunchKernelGGL(conv1_fwd_kernel<N_META>, dim3(wb.n * bpw), dim3(CONV1_NT), 0, s, wb, bpw, ipw, args);
+    hipLaunchKernelGGL(conv1_fwd_kernel<N_META>, dim3(wb.n * bpw), dim3(CONV1_NT), 0, s, wb, bpw, ipw, parts, args);
 }
 
 void launch_conv1_fwd(const WorkerBuffers& wb, hipStream_t s)

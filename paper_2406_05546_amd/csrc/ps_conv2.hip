@@ -4,6 +4,7 @@
 // operands go from memory to registers, are split there once and reused for several taps, and what a
 // wavefront needs to turn round inside an image goes through LDS of its own: no block barrier in any loop.
 #include "ps_common.h"
+#include "ps_fc1_dw.h"
 #include "ps_split.h"
 
 namespace ps {
@@ -24,6 +25,7 @@ __device__ __forceinline__ bool any_nan(const floatx4& a) { return __builtin_isu
 // same operand moved by 0, 1, 2 lanes, and the pair of dy = 2 is that of dy = 0 one pooled row further on.
 // A lane ends up with both rows of four windows of one output channel, so pooling stays in its registers;
 // the pooled image is turned to [channel][position] in LDS and leaves in 16-byte stores.
+// In launches that would leave SIMDs idle, `parts` wavefronts share an image, two or four pooled rows each.
 // 14 of 16 columns are real: 378 MFMAs per image, 12,100 cycles of a SIMD's matrix pipe.
 // 65,536 images: 1.005 -> 0.61 ms against the fp32 MFMA kernel that staged padded planes in LDS (matrix pipe busy
 // 68 % of the cycles at the 2.0 GHz the chip then runs at; a loop of nothing but these MFMAs on random operands
@@ -51,13 +53,14 @@ __device__ __forceinline__ float conv2_fwd_plain(const float* __restrict__ p1, c
     return sum;
 }
 
-__global__ __launch_bounds__(FWD_NT, 2) void conv2_fwd_kernel(WorkerBuffers wb, int blocks_per_worker, int ipw)
+__global__ __launch_bounds__(FWD_NT, 2) void conv2_fwd_kernel(WorkerBuffers wb, int blocks_per_worker, int ipw, int parts)
 {
     __shared__ __attribute__((aligned(16))) FwdImage images[FWD_NW];
     const int lane = threadIdx.x & 63, wave = uniform(threadIdx.x >> 6);
     const int h = lane >> 5, l32 = lane & 31, e = l32 >> 4, x = (lane & 15) - 1;
     const int w = blockIdx.x / blocks_per_worker, chunk = blockIdx.x % blocks_per_worker;
-    const int B = wb.B, s_begin = (chunk * FWD_NW + wave) * ipw, s_end = min(B, s_begin + ipw);
+    const int unit = chunk * FWD_NW + wave, t_begin = unit % parts * 8 / parts, t_end = min(P2_W, t_begin + 8 / parts);
+    const int B = wb.B, s_begin = unit / parts * ipw, s_end = min(B, s_begin + ipw);
     if (s_begin >= s_end) return;
     FwdImage& im = images[wave];
     const float* __restrict__ W2 = worker_theta(wb, w) + OFF_W2;
@@ -76,7 +79,14 @@ __global__ __launch_bounds__(FWD_NT, 2) void conv2_fwd_kernel(WorkerBuffers wb, 
         const float v[8] = {raw[i][0][0], raw[i][0][1], raw[i][0][2], raw[i][0][3], raw[i][1][0], raw[i][1][1], raw[i][1][2], raw[i][1][3]};
         return split8(v);
     };
-    prefetch((size_t)w * B + s_begin, 0);
+    Split8 up;  // rows 2t - 1 and 2t; for an image shared by wavefronts, the rows above the first of this one's
+    if (t_begin > 0) {
+        const Buffer b = buffer_of(wb.p1 + ((size_t)w * B + s_begin) * P1_SIZE, IMAGE_BYTES);
+#pragma unroll
+        for (int k = 0; k < 2; ++k) raw[0][k] = buffer_float4(b, at + (uint32_t)(2 * t_begin - 1) * ROW_BYTES + 16 * k);
+        up = split_raw(0);
+    }
+    prefetch((size_t)w * B + s_begin, t_begin);
 
     Split8 wt[9];  // lane (h, l32): W2[o = l32][c = 8h + j][tap]
 #pragma unroll
@@ -91,9 +101,8 @@ __global__ __launch_bounds__(FWD_NT, 2) void conv2_fwd_kernel(WorkerBuffers wb, 
     for (int s = s_begin; s < s_end; ++s) {
         const size_t g = (size_t)w * B + s;
         wave_lds_fence();  // the last image has been stored
-        Split8 up;  // rows 2t - 1 and 2t
 #pragma unroll 1
-        for (int t = 0; t < P2_W; ++t) {
+        for (int t = t_begin; t < t_end; ++t) {
             const Split8 mid = split_raw(0), low = split_raw(1);  // rows 2t, 2t + 1 and 2t + 1, 2t + 2
             if (t == 0) {  // rows -1 (zero) and 0: the odd groups of 16 lanes take what the even ones of `mid` hold
 #pragma unroll
@@ -101,7 +110,7 @@ __global__ __launch_bounds__(FWD_NT, 2) void conv2_fwd_kernel(WorkerBuffers wb, 
 #pragma unroll
                     for (int j = 0; j < 4; ++j) up.p[i][j] = __builtin_amdgcn_permlane16_swap(0u, mid.p[i][j], false, false)[0];
             }
-            if (t + 1 < P2_W)
+            if (t + 1 < t_end)
                 prefetch(g, t + 1);
             else if (s + 1 < s_end)
                 prefetch(g + 1, 0);
@@ -122,7 +131,8 @@ __global__ __launch_bounds__(FWD_NT, 2) void conv2_fwd_kernel(WorkerBuffers wb, 
             for (int i = 0; i < 16; i += 2) nan |= __builtin_isunordered(acc[i], acc[i + 1]);
             if (__any(nan)) {
 #pragma unroll
-                for (int i = 0; i < 16; ++i) acc[i] = conv2_fwd_plain(wb.p1 + g * P1_SIZE, W2, l32, 2 * t + i / 8, 8 * (i / 4 % 2) + 4 * h + i % 4);
+                for (int i = 0; i < 16; ++i)
+                    if (acc[i] != acc[i]) acc[i] = conv2_fwd_plain(wb.p1 + g * P1_SIZE, W2, l32, 2 * t + i / 8, 8 * (i / 4 % 2) + 4 * h + i % 4);
             }
 #pragma unroll
             for (int half = 0; half < 2; ++half) {
@@ -144,6 +154,20 @@ __global__ __launch_bounds__(FWD_NT, 2) void conv2_fwd_kernel(WorkerBuffers wb, 
             }
         }
         wave_lds_fence();
+        if (parts > 1) {  // windows 7 t_begin .. of every channel
+            const int first = P2_W * t_begin, count = P2_W * (t_end - t_begin);
+            for (int i = lane; i < count * C2; i += 64) {
+                const int o = i / count, p = first + i % count;
+                wb.p2[g * P2_SIZE + o * P2_POS + p] = im.p2[o * P2_POS + p];
+                wb.am2t[g * P2_SIZE + first * C2 + i] = im.am2t[first * C2 + i];
+            }
+            const int pitch = AM2_PITCH * (t_end - t_begin);
+            for (int i = lane; i < pitch * C2; i += 64) {
+                const int at2 = i / pitch * P2_W * AM2_PITCH + t_begin * AM2_PITCH + i % pitch;
+                wb.am2[g * AM2_SIZE + at2] = im.am2[at2];
+            }
+            continue;
+        }
 #pragma unroll
         for (int k = 0; k < 7; ++k)
             if (64 * (k + 1) <= P2_SIZE / 4 || lane + 64 * k < P2_SIZE / 4)
@@ -170,8 +194,10 @@ __global__ __launch_bounds__(FWD_NT, 2) void conv2_fwd_kernel(WorkerBuffers wb, 
 // The result never goes to memory: conv1 has no input gradient, so each value is routed to its pool1
 // window's winner and multiplied right away with the 3x3 neighbourhood of input pixels there,
 //   d W1[c][dy][dx] += d pool1[c][p] * xpad[winner(c,p) + (dy,dx)],   d b1[c] += d pool1[c][p],
-// on the vector ALU.  A wavefront works on whole images by itself (no block barrier anywhere) and writes
-// one partial slot of conv1 sums per image, so that nothing depends on how a launch is cut up.
+// on the vector ALU.  A wavefront works on whole images by itself and writes one partial slot of conv1 sums per
+// image: the sum over rows 0-6 plus the sum over rows 7-13.  In launches that would leave SIMDs idle, two
+// wavefronts of a block share an image, a half each, and add up the same two sums: nothing depends on how a
+// launch is cut up.
 // 65,536 images: 1.146 -> 0.65 ms against the fp32 MFMA kernel in two-wavefront blocks; two workers of 32
 // images: 87 -> 16 us (a wavefront walked eight images there, now one).  Matrix pipe busy 58 % of the cycles.
 constexpr int DX_NW = 4, DX_NT = 64 * DX_NW, DX_IPW = 8;  // wavefronts per block, most images per wavefront
@@ -208,13 +234,34 @@ __device__ __forceinline__ float conv2_dx_plain(const WorkerBuffers& wb, size_t 
     return sum;
 }
 
-__global__ __launch_bounds__(DX_NT, 2) void conv2_dx_kernel(WorkerBuffers wb, int blocks_per_worker, int ipw)
+struct Conv1Sums {
+    float v[10];
+};
+
+// conv1's sums of image g, channel c: the first half's plus the second half's.
+__device__ __forceinline__ void store_conv1_sums(const WorkerBuffers& wb, size_t g, int c, const float* first, const float (&second)[10])
 {
-    __shared__ __attribute__((aligned(16))) DxImage images[DX_NW];
+    float* part = wb.part1 + g * OFF_W2;
+#pragma unroll
+    for (int i = 0; i < 9; ++i) part[OFF_W1 + c * 9 + i] = first[c * 10 + i] + second[i];
+    part[OFF_B1 + c] = first[c * 10 + 9] + second[9];
+}
+
+// How conv2's gradients are cut up: blocks of the input gradient, then blocks of the weight gradient.
+struct BwdShape {
+    int dx_blocks, dx_blocks_per_worker, dx_ipw, dx_parts;
+    int dw_blocks, dw_slots, dw_ipw, dw_shared;
+};
+
+__device__ __forceinline__ void conv2_dx_block(const WorkerBuffers& wb, const BwdShape& sh, int block, DxImage* images)
+{
     const int lane = threadIdx.x & 63, wave = uniform(threadIdx.x >> 6), q = lane >> 4, l16 = lane & 15;
-    const int w = blockIdx.x / blocks_per_worker, chunk = blockIdx.x % blocks_per_worker;
-    const int B = wb.B, s_begin = (chunk * DX_NW + wave) * ipw, s_end = min(B, s_begin + ipw);
-    if (s_begin >= s_end) return;
+    const int w = block / sh.dx_blocks_per_worker, chunk = block % sh.dx_blocks_per_worker;
+    const int unit = chunk * DX_NW + wave, half = unit % sh.dx_parts;
+    const int B = wb.B, s_begin = min(B, unit / sh.dx_parts * sh.dx_ipw), s_end = min(B, s_begin + sh.dx_ipw);
+    // rows of d pool1 to finish; d2 rows from one before to one behind them
+    const int Y_begin = P1_W / 2 * half, Y_end = half + 1 == sh.dx_parts ? P1_W : P1_W / 2;
+    const int py_begin = half == 0 ? 0 : 3, py_end = Y_end == P1_W ? P2_W : 4;
     DxImage& im = images[wave];
     const float* __restrict__ W2 = worker_theta(wb, w) + OFF_W2;
 
@@ -237,6 +284,7 @@ __global__ __launch_bounds__(DX_NT, 2) void conv2_dx_kernel(WorkerBuffers wb, in
     // lane (o, half) = (lane / 2, lane % 2) brings in windows 25 half .. of channel o: 25 or 24 of them
     const int o_in = lane >> 1, win_in = 25 * (lane & 1), last_in = o_in * P2_POS + (lane & 1 ? P2_POS - 1 : 24);
 
+    Conv1Sums shared_sum{};
     for (int s = s_begin; s < s_end; ++s) {
         const size_t g = (size_t)w * B + s;
         // the image's pooled gradients, window bytes (98 uint4), pool1 window bytes and pixels (196 of either;
@@ -274,15 +322,25 @@ __global__ __launch_bounds__(DX_NT, 2) void conv2_dx_kernel(WorkerBuffers wb, in
             if (64 * (k + 1) <= P2_SIZE / 16 || lane + 64 * k < P2_SIZE / 16) reinterpret_cast<uintx4*>(im.am2t)[lane + 64 * k] = pc[k];
         wave_lds_fence();
 
-        float g1[9], gb1 = 0.f;  // this lane's share of d W1[l16][.] and d b1[l16]
+        float g1[10];  // this lane's share of d W1[l16][.] and d b1[l16]
 #pragma unroll
-        for (int i = 0; i < 9; ++i) g1[i] = 0.f;
+        for (int i = 0; i < 10; ++i) g1[i] = 0.f;
+        float* half_sum = reinterpret_cast<float*>(im.am1);  // [16][10], in the place of window bytes that have been used
+        // folds the four lane quarters: every lane then holds the sums for channel l16
+        auto fold = [&]() {
+#pragma unroll
+            for (int i = 0; i < 10; ++i) {
+                g1[i] += __shfl_xor(g1[i], 16, 64);
+                g1[i] += __shfl_xor(g1[i], 32, 64);
+            }
+        };
 
         // conv1's gradient from d pool1 row Y: lane (q, l16) holds channel l16 at X = 4q .. 4q + 3
         auto finish_row = [&](int Y, floatx4 acc) {
             if (__any(any_nan(acc))) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) acc[i] = conv2_dx_plain(wb, g, W2, l16, Y, 4 * q + i);
+                for (int i = 0; i < 4; ++i)
+                    if (acc[i] != acc[i]) acc[i] = conv2_dx_plain(wb, g, W2, l16, Y, 4 * q + i);
             }
             const uint8_t* bytes = im.am1 + (P1_W * Y + 4 * q) * C1 + l16;
             const float* row = im.xs + 2 * Y * DX_XW + 8 * q;
@@ -293,7 +351,7 @@ __global__ __launch_bounds__(DX_NT, 2) void conv2_dx_kernel(WorkerBuffers wb, in
                 const float* p = row + 2 * i + (b & 0x7fu);
                 const uint32_t keep = (uint32_t)__builtin_amdgcn_sbfe((int)b, 7, 1);  // gate bit -> all ones or zero
                 const float v = __uint_as_float(__float_as_uint(acc[i]) & keep);
-                gb1 += v;
+                g1[9] += v;
 #pragma unroll
                 for (int k = 0; k < 9; ++k) g1[k] = fmaf(v, p[(k / 3) * DX_XW + k % 3], g1[k]);
             }
@@ -303,7 +361,7 @@ __global__ __launch_bounds__(DX_NT, 2) void conv2_dx_kernel(WorkerBuffers wb, in
 #pragma unroll
         for (int i = 0; i < 3; ++i) acc[i].clear();
 #pragma unroll 1
-        for (int py = 0; py < P2_W; ++py) {
+        for (int py = py_begin; py < py_end; ++py) {
             const int win = py * P2_W + px;
             uintx4 part[3];
 #pragma unroll
@@ -331,7 +389,7 @@ __global__ __launch_bounds__(DX_NT, 2) void conv2_dx_kernel(WorkerBuffers wb, in
                         acc[2].add(t, a, wt[6 + dx]);
                     }
                 }
-                if (y == 0) {  // the rest of the image, which row 0 of the result needs first
+                if (y == 2 * py_begin) {  // the rest of the image, which the first finished row needs first
 #pragma unroll
                     for (int k = 0; k < 4; ++k) {
                         const int i = lane + 64 * k;
@@ -343,30 +401,42 @@ __global__ __launch_bounds__(DX_NT, 2) void conv2_dx_kernel(WorkerBuffers wb, in
                         }
                     }
                     wave_lds_fence();
-                } else {
+                } else if (y - 1 >= Y_begin) {
                     finish_row(y - 1, acc[0].value());
+                    if (y == P1_W / 2 && Y_end == P1_W) {  // the first half is complete: rows 0-6 of the window bytes are free
+                        fold();
+                        wave_lds_fence();
+                        if (q == 0) {
+#pragma unroll
+                            for (int i = 0; i < 10; ++i) half_sum[l16 * 10 + i] = g1[i];
+                        }
+#pragma unroll
+                        for (int i = 0; i < 10; ++i) g1[i] = 0.f;
+                    }
                 }
                 acc[0] = acc[1];
                 acc[1] = acc[2];
                 acc[2].clear();
             }
         }
-        finish_row(P1_W - 1, acc[0].value());
-
-        // fold the four lane quarters; lanes of quarter 0 hold the image's sums for channel l16
+        if (Y_end == P1_W) finish_row(P1_W - 1, acc[0].value());
+        fold();
+        wave_lds_fence();
+        if (sh.dx_parts == 1) {
+            if (q == 0) store_conv1_sums(wb, g, l16, half_sum, g1);
+        } else {
+            if (half == 0 && q == 0) {
 #pragma unroll
-        for (int i = 0; i < 9; ++i) {
-            g1[i] += __shfl_xor(g1[i], 16, 64);
-            g1[i] += __shfl_xor(g1[i], 32, 64);
+                for (int i = 0; i < 10; ++i) half_sum[l16 * 10 + i] = g1[i];
+            }
+            #pragma unroll
+            for (int i = 0; i < 10; ++i) shared_sum.v[i] = g1[i];
         }
-        gb1 += __shfl_xor(gb1, 16, 64);
-        gb1 += __shfl_xor(gb1, 32, 64);
-        if (q == 0) {
-            float* part = wb.part1 + g * OFF_W2;
-#pragma unroll
-            for (int i = 0; i < 9; ++i) part[OFF_W1 + l16 * 9 + i] = g1[i];
-            part[OFF_B1 + l16] = gb1;
-        }
+    }
+    if (sh.dx_parts == 2) {  // one image (or none) per wavefront
+        __syncthreads();
+        if (half == 1 && s_begin < s_end && q == 0)
+            store_conv1_sums(wb, (size_t)w * B + s_begin, l16, reinterpret_cast<const float*>(images[wave - 1].am1), shared_sum.v);
     }
 }
 
@@ -434,40 +504,74 @@ __device__ __forceinline__ float conv2_dw_plain(const WorkerBuffers& wb, int w, 
     return sum;
 }
 
-__global__ __launch_bounds__(DW_NT, 2) void conv2_dw_kernel(WorkerBuffers wb, int slots, int ipw)
+typedef float DwSums[DW_NW][DW_REGS + 2][64];  // 75,776 B
+
+// SHARES > 1: a launch that would leave SIMDs idle has six blocks for a slot, one for every (tap row, half of the
+// output channels); each sum is formed as in the one block, only fewer of them (one worker of 256 images: 45 us, or 22 us
+// with the input gradient and fc1's weight gradient in the same launch).
+constexpr int DW_SHARES = 6;
+
+// Four pooled gradients and their window bytes -> the d2 operand of lane (q = 2e + xh, l16).
+__device__ __forceinline__ Split8 d2_operand(const floatx4& pooled, uint32_t bytes, int e)
 {
-    __shared__ __attribute__((aligned(16))) float red[DW_NW][DW_REGS + 2][64];  // 75,776 B
+    Split8 d2;
+    const uint32_t bits = bytes >> (2 * e);  // bits 0, 1 of every byte: winner in this row, left or right
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+        const uint32_t left = (uint32_t)__builtin_amdgcn_sbfe((int)bits, 8 * m, 1), right = (uint32_t)__builtin_amdgcn_sbfe((int)bits, 8 * m + 1, 1);
+        const uint32_t mask = (left & 0xffffu) | (right & 0xffff0000u);
+        uint32_t p0, p1, p2;
+        split2(pooled[m], pooled[m], p0, p1, p2);
+        d2.p[0][m] = p0 & mask;
+        d2.p[1][m] = p1 & mask;
+        d2.p[2][m] = p2 & mask;
+    }
+    return d2;
+}
+
+template <bool SHARED>
+__device__ __forceinline__ void conv2_dw_block(const WorkerBuffers& wb, const BwdShape& sh, int block, DwSums& red)
+{
+    constexpr int MTS = SHARED ? 1 : 2, DYS = SHARED ? 1 : 3;  // halves of the output channels and tap rows of this block
+    const int share = SHARED ? block % DW_SHARES : 0, mt0 = share / 3, dy0 = share % 3;
+    if (SHARED) block /= DW_SHARES;
+    const int slots = sh.dw_slots, ipw = sh.dw_ipw;
     const int lane = threadIdx.x & 63, wave = uniform(threadIdx.x >> 6), q = lane >> 4, l16 = lane & 15, e = q >> 1, xh = q & 1;
-    const int w = blockIdx.x / slots, slot = blockIdx.x % slots;
+    const int w = block / slots, slot = block % slots;
     const int B = wb.B, s_begin = min(B, (slot * DW_NW + wave) * ipw), s_end = min(B, s_begin + ipw);
 
-    floatx4 acc[2][9], acc_b[2];
+    floatx4 acc[MTS][3 * DYS], acc_b[MTS];
 #pragma unroll
-    for (int mt = 0; mt < 2; ++mt) {
+    for (int mt = 0; mt < MTS; ++mt) {
         acc_b[mt] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int j = 0; j < 9; ++j) acc[mt][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < 3 * DYS; ++j) acc[mt][j] = floatx4{0.f, 0.f, 0.f, 0.f};
     }
 
     constexpr uint32_t POS_BYTES = C1 * 4, ROW_BYTES = P1_W * POS_BYTES;
     // columns 8xh - 1 .. 8xh + 8 of row e; of those outside the map only -1 and 14 ever meet a d2 value
     const uint32_t at = (uint32_t)e * ROW_BYTES + (uint32_t)(8 * xh) * POS_BYTES + 4 * l16;  // column 8xh
     const uint32_t at_first = xh == 0 ? BUFFER_NOWHERE : at - POS_BYTES, at_col14 = xh == 1 ? BUFFER_NOWHERE : at + 6 * POS_BYTES;
-    float raw[2][10];   // rows R + e of the next pooled row: R = 2py and R = 2py + 1
-    floatx4 pooled[2];  // pool2 gradients of windows px = 4xh .. 4xh + 3 (px = 7: whatever follows, masked) and their bytes
-    uint32_t bytes[2];
+    // rows R + e of the next pooled row: R = 2py and R = 2py + 1, or SHARED, R = 2py - 1 + dy0 alone
+    float raw[SHARED ? 1 : 2][10];
+    floatx4 pooled[MTS];  // pool2 gradients of windows px = 4xh .. 4xh + 3 (px = 7: whatever follows, masked) and their bytes
+    uint32_t bytes[MTS];
     auto prefetch = [&](size_t g, int py) {
         const Buffer b = buffer_of(wb.p1 + g * P1_SIZE, P1_SIZE * 4);
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const uint32_t row = (uint32_t)(2 * py + i) * ROW_BYTES;
+        for (int i = 0; i < (SHARED ? 1 : 2); ++i) {
+            const int R = SHARED ? 2 * py - 1 + dy0 : 2 * py + i;
+            const bool above = SHARED && R + e < 0;  // row -1
+            const uint32_t row = (uint32_t)max(R, 0) * ROW_BYTES - (SHARED && R < 0 && e > 0 ? ROW_BYTES : 0u);
 #pragma unroll
-            for (int k = 0; k < 10; ++k)
-                raw[i][k] = buffer_float(b, k == 0 ? at_first + row : k == 7 ? at_col14 + row : at + row + (k - 1) * POS_BYTES);
+            for (int k = 0; k < 10; ++k) {
+                const uint32_t o = k == 0 ? at_first + row : k == 7 ? at_col14 + row : at + row + (k - 1) * POS_BYTES;
+                raw[i][k] = buffer_float(b, above ? BUFFER_NOWHERE : o);
+            }
         }
 #pragma unroll
-        for (int mt = 0; mt < 2; ++mt) {
-            const int r = (16 * mt + l16) * P2_W + py;
+        for (int mt = 0; mt < MTS; ++mt) {
+            const int r = (16 * (mt0 + mt) + l16) * P2_W + py;
             __builtin_memcpy(&pooled[mt], wb.dp2g + g * P2_SIZE + r * P2_W + 4 * xh, 16);
             bytes[mt] = *reinterpret_cast<const uint32_t*>(wb.am2 + g * AM2_SIZE + r * AM2_PITCH + 4 * xh);
         }
@@ -479,23 +583,11 @@ __global__ __launch_bounds__(DW_NT, 2) void conv2_dw_kernel(WorkerBuffers wb, in
         ShiftedRow up;  // rows 2py - 1 + e
 #pragma unroll 1
         for (int py = 0; py < P2_W; ++py) {
-            Split8 d2[2];
+            Split8 d2[MTS];
 #pragma unroll
-            for (int mt = 0; mt < 2; ++mt) {
-                const uint32_t bits = bytes[mt] >> (2 * e);  // bits 0, 1 of every byte: winner in this row, left or right
-#pragma unroll
-                for (int m = 0; m < 4; ++m) {
-                    const uint32_t left = (uint32_t)__builtin_amdgcn_sbfe((int)bits, 8 * m, 1), right = (uint32_t)__builtin_amdgcn_sbfe((int)bits, 8 * m + 1, 1);
-                    const uint32_t mask = (left & 0xffffu) | (right & 0xffff0000u);
-                    uint32_t p0, p1, p2;
-                    split2(pooled[mt][m], pooled[mt][m], p0, p1, p2);
-                    d2[mt].p[0][m] = p0 & mask;
-                    d2[mt].p[1][m] = p1 & mask;
-                    d2[mt].p[2][m] = p2 & mask;
-                }
-            }
+            for (int mt = 0; mt < MTS; ++mt) d2[mt] = d2_operand(pooled[mt], bytes[mt], e);
             const ShiftedRow mid = shifted_row(raw[0]);
-            if (py == 0) {  // rows -1 (zero) and 0: lanes 32..63 take what lanes 0..31 of `mid` hold
+            if (!SHARED && py == 0) {  // rows -1 (zero) and 0: lanes 32..63 take what lanes 0..31 of `mid` hold
 #pragma unroll
                 for (int i = 0; i < 3; ++i) {
 #pragma unroll
@@ -504,61 +596,88 @@ __global__ __launch_bounds__(DW_NT, 2) void conv2_dw_kernel(WorkerBuffers wb, in
                     for (int j = 0; j < 4; ++j) up.odd[i][j] = __builtin_amdgcn_permlane32_swap(0u, mid.odd[i][j], false, false)[0];
                 }
             }
-            const ShiftedRow low = shifted_row(raw[1]);
+            const ShiftedRow low = shifted_row(raw[SHARED ? 0 : 1]);
             if (py + 1 < P2_W)
                 prefetch(g, py + 1);
             else if (s + 1 < s_end)
                 prefetch(g + 1, 0);
-            const ShiftedRow* const rows[3] = {&up, &mid, &low};
+            const ShiftedRow* const rows[3] = {SHARED ? &mid : &up, &mid, &low};
 #pragma unroll
-            for (int dy = 0; dy < 3; ++dy)
+            for (int dy = 0; dy < DYS; ++dy)
 #pragma unroll
                 for (int dx = 0; dx < 3; ++dx) {
                     const Split8 b = rows[dy]->columns(dx);
 #pragma unroll
                     for (int t = 0; t <= SPLIT_SMALL; ++t)
 #pragma unroll
-                        for (int mt = 0; mt < 2; ++mt)
+                        for (int mt = 0; mt < MTS; ++mt)
                             acc[mt][3 * dy + dx] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(d2[mt].part(TERM_A[t]), b.part(TERM_B[t]), acc[mt][3 * dy + dx], 0, 0, 0);
                 }
             const bf16x8 ones = __builtin_bit_cast(bf16x8, uintx4{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u});
 #pragma unroll
             for (int i = 2; i >= 0; --i)
 #pragma unroll
-                for (int mt = 0; mt < 2; ++mt) acc_b[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(d2[mt].part(i), ones, acc_b[mt], 0, 0, 0);
-            up = low;
+                for (int mt = 0; mt < MTS; ++mt) acc_b[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(d2[mt].part(i), ones, acc_b[mt], 0, 0, 0);
+            if (!SHARED) up = low;
         }
     }
 
     // register i of tile (mt, j): output channel 16 mt + 4q + i, input channel l16, tap j (every column of the bias tile alike)
     bool nan = false;
 #pragma unroll
-    for (int mt = 0; mt < 2; ++mt) {
+    for (int mt = 0; mt < MTS; ++mt) {
         nan |= any_nan(acc_b[mt]);
 #pragma unroll
-        for (int j = 0; j < 9; ++j) {
+        for (int j = 0; j < 3 * DYS; ++j) {
             nan |= any_nan(acc[mt][j]);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) red[wave][(mt * 9 + j) * 4 + i][lane] = acc[mt][j][i];
+            for (int i = 0; i < 4; ++i) red[wave][((mt0 + mt) * 9 + 3 * dy0 + j) * 4 + i][lane] = acc[mt][j][i];
         }
-        if (l16 == 0) *reinterpret_cast<floatx4*>(&red[wave][DW_REGS + mt][4 * q]) = acc_b[mt];
+        if (l16 == 0) *reinterpret_cast<floatx4*>(&red[wave][DW_REGS + mt0 + mt][4 * q]) = acc_b[mt];
     }
+    const int r_begin = (mt0 * 9 + 3 * dy0) * 4;  // of this block's DYS * MTS * 12 registers
     if (__any(nan)) {
 #pragma unroll 1
-        for (int r = 0; r < DW_REGS; ++r)
-            red[wave][r][lane] = conv2_dw_plain(wb, w, s_begin, s_end, 16 * (r / 36) + 4 * q + r % 4, l16, r % 36 / 4);
-        if (lane < 32) red[wave][DW_REGS + lane / 16][lane % 16] = conv2_dw_plain(wb, w, s_begin, s_end, lane, 0, 9);
+        for (int r = r_begin; r < r_begin + 12 * DYS * MTS; ++r)
+            if (red[wave][r][lane] != red[wave][r][lane])
+                red[wave][r][lane] = conv2_dw_plain(wb, w, s_begin, s_end, 16 * (r / 36) + 4 * q + r % 4, l16, r % 36 / 4);
+        if (lane < 16 * MTS && red[wave][DW_REGS + mt0 + lane / 16][lane % 16] != red[wave][DW_REGS + mt0 + lane / 16][lane % 16])
+            red[wave][DW_REGS + mt0 + lane / 16][lane % 16] = conv2_dw_plain(wb, w, s_begin, s_end, 16 * mt0 + lane, 0, 9);
     }
     __syncthreads();
     float* part = wb.part + ((size_t)w * slots + slot) * CONV2_PART;
 #pragma unroll
-    for (int i = 0; i < CONV2_PART_B2 / DW_NT; ++i) {
-        const int r = (threadIdx.x >> 6) + DW_NW * i;
+    for (int i = 0; i < 12 * DYS * MTS / DW_NW; ++i) {
+        const int r = r_begin + (threadIdx.x >> 6) + DW_NW * i;
         part[r * 64 + lane] = (red[0][r][lane] + red[1][r][lane]) + (red[2][r][lane] + red[3][r][lane]);
     }
-    if (threadIdx.x < C2) {
-        const int r = DW_REGS + threadIdx.x / 16, j = threadIdx.x % 16;
-        part[CONV2_PART_B2 + threadIdx.x] = (red[0][r][j] + red[1][r][j]) + (red[2][r][j] + red[3][r][j]);
+    if (dy0 == 0 && threadIdx.x < 16 * MTS) {
+        const int r = DW_REGS + mt0 + threadIdx.x / 16, j = threadIdx.x % 16;
+        part[CONV2_PART_B2 + 16 * mt0 + threadIdx.x] = (red[0][r][j] + red[1][r][j]) + (red[2][r][j] + red[3][r][j]);
+    }
+}
+
+// conv2's two gradients in one launch, and in small launches (FC1 > 0) fc1's weight gradient with them: none needs
+// another, the one fills the SIMDs that the others leave idle, and one or two launches are saved.  In large ones
+// fc1's blocks only get in the way: sharing the compute units with conv2's, 256 workers of 256 images took 2.11 ms
+// instead of 1.29 + 0.73.
+template <int FC1_DW>  // 0: without fc1, 1: with, 2: with, and a batch that is not a multiple of its stages
+__global__ __launch_bounds__(256, 2) void backward_kernel(WorkerBuffers wb, BwdShape sh, GemmShape fc1)
+{
+    static_assert(DX_NT == 256 && DW_NT == 256, "one block size");
+    __shared__ __attribute__((aligned(16))) union {
+        DxImage images[DX_NW];
+        DwSums red;
+        char stages[FC1_DW ? 2 * Fc1DwFew::STAGE : 1];
+    } lds;
+    int block = blockIdx.x;
+    if (block < sh.dx_blocks) return conv2_dx_block(wb, sh, block, lds.images);
+    block -= sh.dx_blocks;
+    if (block < sh.dw_blocks) return sh.dw_shared ? conv2_dw_block<true>(wb, sh, block, lds.red) : conv2_dw_block<false>(wb, sh, block, lds.red);
+    // fc1's blocks start at a multiple of 8: block number mod 8 says which XCD a tile runs on
+    if constexpr (FC1_DW > 0) {
+        block = blockIdx.x - (sh.dx_blocks + sh.dw_blocks + 7) / 8 * 8;
+        if (block >= 0) fc1_dw_few_block<FC1_DW == 2>(wb, fc1, block, lds.stages);
     }
 }
 
@@ -566,17 +685,12 @@ __global__ __launch_bounds__(DW_NT, 2) void conv2_dw_kernel(WorkerBuffers wb, in
 
 void launch_conv2_fwd(const WorkerBuffers& wb, hipStream_t s)
 {
-    const int ipw = images_per_wavefront(wb.n, wb.B, FWD_IPW), bpw = (wb.B + FWD_NW * ipw - 1) / (FWD_NW * ipw);
-    hipLaunchKernelGGL(conv2_fwd_kernel, dim3(wb.n * bpw), dim3(FWD_NT), 0, s, wb, bpw, ipw);
+    const int ipw = images_per_wavefront(wb.n, wb.B, FWD_IPW), parts = wavefronts_per_image(wb.n, wb.B, 4);
+    const int bpw = blocks_per_worker(wb.B, ipw, parts, FWD_NW);
+    hipLaunchKernelGGL(conv2_fwd_kernel, dim3(wb.n * bpw), dim3(FWD_NT), 0, s, wb, bpw, ipw, parts);
 }
 
 int conv1_part_slots(int batch) { return batch; }
-
-void launch_conv2_dx(const WorkerBuffers& wb, hipStream_t s)
-{
-    const int ipw = images_per_wavefront(wb.n, wb.B, DX_IPW), bpw = (wb.B + DX_NW * ipw - 1) / (DX_NW * ipw);
-    hipLaunchKernelGGL(conv2_dx_kernel, dim3(wb.n * bpw), dim3(DX_NT), 0, s, wb, bpw, ipw);
-}
 
 static int conv2_dw_ipw(int batch) { return (batch + DW_NW * DW_MAX_SLOTS - 1) / (DW_NW * DW_MAX_SLOTS); }
 
@@ -586,10 +700,25 @@ int conv2_part_slots(int batch)
     return (batch + per_slot - 1) / per_slot;
 }
 
-void launch_conv2_dw(const WorkerBuffers& wb, hipStream_t s)
+void launch_backward(const WorkerBuffers& wb, hipStream_t s, int which)
 {
-    const int slots = conv2_part_slots(wb.B);
-    hipLaunchKernelGGL(conv2_dw_kernel, dim3(wb.n * slots), dim3(DW_NT), 0, s, wb, slots, conv2_dw_ipw(wb.B));
+    BwdShape sh;
+    sh.dx_ipw = images_per_wavefront(wb.n, wb.B, DX_IPW);
+    sh.dx_parts = wavefronts_per_image(wb.n, wb.B, 2);
+    sh.dx_blocks_per_worker = blocks_per_worker(wb.B, sh.dx_ipw, sh.dx_parts, DX_NW);
+    sh.dx_blocks = which & BWD_CONV2_DX ? wb.n * sh.dx_blocks_per_worker : 0;
+    sh.dw_slots = conv2_part_slots(wb.B);
+    sh.dw_ipw = conv2_dw_ipw(wb.B);
+    sh.dw_shared = DW_SHARES * DW_NW * wb.n * sh.dw_slots <= 2 * 4 * compute_units();
+    sh.dw_blocks = which & BWD_CONV2_DW ? wb.n * sh.dw_slots * (sh.dw_shared ? DW_SHARES : 1) : 0;
+    const GemmShape fc1 = fc1_dw_few_shape(wb.n, wb.B);
+    const int conv_blocks = (sh.dx_blocks + sh.dw_blocks + 7) / 8 * 8;
+    if (!(which & BWD_FC1_DW))
+        hipLaunchKernelGGL(backward_kernel<0>, dim3(conv_blocks), dim3(256), 0, s, wb, sh, fc1);
+    else
+        hipLaunchKernelGGL((wb.B % Fc1DwFew::KS == 0 ? backward_kernel<1> : backward_kernel<2>), dim3(conv_blocks + gemm_grid(fc1)), dim3(256), 0, s, wb, sh, fc1);
 }
+
+bool fc1_dw_is_few(int n) { return fc1_dw_few(n); }
 
 }  // namespace ps

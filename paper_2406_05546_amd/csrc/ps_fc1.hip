@@ -1,6 +1,8 @@
-// The three contractions of the 1568 -> 512 fully connected layer on the matrix cores: forward with
-// fused bias + ReLU + dropout, input gradient, and the per-worker weight gradient written straight into the worker's queue entry.
+// The three contractions of the 1568 -> 512 fully connected layer on the matrix cores: forward with fused bias +
+// ReLU + dropout, input gradient, and the per-worker weight gradient (which in small launches runs next to
+// conv2's gradients instead, ps_fc1_dw.h).
 #include "ps_common.h"
+#include "ps_fc1_dw.h"
 #include "ps_gemm.h"
 #include "ps_philox.h"
 
@@ -42,22 +44,6 @@ struct Fc1DxEpi {
     }
 };
 
-// Per-worker d fc1.W[u][i] = sum_s d3[s][u] * pool2[s][i], written into the worker's queue entry.
-// Rows m are units, columns n features, so a wavefront's lanes run along contiguous memory.
-struct Fc1DwEpi {
-    WorkerBuffers wb;
-    __device__ const float* a_ptr(int z) const { return wb.d3 + (size_t)z * wb.B * FC1; }
-    __device__ const float* b_ptr(int z) const { return wb.p2 + (size_t)z * wb.B * P2_SIZE; }
-    __device__ void operator()(int z, int m, int n, float4 acc) const
-    {
-        float* g = worker_grad(wb, z) + OFF_W3 + (size_t)m * P2_SIZE + n;
-        g[0] = acc.x;
-        g[P2_SIZE] = acc.y;
-        g[2 * P2_SIZE] = acc.z;
-        g[3 * P2_SIZE] = acc.w;
-    }
-};
-
 }  // namespace
 
 // Block tiles are 128 x 128 (four wavefronts of 64 x 64).  The 1568 features are 12 such tiles plus 32: that
@@ -68,20 +54,13 @@ struct Fc1DwEpi {
 // 32 x 32 tiles with a wavefront for every chunk of K (1568 = 7 x 14 stages, 512 = 4 x 8).  Whether a batch
 // is summed in chunks depends on its size alone, so that a worker's gradient has the same bits whatever else
 // is in the launch; beyond 64 the chunks' totals would not fit the registers of 64 x 64 wavefront tiles.
-// 256 workers of 256 images: forward 0.79 -> 0.55 ms, input gradient 0.805 -> 0.57, weight gradient 0.845 -> 0.74
-// against fp32 MFMAs (the chip runs at 1.85-2.05 GHz under these kernels; wavefront priorities and fixed
-// MFMA : vector instruction patterns change nothing).  Two workers of 32: 65 -> 14, 40 -> 6 and 10 -> 7 us;
-// one of 256: 67 -> 50, 42 -> 19, 24 -> 12 us.
-constexpr int FEAT_WIDE = P2_SIZE / 128 * 128;  // 1536
 constexpr int FWD_CHUNKS = 7, FWD_CHUNK = 14, DX_CHUNKS = 4, DX_CHUNK = 8, CHUNKED_BATCH = 64;
-static_assert(FWD_CHUNKS * FWD_CHUNK * GEMM_KS == P2_SIZE && DX_CHUNKS * DX_CHUNK * GEMM_KS == FC1, "whole chunks");
-
-static bool few_tiles(int wide_tiles) { return wide_tiles < compute_units(); }
+static_assert(FWD_CHUNKS * FWD_CHUNK * GEMM_K == P2_SIZE && DX_CHUNKS * DX_CHUNK * GEMM_K == FC1, "whole chunks");
 
 // forward: rows = 512 units (W3, k-contiguous), columns = the worker's samples (pool2, k-contiguous)
 void launch_fc1_fwd(const WorkerBuffers& wb, hipStream_t s)
 {
-    const bool few = few_tiles(FC1 / 128 * ((wb.B + 127) / 128) * wb.n);
+    const bool few = gemm_few_tiles(FC1 / 128 * ((wb.B + 127) / 128) * wb.n);
     const Fc1FwdEpi epi{wb};
     if (wb.B <= CHUNKED_BATCH) {
         if (few)
@@ -89,29 +68,23 @@ void launch_fc1_fwd(const WorkerBuffers& wb, hipStream_t s)
         else
             gemm_launch<GemmCfg<true, true, 2, 1, 2, 2, 2>, FWD_CHUNK, 2>(FC1, wb.B, P2_SIZE, P2_SIZE, P2_SIZE, wb.n, epi, s);
     } else if (few) {
-        gemm_launch<GemmCfg<true, true, 1, 1, 2, 2, 6>, 0, 2>(FC1, wb.B, P2_SIZE, P2_SIZE, P2_SIZE, wb.n, epi, s);
+        gemm_launch<GemmCfg<true, true, 1, 1, 2, 2, 4, 32>, 0, 2>(FC1, wb.B, P2_SIZE, P2_SIZE, P2_SIZE, wb.n, epi, s);
     } else {
         gemm_launch<GemmCfg<true, true, 2, 2, 2, 2, 2>, 0, 2>(FC1, wb.B, P2_SIZE, P2_SIZE, P2_SIZE, wb.n, epi, s);
     }
 }
 
-// weight gradient: rows = 512 units (d3, row-contiguous), columns = 1568 features (pool2, row-contiguous),
-// contraction over the worker's samples
+// weight gradient of a launch that is not FEW (see ps_fc1_dw.h)
 void launch_fc1_dw(const WorkerBuffers& wb, hipStream_t s)
 {
-    const Fc1DwEpi epi{wb};
-    if (few_tiles(FC1 / 128 * (FEAT_WIDE / 128) * wb.n))
-        gemm_launch<GemmCfg<false, false, 1, 1, 2, 2, 6>, 0, 2>(FC1, P2_SIZE, wb.B, FC1, P2_SIZE, wb.n, epi, s);
-    else
-        gemm_launch_edge<GemmCfg<false, false, 2, 2, 2, 2, 2>, GemmCfg<false, false, 1, 1, 4, 1, 2>, 0, 2>(FC1, P2_SIZE, wb.B, FC1, P2_SIZE, wb.n,
-                                                                                                   FC1, FEAT_WIDE, epi, s);
+    gemm_launch_edge<Fc1DwMain, Fc1DwEdge, 0, 2>(FC1, P2_SIZE, wb.B, FC1, P2_SIZE, wb.n, FC1, FEAT_WIDE, Fc1DwEpi{wb}, s);
 }
 
 // input gradient: rows = 1568 features (W3, row-contiguous), columns = samples (d3, k-contiguous),
 // contraction over the 512 units
 void launch_fc1_dx(const WorkerBuffers& wb, hipStream_t s)
 {
-    const bool few = few_tiles(FEAT_WIDE / 128 * ((wb.B + 127) / 128) * wb.n);
+    const bool few = gemm_few_tiles(FEAT_WIDE / 128 * ((wb.B + 127) / 128) * wb.n);
     const Fc1DxEpi epi{wb};
     if (wb.B <= CHUNKED_BATCH) {
         if (few)
@@ -120,7 +93,7 @@ void launch_fc1_dx(const WorkerBuffers& wb, hipStream_t s)
             gemm_launch_edge<GemmCfg<false, true, 2, 1, 2, 2, 2>, GemmCfg<false, true, 1, 1, 1, 4, 2>, DX_CHUNK, 2>(P2_SIZE, wb.B, FC1, P2_SIZE, FC1, wb.n,
                                                                                                           FEAT_WIDE, wb.B, epi, s);
     } else if (few) {
-        gemm_launch<GemmCfg<false, true, 1, 1, 2, 2, 6>, 0, 2>(P2_SIZE, wb.B, FC1, P2_SIZE, FC1, wb.n, epi, s);
+        gemm_launch<GemmCfg<false, true, 1, 1, 2, 2, 4, 32>, 0, 2>(P2_SIZE, wb.B, FC1, P2_SIZE, FC1, wb.n, epi, s);
     } else {
         gemm_launch_edge<GemmCfg<false, true, 2, 2, 2, 2, 2>, GemmCfg<false, true, 1, 1, 1, 4, 2>, 0, 2>(P2_SIZE, wb.B, FC1, P2_SIZE, FC1, wb.n,
                                                                                                FEAT_WIDE, wb.B, epi, s);

@@ -112,6 +112,21 @@ int images_per_wavefront(int n, int batch, int most)
     return ipw;
 }
 
+// How many wavefronts (1, 2 or 4, up to `most`) can share an image and still find SIMDs to run on, one each.
+int wavefronts_per_image(int n, int batch, int most)
+{
+    int parts = 1;
+    while (parts < most && 2 * parts * n * batch <= 4 * compute_units()) parts *= 2;
+    return parts;
+}
+
+// Blocks of `wavefronts` for one worker; with several wavefronts per image every one takes (a part of) one image.
+int blocks_per_worker(int batch, int images_per_wavefront, int wavefronts_per_image, int wavefronts)
+{
+    const int units = (batch + images_per_wavefront - 1) / images_per_wavefront * wavefronts_per_image;
+    return (units + wavefronts - 1) / wavefronts;
+}
+
 #define PS_TIMED(id, ...)      \
     do {                       \
         prof.begin(id, s);     \
@@ -132,10 +147,17 @@ hipError_t launch_worker_backward(const WorkerBuffers& wb, hipStream_t s, Profil
 {
     if (wb.n * wb.B <= 0) return hipSuccess;
     PS_TIMED(K_FC2, launch_fc2(wb, s));
-    PS_TIMED(K_FC1_DW, launch_fc1_dw(wb, s));
-    PS_TIMED(K_FC1_DX, launch_fc1_dx(wb, s));
-    PS_TIMED(K_CONV2_DW, launch_conv2_dw(wb, s));
-    PS_TIMED(K_CONV2_DX, launch_conv2_dx(wb, s));
+    const bool few = fc1_dw_is_few(wb.n);
+    if (prof.enabled) {  // timed one by one
+        PS_TIMED(K_FC1_DW, few ? launch_backward(wb, s, BWD_FC1_DW) : launch_fc1_dw(wb, s));
+        PS_TIMED(K_FC1_DX, launch_fc1_dx(wb, s));
+        PS_TIMED(K_CONV2_DW, launch_backward(wb, s, BWD_CONV2_DW));
+        PS_TIMED(K_CONV2_DX, launch_backward(wb, s, BWD_CONV2_DX));
+    } else {
+        if (!few) launch_fc1_dw(wb, s);
+        launch_fc1_dx(wb, s);
+        launch_backward(wb, s, BWD_CONV2_DX | BWD_CONV2_DW | (few ? BWD_FC1_DW : 0));
+    }
     // one value per thread while the chip has room, at least the blocks that the conv1 values take
     const int reduce_y = wb.n * (REDUCE_ITEMS / 256 + 1) <= 8 * compute_units() ? REDUCE_ITEMS / 256 + 1 : 8;
     PS_TIMED(K_GRAD_REDUCE, hipLaunchKernelGGL(grad_reduce_kernel, dim3(wb.n, reduce_y), dim3(256), 0, s, wb, fc2_split(wb.n),

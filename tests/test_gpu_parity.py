@@ -828,3 +828,67 @@ def test_applies_over_consecutive_and_listed_rows(ps, order):
         assert np.abs(ps.ps_get_weights(ctx) - want).max() <= 12 * 2.0 ** -24
     finally:
         ps.ps_destroy(ctx)
+
+
+@pytest.mark.parametrize("n,B", [(70, 40), (32, 130)])
+def test_gradient_bits_do_not_depend_on_the_launch(ps, n, B):
+    """One worker alone runs in the small-launch forms of the kernels (several wavefronts to an image, a wavefront to
+    each chunk of K, small tiles), among `n` in the large-launch forms: the same bytes, for batches on both sides of
+    64, up to which fc1 is summed in chunks."""
+    theta = synth.he_uniform_theta(21)
+    mbs = [synth.minibatch_id(w, 7) for w in range(n)]
+    x, y = synth.minibatches(DATA_SEED, mbs, B)
+    ctx = ps.ps_init(ps.make_config(n, B, 1, n + 1, DROP_SEED, P_DROP))
+    try:
+        ps.ps_set_weights(ctx, theta)
+        xd, yd = _torch_inputs(x, y)
+        entries = ps.worker_grads_batched(ctx, range(n), [0] * n, mbs, xd, yd)
+        for i in (0, n - 1):
+            (q,) = ps.worker_grads_batched(ctx, [i], [0], [mbs[i]], xd[i:i + 1], yd[i:i + 1])
+            ps.ps_sync(ctx)
+            assert np.array_equal(ps.ps_get_grad(ctx, entries[i]), ps.ps_get_grad(ctx, q)), f"n={n} B={B} worker {i}"
+            ps.ps_apply_async(ctx, q, 0.0)
+    finally:
+        ps.ps_destroy(ctx)
+
+
+@pytest.mark.parametrize("n,B", [(2, 16), (80, 40), (2, 130), (70, 130)])
+@pytest.mark.parametrize("bad", [np.inf, 3.3999e38])
+def test_operands_that_cannot_be_split(ps, n, B, bad):
+    """An infinite weight, or a finite one that rounds to infinity in 16 bits, cannot be split into three parts.  The
+    products it enters must come out as fp32 arithmetic has them, the rest must stay as it was: the last worker, on
+    weights of its own, has one such fc1 weight."""
+    theta = synth.he_uniform_theta(22)
+    unit = 77
+    mbs = [synth.minibatch_id(w, 9) for w in range(n)]
+    x, y = synth.minibatches(DATA_SEED, mbs, B)
+    ctx = ps.ps_init(ps.make_config(n, B, 2, 2 * n, DROP_SEED, P_DROP))
+    try:
+        ps.ps_set_weights(ctx, theta)
+        xd, yd = _torch_inputs(x, y)
+        want = ps.worker_grads_batched(ctx, range(n), [0] * n, mbs, xd, yd)
+        good = ps.ps_debug_last_batch(ctx, n - 1)
+        feat = int(ps.ps_debug_last_activations(ctx, n - 1)["pool2_val"].mean(0).argmax())     # of the liveliest feature
+        broken = theta.copy()
+        broken[4800 + unit * 1568 + feat] = bad
+        ps.ps_load_snapshot(ctx, 1, broken, 0)
+        got = ps.worker_grads_batched(ctx, range(n), [0] * (n - 1) + [1], mbs, xd, yd)
+        ps.ps_sync(ctx)
+        dbg, act = ps.ps_debug_last_batch(ctx, n - 1), ps.ps_debug_last_activations(ctx, n - 1)
+        assert np.array_equal(ps.ps_get_grad(ctx, want[0]), ps.ps_get_grad(ctx, got[0]))
+        h, p2 = dbg["hdrop"], act["pool2_val"][:, feat]
+        other = np.arange(512) != unit
+        assert np.array_equal(h[:, other], good["hdrop"][:, other])
+        kept = dbg["keep"][:, unit] == 1
+        with np.errstate(over="ignore", invalid="ignore"):
+            product = p2 * np.float32(bad)                     # inf * 0 is NaN, which the ReLU turns into 0
+            ideal = np.where(product > 0, product / np.float32(1 - P_DROP), 0).astype(np.float32)
+        assert (p2[kept] > 0).any()
+        # the other 1567 products are nothing next to such a weight's; without one the unit is an ordinary sum
+        on = kept & ((p2 > 0) | np.isinf(bad))
+        np.testing.assert_allclose(h[on, unit], ideal[on], rtol=1e-5)
+        assert not h[~kept, unit].any()
+        if np.isinf(bad):       # and the gradient of that worker is not a number any more where the unit enters it
+            assert not np.isfinite(ps.ps_get_grad(ctx, got[-1])).all()
+    finally:
+        ps.ps_destroy(ctx)
