@@ -15,7 +15,9 @@
 //              consecutive units: one 16-byte LDS read for the gate, one 16-byte store for d3;
 //   d W4       rows = classes, columns = units, K = images; its A operand is d4 exactly as the
 //              accumulator layout holds it, its B operand the activations that also gate d3.
-// W4 sits in registers in both operand layouts (64 per lane), d W4 in 32 accumulators per lane.  Each
+// W4 sits in registers in both operand layouts (64 per lane, brought in 16 bytes at a time behind the first
+// activations: in single values, more loads than can be in flight, it took 2.1 of the kernel's 10 us in small
+// launches; 65,536 images 73 -> 67 us), d W4 in 32 accumulators per lane.  Each
 // block's sums go to its own partial slot and are added up in fixed order by the reduction kernel.
 #include "ps_common.h"
 
@@ -53,31 +55,6 @@ __global__ __launch_bounds__(256, 2) void fc2_kernel(WorkerBuffers wb)
     const bool cls_ok = l16 < NCLS;
     const int u0 = 128 * wave;
 
-    // B operand of the logits: k-step (j, e) pairs lane quarter q with unit u0 + 16j + 4q + e
-    float wa[8][4];
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) wa[j][e] = cls_ok ? W4[l16 * FC1 + u0 + 16 * j + 4 * q + e] : 0.f;
-    // B operand of d3: tile t = 4T + e, k-step i pairs lane quarter q with class 4q + i; column l16 = unit
-    // u0 + 64T + 4*l16 + e
-    float wbk[8][4];
-#pragma unroll
-    for (int t = 0; t < 8; ++t)
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            wbk[t][i] = 4 * q + i < NCLS ? W4[(4 * q + i) * FC1 + u0 + 64 * (t >> 2) + 4 * l16 + (t & 3)] : 0.f;
-    const float b4 = cls_ok ? theta[OFF_B4 + l16] : 0.f;
-    const float inv_b = 1.f / (float)B;
-
-    floatx4 acc_w4[8];  // d W4 tile t = 4T + e: register i = class 4q + i, column l16 = unit u0 + 64T + 4*l16 + e
-    float acc_b3[8], acc_b4 = 0.f, acc_loss = 0.f;
-#pragma unroll
-    for (int t = 0; t < 8; ++t) {
-        acc_w4[t] = floatx4{0.f, 0.f, 0.f, 0.f};
-        acc_b3[t] = 0.f;
-    }
-
     // activations of a group: 16 x 128 float4, eight per thread; rows beyond the batch are zero
     float4 hv[8];
     auto prefetch = [&](int grp) {
@@ -91,6 +68,35 @@ __global__ __launch_bounds__(256, 2) void fc2_kernel(WorkerBuffers wb)
     };
     int grp = blockIdx.y, buf = 0;
     if (grp < n_groups) prefetch(grp);
+
+    // B operand of the logits: k-step (j, e) pairs lane quarter q with unit u0 + 16j + 4q + e
+    floatx4 wa[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        wa[j] = *reinterpret_cast<const floatx4*>(W4 + min(l16, NCLS - 1) * FC1 + u0 + 16 * j + 4 * q);
+        if (!cls_ok) wa[j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    }
+    // B operand of d3: tile t = 4T + e, k-step i pairs lane quarter q with class 4q + i; column l16 = unit
+    // u0 + 64T + 4*l16 + e
+    floatx4 wbk[2][4];
+#pragma unroll
+    for (int T = 0; T < 2; ++T)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            wbk[T][i] = *reinterpret_cast<const floatx4*>(W4 + min(4 * q + i, NCLS - 1) * FC1 + u0 + 64 * T + 4 * l16);
+            if (4 * q + i >= NCLS) wbk[T][i] = floatx4{0.f, 0.f, 0.f, 0.f};
+        }
+    const float b4 = cls_ok ? theta[OFF_B4 + l16] : 0.f;
+    const float inv_b = 1.f / (float)B;
+
+    floatx4 acc_w4[8];  // d W4 tile t = 4T + e: register i = class 4q + i, column l16 = unit u0 + 64T + 4*l16 + e
+    float acc_b3[8], acc_b4 = 0.f, acc_loss = 0.f;
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+        acc_w4[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+        acc_b3[t] = 0.f;
+    }
+
     for (; grp < n_groups; grp += split, buf ^= 1) {
         const size_t g0 = (size_t)w * B + (size_t)grp * FC2_G;
         const int valid = min(FC2_G, B - grp * FC2_G);
@@ -156,7 +162,7 @@ __global__ __launch_bounds__(256, 2) void fc2_kernel(WorkerBuffers wb)
             for (int e = 0; e < 4; ++e) {
                 dh[e] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int i = 0; i < 4; ++i) dh[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(d4a[i], wbk[4 * T + e][i], dh[e], 0, 0, 0);
+                for (int i = 0; i < 4; ++i) dh[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(d4a[i], wbk[T][i][e], dh[e], 0, 0, 0);
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
                     acc_w4[4 * T + e] = __builtin_amdgcn_mfma_f32_16x16x4f32(d4[i], hc[i][e], acc_w4[4 * T + e], 0, 0, 0);
