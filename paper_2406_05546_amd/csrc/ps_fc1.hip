@@ -77,25 +77,28 @@ void launch_fc1_fwd(const WorkerBuffers& wb, hipStream_t s)
 // weight gradient of a launch that is not FEW (see ps_fc1_dw.h)
 void launch_fc1_dw(const WorkerBuffers& wb, hipStream_t s)
 {
-    gemm_launch_edge<Fc1DwMain, Fc1DwEdge, 0, 2>(FC1, P2_SIZE, wb.B, FC1, P2_SIZE, wb.n, FC1, FEAT_WIDE, Fc1DwEpi{wb}, s);
+    gemm_launch_edge<Fc1DwMain, Fc1DwEdge, true, 0, 2>(FC1, P2_SIZE, wb.B, FC1, P2_SIZE, wb.n, FC1, FEAT_WIDE, Fc1DwEpi<true>{wb}, s);
 }
 
 // input gradient: rows = 1568 features (W3, row-contiguous), columns = samples (d3, k-contiguous),
 // contraction over the 512 units
 void launch_fc1_dx(const WorkerBuffers& wb, hipStream_t s)
 {
-    const bool few = gemm_few_tiles(FEAT_WIDE / 128 * ((wb.B + 127) / 128) * wb.n);
+    // 64 x 64 tiles already fall behind where there is a wide tile for two compute units (8 workers of 128 images, 96
+    // tiles: 22 against 28 us; 16 of 128: 37 against 31)
+    const int wide_tiles = FEAT_WIDE / 128 * ((wb.B + 127) / 128) * wb.n;
+    const bool few = gemm_few_tiles(wb.B <= CHUNKED_BATCH ? wide_tiles : 2 * wide_tiles);
     const Fc1DxEpi epi{wb};
     if (wb.B <= CHUNKED_BATCH) {
         if (few)
             gemm_launch_chunks<false, true, DX_CHUNKS, DX_CHUNK>(P2_SIZE, wb.B, P2_SIZE, FC1, wb.n, epi, s);
         else
-            gemm_launch_edge<GemmCfg<false, true, 2, 1, 2, 2, 2>, GemmCfg<false, true, 1, 1, 1, 4, 2>, DX_CHUNK, 2>(P2_SIZE, wb.B, FC1, P2_SIZE, FC1, wb.n,
+            gemm_launch_edge<GemmCfg<false, true, 2, 1, 2, 2, 2>, GemmCfg<false, true, 1, 1, 1, 4, 2>, false, DX_CHUNK, 2>(P2_SIZE, wb.B, FC1, P2_SIZE, FC1, wb.n,
                                                                                                           FEAT_WIDE, wb.B, epi, s);
     } else if (few) {
         gemm_launch<GemmCfg<false, true, 1, 1, 2, 2, 4, 32>, 0, 2>(P2_SIZE, wb.B, FC1, P2_SIZE, FC1, wb.n, epi, s);
     } else {
-        gemm_launch_edge<GemmCfg<false, true, 2, 2, 2, 2, 2>, GemmCfg<false, true, 1, 1, 1, 4, 2>, 0, 2>(P2_SIZE, wb.B, FC1, P2_SIZE, FC1, wb.n,
+        gemm_launch_edge<GemmCfg<false, true, 2, 2, 2, 2, 2>, GemmCfg<false, true, 1, 1, 1, 4, 2>, false, 0, 2>(P2_SIZE, wb.B, FC1, P2_SIZE, FC1, wb.n,
                                                                                                FEAT_WIDE, wb.B, epi, s);
     }
 }

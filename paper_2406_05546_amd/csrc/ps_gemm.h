@@ -309,28 +309,28 @@ __device__ __forceinline__ void gemm_block(const GemmShape& sh, const Epi& epi, 
             gemm_finish<Cfg::A_KC, Cfg::B_KC>(sh, epi, z, m0 + (wm * TM + a) * 32, n0 + (wn * TN + b) * 32, lane, CHUNK > 0 ? total[a][b] : acc[a][b].value());
 }
 
-// The same sums for a launch with too few tiles to fill the chip: a block owns one 32x32 tile and its wavefronts
-// one CHUNK of MFMA steps each; the chunks' sums meet in LDS and are added up in order, so that a value is bit for
+// The same sums for a launch with too few tiles to fill the chip: a block owns one tile of 32 x 32 NT and its
+// wavefronts one CHUNK of MFMA steps each; the chunks' sums meet in LDS and are added up in order, so that a value is bit for
 // bit what gemm_block<..., CHUNK> makes of it.  A wavefront brings its operands through LDS of its own, 32
 // contraction indices at a time, so that a load touches whole cache lines: straight into the MFMA layout a load
 // touched 32 lines, which took all of the 14 us of the forward pass of two workers of 32 images and of the 30 us of
 // 16 of 64.
-template <bool A_KC, bool B_KC, int CHUNKS, int CHUNK, class Epi>
+template <bool A_KC, bool B_KC, int NT, int CHUNKS, int CHUNK, class Epi>
 __global__ __launch_bounds__(64 * CHUNKS) void gemm_split_chunks(GemmShape sh, Epi epi)
 {
     static_assert(CHUNKS >= 4, "four wavefronts store the tile");
     constexpr int KS = 2 * GEMM_K, STAGES = CHUNK / 2;
     static_assert(CHUNK % 2 == 0, "whole stages");
     using OpA = GemmOperand<32, A_KC, false, 64, KS>;
-    using OpB = GemmOperand<32, B_KC, false, 64, KS>;
+    using OpB = GemmOperand<32 * NT, B_KC, false, 64, KS>;
     __shared__ __attribute__((aligned(16))) union {
         char stage[CHUNKS][OpA::BYTES + OpB::BYTES];
-        float part[CHUNKS][16][64];
+        float part[CHUNKS][NT][16][64];
     } lds;
     const int lane = threadIdx.x & 63, wave = uniform(threadIdx.x >> 6);
     const int t = gemm_tile(blockIdx.x, sh.gx * sh.gy * sh.gz);
     if (t >= sh.gx * sh.gy * sh.gz) return;
-    const int m0 = t % sh.gx * 32, n0 = t / sh.gx % sh.gy * 32, z = t / (sh.gx * sh.gy);
+    const int m0 = t % sh.gx * 32, n0 = t / sh.gx % sh.gy * 32 * NT, z = t / (sh.gx * sh.gy);
     OpA opa;
     OpB opb;
     opa.init(epi.a_ptr(z), sh.lda, m0, sh.M, sh.K, lane);
@@ -344,8 +344,9 @@ __global__ __launch_bounds__(64 * CHUNKS) void gemm_split_chunks(GemmShape sh, E
         opa.load(k0 + i, a[i]);
         opb.load(k0 + i, b[i]);
     }
-    SplitSum<floatx16> sum;
-    sum.clear();
+    SplitSum<floatx16> sum[NT];
+#pragma unroll
+    for (int i = 0; i < NT; ++i) sum[i].clear();
 #pragma unroll
     for (int kt = 0; kt < STAGES; ++kt) {
         wave_lds_fence();  // the last stage has been read
@@ -357,22 +358,37 @@ __global__ __launch_bounds__(64 * CHUNKS) void gemm_split_chunks(GemmShape sh, E
         }
         wave_lds_fence();
 #pragma unroll
-        for (int sub = 0; sub < KS / GEMM_K; ++sub) sum.add(OpA::fetch(tile, 0, sub, lane), OpB::fetch(tile + OpA::BYTES, 0, sub, lane));
+        for (int sub = 0; sub < KS / GEMM_K; ++sub) {
+            const Split8 fa = OpA::fetch(tile, 0, sub, lane);
+            Split8 fb[NT];
+#pragma unroll
+            for (int i = 0; i < NT; ++i) fb[i] = OpB::fetch(tile + OpA::BYTES, i, sub, lane);
+#pragma unroll
+            for (int t = 0; t <= SPLIT_SMALL; ++t)
+#pragma unroll
+                for (int i = 0; i < NT; ++i) sum[i].add(t, fa, fb[i]);
+        }
     }
-    const floatx16 acc = sum.value();
     __syncthreads();  // everybody has read its stages, whose place the sums take
 #pragma unroll
-    for (int i = 0; i < 16; ++i) lds.part[wave][i][lane] = acc[i];
+    for (int j = 0; j < NT; ++j) {
+        const floatx16 acc = sum[j].value();
+#pragma unroll
+        for (int i = 0; i < 16; ++i) lds.part[wave][j][i][lane] = acc[i];
+    }
     __syncthreads();
     if (wave >= 4) return;
-    float v[4];  // wavefront g stores rows 8g + 4h .. +3
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        v[i] = lds.part[0][4 * wave + i][lane];
+    for (int j = 0; j < NT; ++j) {
+        float v[4];  // wavefront g stores rows 8g + 4h .. +3
 #pragma unroll
-        for (int c = 1; c < CHUNKS; ++c) v[i] += lds.part[c][4 * wave + i][lane];
+        for (int i = 0; i < 4; ++i) {
+            v[i] = lds.part[0][j][4 * wave + i][lane];
+#pragma unroll
+            for (int c = 1; c < CHUNKS; ++c) v[i] += lds.part[c][j][4 * wave + i][lane];
+        }
+        gemm_store<A_KC, B_KC>(sh, epi, z, m0 + 8 * wave + 4 * (lane >> 5), n0 + 32 * j + (lane & 31), v[0], v[1], v[2], v[3]);
     }
-    gemm_store<A_KC, B_KC>(sh, epi, z, m0 + 8 * wave + 4 * (lane >> 5), n0 + (lane & 31), v[0], v[1], v[2], v[3]);
 }
 
 // Whether a launch over this many 128 x 128 tiles leaves compute units idle.
@@ -387,19 +403,32 @@ __global__ __launch_bounds__(256, MINW) void gemm_split(GemmShape sh, Epi epi)
     gemm_block<Cfg, false, CHUNK>(sh, epi, blockIdx.x, lds);
 }
 
-// Two tile shapes in one launch: the first `main_blocks` blocks cover the main part of C with Main tiles,
-// the rest cover an edge strip with Edge tiles.  The edge blocks are dispatched last and run next to the
-// last main blocks instead of as a launch of their own behind them.
-template <class Main, class Edge, bool RAGGED, int CHUNK, int MINW, class Epi>
+// Two tile shapes in one launch: `main_blocks` blocks cover the main part of C with Main tiles, the rest cover an
+// edge strip with Edge tiles.  The edge blocks are dispatched last and run next to the last main blocks instead of
+// as a launch of their own behind them; or, with MIXED, evenly among the main blocks, a block for every XCD at a time.
+// Blocks of one shape all reach their stores at the same time, over and over: where those make up a fifth of a
+// tile's time, the shorter blocks among them put the compute units out of step and the stores of some run under the
+// products of others (fc1 weight gradient, 256 workers of 256 images: 0.77 -> 0.68 ms; nothing stored at all 0.61).
+// The input gradient stores half as much per product and loses more at the end than it wins (0.607 -> 0.621).
+template <class Main, class Edge, bool RAGGED, bool MIXED, int CHUNK, int MINW, class Epi>
 __global__ __launch_bounds__(256, MINW) void gemm_split_edge(GemmShape sh_main, GemmShape sh_edge, int main_blocks, Epi epi)
 {
     static_assert(Main::KS == Edge::KS, "one stage for both tile shapes");
     constexpr int STAGE = Main::STAGE > Edge::STAGE ? Main::STAGE : Edge::STAGE;
     __shared__ __attribute__((aligned(16))) char lds[2 * STAGE];
-    if ((int)blockIdx.x < main_blocks)  // uniform over the block
-        gemm_block<Main, RAGGED, CHUNK>(sh_main, epi, blockIdx.x, lds);
+    int block = blockIdx.x;
+    bool main = block < main_blocks;  // uniform over the block
+    if (MIXED) {  // of every `period` groups of blocks the first is an edge group, until there are none left
+        const int group = block / GEMM_XCDS, edge_groups = (gridDim.x - main_blocks) / GEMM_XCDS, period = gridDim.x / (gridDim.x - main_blocks);
+        main = group % period != 0 || group / period >= edge_groups;
+        block -= GEMM_XCDS * (main ? min(edge_groups, group / period + 1) : group - group / period);
+    } else if (!main) {
+        block -= main_blocks;
+    }
+    if (main)
+        gemm_block<Main, RAGGED, CHUNK>(sh_main, epi, block, lds);
     else
-        gemm_block<Edge, RAGGED, CHUNK>(sh_edge, epi, blockIdx.x - main_blocks, lds);
+        gemm_block<Edge, RAGGED, CHUNK>(sh_edge, epi, block, lds);
 }
 
 template <class Cfg>
@@ -419,19 +448,25 @@ void gemm_launch(int M, int N, int K, int lda, int ldb, int batch, const Epi& ep
     hipLaunchKernelGGL((gemm_split<Cfg, CHUNK, MINW, Epi>), dim3(gemm_grid(sh)), dim3(256), 0, s, sh, epi);
 }
 
-// One problem per batch index in 32x32 tiles, K = CHUNKS * CHUNK stages.
+// One problem per batch index in tiles of 32 x 32, or 32 x 64 if those alone give every compute unit a block; K =
+// CHUNKS * CHUNK MFMA steps.
 template <bool A_KC, bool B_KC, int CHUNKS, int CHUNK, class Epi>
 void gemm_launch_chunks(int M, int N, int lda, int ldb, int batch, const Epi& epi, hipStream_t s)
 {
     if (M <= 0 || N <= 0 || batch <= 0) return;
-    const GemmShape sh{M, N, CHUNKS * CHUNK * GEMM_K, lda, ldb, (M + 31) / 32, (N + 31) / 32, batch, 0, 0};
-    hipLaunchKernelGGL((gemm_split_chunks<A_KC, B_KC, CHUNKS, CHUNK, Epi>), dim3(gemm_grid(sh)), dim3(64 * CHUNKS), 0, s, sh, epi);
+    GemmShape sh{M, N, CHUNKS * CHUNK * GEMM_K, lda, ldb, (M + 31) / 32, (N + 31) / 32, batch, 0, 0};
+    if (N <= 32 || sh.gx * sh.gy * batch <= compute_units()) {
+        hipLaunchKernelGGL((gemm_split_chunks<A_KC, B_KC, 1, CHUNKS, CHUNK, Epi>), dim3(gemm_grid(sh)), dim3(64 * CHUNKS), 0, s, sh, epi);
+    } else {
+        sh.gy = (N + 63) / 64;
+        hipLaunchKernelGGL((gemm_split_chunks<A_KC, B_KC, 2, CHUNKS, CHUNK, Epi>), dim3(gemm_grid(sh)), dim3(64 * CHUNKS), 0, s, sh, epi);
+    }
 }
 
 // Rows [0, m_split) x columns [0, n_split) of C with Main tiles and the rest with Edge tiles, where exactly
 // one of the splits is inside C (the other equals M or N) and is a multiple of Main's tile: covering a
 // ragged edge with narrow tiles avoids a mostly empty wide tile.
-template <class Main, class Edge, int CHUNK, int MINW, class Epi>
+template <class Main, class Edge, bool MIXED, int CHUNK, int MINW, class Epi>
 void gemm_launch_edge(int M, int N, int K, int lda, int ldb, int batch, int m_split, int n_split, const Epi& epi, hipStream_t s)
 {
     if (M <= 0 || N <= 0 || batch <= 0) return;
@@ -441,9 +476,9 @@ void gemm_launch_edge(int M, int N, int K, int lda, int ldb, int batch, int m_sp
     const int main_blocks = gemm_grid(sh_main), grid = main_blocks + gemm_grid(sh_edge);
     constexpr bool CAN_BE_RAGGED = !Main::A_KC && !Main::B_KC;
     if (!CAN_BE_RAGGED || K % Main::KS == 0)
-        hipLaunchKernelGGL((gemm_split_edge<Main, Edge, false, CHUNK, MINW, Epi>), dim3(grid), dim3(256), 0, s, sh_main, sh_edge, main_blocks, epi);
+        hipLaunchKernelGGL((gemm_split_edge<Main, Edge, false, MIXED, CHUNK, MINW, Epi>), dim3(grid), dim3(256), 0, s, sh_main, sh_edge, main_blocks, epi);
     else
-        hipLaunchKernelGGL((gemm_split_edge<Main, Edge, CAN_BE_RAGGED, CHUNK, MINW, Epi>), dim3(grid), dim3(256), 0, s, sh_main, sh_edge, main_blocks, epi);
+        hipLaunchKernelGGL((gemm_split_edge<Main, Edge, CAN_BE_RAGGED, MIXED, CHUNK, MINW, Epi>), dim3(grid), dim3(256), 0, s, sh_main, sh_edge, main_blocks, epi);
 }
 
 }  // namespace ps

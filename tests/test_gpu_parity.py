@@ -830,7 +830,7 @@ def test_applies_over_consecutive_and_listed_rows(ps, order):
         ps.ps_destroy(ctx)
 
 
-@pytest.mark.parametrize("n,B", [(70, 40), (32, 130)])
+@pytest.mark.parametrize("n,B", [(20, 40), (70, 40), (32, 130)])
 def test_gradient_bits_do_not_depend_on_the_launch(ps, n, B):
     """One worker alone runs in the small-launch forms of the kernels (several wavefronts to an image, a wavefront to
     each chunk of K, small tiles), among `n` in the large-launch forms: the same bytes, for batches on both sides of
