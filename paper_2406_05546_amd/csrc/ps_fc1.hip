@@ -50,7 +50,8 @@ struct Fc1DxEpi {
 // edge is covered with 32-wide tiles (four wavefronts of 32 x 32 side by side) instead of a thirteenth wide
 // tile that would be three quarters empty, by extra blocks of the same launch that run next to the last wide
 // tiles.  A launch with fewer wide tiles than compute units takes as long as the serial loop over K of one
-// tile, and is cut up: into 64 x 64 tiles, or, in the forward and the input gradient of batches up to 64, into
+// tile, and is cut up: into 64 x 64 tiles (32 x 32, with wavefronts that only multiply, where those find a compute unit
+// each), or, in the forward and the input gradient of batches up to 64, into
 // 32 x 32 tiles with a wavefront for every chunk of K (1568 = 7 x 14 stages, 512 = 4 x 8).  Whether a batch
 // is summed in chunks depends on its size alone, so that a worker's gradient has the same bits whatever else
 // is in the launch; beyond 64 the chunks' totals would not fit the registers of 64 x 64 wavefront tiles.
@@ -67,6 +68,8 @@ void launch_fc1_fwd(const WorkerBuffers& wb, hipStream_t s)
             gemm_launch_chunks<true, true, FWD_CHUNKS, FWD_CHUNK>(FC1, wb.B, P2_SIZE, P2_SIZE, wb.n, epi, s);
         else
             gemm_launch<GemmCfg<true, true, 2, 1, 2, 2, 2>, FWD_CHUNK, 2>(FC1, wb.B, P2_SIZE, P2_SIZE, P2_SIZE, wb.n, epi, s);
+    } else if (gemm_roles_fit(FC1, wb.B, wb.n)) {
+        gemm_launch_roles<true, true>(FC1, wb.B, P2_SIZE, P2_SIZE, P2_SIZE, wb.n, epi, s);
     } else if (few) {
         gemm_launch<GemmCfg<true, true, 1, 1, 2, 2, 4, 32>, 0, 2>(FC1, wb.B, P2_SIZE, P2_SIZE, P2_SIZE, wb.n, epi, s);
     } else {
@@ -95,6 +98,8 @@ void launch_fc1_dx(const WorkerBuffers& wb, hipStream_t s)
         else
             gemm_launch_edge<GemmCfg<false, true, 2, 1, 2, 2, 2>, GemmCfg<false, true, 1, 1, 1, 4, 2>, false, DX_CHUNK, 2>(P2_SIZE, wb.B, FC1, P2_SIZE, FC1, wb.n,
                                                                                                           FEAT_WIDE, wb.B, epi, s);
+    } else if (gemm_roles_fit(P2_SIZE, wb.B, wb.n)) {
+        gemm_launch_roles<false, true>(P2_SIZE, wb.B, FC1, P2_SIZE, FC1, wb.n, epi, s);
     } else if (few) {
         gemm_launch<GemmCfg<false, true, 1, 1, 2, 2, 4, 32>, 0, 2>(P2_SIZE, wb.B, FC1, P2_SIZE, FC1, wb.n, epi, s);
     } else {

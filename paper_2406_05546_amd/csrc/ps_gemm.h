@@ -77,6 +77,14 @@ struct GemmOperand {
         }
     }
 
+    // Global -> registers for a stage that begins at k, anywhere.
+    __device__ __forceinline__ void load_at(int k, floatx4 (&r)[NV]) const
+    {
+        static_assert(!RAGGED, "whole stages");
+#pragma unroll
+        for (int i = 0; i < NV; ++i) r[i] = *reinterpret_cast<const floatx4*>(base + (off[i] + (uint32_t)k * (KC ? 1 : ld)));
+    }
+
     // Global -> registers for stage kt.
     __device__ __forceinline__ void load(int kt, floatx4 (&r)[NV]) const
     {
@@ -391,6 +399,118 @@ __global__ __launch_bounds__(64 * CHUNKS) void gemm_split_chunks(GemmShape sh, E
     }
 }
 
+// The sums of gemm_block<..., 0> for a launch with so few tiles that its time is that of one block's serial loop over K:
+// of five wavefronts one does nothing but multiply, a tile of 32 x 32, and four bring its operands in and split them,
+// 64 contraction indices at a time.  (A last stage of fewer begins earlier instead, and what comes twice is passed
+// over.)  Bound by the chain of the five small terms of a step, each of which waits for the one before: 190 ns for 16
+// contraction indices.  Forward of one worker of 256 images or four of 128 against 64 x 64 tiles, whose wavefronts do
+// everything: 38 -> 22 us, but eight of 128, two 32 x 32 tiles for a compute unit, 39 -> 44; input gradient of one of
+// 100 15.4 -> 9.4 us, of two 15.4 -> 16.3.
+template <bool A_KC, bool B_KC, class Epi>
+__global__ __launch_bounds__(320) void gemm_split_roles(GemmShape sh, Epi epi)
+{
+    constexpr int KS = 4 * GEMM_K, SUBS = KS / GEMM_K, AHEAD = 2;  // stages on their way in registers
+    using OpA = GemmOperand<32, A_KC, false, 128, KS>;
+    using OpB = GemmOperand<32, B_KC, false, 128, KS>;
+    constexpr int STAGE = OpA::BYTES + OpB::BYTES;
+    static_assert(OpA::NV == OpB::NV, "one register set for either operand");
+    static_assert(AHEAD == 2, "stage kt + 2 comes out of the registers of stage kt");
+    __shared__ __attribute__((aligned(16))) char lds[3 * STAGE];
+    const int lane = threadIdx.x & 63, wave = uniform(threadIdx.x >> 6), t = (threadIdx.x - 64) & 127;
+    const int v = gemm_tile(blockIdx.x, sh.gx * sh.gy * sh.gz);
+    if (v >= sh.gx * sh.gy * sh.gz) return;
+    const int m0 = v % sh.gx * 32, n0 = v / sh.gx % sh.gy * 32, z = v / (sh.gx * sh.gy);
+    const bool multiplies = wave == 0, brings_b = wave >= 3;
+
+    const int nk = (sh.K + KS - 1) / KS, tail = (nk * KS - sh.K) / GEMM_K;  // MFMA steps that the last stage repeats
+    OpA opa;
+    OpB opb;
+    if (brings_b)
+        opb.init(epi.b_ptr(z), sh.ldb, n0, sh.N, sh.K, t);
+    else
+        opa.init(epi.a_ptr(z), sh.lda, m0, sh.M, sh.K, t);
+    auto load = [&](int kt, floatx4 (&x)[OpA::NV]) {  // past the end the last stage again, which nobody reads
+        const int k = min(kt * KS, sh.K - KS);
+        if (brings_b)
+            opb.load_at(k, x);
+        else
+            opa.load_at(k, x);
+    };
+    auto store = [&](char* stage, const floatx4 (&x)[OpA::NV]) {
+        if (brings_b)
+            OpB::store(stage + OpA::BYTES, t, x);
+        else
+            OpA::store(stage, t, x);
+    };
+    // While stage kt is multiplied, out of one buffer, stage kt + 1 lies in the second and stage kt + 2 comes into the
+    // third: the multiplying wavefront reads one MFMA step ahead, also from one stage into the next.
+    // The two kinds of wavefronts run loops of their own: the same barriers (nk + 1), but in a common loop the compiler
+    // would wait for every load in flight where their ways meet.
+    char *now = lds, *next = lds + STAGE, *later = lds + 2 * STAGE;
+    if (!multiplies) {
+        floatx4 r[AHEAD][OpA::NV];
+#pragma unroll
+        for (int i = 0; i < AHEAD; ++i) {
+            load(i, r[i]);
+            __builtin_amdgcn_sched_barrier(0);  // in this order
+        }
+        store(now, r[0]);
+        load(AHEAD, r[0]);
+        store(next, r[1]);
+        load(AHEAD + 1, r[1]);
+        __syncthreads();
+        auto stage = [&](int u, int kt) __attribute__((always_inline)) {
+            store(later, r[u]);
+            load(kt + 2 + AHEAD, r[u]);
+            __syncthreads();
+            __builtin_amdgcn_sched_barrier(0);  // or the next stages are split, and so waited for, up here
+            char* const read = now;
+            now = next;
+            next = later;
+            later = read;
+        };
+        int kt0 = 0;
+        for (; kt0 + AHEAD <= nk; kt0 += AHEAD) {
+#pragma unroll
+            for (int u = 0; u < AHEAD; ++u) stage(u, kt0 + u);
+        }
+#pragma unroll
+        for (int u = 0; u < AHEAD - 1; ++u) {
+            if (kt0 + u >= nk) break;
+            stage(u, kt0 + u);
+        }
+        return;
+    }
+    __syncthreads();
+
+    SplitSum<floatx16> acc;
+    acc.clear();
+    Split8 fa, fb;
+    auto fetch = [&](const char* stage, int sub) {
+        fa = OpA::fetch(stage, 0, sub, lane);
+        fb = OpB::fetch(stage + OpA::BYTES, 0, sub, lane);
+    };
+    fetch(now, nk == 1 ? tail : 0);
+    for (int kt = 0; kt < nk; ++kt) {
+#pragma unroll
+        for (int sub = 0; sub < SUBS; ++sub) {
+            if (kt == nk - 1 && sub < tail) continue;
+            const Split8 a = fa, b = fb;
+            if (sub + 1 < SUBS)
+                fetch(now, sub + 1);
+            else
+                fetch(next, kt + 2 == nk ? tail : 0);
+            acc.add(a, b);
+        }
+        __syncthreads();
+        char* const read = now;
+        now = next;
+        next = later;
+        later = read;
+    }
+    gemm_finish<A_KC, B_KC>(sh, epi, z, m0, n0, lane, acc.value());
+}
+
 // Whether a launch over this many 128 x 128 tiles leaves compute units idle.
 inline bool gemm_few_tiles(int wide_tiles) { return wide_tiles < compute_units(); }
 
@@ -446,6 +566,18 @@ void gemm_launch(int M, int N, int K, int lda, int ldb, int batch, const Epi& ep
     if (M <= 0 || N <= 0 || batch <= 0) return;
     const GemmShape sh = gemm_shape<Cfg>(M, N, K, lda, ldb, batch, 0, M, 0, N);
     hipLaunchKernelGGL((gemm_split<Cfg, CHUNK, MINW, Epi>), dim3(gemm_grid(sh)), dim3(256), 0, s, sh, epi);
+}
+
+// Whether every tile of 32 x 32 finds a compute unit of its own (both sides measured: gemm_split_roles).
+inline bool gemm_roles_fit(int M, int N, int batch) { return (M + 31) / 32 * ((N + 31) / 32) * batch <= compute_units(); }
+
+// K: at least 64, a multiple of 16.
+template <bool A_KC, bool B_KC, class Epi>
+void gemm_launch_roles(int M, int N, int K, int lda, int ldb, int batch, const Epi& epi, hipStream_t s)
+{
+    if (M <= 0 || N <= 0 || batch <= 0) return;
+    const GemmShape sh{M, N, K, lda, ldb, (M + 31) / 32, (N + 31) / 32, batch, 0, 0};
+    hipLaunchKernelGGL((gemm_split_roles<A_KC, B_KC, Epi>), dim3(gemm_grid(sh)), dim3(320), 0, s, sh, epi);
 }
 
 // One problem per batch index in tiles of 32 x 32, or 32 x 64 if those alone give every compute unit a block; K =
