@@ -21,7 +21,7 @@ constexpr int OFF_W1 = 0, OFF_B1 = 144, OFF_W2 = 160, OFF_B2 = 4768, OFF_W3 = 48
               OFF_W4 = 808128, OFF_B4 = 813248, P = 813258;
 // Row pitch of every P-vector in HBM (weights, ring slots, queue entries): P rounded up to 256 B.
 constexpr int PSTRIDE = 813312;
-// Partial slots of the conv2 weight gradient: d W2 as conv2_dw_kernel's registers hold it, then d b2.
+// Partial slots of the conv2 weight gradient: d W2 as that kernel's registers hold it, then d b2.
 constexpr int CONV2_PART_B2 = C2 * C1 * 9, CONV2_PART = CONV2_PART_B2 + C2;
 
 constexpr int PER_WORKER = -2;  // WorkerBuffers::all_slot: every worker has a slot of its own
@@ -128,13 +128,12 @@ hipError_t launch_eval_collect(int n_images, const float* loss_i, const int32_t*
 
 void launch_conv2_fwd(const WorkerBuffers& wb, hipStream_t s);
 void launch_fc1_dw(const WorkerBuffers& wb, hipStream_t s);
-bool fc1_dw_is_few(int n);  // whether fc1's weight gradient runs in launch_backward's launch, next to conv2's gradients
-enum { BWD_CONV2_DX = 1, BWD_CONV2_DW = 2, BWD_FC1_DW = 4 };
-void launch_backward(const WorkerBuffers& wb, hipStream_t s, int which);
+bool fc1_dw_is_few(int n);  // whether fc1's weight gradient runs in launch_backward's launch instead of one of its own
+void launch_backward(const WorkerBuffers& wb, hipStream_t s);  // conv2's gradients (and conv1's)
 
 // Kernels of the path, in launch order; ids index the per-kernel timing table.
 enum KernelId {
-    K_CONV1_FWD, K_CONV2_FWD, K_FC1_FWD, K_FC2, K_FC1_DW, K_FC1_DX, K_CONV2_DW, K_CONV2_DX,
+    K_CONV1_FWD, K_CONV2_FWD, K_FC1_FWD, K_FC2, K_FC1_DW, K_FC1_DX, K_BACKWARD, K_BACKWARD_FC1,
     K_GRAD_REDUCE, K_APPLY_SUM, K_APPLY_SEQ, K_GRAD_SQNORM, K_APPLY_SUM_CLIP, K_APPLY_SEQ_CLIP, K_APPLY_ADADELTA, K_LOCAL_STEP,
     K_ELASTIC, K_COUNT
 };

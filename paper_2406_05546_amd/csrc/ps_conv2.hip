@@ -700,20 +700,20 @@ int conv2_part_slots(int batch)
     return (batch + per_slot - 1) / per_slot;
 }
 
-void launch_backward(const WorkerBuffers& wb, hipStream_t s, int which)
+void launch_backward(const WorkerBuffers& wb, hipStream_t s)
 {
     BwdShape sh;
     sh.dx_ipw = images_per_wavefront(wb.n, wb.B, DX_IPW);
     sh.dx_parts = wavefronts_per_image(wb.n, wb.B, 2);
     sh.dx_blocks_per_worker = blocks_per_worker(wb.B, sh.dx_ipw, sh.dx_parts, DX_NW);
-    sh.dx_blocks = which & BWD_CONV2_DX ? wb.n * sh.dx_blocks_per_worker : 0;
+    sh.dx_blocks = wb.n * sh.dx_blocks_per_worker;
     sh.dw_slots = conv2_part_slots(wb.B);
     sh.dw_ipw = conv2_dw_ipw(wb.B);
     sh.dw_shared = DW_SHARES * DW_NW * wb.n * sh.dw_slots <= 2 * 4 * compute_units();
-    sh.dw_blocks = which & BWD_CONV2_DW ? wb.n * sh.dw_slots * (sh.dw_shared ? DW_SHARES : 1) : 0;
+    sh.dw_blocks = wb.n * sh.dw_slots * (sh.dw_shared ? DW_SHARES : 1);
     const GemmShape fc1 = fc1_dw_few_shape(wb.n, wb.B);
     const int conv_blocks = (sh.dx_blocks + sh.dw_blocks + 7) / 8 * 8;
-    if (!(which & BWD_FC1_DW))
+    if (!fc1_dw_few(wb.n))
         hipLaunchKernelGGL(backward_kernel<0>, dim3(conv_blocks), dim3(256), 0, s, wb, sh, fc1);
     else
         hipLaunchKernelGGL((wb.B % Fc1DwFew::KS == 0 ? backward_kernel<1> : backward_kernel<2>), dim3(conv_blocks + gemm_grid(fc1)), dim3(256), 0, s, wb, sh, fc1);

@@ -147,17 +147,9 @@ hipError_t launch_worker_backward(const WorkerBuffers& wb, hipStream_t s, Profil
 {
     if (wb.n * wb.B <= 0) return hipSuccess;
     PS_TIMED(K_FC2, launch_fc2(wb, s));
-    const bool few = fc1_dw_is_few(wb.n);
-    if (prof.enabled) {  // timed one by one
-        PS_TIMED(K_FC1_DW, few ? launch_backward(wb, s, BWD_FC1_DW) : launch_fc1_dw(wb, s));
-        PS_TIMED(K_FC1_DX, launch_fc1_dx(wb, s));
-        PS_TIMED(K_CONV2_DW, launch_backward(wb, s, BWD_CONV2_DW));
-        PS_TIMED(K_CONV2_DX, launch_backward(wb, s, BWD_CONV2_DX));
-    } else {
-        if (!few) launch_fc1_dw(wb, s);
-        launch_fc1_dx(wb, s);
-        launch_backward(wb, s, BWD_CONV2_DX | BWD_CONV2_DW | (few ? BWD_FC1_DW : 0));
-    }
+    if (!fc1_dw_is_few(wb.n)) PS_TIMED(K_FC1_DW, launch_fc1_dw(wb, s));
+    PS_TIMED(K_FC1_DX, launch_fc1_dx(wb, s));
+    PS_TIMED(fc1_dw_is_few(wb.n) ? K_BACKWARD_FC1 : K_BACKWARD, launch_backward(wb, s));
     // one value per thread while the chip has room, at least the blocks that the conv1 values take
     const int reduce_y = wb.n * (REDUCE_ITEMS / 256 + 1) <= 8 * compute_units() ? REDUCE_ITEMS / 256 + 1 : 8;
     PS_TIMED(K_GRAD_REDUCE, hipLaunchKernelGGL(grad_reduce_kernel, dim3(wb.n, reduce_y), dim3(256), 0, s, wb, fc2_split(wb.n),
@@ -168,9 +160,8 @@ hipError_t launch_worker_backward(const WorkerBuffers& wb, hipStream_t s, Profil
 const char* kernel_name(int id)
 {
     static const char* const names[K_COUNT] = {
-        "conv1_fwd_kernel", "conv2_fwd_kernel", "gemm_f32_mfma<Fc1FwdEpi>", "fc2_kernel",
-        "gemm_f32_mfma<Fc1DwEpi>", "gemm_f32_mfma<Fc1DxEpi>", "conv2_dw_kernel",
-        "conv2_dx_kernel", "grad_reduce_kernel", "apply_kernel<0>", "apply_kernel<1>", "grad_sqnorm_kernel",
+        "conv1_fwd_kernel", "conv2_fwd_kernel", "gemm_split<Fc1FwdEpi>", "fc2_kernel", "gemm_split<Fc1DwEpi>", "gemm_split<Fc1DxEpi>",
+        "backward_kernel", "backward_kernel<fc1>", "grad_reduce_kernel", "apply_kernel<0>", "apply_kernel<1>", "grad_sqnorm_kernel",
         "apply_kernel<0, clip>", "apply_kernel<1, clip>", "apply_adadelta_kernel", "local_step_kernel",
         "elastic_average_kernel"};
     return id >= 0 && id < K_COUNT ? names[id] : "";

@@ -852,6 +852,30 @@ def test_gradient_bits_do_not_depend_on_the_launch(ps, n, B):
         ps.ps_destroy(ctx)
 
 
+@pytest.mark.parametrize("extra", [1, 3])
+def test_evaluations_too_large_to_be_collected_on_the_gpu(ps, extra):
+    """The results of up to 65,536 images are collected by a kernel, those of more are copied out: the same classes and
+    hits, and the same losses, added up in another order of 64-bit sums."""
+    import torch
+    B, n = 512, 128
+    ctx = ps.ps_init(ps.make_config(n + extra, B, 1, 1, DROP_SEED, P_DROP))
+    try:
+        ps.ps_set_weights(ctx, synth.he_uniform_theta(23))
+        g = torch.Generator(device="cuda")
+        g.manual_seed(5)
+        x = torch.rand((n + extra) * B, ps.IMAGE_PIXELS, device="cuda", generator=g)
+        y = torch.randint(0, 10, ((n + extra) * B,), device="cuda", generator=g, dtype=torch.int32)
+        loss, acc, pred = ps.ps_evaluate(ctx, -1, x, y)
+        parts = [ps.ps_evaluate(ctx, -1, x[:n * B], y[:n * B]), ps.ps_evaluate(ctx, -1, x[n * B:], y[n * B:])]
+        sizes = np.array([n * B, extra * B])
+        assert np.array_equal(pred, np.concatenate([p[2] for p in parts]))
+        assert round(acc * sizes.sum()) == sum(round(p[1] * k) for p, k in zip(parts, sizes))
+        want = sum(p[0] * k for p, k in zip(parts, sizes)) / sizes.sum()
+        assert abs(loss - want) <= sizes.sum() * 2.0 ** -53 * want  # one rounding for every image
+    finally:
+        ps.ps_destroy(ctx)
+
+
 @pytest.mark.parametrize("n,B", [(2, 16), (80, 40), (2, 130), (70, 130)])
 @pytest.mark.parametrize("bad", [np.inf, 3.3999e38])
 def test_operands_that_cannot_be_split(ps, n, B, bad):
