@@ -1,3 +1,4 @@
+import gc
 import os
 import sys
 
@@ -17,3 +18,10 @@ def pytest_configure(config):
 @pytest.fixture(scope="session")
 def golden_dir():
     return GOLDEN
+
+
+@pytest.fixture(autouse=True)
+def _garbage_of_earlier_tests():
+    """Tensors that an earlier test left in a reference cycle go before a test begins, not in the middle of one that
+    compares how much device memory is allocated."""
+    gc.collect()
