@@ -450,11 +450,13 @@ __device__ __forceinline__ void conv2_dx_block(const WorkerBuffers& wb, const Bw
 // pairs, those from 0 on the pairs shifted by one value.  d b2 is the product with a column of ones.
 // A block's four wavefronts take DW_IPW images each at most, meet in LDS once, and write one partial slot;
 // the slots depend on the batch alone, so that the order of a worker's sums does not depend on the launch.
-// All six terms share one accumulator here: the 72 more of a second one do not fit next to the operands.  The
-// sums are final results, so the cut-off bits of ps_split.h are not added up any further: d W2 is off by 1.2e-7
-// to 3.6e-7, as it was with fp32 MFMAs.
-// 65,536 images: 0.93 -> 0.63 ms against the fp32 MFMA kernel; one worker of 256 images 162 -> 45 us, two of 32
-// 24 -> 14 us (more, smaller shares).
+// The 72 registers of a second accumulator (ps_split.h) do not fit next to the operands: the five small terms of
+// a k-step are summed from zero and added on the vector ALU.  What is then cut off towards minus infinity is
+// -3.5e-9 to -7.5e-9 of the mean result, and the odd wavefronts take d2 negated and are subtracted, so that it
+// cancels in a slot.  Against 64 bits d W2 is off by 0.63-0.80e-7 (1.09-1.51e-7 with fp32 MFMAs; 0.91-1.74e-7, with a
+// mean error of -2.9e-8 to -1.2e-7, with all six terms in one accumulator), 4 % of the launch's time.
+// 65,536 images, this and the input gradient: 2.09 -> 1.31 ms against the fp32 MFMA kernels; one worker of 256
+// images 162 -> 45 us, two of 32 24 -> 14 us (more, smaller shares).
 constexpr int DW_NW = 4, DW_NT = 64 * DW_NW, DW_MAX_SLOTS = 16;
 constexpr int DW_REGS = 2 * 9 * 4;  // sums per lane without the bias
 
@@ -512,7 +514,7 @@ typedef float DwSums[DW_NW][DW_REGS + 2][64];  // 75,776 B
 constexpr int DW_SHARES = 6;
 
 // Four pooled gradients and their window bytes -> the d2 operand of lane (q = 2e + xh, l16).
-__device__ __forceinline__ Split8 d2_operand(const floatx4& pooled, uint32_t bytes, int e)
+__device__ __forceinline__ Split8 d2_operand(const floatx4& pooled, uint32_t bytes, int e, float sign)
 {
     Split8 d2;
     const uint32_t bits = bytes >> (2 * e);  // bits 0, 1 of every byte: winner in this row, left or right
@@ -521,7 +523,7 @@ __device__ __forceinline__ Split8 d2_operand(const floatx4& pooled, uint32_t byt
         const uint32_t left = (uint32_t)__builtin_amdgcn_sbfe((int)bits, 8 * m, 1), right = (uint32_t)__builtin_amdgcn_sbfe((int)bits, 8 * m + 1, 1);
         const uint32_t mask = (left & 0xffffu) | (right & 0xffff0000u);
         uint32_t p0, p1, p2;
-        split2(pooled[m], pooled[m], p0, p1, p2);
+        split2(sign * pooled[m], sign * pooled[m], p0, p1, p2);
         d2.p[0][m] = p0 & mask;
         d2.p[1][m] = p1 & mask;
         d2.p[2][m] = p2 & mask;
@@ -540,6 +542,7 @@ __device__ __forceinline__ void conv2_dw_block(const WorkerBuffers& wb, const Bw
     const int w = block / slots, slot = block % slots;
     const int B = wb.B, s_begin = min(B, (slot * DW_NW + wave) * ipw), s_end = min(B, s_begin + ipw);
 
+    const float sign = wave & 1 ? -1.f : 1.f;
     floatx4 acc[MTS][3 * DYS], acc_b[MTS];
 #pragma unroll
     for (int mt = 0; mt < MTS; ++mt) {
@@ -585,7 +588,7 @@ __device__ __forceinline__ void conv2_dw_block(const WorkerBuffers& wb, const Bw
         for (int py = 0; py < P2_W; ++py) {
             Split8 d2[MTS];
 #pragma unroll
-            for (int mt = 0; mt < MTS; ++mt) d2[mt] = d2_operand(pooled[mt], bytes[mt], e);
+            for (int mt = 0; mt < MTS; ++mt) d2[mt] = d2_operand(pooled[mt], bytes[mt], e, sign);
             const ShiftedRow mid = shifted_row(raw[0]);
             if (!SHARED && py == 0) {  // rows -1 (zero) and 0: lanes 32..63 take what lanes 0..31 of `mid` hold
 #pragma unroll
@@ -597,27 +600,41 @@ __device__ __forceinline__ void conv2_dw_block(const WorkerBuffers& wb, const Bw
                 }
             }
             const ShiftedRow low = shifted_row(raw[SHARED ? 0 : 1]);
-            if (py + 1 < P2_W)
-                prefetch(g, py + 1);
-            else if (s + 1 < s_end)
-                prefetch(g + 1, 0);
             const ShiftedRow* const rows[3] = {SHARED ? &mid : &up, &mid, &low};
+            const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int dy = 0; dy < DYS; ++dy)
+            for (int dy = 0; dy < DYS; ++dy) {
+                // the next pooled row's loads once the first tap row's operand is dead: in front of it they spill
+                if (!SHARED) __builtin_amdgcn_sched_barrier(0);
+                if (dy == 1 || SHARED) {
+                    if (py + 1 < P2_W)
+                        prefetch(g, py + 1);
+                    else if (s + 1 < s_end)
+                        prefetch(g + 1, 0);
+                }
 #pragma unroll
                 for (int dx = 0; dx < 3; ++dx) {
                     const Split8 b = rows[dy]->columns(dx);
+                    floatx4 small[MTS];
 #pragma unroll
-                    for (int t = 0; t <= SPLIT_SMALL; ++t)
+                    for (int t = 0; t < SPLIT_SMALL; ++t)
 #pragma unroll
                         for (int mt = 0; mt < MTS; ++mt)
-                            acc[mt][3 * dy + dx] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(d2[mt].part(TERM_A[t]), b.part(TERM_B[t]), acc[mt][3 * dy + dx], 0, 0, 0);
+                            small[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(d2[mt].part(TERM_A[t]), b.part(TERM_B[t]), t == 0 ? zero : small[mt], 0, 0, 0);
+#pragma unroll
+                    for (int mt = 0; mt < MTS; ++mt) {
+                        floatx4& sum = acc[mt][3 * dy + dx];
+                        sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(d2[mt].part(0), b.part(0), sum, 0, 0, 0) + small[mt];
+                    }
                 }
+            }
             const bf16x8 ones = __builtin_bit_cast(bf16x8, uintx4{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u});
 #pragma unroll
-            for (int i = 2; i >= 0; --i)
-#pragma unroll
-                for (int mt = 0; mt < MTS; ++mt) acc_b[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(d2[mt].part(i), ones, acc_b[mt], 0, 0, 0);
+            for (int mt = 0; mt < MTS; ++mt) {
+                floatx4 small = __builtin_amdgcn_mfma_f32_16x16x32_bf16(d2[mt].part(2), ones, zero, 0, 0, 0);
+                small = __builtin_amdgcn_mfma_f32_16x16x32_bf16(d2[mt].part(1), ones, small, 0, 0, 0);
+                acc_b[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(d2[mt].part(0), ones, acc_b[mt], 0, 0, 0) + small;
+            }
             if (!SHARED) up = low;
         }
     }
@@ -640,20 +657,20 @@ __device__ __forceinline__ void conv2_dw_block(const WorkerBuffers& wb, const Bw
 #pragma unroll 1
         for (int r = r_begin; r < r_begin + 12 * DYS * MTS; ++r)
             if (red[wave][r][lane] != red[wave][r][lane])
-                red[wave][r][lane] = conv2_dw_plain(wb, w, s_begin, s_end, 16 * (r / 36) + 4 * q + r % 4, l16, r % 36 / 4);
+                red[wave][r][lane] = sign * conv2_dw_plain(wb, w, s_begin, s_end, 16 * (r / 36) + 4 * q + r % 4, l16, r % 36 / 4);
         if (lane < 16 * MTS && red[wave][DW_REGS + mt0 + lane / 16][lane % 16] != red[wave][DW_REGS + mt0 + lane / 16][lane % 16])
-            red[wave][DW_REGS + mt0 + lane / 16][lane % 16] = conv2_dw_plain(wb, w, s_begin, s_end, 16 * mt0 + lane, 0, 9);
+            red[wave][DW_REGS + mt0 + lane / 16][lane % 16] = sign * conv2_dw_plain(wb, w, s_begin, s_end, 16 * mt0 + lane, 0, 9);
     }
     __syncthreads();
     float* part = wb.part + ((size_t)w * slots + slot) * CONV2_PART;
 #pragma unroll
     for (int i = 0; i < 12 * DYS * MTS / DW_NW; ++i) {
         const int r = r_begin + (threadIdx.x >> 6) + DW_NW * i;
-        part[r * 64 + lane] = (red[0][r][lane] + red[1][r][lane]) + (red[2][r][lane] + red[3][r][lane]);
+        part[r * 64 + lane] = (red[0][r][lane] - red[1][r][lane]) + (red[2][r][lane] - red[3][r][lane]);
     }
     if (dy0 == 0 && threadIdx.x < 16 * MTS) {
         const int r = DW_REGS + mt0 + threadIdx.x / 16, j = threadIdx.x % 16;
-        part[CONV2_PART_B2 + 16 * mt0 + threadIdx.x] = (red[0][r][j] + red[1][r][j]) + (red[2][r][j] + red[3][r][j]);
+        part[CONV2_PART_B2 + 16 * mt0 + threadIdx.x] = (red[0][r][j] - red[1][r][j]) + (red[2][r][j] - red[3][r][j]);
     }
 }
 
