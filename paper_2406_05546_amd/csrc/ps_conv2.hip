@@ -15,8 +15,6 @@ namespace {
 // Bits 0-3: bit (2 dy + dx) of the winner, set only where the winner's activation is > 0; bits 4-5: the winner.
 // The input gradient reads bits 0-3 from a second copy, [window][channel].
 
-__device__ __forceinline__ bool any_nan(const floatx4& a) { return __builtin_isunordered(a[0], a[1]) || __builtin_isunordered(a[2], a[3]); }
-
 // ---------------------------------------------------------------------------------------------
 // Forward (32x32x16).  GEMM rows are two rows of the map, 16 padded columns each; columns the 32 output
 // channels; one k-step the 16 input channels of one tap.  Lane (h, e, column) of the A operand holds eight
@@ -38,19 +36,31 @@ struct FwdImage {  // one wavefront's pooled image
     uint8_t am2t[P2_SIZE];
 };
 
-// Pre-activation (without bias) of output channel o at (y, x) with fp32 FMAs (see ps_split.h).
-__device__ __forceinline__ float conv2_fwd_plain(const float* __restrict__ p1, const float* __restrict__ W2, int o, int y, int x)
+// The sums of rows 2t, 2t + 1 for which the split does not hold (ps_split.h), formed again with fp32 matrix
+// instructions, operands straight from memory.
+__device__ __forceinline__ void conv2_fwd_again(const float* __restrict__ p1, const float* __restrict__ W2, int t, int lane, floatx16& sums)
 {
-    float sum = 0.f;
+    lane = rarely(lane);
+    const int h = lane >> 5, l32 = lane & 31, e = l32 >> 4, column = lane & 15;
+    floatx16 again;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) again[i] = 0.f;
 #pragma unroll 1
-    for (int t = 0; t < 9; ++t) {
-        const int yy = y + t / 3 - 1, xx = x + t % 3 - 1;
-        const bool inside = yy >= 0 && yy < P1_W && xx >= 0 && xx < P1_W;
-        const float* p = p1 + (inside ? yy * P1_W + xx : 0) * C1;
-#pragma unroll 1
-        for (int c = 0; c < C1; ++c) sum = fmaf(inside ? p[c] : 0.f, W2[(o * C1 + c) * 9 + t], sum);
+    for (int tap = 0; tap < 9; ++tap) {
+        const int y = 2 * t + e + tap / 3 - 1, x = column + tap % 3 - 1;
+        const bool inside = y >= 0 && y < P1_W && x >= 0 && x < P1_W;
+        const float* p = p1 + (inside ? y * P1_W + x : 0) * C1 + 8 * h;
+        const float* w = W2 + (l32 * C1 + 8 * h) * 9 + tap;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const float v = p[j];
+            again = __builtin_amdgcn_mfma_f32_32x32x2f32(inside ? v : 0.f, w[9 * j], again, 0, 0, 0);
+        }
+        if (!worth_going_on<16>(sums, again)) break;
     }
-    return sum;
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+        if (split_lost(sums[i])) sums[i] = again[i];
 }
 
 __global__ __launch_bounds__(FWD_NT, 2) void conv2_fwd_kernel(WorkerBuffers wb, int blocks_per_worker, int ipw, int parts)
@@ -126,14 +136,7 @@ __global__ __launch_bounds__(FWD_NT, 2) void conv2_fwd_kernel(WorkerBuffers wb, 
             up = low;
             floatx16 acc = sum.value();
             // register i of lane (h, l32): channel l32 at row 2t + i / 8, column 8 (i / 4 % 2) + 4h + i % 4
-            bool nan = false;
-#pragma unroll
-            for (int i = 0; i < 16; i += 2) nan |= __builtin_isunordered(acc[i], acc[i + 1]);
-            if (__any(nan)) {
-#pragma unroll
-                for (int i = 0; i < 16; ++i)
-                    if (acc[i] != acc[i]) acc[i] = conv2_fwd_plain(wb.p1 + g * P1_SIZE, W2, l32, 2 * t + i / 8, 8 * (i / 4 % 2) + 4 * h + i % 4);
-            }
+            if (any_lost<16>(acc)) conv2_fwd_again(wb.p1 + g * P1_SIZE, W2, t, lane, acc);
 #pragma unroll
             for (int half = 0; half < 2; ++half) {
                 uint32_t bytes = 0;
@@ -215,23 +218,31 @@ struct DxImage {  // one wavefront's image
     float xs[DX_XS];
 };
 
-// d pool1 of channel c at (Y, X) of image g with fp32 FMAs: for sums the split cannot hold (see ps_split.h).
-__device__ __forceinline__ float conv2_dx_plain(const WorkerBuffers& wb, size_t g, const float* __restrict__ W2, int c, int Y, int X)
+// The same as conv2_fwd_again for d pool1 row Y of image g: lane (q, l16) holds channel l16 at X = 4q .. 4q + 3.
+__device__ __forceinline__ void conv2_dx_again(const WorkerBuffers& wb, size_t g, const float* __restrict__ W2, int Y, int lane, floatx4& sums)
 {
-    float sum = 0.f;
+    lane = rarely(lane);
+    const int q = lane >> 4, l16 = lane & 15;
+    const uint8_t* codes = wb.am2t + g * P2_SIZE;
+    const float* dp = wb.dp2g + g * P2_SIZE;
+    floatx4 again = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll 1
-    for (int o = 0; o < C2; ++o)
-#pragma unroll 1
-        for (int t = 0; t < 9; ++t) {
-            const int y = Y + 1 - t / 3, x = X + 1 - t % 3;
-            float v = 0.f;
-            if (y >= 0 && y < P1_W && x >= 0 && x < P1_W) {
-                const int p = (y >> 1) * P2_W + (x >> 1);
-                v = wb.am2t[g * P2_SIZE + p * C2 + o] >> (2 * (y & 1) + (x & 1)) & 1 ? wb.dp2g[g * P2_SIZE + o * P2_POS + p] : 0.f;
-            }
-            sum = fmaf(v, W2[(o * C1 + c) * 9 + t], sum);
+    for (int tap = 0; tap < 9; ++tap) {
+        const int y = Y + 1 - tap / 3, x = l16 + 1 - tap % 3;  // of d2, for the result at X = l16
+        const bool inside = y >= 0 && y < P1_W && x >= 0 && x < P1_W;
+        const int p = inside ? (y >> 1) * P2_W + (x >> 1) : 0, bit = 2 * (y & 1) + (x & 1);
+#pragma unroll 2
+        for (int k = 0; k < C2 / 4; ++k) {
+            const int o = 4 * k + q;
+            const float d = dp[o * P2_POS + p];
+            const bool winner = inside & (codes[p * C2 + o] >> bit & 1);
+            again = __builtin_amdgcn_mfma_f32_16x16x4f32(winner ? d : 0.f, W2[(o * C1 + l16) * 9 + tap], again, 0, 0, 0);
         }
-    return sum;
+        if (!worth_going_on<4>(sums, again)) break;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        if (split_lost(sums[i])) sums[i] = again[i];
 }
 
 struct Conv1Sums {
@@ -337,11 +348,7 @@ __device__ __forceinline__ void conv2_dx_block(const WorkerBuffers& wb, const Bw
 
         // conv1's gradient from d pool1 row Y: lane (q, l16) holds channel l16 at X = 4q .. 4q + 3
         auto finish_row = [&](int Y, floatx4 acc) {
-            if (__any(any_nan(acc))) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    if (acc[i] != acc[i]) acc[i] = conv2_dx_plain(wb, g, W2, l16, Y, 4 * q + i);
-            }
+            if (any_lost<4>(acc)) conv2_dx_again(wb, g, W2, Y, lane, acc);
             const uint8_t* bytes = im.am1 + (P1_W * Y + 4 * q) * C1 + l16;
             const float* row = im.xs + 2 * Y * DX_XW + 8 * q;
 #pragma unroll
@@ -486,24 +493,31 @@ __device__ __forceinline__ ShiftedRow shifted_row(const float (&v)[10])
     return r;
 }
 
-// One sum over images [s_begin, s_end) of worker w with fp32 FMAs (see ps_split.h): tap 0..8, or 9 for the bias.
-__device__ __forceinline__ float conv2_dw_plain(const WorkerBuffers& wb, int w, int s_begin, int s_end, int o, int c, int tap)
+// The same as conv2_fwd_again for the sums over images [s_begin, s_end) of worker w: output channels 16 mt + 4q + i,
+// input channel l16, tap 0..8, or 9 for the bias.  The sums are times `sign`.
+__device__ __forceinline__ void conv2_dw_again(const WorkerBuffers& wb, int w, int s_begin, int s_end, int mt, int tap, float sign, int lane, floatx4& sums)
 {
-    float sum = 0.f;
+    lane = rarely(lane);
+    const int q = lane >> 4, l16 = lane & 15, o = 16 * mt + l16;
+    floatx4 again = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll 1
     for (int s = s_begin; s < s_end; ++s) {
         const size_t g = (size_t)w * wb.B + s;
-#pragma unroll 1
-        for (int p = 0; p < P1_POS; ++p) {
-            const int y = p / P1_W, x = p % P1_W, r = o * P2_W + (y >> 1);
-            const float d = wb.am2[g * AM2_SIZE + r * AM2_PITCH + (x >> 1)] >> (2 * (y & 1) + (x & 1)) & 1
-                                ? wb.dp2g[g * P2_SIZE + r * P2_W + (x >> 1)] : 0.f;
+#pragma unroll 7
+        for (int k = 0; k < P1_POS / 4; ++k) {
+            const int pos = 4 * k + q, y = pos / P1_W, x = pos % P1_W, r = o * P2_W + (y >> 1);
+            const bool winner = wb.am2[g * AM2_SIZE + r * AM2_PITCH + (x >> 1)] >> (2 * (y & 1) + (x & 1)) & 1;
+            const float d = sign * wb.dp2g[g * P2_SIZE + r * P2_W + (x >> 1)];
             const int yy = y + tap / 3 - 1, xx = x + tap % 3 - 1;
             const bool inside = yy >= 0 && yy < P1_W && xx >= 0 && xx < P1_W;
-            sum = tap == 9 ? sum + d : fmaf(d, inside ? wb.p1[g * P1_SIZE + (yy * P1_W + xx) * C1 + c] : 0.f, sum);
+            const float v = wb.p1[g * P1_SIZE + (inside ? yy * P1_W + xx : 0) * C1 + l16];
+            again = __builtin_amdgcn_mfma_f32_16x16x4f32(winner ? d : 0.f, tap == 9 ? 1.f : inside ? v : 0.f, again, 0, 0, 0);
         }
+        if (!worth_going_on<4>(sums, again)) break;
     }
-    return sum;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        if (split_lost(sums[i])) sums[i] = again[i];
 }
 
 typedef float DwSums[DW_NW][DW_REGS + 2][64];  // 75,776 B
@@ -640,26 +654,30 @@ __device__ __forceinline__ void conv2_dw_block(const WorkerBuffers& wb, const Bw
     }
 
     // register i of tile (mt, j): output channel 16 mt + 4q + i, input channel l16, tap j (every column of the bias tile alike)
-    bool nan = false;
+    bool lost = false;
 #pragma unroll
     for (int mt = 0; mt < MTS; ++mt) {
-        nan |= any_nan(acc_b[mt]);
+        if (any_lost<4>(acc_b[mt])) conv2_dw_again(wb, w, s_begin, s_end, mt0 + mt, 9, sign, lane, acc_b[mt]);
 #pragma unroll
         for (int j = 0; j < 3 * DYS; ++j) {
-            nan |= any_nan(acc[mt][j]);
+            lost |= !split_holds(largest<4>(acc[mt][j]));
 #pragma unroll
             for (int i = 0; i < 4; ++i) red[wave][((mt0 + mt) * 9 + 3 * dy0 + j) * 4 + i][lane] = acc[mt][j][i];
         }
         if (l16 == 0) *reinterpret_cast<floatx4*>(&red[wave][DW_REGS + mt0 + mt][4 * q]) = acc_b[mt];
     }
     const int r_begin = (mt0 * 9 + 3 * dy0) * 4;  // of this block's DYS * MTS * 12 registers
-    if (__any(nan)) {
+    if (__builtin_expect(__any(lost), 0)) {
 #pragma unroll 1
-        for (int r = r_begin; r < r_begin + 12 * DYS * MTS; ++r)
-            if (red[wave][r][lane] != red[wave][r][lane])
-                red[wave][r][lane] = sign * conv2_dw_plain(wb, w, s_begin, s_end, 16 * (r / 36) + 4 * q + r % 4, l16, r % 36 / 4);
-        if (lane < 16 * MTS && red[wave][DW_REGS + mt0 + lane / 16][lane % 16] != red[wave][DW_REGS + mt0 + lane / 16][lane % 16])
-            red[wave][DW_REGS + mt0 + lane / 16][lane % 16] = sign * conv2_dw_plain(wb, w, s_begin, s_end, 16 * mt0 + lane, 0, 9);
+        for (int r = r_begin; r < r_begin + 12 * DYS * MTS; r += 4) {
+            floatx4 sums;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) sums[i] = red[wave][r + i][lane];
+            if (!any_lost<4>(sums)) continue;
+            conv2_dw_again(wb, w, s_begin, s_end, r / 36, r % 36 / 4, sign, lane, sums);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) red[wave][r + i][lane] = sums[i];
+        }
     }
     __syncthreads();
     float* part = wb.part + ((size_t)w * slots + slot) * CONV2_PART;

@@ -152,41 +152,62 @@ struct GemmOperand {
     }
 };
 
-// One element of C with fp32 FMAs (see ps_split.h).
-template <bool A_KC, bool B_KC>
-__device__ __forceinline__ float gemm_plain(const GemmShape& sh, const float* __restrict__ A, const float* __restrict__ B, int m, int n)
+// Four consecutive k of one row of an operand, from memory; zero past K (RC).
+template <bool KC>
+__device__ __forceinline__ floatx4 gemm_operand4(const float* __restrict__ base, int ld, int row, int k, int K)
 {
-    float sum = 0.f;
-#pragma unroll 1
-    for (int k = 0; k < sh.K; ++k)
-        sum = fmaf(A[A_KC ? (size_t)m * sh.lda + k : (size_t)k * sh.lda + m], B[B_KC ? (size_t)n * sh.ldb + k : (size_t)k * sh.ldb + n], sum);
-    return sum;
+    if (KC) return *reinterpret_cast<const floatx4*>(base + (size_t)row * ld + k);
+    floatx4 v;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float x = base[(size_t)min(k + i, K - 1) * ld + row];
+        v[i] = k + i < K ? x : 0.f;
+    }
+    return v;
 }
 
-// Hands rows m .. m + 3 of column n to the epilogue.
+// The sums of a 32x32 tile at (m0, n0) for which the split does not hold (ps_split.h), formed again with fp32 matrix
+// instructions, whose registers lie as those of the bf16 ones do.  Operands come straight from memory, so it takes
+// about four times as long as the tile did, unless the sums turn out NaN anyway: a network of NaN weights is not
+// slowed down by more than that first look.
 template <bool A_KC, bool B_KC, class Epi>
-__device__ __forceinline__ void gemm_store(const GemmShape& sh, const Epi& epi, int z, int m, int n, float v0, float v1, float v2, float v3)
+__device__ __forceinline__ void gemm_again(const GemmShape& sh, const Epi& epi, int z, int m0, int n0, int lane, floatx16& sums)
 {
-    if (m >= sh.M || n >= sh.N) return;
-    float4 v = make_float4(v0, v1, v2, v3);
-    if (__builtin_isunordered(v0, v1) || __builtin_isunordered(v2, v3)) {
-        const float* A = epi.a_ptr(z);
-        const float* B = epi.b_ptr(z);
-        if (v0 != v0) v.x = gemm_plain<A_KC, B_KC>(sh, A, B, m, n);
-        if (v1 != v1) v.y = gemm_plain<A_KC, B_KC>(sh, A, B, m + 1, n);
-        if (v2 != v2) v.z = gemm_plain<A_KC, B_KC>(sh, A, B, m + 2, n);
-        if (v3 != v3) v.w = gemm_plain<A_KC, B_KC>(sh, A, B, m + 3, n);
+    lane = rarely(lane);
+    const float* __restrict__ A = epi.a_ptr(z);
+    const float* __restrict__ B = epi.b_ptr(z);
+    const int row = min(m0 + (lane & 31), sh.M - 1), col = min(n0 + (lane & 31), sh.N - 1), h = lane >> 5;
+    floatx16 again;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) again[i] = 0.f;
+#pragma unroll 1
+    for (int k0 = 0; k0 < sh.K; k0 += 32) {
+#pragma unroll
+        for (int k = 0; k < 32; k += 8) {
+            if (k0 + k >= sh.K) break;  // K is a multiple of 8, or the operands read as zero past it
+            const floatx4 a = gemm_operand4<A_KC>(A, sh.lda, row, k0 + k + 4 * h, sh.K);
+            const floatx4 b = gemm_operand4<B_KC>(B, sh.ldb, col, k0 + k + 4 * h, sh.K);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) again = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[i], again, 0, 0, 0);
+        }
+        if (!worth_going_on<16>(sums, again)) break;
     }
-    epi(z, m, n, v);
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+        if (split_lost(sums[i])) sums[i] = again[i];
 }
 
 // Stores one 32x32 tile of sums at (m0, n0): register i of lane (h, l32) is row 8*(i/4) + 4*h + i%4, column l32.
 template <bool A_KC, bool B_KC, class Epi>
-__device__ __forceinline__ void gemm_finish(const GemmShape& sh, const Epi& epi, int z, int m0, int n0, int lane, const floatx16& acc)
+__device__ __forceinline__ void gemm_finish(const GemmShape& sh, const Epi& epi, int z, int m0, int n0, int lane, floatx16 sums)
 {
+    if (any_lost<16>(sums)) gemm_again<A_KC, B_KC>(sh, epi, z, m0, n0, lane, sums);
+    const int n = n0 + (lane & 31);
 #pragma unroll
-    for (int g = 0; g < 4; ++g)
-        gemm_store<A_KC, B_KC>(sh, epi, z, m0 + 8 * g + 4 * (lane >> 5), n0 + (lane & 31), acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]);
+    for (int g = 0; g < 4; ++g) {
+        const int m = m0 + 8 * g + 4 * (lane >> 5);
+        if (m < sh.M && n < sh.N) epi(z, m, n, make_float4(sums[4 * g], sums[4 * g + 1], sums[4 * g + 2], sums[4 * g + 3]));
+    }
 }
 
 // Tile configuration of one launch.
@@ -388,14 +409,24 @@ __global__ __launch_bounds__(64 * CHUNKS) void gemm_split_chunks(GemmShape sh, E
     if (wave >= 4) return;
 #pragma unroll
     for (int j = 0; j < NT; ++j) {
-        float v[4];  // wavefront g stores rows 8g + 4h .. +3
+        floatx4 v;  // wavefront g stores rows 8g + 4h .. +3
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             v[i] = lds.part[0][j][4 * wave + i][lane];
 #pragma unroll
             for (int c = 1; c < CHUNKS; ++c) v[i] += lds.part[c][j][4 * wave + i][lane];
         }
-        gemm_store<A_KC, B_KC>(sh, epi, z, m0 + 8 * wave + 4 * (lane >> 5), n0 + 32 * j + (lane & 31), v[0], v[1], v[2], v[3]);
+        if (any_lost<4>(v)) {
+            floatx16 sums;  // the others are not looked at
+#pragma unroll
+            for (int i = 0; i < 16; ++i) sums[i] = i / 4 == wave ? v[i % 4] : 1.f;
+            gemm_again<A_KC, B_KC>(sh, epi, z, m0, n0 + 32 * j, lane, sums);
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+                if (i / 4 == wave) v[i % 4] = sums[i];
+        }
+        const int m = m0 + 8 * wave + 4 * (lane >> 5), n = n0 + 32 * j + (lane & 31);
+        if (m < sh.M && n < sh.N) epi(z, m, n, make_float4(v[0], v[1], v[2], v[3]));
     }
 }
 

@@ -14,7 +14,10 @@
 // eight 19.0 ns, per 16x16x32 MFMA (6.9 ns) one, two and three make 7.1, 7.8 and 9.2 ns; next to the fp32
 // 32x32x2 MFMA (27.1 ns) eight take their full time (44.2 ns).
 // What the split cannot hold: an infinity, or a value that rounds to one (above 3.39e38), leaves NaN in x1
-// and so in every sum it enters; the kernels look for NaN in their sums and redo such a sum with fp32 FMAs.
+// and so in every sum it enters; the kernels look for NaN in their sums and form such sums again with fp32 matrix
+// instructions, a wavefront's tile at a time, until those are NaN themselves.  A step on weights that are all NaN
+// takes 1.1-1.2 times as long as an ordinary one, one on a single infinite weight 2.6-4 times (64 workers of 128
+// images 0.72 -> 0.78 and 2.7 ms; with a loop of fp32 FMAs for every lost sum 55 and 77 ms).
 // Parts below 2^-126 are flushed to zero: operands under 2^-110 keep their leading 16 bits.
 #pragma once
 #include <hip/hip_runtime.h>
@@ -90,6 +93,46 @@ struct SplitSum {
         for (int t = 0; t <= SPLIT_SMALL; ++t) add(t, a, b);
     }
 };
+
+// Largest magnitude of N values; NaN if one of them is.
+template <int N, class V>
+__device__ __forceinline__ float largest(const V& v, int first = 0)
+{
+    float m = fabsf(v[first]);
+#pragma unroll
+    for (int i = 1; i < N; ++i) m = __builtin_elementwise_maximum(m, fabsf(v[first + i]));
+    return m;
+}
+
+// Whether sums of which the largest is `m` (see largest) are what their operands make; and whether sum `v` among such
+// as are not has to be formed again.
+__device__ __forceinline__ bool split_holds(float m) { return m == m; }
+__device__ __forceinline__ bool split_lost(float v) { return v != v; }
+
+// Whether a wavefront has to form sums again.
+template <int N, class V>
+__device__ __forceinline__ bool any_lost(const V& sums)
+{
+    return __builtin_expect(__any(!split_holds(largest<N>(sums))), 0);
+}
+
+// The same value, of which the compiler knows nothing: what is worked out from it in the rare block that forms sums
+// again stays there, instead of being kept in registers all through the loop around it.
+__device__ __forceinline__ int rarely(int v)
+{
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
+// Whether forming sums again can still give any of those that were lost: NaN, once in a sum, stays.
+template <int N, class V>
+__device__ __forceinline__ bool worth_going_on(const V& lost, const V& again)
+{
+    bool going = false;
+#pragma unroll
+    for (int i = 0; i < N; ++i) going |= split_lost(lost[i]) && again[i] == again[i];
+    return __any(going);
+}
 
 // The same operand with every lane taking the value S lanes further on in its row of 16 (zero past the end).
 template <int S>
