@@ -92,3 +92,97 @@ def test_a_diverged_network_is_not_slow(ps, n, B, what):
         assert min(times[1]) <= 8 * min(times[0])
     finally:
         ps.ps_destroy(ctx)
+
+
+# ------------------------------------------------------- every contraction against 64 bits on its own operands
+
+OFF_W3, OFF_B3 = 4800, 807616
+LAYERS = ("conv2 forward", "fc1 forward", "fc1 input gradient", "fc1 weight gradient", "conv2 input gradient", "conv2 weight gradient")
+
+
+def _results(ps, ctx, i, q, theta, x):
+    """{layer: (what the kernels made, the same in 64 bits from what they were given, the same of all magnitudes)} of
+    worker i, entry q.  No dropout."""
+    import torch
+    act, dbg = ps.ps_debug_last_activations(ctx, i), ps.ps_debug_last_batch(ctx, i)
+    B = dbg["pred"].size
+    grad, th = ps.ps_get_grad(ctx, q), torch.from_numpy(theta).cuda().double()
+    code2, code1 = (torch.from_numpy(dbg[k]).cuda().long().view(B, c, -1) for k, c in (("pool2", 32), ("pool1", 16)))
+    d2, u = _d2(ps, ctx, i)
+    pix = torch.nn.functional.unfold(x.double().view(B, 1, 28, 28), 3, padding=1)
+
+    def layers(f):
+        W2, b2, W3, b3 = f(th[160:4768]).view(32, 144), f(th[4768:4800]), f(th[4800:807616]).view(512, 1568), f(th[807616:808128])
+        p2, d3 = (f(torch.from_numpy(act[k]).cuda().double()) for k in ("pool2_val", "d3"))
+        z = torch.matmul(W2, f(u)).view(B, 32, 7, 2, 7, 2).permute(0, 1, 2, 4, 3, 5).reshape(B, 32, 49, 4)
+        z = (z.gather(-1, (code2 & 3).unsqueeze(-1))[..., 0] + b2.view(1, 32, 1)) * ((code2 & 4) > 0)
+        dp1 = torch.nn.functional.fold(torch.matmul(W2.t(), f(d2)), (14, 14), 3, padding=1).view(B, 16, 196) * ((code1 & 4) > 0)
+        w1 = torch.zeros(B, 16, 196, 4, device="cuda", dtype=torch.float64).scatter_(-1, (code1 & 3).unsqueeze(-1), dp1.unsqueeze(-1))
+        d1 = w1.view(B, 16, 14, 14, 2, 2).permute(0, 1, 2, 4, 3, 5).reshape(B, 16, 784)
+        out = (z, (p2 @ W3.t() + b3).clamp_min(0), d3 @ W3 * ((code2 & 4) > 0).view(B, 1568), d3.t() @ p2,
+               torch.matmul(d1, f(pix).transpose(1, 2)).sum(0), torch.matmul(f(d2), f(u).transpose(1, 2)).sum(0))
+        return [t.flatten().cpu().numpy() for t in out]
+
+    got = (act["pool2_val"], dbg["hdrop"], act["dpool2"], grad[OFF_W3:OFF_B3], grad[:144], grad[OFF_W2:OFF_B2])
+    return {k: (g.astype(np.float64).ravel(), w, m) for k, g, w, m in zip(LAYERS, got, layers(lambda t: t), layers(torch.abs))}
+
+
+# 2.5 u sqrt(K) of what is summed, as in the parity tests, at K = 1568, and half a unit of the smallest number
+def _compare(res):
+    for k in LAYERS:
+        got, want, size = res[k]
+        assert np.isfinite(got).all() and np.isfinite(want).all(), k
+        over = np.abs(got - want) / (2.5 * 2.0 ** -24 * 1568 ** 0.5 * size + 2.0 ** -150)
+        assert over.max() <= 1, (k, over.max(), np.abs(want).max())
+
+
+def _run(ps, theta, n, B, seed=17, labels=None):
+    """The last of n workers on `theta`, the others on ordinary weights; no dropout, which would scale values up."""
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    x = torch.rand(n, B, ps.IMAGE_PIXELS, device="cuda", generator=g)
+    y = torch.randint(0, 10, (n, B), device="cuda", generator=g, dtype=torch.int32)
+    if labels is not None:
+        y[:] = labels
+    ctx = ps.ps_init(ps.make_config(n, B, 2, n, DROP_SEED, 0.0))
+    try:
+        ps.ps_set_weights(ctx, synth.he_uniform_theta(5))
+        ps.ps_load_snapshot(ctx, 1, theta, 0)
+        q = ps.worker_grads_batched(ctx, range(n), [0] * (n - 1) + [1], [synth.minibatch_id(w, 0) for w in range(n)], x, y)
+        ps.ps_sync(ctx)
+        return _results(ps, ctx, n - 1, q[-1], theta, x[-1]), _results(ps, ctx, 0, q[0], synth.he_uniform_theta(5), x[0])
+    finally:
+        ps.ps_destroy(ctx)
+
+
+HUGE = np.float32(3.3999e38)  # finite, and infinite when rounded to 16 bits
+
+# launches of every form: images shared or not, fc1 in chunks, in one chain on tiles of every shape, its weight gradient
+# with conv2's (ragged or not) or by itself, conv2's weight gradient in shares or not
+FORMS = [(2, 16), (3, 33), (20, 40), (80, 40), (2, 130), (10, 130), (70, 130), (12, 65)]
+
+
+@pytest.mark.parametrize("n,B", FORMS)
+@pytest.mark.parametrize("where", ["pool1", "conv2 weight", "fc1 weight", "pool2"])
+def test_values_that_cannot_be_split(ps, n, B, where):
+    """Finite operands of 3.4e38 in each contraction, next to other operands so small that every sum is finite."""
+    theta = synth.he_uniform_theta(5)
+    W2, W3 = theta[160:4768].reshape(32, 16, 9), theta[4800:807616].reshape(512, 1568)
+    if where == "pool1":            # operand of conv2's forward and weight gradient: channel 13
+        theta[144 + 13] = HUGE
+        W2[:, 13] *= 1e-5
+        W3 *= 1e-3
+    elif where == "conv2 weight":   # of conv2's forward and input gradient
+        theta[:144] *= 1e-3
+        W2[21, 7, 2] = HUGE         # a corner of the window: what lies outside the map must not count
+        W3[:, 21 * 49:22 * 49] *= 1e-3
+    elif where == "fc1 weight":     # of fc1's forward and input gradient: a feature of the edge tiles
+        W2[31] *= 1e-6
+        W3[300, 1560] = HUGE
+    else:                           # of fc1's forward and weight gradient, features on both sides of the edge
+        theta[4768 + 31] = HUGE
+        W3[:, 31 * 49:] *= 1e-6
+    broken, good = _run(ps, theta, n, B)
+    _compare(broken)
+    _compare(good)
