@@ -14,8 +14,9 @@
 // eight 19.0 ns, per 16x16x32 MFMA (6.9 ns) one, two and three make 7.1, 7.8 and 9.2 ns; next to the fp32
 // 32x32x2 MFMA (27.1 ns) eight take their full time (44.2 ns).
 // What the split cannot hold: an infinity, or a value that rounds to one (above 3.39e38), leaves NaN in x1
-// and so in every sum it enters; the kernels look for NaN in their sums and form such sums again with fp32 matrix
-// instructions, a wavefront's tile at a time, until those are NaN themselves.  A step on weights that are all NaN
+// and so in every sum it enters; and a0b0 can be infinite where a*b, within 2^-8 of the largest float, is not.  The
+// kernels look for sums that are not finite and form them again with fp32 matrix instructions, a wavefront's tile at
+// a time, until those are NaN themselves.  A step on weights that are all NaN
 // takes 1.1-1.2 times as long as an ordinary one, one on a single infinite weight 2.6-4 times (64 workers of 128
 // images 0.72 -> 0.78 and 2.7 ms; with a loop of fp32 FMAs for every lost sum 55 and 77 ms).
 // Parts below 2^-126 are flushed to zero: operands under 2^-110 keep their leading 16 bits.
@@ -106,8 +107,8 @@ __device__ __forceinline__ float largest(const V& v, int first = 0)
 
 // Whether sums of which the largest is `m` (see largest) are what their operands make; and whether sum `v` among such
 // as are not has to be formed again.
-__device__ __forceinline__ bool split_holds(float m) { return m == m; }
-__device__ __forceinline__ bool split_lost(float v) { return v != v; }
+__device__ __forceinline__ bool split_holds(float m) { return m < INFINITY; }
+__device__ __forceinline__ bool split_lost(float v) { return !(fabsf(v) < INFINITY); }
 
 // Whether a wavefront has to form sums again.
 template <int N, class V>

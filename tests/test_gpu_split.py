@@ -115,7 +115,7 @@ def _results(ps, ctx, i, q, theta, x):
         W2, b2, W3, b3 = f(th[160:4768]).view(32, 144), f(th[4768:4800]), f(th[4800:807616]).view(512, 1568), f(th[807616:808128])
         p2, d3 = (f(torch.from_numpy(act[k]).cuda().double()) for k in ("pool2_val", "d3"))
         z = torch.matmul(W2, f(u)).view(B, 32, 7, 2, 7, 2).permute(0, 1, 2, 4, 3, 5).reshape(B, 32, 49, 4)
-        z = (z.gather(-1, (code2 & 3).unsqueeze(-1))[..., 0] + b2.view(1, 32, 1)) * ((code2 & 4) > 0)
+        z = (z.gather(-1, (code2 & 3).unsqueeze(-1))[..., 0] + b2.view(1, 32, 1)).clamp_min(0)
         dp1 = torch.nn.functional.fold(torch.matmul(W2.t(), f(d2)), (14, 14), 3, padding=1).view(B, 16, 196) * ((code1 & 4) > 0)
         w1 = torch.zeros(B, 16, 196, 4, device="cuda", dtype=torch.float64).scatter_(-1, (code1 & 3).unsqueeze(-1), dp1.unsqueeze(-1))
         d1 = w1.view(B, 16, 14, 14, 2, 2).permute(0, 1, 2, 4, 3, 5).reshape(B, 16, 784)
@@ -136,7 +136,7 @@ def _compare(res):
         assert over.max() <= 1, (k, over.max(), np.abs(want).max())
 
 
-def _run(ps, theta, n, B, seed=17, labels=None):
+def _run(ps, theta, n, B, seed=17, labels=None, seen=None):
     """The last of n workers on `theta`, the others on ordinary weights; no dropout, which would scale values up."""
     import torch
     g = torch.Generator(device="cuda")
@@ -151,6 +151,8 @@ def _run(ps, theta, n, B, seed=17, labels=None):
         ps.ps_load_snapshot(ctx, 1, theta, 0)
         q = ps.worker_grads_batched(ctx, range(n), [0] * (n - 1) + [1], [synth.minibatch_id(w, 0) for w in range(n)], x, y)
         ps.ps_sync(ctx)
+        if seen is not None:
+            seen.update(ps.ps_debug_last_activations(ctx, n - 1))
         return _results(ps, ctx, n - 1, q[-1], theta, x[-1]), _results(ps, ctx, 0, q[0], synth.he_uniform_theta(5), x[0])
     finally:
         ps.ps_destroy(ctx)
@@ -186,3 +188,29 @@ def test_values_that_cannot_be_split(ps, n, B, where):
     broken, good = _run(ps, theta, n, B)
     _compare(broken)
     _compare(good)
+
+
+@pytest.mark.parametrize("n,B", FORMS)
+def test_products_just_below_overflow(ps, n, B):
+    """A product within 2^-9 of the largest float, whose factors both round up in 16 bits: the leading product of the
+    split is infinite, the sum is not."""
+    import torch
+    theta = synth.he_uniform_theta(5)
+    W3 = theta[4800:807616].reshape(512, 1568)
+    top = float(np.finfo(np.float32).max)
+    with_pool2 = {}
+    _run(ps, theta, n, B, seen=with_pool2)
+    p2 = torch.from_numpy(with_pool2["pool2_val"])
+    bf16 = lambda v: float(torch.tensor(v, dtype=torch.float32).bfloat16())  # noqa: E731
+    for feat in range(1567, -1, -1):                            # its largest value is to meet a weight as large as can be
+        value = float(p2[:, feat].max())
+        w = np.float32(top * (1 - 2.0 ** -12) / max(value, 1.1))
+        if value > 1.1 and bf16(w) * bf16(value) > top * (1 + 2.0 ** -20):
+            break
+    assert feat and top * (1 - 2.0 ** -9) < float(w) * value < top
+    W3[300] = 0
+    W3[300, feat] = w
+    broken, _ = _run(ps, theta, n, B)
+    got, want, _ = (a.reshape(B, 512)[:, 300] for a in broken["fc1 forward"])
+    assert np.isfinite(want).all() and want.max() > top * (1 - 2.0 ** -9)
+    np.testing.assert_allclose(got, want, rtol=2.0 ** -22)     # one product and 1567 zeros, however they are added
