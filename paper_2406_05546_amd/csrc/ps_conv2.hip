@@ -40,6 +40,7 @@ struct FwdImage {  // one wavefront's pooled image
 // instructions, operands straight from memory.
 __device__ __forceinline__ void conv2_fwd_again(const float* __restrict__ p1, const float* __restrict__ W2, int t, int lane, floatx16& sums)
 {
+    const uint32_t which = lost_sums<16, 16>(sums);
     lane = rarely(lane);
     const int h = lane >> 5, l32 = lane & 31, e = l32 >> 4, column = lane & 15;
     floatx16 again;
@@ -56,11 +57,11 @@ __device__ __forceinline__ void conv2_fwd_again(const float* __restrict__ p1, co
             const float v = p[j];
             again = __builtin_amdgcn_mfma_f32_32x32x2f32(inside ? v : 0.f, w[9 * j], again, 0, 0, 0);
         }
-        if (!worth_going_on<16>(sums, again)) break;
+        if (!worth_going_on<16>(which, again)) break;
     }
 #pragma unroll
     for (int i = 0; i < 16; ++i)
-        if (split_lost(sums[i])) sums[i] = again[i];
+        if (which >> i & 1) sums[i] = again[i];
 }
 
 __global__ __launch_bounds__(FWD_NT, 2) void conv2_fwd_kernel(WorkerBuffers wb, int blocks_per_worker, int ipw, int parts)
@@ -136,7 +137,7 @@ __global__ __launch_bounds__(FWD_NT, 2) void conv2_fwd_kernel(WorkerBuffers wb, 
             up = low;
             floatx16 acc = sum.value();
             // register i of lane (h, l32): channel l32 at row 2t + i / 8, column 8 (i / 4 % 2) + 4h + i % 4
-            if (any_lost<16>(acc)) conv2_fwd_again(wb.p1 + g * P1_SIZE, W2, t, lane, acc);
+            if (any_lost<16, 16>(acc)) conv2_fwd_again(wb.p1 + g * P1_SIZE, W2, t, lane, acc);
 #pragma unroll
             for (int half = 0; half < 2; ++half) {
                 uint32_t bytes = 0;
@@ -221,6 +222,7 @@ struct DxImage {  // one wavefront's image
 // The same as conv2_fwd_again for d pool1 row Y of image g: lane (q, l16) holds channel l16 at X = 4q .. 4q + 3.
 __device__ __forceinline__ void conv2_dx_again(const WorkerBuffers& wb, size_t g, const float* __restrict__ W2, int Y, int lane, floatx4& sums)
 {
+    const uint32_t which = lost_sums<4, 4>(sums);
     lane = rarely(lane);
     const int q = lane >> 4, l16 = lane & 15;
     const uint8_t* codes = wb.am2t + g * P2_SIZE;
@@ -238,11 +240,11 @@ __device__ __forceinline__ void conv2_dx_again(const WorkerBuffers& wb, size_t g
             const bool winner = inside & (codes[p * C2 + o] >> bit & 1);
             again = __builtin_amdgcn_mfma_f32_16x16x4f32(winner ? d : 0.f, W2[(o * C1 + l16) * 9 + tap], again, 0, 0, 0);
         }
-        if (!worth_going_on<4>(sums, again)) break;
+        if (!worth_going_on<4>(which, again)) break;
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-        if (split_lost(sums[i])) sums[i] = again[i];
+        if (which >> i & 1) sums[i] = again[i];
 }
 
 struct Conv1Sums {
@@ -348,7 +350,7 @@ __device__ __forceinline__ void conv2_dx_block(const WorkerBuffers& wb, const Bw
 
         // conv1's gradient from d pool1 row Y: lane (q, l16) holds channel l16 at X = 4q .. 4q + 3
         auto finish_row = [&](int Y, floatx4 acc) {
-            if (any_lost<4>(acc)) conv2_dx_again(wb, g, W2, Y, lane, acc);
+            if (any_lost<4, 4>(acc)) conv2_dx_again(wb, g, W2, Y, lane, acc);
             const uint8_t* bytes = im.am1 + (P1_W * Y + 4 * q) * C1 + l16;
             const float* row = im.xs + 2 * Y * DX_XW + 8 * q;
 #pragma unroll
@@ -497,6 +499,7 @@ __device__ __forceinline__ ShiftedRow shifted_row(const float (&v)[10])
 // input channel l16, tap 0..8, or 9 for the bias.  The sums are times `sign`.
 __device__ __forceinline__ void conv2_dw_again(const WorkerBuffers& wb, int w, int s_begin, int s_end, int mt, int tap, float sign, int lane, floatx4& sums)
 {
+    const uint32_t which = lost_sums<4, 4>(sums);
     lane = rarely(lane);
     const int q = lane >> 4, l16 = lane & 15, o = 16 * mt + l16;
     floatx4 again = {0.f, 0.f, 0.f, 0.f};
@@ -513,11 +516,11 @@ __device__ __forceinline__ void conv2_dw_again(const WorkerBuffers& wb, int w, i
             const float v = wb.p1[g * P1_SIZE + (inside ? yy * P1_W + xx : 0) * C1 + l16];
             again = __builtin_amdgcn_mfma_f32_16x16x4f32(winner ? d : 0.f, tap == 9 ? 1.f : inside ? v : 0.f, again, 0, 0, 0);
         }
-        if (!worth_going_on<4>(sums, again)) break;
+        if (!worth_going_on<4>(which, again)) break;
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-        if (split_lost(sums[i])) sums[i] = again[i];
+        if (which >> i & 1) sums[i] = again[i];
 }
 
 typedef float DwSums[DW_NW][DW_REGS + 2][64];  // 75,776 B
@@ -657,7 +660,7 @@ __device__ __forceinline__ void conv2_dw_block(const WorkerBuffers& wb, const Bw
     bool lost = false;
 #pragma unroll
     for (int mt = 0; mt < MTS; ++mt) {
-        if (any_lost<4>(acc_b[mt])) conv2_dw_again(wb, w, s_begin, s_end, mt0 + mt, 9, sign, lane, acc_b[mt]);
+        if (any_lost<4, 4>(acc_b[mt])) conv2_dw_again(wb, w, s_begin, s_end, mt0 + mt, 9, sign, lane, acc_b[mt]);
 #pragma unroll
         for (int j = 0; j < 3 * DYS; ++j) {
             lost |= !split_holds(largest<4>(acc[mt][j]));
@@ -673,7 +676,7 @@ __device__ __forceinline__ void conv2_dw_block(const WorkerBuffers& wb, const Bw
             floatx4 sums;
 #pragma unroll
             for (int i = 0; i < 4; ++i) sums[i] = red[wave][r + i][lane];
-            if (!any_lost<4>(sums)) continue;
+            if (!any_lost<4, 4>(sums)) continue;
             conv2_dw_again(wb, w, s_begin, s_end, r / 36, r % 36 / 4, sign, lane, sums);
 #pragma unroll
             for (int i = 0; i < 4; ++i) red[wave][r + i][lane] = sums[i];

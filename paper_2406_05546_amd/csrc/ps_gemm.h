@@ -166,12 +166,12 @@ __device__ __forceinline__ floatx4 gemm_operand4(const float* __restrict__ base,
     return v;
 }
 
-// The sums of a 32x32 tile at (m0, n0) for which the split does not hold (ps_split.h), formed again with fp32 matrix
+// The sums `which` of a 32x32 tile at (m0, n0), for which the split does not hold (ps_split.h), formed again with fp32 matrix
 // instructions, whose registers lie as those of the bf16 ones do.  Operands come straight from memory, so it takes
 // about four times as long as the tile did, unless the sums turn out NaN anyway: a network of NaN weights is not
 // slowed down by more than that first look.
 template <bool A_KC, bool B_KC, class Epi>
-__device__ __forceinline__ void gemm_again(const GemmShape& sh, const Epi& epi, int z, int m0, int n0, int lane, floatx16& sums)
+__device__ __forceinline__ void gemm_again(const GemmShape& sh, const Epi& epi, int z, int m0, int n0, int lane, uint32_t which, floatx16& sums)
 {
     lane = rarely(lane);
     const float* __restrict__ A = epi.a_ptr(z);
@@ -190,18 +190,19 @@ __device__ __forceinline__ void gemm_again(const GemmShape& sh, const Epi& epi, 
 #pragma unroll
             for (int i = 0; i < 4; ++i) again = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[i], again, 0, 0, 0);
         }
-        if (!worth_going_on<16>(sums, again)) break;
+        if (!worth_going_on<16>(which, again)) break;
     }
 #pragma unroll
     for (int i = 0; i < 16; ++i)
-        if (split_lost(sums[i])) sums[i] = again[i];
+        if (which >> i & 1) sums[i] = again[i];
 }
 
 // Stores one 32x32 tile of sums at (m0, n0): register i of lane (h, l32) is row 8*(i/4) + 4*h + i%4, column l32.
 template <bool A_KC, bool B_KC, class Epi>
 __device__ __forceinline__ void gemm_finish(const GemmShape& sh, const Epi& epi, int z, int m0, int n0, int lane, floatx16 sums)
 {
-    if (any_lost<16>(sums)) gemm_again<A_KC, B_KC>(sh, epi, z, m0, n0, lane, sums);
+    constexpr int G = A_KC || B_KC ? 4 : 16;  // as gemm_split_chunks looks at them, where that may have the same sums to form
+    if (any_lost<16, G>(sums)) gemm_again<A_KC, B_KC>(sh, epi, z, m0, n0, lane, lost_sums<16, G>(sums), sums);
     const int n = n0 + (lane & 31);
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
@@ -416,14 +417,13 @@ __global__ __launch_bounds__(64 * CHUNKS) void gemm_split_chunks(GemmShape sh, E
 #pragma unroll
             for (int c = 1; c < CHUNKS; ++c) v[i] += lds.part[c][j][4 * wave + i][lane];
         }
-        if (any_lost<4>(v)) {
-            floatx16 sums;  // the others are not looked at
-#pragma unroll
-            for (int i = 0; i < 16; ++i) sums[i] = i / 4 == wave ? v[i % 4] : 1.f;
-            gemm_again<A_KC, B_KC>(sh, epi, z, m0, n0 + 32 * j, lane, sums);
+        if (any_lost<4, 4>(v)) {
+            const uint32_t which = lost_sums<4, 4>(v);
+            floatx16 sums;
+            gemm_again<A_KC, B_KC>(sh, epi, z, m0, n0 + 32 * j, lane, which << (4 * wave), sums);
 #pragma unroll
             for (int i = 0; i < 16; ++i)
-                if (i / 4 == wave) v[i % 4] = sums[i];
+                if (i / 4 == wave && (which >> (i % 4) & 1)) v[i % 4] = sums[i];
         }
         const int m = m0 + 8 * wave + 4 * (lane >> 5), n = n0 + 32 * j + (lane & 31);
         if (m < sh.M && n < sh.N) epi(z, m, n, make_float4(v[0], v[1], v[2], v[3]));

@@ -14,12 +14,15 @@
 // eight 19.0 ns, per 16x16x32 MFMA (6.9 ns) one, two and three make 7.1, 7.8 and 9.2 ns; next to the fp32
 // 32x32x2 MFMA (27.1 ns) eight take their full time (44.2 ns).
 // What the split cannot hold: an infinity, or a value that rounds to one (above 3.39e38), leaves NaN in x1
-// and so in every sum it enters; and a0b0 can be infinite where a*b, within 2^-8 of the largest float, is not.  The
-// kernels look for sums that are not finite and form them again with fp32 matrix instructions, a wavefront's tile at
-// a time, until those are NaN themselves.  A step on weights that are all NaN
-// takes 1.1-1.2 times as long as an ordinary one, one on a single infinite weight 2.6-4 times (64 workers of 128
-// images 0.72 -> 0.78 and 2.7 ms; with a loop of fp32 FMAs for every lost sum 55 and 77 ms).
-// Parts below 2^-126 are flushed to zero: operands under 2^-110 keep their leading 16 bits.
+// and so in every sum it enters; a0b0 can be infinite where a*b, within 2^-8 of the largest float, is not; and parts
+// are multiples of 2^-133, so that operands below 2^-110 lose bits.  The kernels look for sums that are not finite, and
+// for groups of sums all below 2^-80 and not all zero (the gradients of a minibatch whose every image is classified
+// with a margin of 60 or so), and form them again with fp32 matrix instructions, a wavefront's tile at a time, until
+// those are NaN.  Of sums that are not formed again, small operands take less than 2^-24 with up to 2^11 products and
+// the other operands below 2^20.  Operands below 2^-134, which hold at most 15 bits, count as zero in a tile that
+// has no others.  A step on weights that are all NaN takes 1.1-1.2 times as long as an ordinary one, one on a single
+// infinite weight 2.6-4 times (64 workers of 128 images 0.72 -> 0.78 and 2.7 ms; with a loop of fp32 FMAs for every
+// lost sum 55 and 77 ms); looking takes 0.3 % of conv2's gradients and nothing measurable elsewhere.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -105,16 +108,40 @@ __device__ __forceinline__ float largest(const V& v, int first = 0)
     return m;
 }
 
-// Whether sums of which the largest is `m` (see largest) are what their operands make; and whether sum `v` among such
-// as are not has to be formed again.
-__device__ __forceinline__ bool split_holds(float m) { return m < INFINITY; }
-__device__ __forceinline__ bool split_lost(float v) { return !(fabsf(v) < INFINITY); }
+// Whether sums of which the largest is `m` (see largest) are what their operands make.
+constexpr float SPLIT_TINY = 0x1p-80f;
+__device__ __forceinline__ bool split_holds(float m) { return m == 0.f || (m >= SPLIT_TINY && m < INFINITY); }
 
-// Whether a wavefront has to form sums again.
-template <int N, class V>
+// Whether a wavefront has to form some of its sums again; they are looked at in groups of G.  (One comparison in the
+// way of the sums that are neither lost nor zero.)
+template <int N, int G, class V>
 __device__ __forceinline__ bool any_lost(const V& sums)
 {
-    return __builtin_expect(__any(!split_holds(largest<N>(sums))), 0);
+    constexpr uint32_t LOW = __builtin_bit_cast(uint32_t, SPLIT_TINY), RANGE = 0x7f800000u - LOW;
+    bool odd = false, lost = false;
+#pragma unroll
+    for (int i = 0; i < N; i += G) odd |= __float_as_uint(largest<G>(sums, i)) - LOW >= RANGE;
+    if (__builtin_expect(!__any(odd), 1)) return false;
+#pragma unroll
+    for (int i = 0; i < N; i += G) lost |= !split_holds(largest<G>(sums, i));
+    return __any(lost);
+}
+
+// Those of this lane's that have to be, a bit for each: what does not hold by itself in a group that does not; and where
+// sums of any lane's group are tiny, what is zero, too.
+template <int N, int G, class V>
+__device__ __forceinline__ uint32_t lost_sums(const V& sums)
+{
+    uint32_t which = 0;
+#pragma unroll
+    for (int i = 0; i < N; i += G) {
+        const float m = largest<G>(sums, i);
+        const bool zero_lost = __any(m > 0.f && m < SPLIT_TINY) && m < SPLIT_TINY;
+#pragma unroll
+        for (int j = i; j < i + G; ++j)
+            if (zero_lost || (!split_holds(m) && !split_holds(fabsf(sums[j])))) which |= 1u << j;
+    }
+    return which;
 }
 
 // The same value, of which the compiler knows nothing: what is worked out from it in the rare block that forms sums
@@ -125,13 +152,13 @@ __device__ __forceinline__ int rarely(int v)
     return v;
 }
 
-// Whether forming sums again can still give any of those that were lost: NaN, once in a sum, stays.
+// Whether forming them again can still give any of those that were lost: NaN, once in a sum, stays.
 template <int N, class V>
-__device__ __forceinline__ bool worth_going_on(const V& lost, const V& again)
+__device__ __forceinline__ bool worth_going_on(uint32_t which, const V& again)
 {
     bool going = false;
 #pragma unroll
-    for (int i = 0; i < N; ++i) going |= split_lost(lost[i]) && again[i] == again[i];
+    for (int i = 0; i < N; ++i) going |= (which >> i & 1) && again[i] == again[i];
     return __any(going);
 }
 

@@ -127,12 +127,12 @@ def _results(ps, ctx, i, q, theta, x):
     return {k: (g.astype(np.float64).ravel(), w, m) for k, g, w, m in zip(LAYERS, got, layers(lambda t: t), layers(torch.abs))}
 
 
-# 2.5 u sqrt(K) of what is summed, as in the parity tests, at K = 1568, and half a unit of the smallest number
+# 2.5 u sqrt(K) of what is summed, as in the parity tests, at K = 1568, and half a unit of the smallest number at each step
 def _compare(res):
     for k in LAYERS:
         got, want, size = res[k]
         assert np.isfinite(got).all() and np.isfinite(want).all(), k
-        over = np.abs(got - want) / (2.5 * 2.0 ** -24 * 1568 ** 0.5 * size + 2.0 ** -150)
+        over = np.abs(got - want) / (2.5 * 2.0 ** -24 * 1568 ** 0.5 * size + 1568 * 2.0 ** -150)
         assert over.max() <= 1, (k, over.max(), np.abs(want).max())
 
 
@@ -214,3 +214,26 @@ def test_products_just_below_overflow(ps, n, B):
     got, want, _ = (a.reshape(B, 512)[:, 300] for a in broken["fc1 forward"])
     assert np.isfinite(want).all() and want.max() > top * (1 - 2.0 ** -9)
     np.testing.assert_allclose(got, want, rtol=2.0 ** -22)     # one product and 1567 zeros, however they are added
+
+
+@pytest.mark.parametrize("n,B", FORMS)
+@pytest.mark.parametrize("what", ["margin 76", "margin 80", "pixels", "conv2 weights", "fc1 weights"])
+def test_tiny_operands_keep_their_bits(ps, n, B, what):
+    """Parts below 2^-133 do not exist, so operands below 2^-110 have fewer than 24 bits in the split: gradients of a
+    minibatch whose every image is classified with a margin of 76 or 80 in the logits, activations and weights of 1e-36."""
+    theta = synth.he_uniform_theta(5)
+    labels = None
+    if what.startswith("margin"):
+        labels = 3
+        theta[808128:813248] *= 0.01
+        theta[813248 + 3] = float(what.split()[1])
+    elif what == "pixels":          # pool1 values, by way of conv1's weights
+        theta[:144] *= 1e-36
+    elif what == "conv2 weights":   # and pool2 values
+        theta[160:4768] *= 1e-36
+    else:
+        theta[4800:807616] *= 1e-36
+    broken, good = _run(ps, theta, n, B, labels=labels)
+    assert 0 < max(np.abs(want).max() for _, want, _ in broken.values())
+    _compare(broken)
+    _compare(good)
