@@ -180,8 +180,9 @@ ps_status row_list(ps_ctx* c, const std::vector<int32_t>& idx, RowList* rows)
 {
     bool consecutive = true;
     for (size_t k = 1; k < idx.size(); ++k) consecutive = consecutive && idx[k] == idx[0] + (int32_t)k;
-    *rows = RowList{consecutive ? nullptr : c->at<int32_t>(c->lay.idx), idx[0]};
-    return consecutive ? PS_OK : upload(c, c->at<int32_t>(c->lay.idx), idx.data(), idx.size() * sizeof(int32_t));
+    int32_t* list = c->at<int32_t>(c->lay.idx);
+    *rows = RowList{consecutive ? nullptr : list, idx[0], list};
+    return consecutive ? PS_OK : upload(c, list, idx.data(), idx.size() * sizeof(int32_t));
 }
 
 ps_status apply_entries(ps_ctx* c, const std::vector<int32_t>& idx, float lr, int mode)
@@ -681,7 +682,7 @@ ps_status ps_store_consume(ps_ctx* c, int32_t mode, float lr, int32_t max_entrie
     }
     const StoreBuffers sb = store_buffers(c);
     PS_HIP(c, launch_store_take(sb, limit, c->server));
-    PS_HIP(c, launch_apply(c->theta(), c->at<float>(c->lay.queue), RowList{sb.idx, 0}, limit, lr, mode, c->server, c->prof, &sb.range->count));
+    PS_HIP(c, launch_apply(c->theta(), c->at<float>(c->lay.queue), RowList{sb.idx, 0, nullptr}, limit, lr, mode, c->server, c->prof, &sb.range->count));
     PS_HIP(c, launch_store_release(sb, mode, c->server));
     HeadReadback& r = c->headrb[c->next_headrb];
     unsigned long long* dst = c->headrb_host + c->next_headrb;

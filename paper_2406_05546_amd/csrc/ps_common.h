@@ -168,6 +168,7 @@ hipError_t launch_keep_mask(uint8_t* keep_dev, int B, uint32_t mb_lo, uint32_t m
 struct RowList {
     const int32_t* list;
     int32_t first;
+    int32_t* room;  // K numbers in device memory that the launch may list consecutive rows in; may be null
 };
 
 // theta -= lr * (sum of the K rows) [mode 0] or K successive updates [mode 1].

@@ -830,6 +830,48 @@ def test_applies_over_consecutive_and_listed_rows(ps, order):
         ps.ps_destroy(ctx)
 
 
+def _append(ps, ctx, count, first, n, x, y):
+    """`count` worker gradients of the weights in slot 0, numbered from `first`."""
+    for k in range(first, first + count, n):
+        m = min(n, first + count - k)
+        ps.worker_grads_batched(ctx, range(m), [0] * m, [synth.minibatch_id(w, k) for w in range(m)], x[:m], y[:m])
+
+
+@pytest.mark.parametrize("K", [767, 768, 1100])
+def test_long_drains_match_short_ones(ps, K):
+    """From 768 rows on a drain reads a list of its rows, below it counts them: in order, a long drain is the short ones
+    it can be cut into, byte for byte, from a context's queue or the caller's rows; summed, it is the sum."""
+    import torch
+    n, B, lr = 100, 2, 0.5
+    x, y = _torch_inputs(*synth.minibatches(DATA_SEED, [synth.minibatch_id(w, 3) for w in range(n)], B))
+    ctx = ps.ps_init(ps.make_config(n, B, 1, K, DROP_SEED, P_DROP))
+    try:
+        theta = synth.he_uniform_theta(31)
+        ps.ps_set_weights(ctx, theta)
+        _append(ps, ctx, K, 0, n, x, y)
+        ps.ps_sync(ctx)
+        rows = ctx.workspace.view(torch.float32).view(-1)[:(2 + K) * ps.ROW_FLOATS].view(-1, ps.ROW_FLOATS)
+        start, grads = rows[0].clone(), rows[2:].clone()
+        for clip in (0.0, 0.05):
+            whole, parts = start.clone(), start.clone()
+            ps.ps_drain_rows_mitigated(whole, grads, ps.DRAIN_SEQ, lr, 0.0, clip)
+            for part in grads.split(300):
+                ps.ps_drain_rows_mitigated(parts, part, ps.DRAIN_SEQ, lr, 0.0, clip)
+            assert torch.equal(whole, parts)
+        summed = start.clone()
+        ps.ps_drain_rows_mitigated(summed, grads, ps.DRAIN_SUM, lr)
+        want, size = start.double(), start.double().abs()
+        for g in grads:
+            want -= lr * g.double()
+            size += lr * g.double().abs()
+        assert bool(((summed.double() - want).abs() <= 2.5 * 2.0 ** -24 * K ** 0.5 * size).all())
+        assert ps.ps_drain_buffered_mitigated(ctx, ps.DRAIN_SEQ, lr, 0.0, 0.05)[0] == K   # from the queue
+        ps.ps_sync(ctx)
+        assert torch.equal(rows[0], whole)
+    finally:
+        ps.ps_destroy(ctx)
+
+
 @pytest.mark.parametrize("n,B", [(20, 40), (70, 40), (32, 130)])
 def test_gradient_bits_do_not_depend_on_the_launch(ps, n, B):
     """One worker alone runs in the small-launch forms of the kernels (several wavefronts to an image, a wavefront to
