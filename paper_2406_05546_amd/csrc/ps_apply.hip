@@ -246,8 +246,8 @@ __global__ __launch_bounds__(256) void row_list_kernel(int32_t* __restrict__ lis
 
 // Many consecutive rows are listed after all: a kernel that reads their numbers keeps its loads in better step than one
 // that counts.  The list is 2 us more: 512 rows 249 us counted or listed, 768 371 either way, 1024 493 against 488, 2048 981
-// against 967.
-constexpr int LISTED_ROWS = 768;
+// against 967; Adadelta steps over 128 rows 83 either way, 400 235 against 229, 1024 576 against 551.
+constexpr int LISTED_ROWS = 768, LISTED_ROWS_ADADELTA = 256;
 
 RowList listed(RowList rows, int K, int from, hipStream_t s)
 {
@@ -299,10 +299,11 @@ hipError_t launch_apply_clipped(float* theta, const float* queue, const RowList&
     return hipGetLastError();
 }
 
-hipError_t launch_apply_adadelta(float* theta, float* acc_g2, float* acc_dx2, const float* queue, const RowList& rows, int K, float lr,
+hipError_t launch_apply_adadelta(float* theta, float* acc_g2, float* acc_dx2, const float* queue, const RowList& given, int K, float lr,
                                  float rho, float eps, hipStream_t s, Profiler& prof)
 {
     if (K <= 0) return hipSuccess;
+    const RowList rows = listed(given, K, LISTED_ROWS_ADADELTA, s);
     prof.begin(K_APPLY_ADADELTA, s);
     hipLaunchKernelGGL(rows.list ? apply_adadelta_kernel<true> : apply_adadelta_kernel<false>, APPLY_GRID, dim3(APPLY_BLOCK), 0, s, (float4*)theta,
                        (float4*)acc_g2, (float4*)acc_dx2, (const float4*)queue, rows, K, lr, rho, eps);

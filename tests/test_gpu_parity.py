@@ -872,6 +872,27 @@ def test_long_drains_match_short_ones(ps, K):
         ps.ps_destroy(ctx)
 
 
+@pytest.mark.parametrize("K", [255, 256, 400])
+def test_long_adadelta_drains_match_short_ones(ps, K):
+    """The same for Adadelta steps, which read a list from 256 rows on: the drain at once and in pieces, whose state
+    passes through memory, byte for byte."""
+    n, B = 100, 2
+    x, y = _torch_inputs(*synth.minibatches(DATA_SEED, [synth.minibatch_id(w, 3) for w in range(n)], B))
+    got = []
+    for piece in (K, 100):
+        ctx = ps.ps_init(ps.make_config(n, B, 1, K, DROP_SEED, P_DROP))
+        try:
+            ps.ps_set_weights(ctx, synth.he_uniform_theta(31))
+            for k in range(0, K, piece):
+                _append(ps, ctx, min(piece, K - k), k, n, x, y)
+                assert ps.ps_drain_buffered_adadelta(ctx, 0.1, 0.9, 1e-6) == min(piece, K - k)
+            assert ps.ps_version(ctx) == K
+            got.append(ps.ps_get_weights(ctx))
+        finally:
+            ps.ps_destroy(ctx)
+    assert np.array_equal(*got) and not np.array_equal(got[0], synth.he_uniform_theta(31))
+
+
 @pytest.mark.parametrize("n,B", [(20, 40), (70, 40), (32, 130)])
 def test_gradient_bits_do_not_depend_on_the_launch(ps, n, B):
     """One worker alone runs in the small-launch forms of the kernels (several wavefronts to an image, a wavefront to
