@@ -108,6 +108,7 @@ Layout make_layout(const ps_config& c)
 
 struct ps_ctx {
     ps_config cfg{};
+    int compute_units = 0;  // of the GPU that was current when the context was made
     hipStream_t stream = nullptr;
     char* ws = nullptr;
     Layout lay{};
@@ -259,6 +260,7 @@ WorkerBuffers buffers(const ps_ctx* c, int n, const float* x, const int32_t* y, 
     wb.seed_hi = (uint32_t)(c->cfg.seed >> 32);
     wb.drop_threshold = (uint32_t)std::floor((double)c->cfg.dropout_p * 4294967296.0);
     wb.drop_scale = (float)(1.0 / (1.0 - (double)c->cfg.dropout_p));
+    wb.compute_units = c->compute_units;
     return wb;
 }
 
@@ -383,7 +385,10 @@ ps_status ps_init(ps_ctx** out, const ps_config* cfg, void* workspace_dev, uint6
     c->ev_slot_written.assign(cfg->n_versions, nullptr);
     c->slot_read_valid.assign(cfg->n_versions, 0);
     c->slot_written_valid.assign(cfg->n_versions, 0);
-    hipError_t e = hipStreamCreateWithFlags(&c->server, hipStreamNonBlocking);  // default priority
+    int device = 0;
+    hipError_t e = hipGetDevice(&device);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&c->compute_units, hipDeviceAttributeMultiprocessorCount, device);
+    if (e == hipSuccess) e = hipStreamCreateWithFlags(&c->server, hipStreamNonBlocking);  // default priority
     if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_join, hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_workers, hipEventDisableTiming);
     for (int i = 0; i < cfg->n_versions && e == hipSuccess; ++i) {

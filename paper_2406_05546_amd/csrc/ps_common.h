@@ -72,6 +72,7 @@ struct WorkerBuffers {
     uint32_t seed_lo, seed_hi;
     uint32_t drop_threshold;  // drop iff word < threshold
     float drop_scale;         // 1/(1-p)
+    int32_t compute_units;    // of the context's GPU
 };
 
 #if defined(__HIPCC__)
@@ -104,10 +105,9 @@ int fc2_split(int n);  // blocks per worker of the fc2 kernel (one partial slot 
 int conv2_part_slots(int batch);  // conv2 partial slots per worker (one per block of its weight-gradient kernel)
 int conv1_part_slots(int batch);  // conv1 partial slots per worker (one per image, written by conv2's input-gradient kernel)
 
-int compute_units();  // of the current GPU
 // For the kernels in which a wavefront works on whole images, or several share one in small launches.
-int images_per_wavefront(int n, int batch, int most);
-int wavefronts_per_image(int n, int batch, int most);
+int images_per_wavefront(const WorkerBuffers& wb, int most);
+int wavefronts_per_image(const WorkerBuffers& wb, int most);
 int blocks_per_worker(int batch, int images_per_wavefront, int wavefronts_per_image, int wavefronts);
 
 void launch_conv1_fwd(const WorkerBuffers& wb, hipStream_t s);
@@ -128,7 +128,7 @@ hipError_t launch_eval_collect(int n_images, const float* loss_i, const int32_t*
 
 void launch_conv2_fwd(const WorkerBuffers& wb, hipStream_t s);
 void launch_fc1_dw(const WorkerBuffers& wb, hipStream_t s);
-bool fc1_dw_is_few(int n);  // whether fc1's weight gradient runs in launch_backward's launch instead of one of its own
+bool fc1_dw_is_few(const WorkerBuffers& wb);  // whether fc1's weight gradient runs in launch_backward's launch instead of one of its own
 void launch_backward(const WorkerBuffers& wb, hipStream_t s);  // conv2's gradients (and conv1's)
 
 // Kernels of the path, in launch order; ids index the per-kernel timing table.

@@ -723,7 +723,7 @@ __global__ __launch_bounds__(256, 2) void backward_kernel(WorkerBuffers wb, BwdS
 
 void launch_conv2_fwd(const WorkerBuffers& wb, hipStream_t s)
 {
-    const int ipw = images_per_wavefront(wb.n, wb.B, FWD_IPW), parts = wavefronts_per_image(wb.n, wb.B, 4);
+    const int ipw = images_per_wavefront(wb, FWD_IPW), parts = wavefronts_per_image(wb, 4);
     const int bpw = blocks_per_worker(wb.B, ipw, parts, FWD_NW);
     hipLaunchKernelGGL(conv2_fwd_kernel, dim3(wb.n * bpw), dim3(FWD_NT), 0, s, wb, bpw, ipw, parts);
 }
@@ -741,22 +741,22 @@ int conv2_part_slots(int batch)
 void launch_backward(const WorkerBuffers& wb, hipStream_t s)
 {
     BwdShape sh;
-    sh.dx_ipw = images_per_wavefront(wb.n, wb.B, DX_IPW);
-    sh.dx_parts = wavefronts_per_image(wb.n, wb.B, 2);
+    sh.dx_ipw = images_per_wavefront(wb, DX_IPW);
+    sh.dx_parts = wavefronts_per_image(wb, 2);
     sh.dx_blocks_per_worker = blocks_per_worker(wb.B, sh.dx_ipw, sh.dx_parts, DX_NW);
     sh.dx_blocks = wb.n * sh.dx_blocks_per_worker;
     sh.dw_slots = conv2_part_slots(wb.B);
     sh.dw_ipw = conv2_dw_ipw(wb.B);
-    sh.dw_shared = DW_SHARES * DW_NW * wb.n * sh.dw_slots <= 2 * 4 * compute_units();
+    sh.dw_shared = DW_SHARES * DW_NW * wb.n * sh.dw_slots <= 2 * 4 * wb.compute_units;
     sh.dw_blocks = wb.n * sh.dw_slots * (sh.dw_shared ? DW_SHARES : 1);
     const GemmShape fc1 = fc1_dw_few_shape(wb.n, wb.B);
     const int conv_blocks = (sh.dx_blocks + sh.dw_blocks + 7) / 8 * 8;
-    if (!fc1_dw_few(wb.n))
+    if (!fc1_dw_few(wb))
         hipLaunchKernelGGL(backward_kernel<0>, dim3(conv_blocks), dim3(256), 0, s, wb, sh, fc1);
     else
         hipLaunchKernelGGL((wb.B % Fc1DwFew::KS == 0 ? backward_kernel<1> : backward_kernel<2>), dim3(conv_blocks + gemm_grid(fc1)), dim3(256), 0, s, wb, sh, fc1);
 }
 
-bool fc1_dw_is_few(int n) { return fc1_dw_few(n); }
+bool fc1_dw_is_few(const WorkerBuffers& wb) { return fc1_dw_few(wb); }
 
 }  // namespace ps

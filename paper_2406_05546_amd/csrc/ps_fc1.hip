@@ -61,14 +61,14 @@ static_assert(FWD_CHUNKS * FWD_CHUNK * GEMM_K == P2_SIZE && DX_CHUNKS * DX_CHUNK
 // forward: rows = 512 units (W3, k-contiguous), columns = the worker's samples (pool2, k-contiguous)
 void launch_fc1_fwd(const WorkerBuffers& wb, hipStream_t s)
 {
-    const bool few = gemm_few_tiles(FC1 / 128 * ((wb.B + 127) / 128) * wb.n);
+    const bool few = gemm_few_tiles(FC1 / 128 * ((wb.B + 127) / 128) * wb.n, wb.compute_units);
     const Fc1FwdEpi epi{wb};
     if (wb.B <= CHUNKED_BATCH) {
         if (few)
-            gemm_launch_chunks<true, true, FWD_CHUNKS, FWD_CHUNK>(FC1, wb.B, P2_SIZE, P2_SIZE, wb.n, epi, s);
+            gemm_launch_chunks<true, true, FWD_CHUNKS, FWD_CHUNK>(FC1, wb.B, P2_SIZE, P2_SIZE, wb.n, wb.compute_units, epi, s);
         else
             gemm_launch<GemmCfg<true, true, 2, 1, 2, 2, 2>, FWD_CHUNK, 2>(FC1, wb.B, P2_SIZE, P2_SIZE, P2_SIZE, wb.n, epi, s);
-    } else if (gemm_roles_fit(FC1, wb.B, wb.n)) {
+    } else if (gemm_roles_fit(FC1, wb.B, wb.n, wb.compute_units)) {
         gemm_launch_roles<true, true>(FC1, wb.B, P2_SIZE, P2_SIZE, P2_SIZE, wb.n, epi, s);
     } else if (few) {
         gemm_launch<GemmCfg<true, true, 1, 1, 2, 2, 4, 32>, 0, 2>(FC1, wb.B, P2_SIZE, P2_SIZE, P2_SIZE, wb.n, epi, s);
@@ -90,15 +90,15 @@ void launch_fc1_dx(const WorkerBuffers& wb, hipStream_t s)
     // 64 x 64 tiles already fall behind where there is a wide tile for two compute units (8 workers of 128 images, 96
     // tiles: 22 against 28 us; 16 of 128: 37 against 31)
     const int wide_tiles = FEAT_WIDE / 128 * ((wb.B + 127) / 128) * wb.n;
-    const bool few = gemm_few_tiles(wb.B <= CHUNKED_BATCH ? wide_tiles : 2 * wide_tiles);
+    const bool few = gemm_few_tiles(wb.B <= CHUNKED_BATCH ? wide_tiles : 2 * wide_tiles, wb.compute_units);
     const Fc1DxEpi epi{wb};
     if (wb.B <= CHUNKED_BATCH) {
         if (few)
-            gemm_launch_chunks<false, true, DX_CHUNKS, DX_CHUNK>(P2_SIZE, wb.B, P2_SIZE, FC1, wb.n, epi, s);
+            gemm_launch_chunks<false, true, DX_CHUNKS, DX_CHUNK>(P2_SIZE, wb.B, P2_SIZE, FC1, wb.n, wb.compute_units, epi, s);
         else
             gemm_launch_edge<GemmCfg<false, true, 2, 1, 2, 2, 2>, GemmCfg<false, true, 1, 1, 1, 4, 2>, false, DX_CHUNK, 2>(P2_SIZE, wb.B, FC1, P2_SIZE, FC1, wb.n,
                                                                                                           FEAT_WIDE, wb.B, epi, s);
-    } else if (gemm_roles_fit(P2_SIZE, wb.B, wb.n)) {
+    } else if (gemm_roles_fit(P2_SIZE, wb.B, wb.n, wb.compute_units)) {
         gemm_launch_roles<false, true>(P2_SIZE, wb.B, FC1, P2_SIZE, FC1, wb.n, epi, s);
     } else if (few) {
         gemm_launch<GemmCfg<false, true, 1, 1, 2, 2, 4, 32>, 0, 2>(P2_SIZE, wb.B, FC1, P2_SIZE, FC1, wb.n, epi, s);

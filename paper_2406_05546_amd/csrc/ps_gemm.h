@@ -543,7 +543,7 @@ __global__ __launch_bounds__(320) void gemm_split_roles(GemmShape sh, Epi epi)
 }
 
 // Whether a launch over this many 128 x 128 tiles leaves compute units idle.
-inline bool gemm_few_tiles(int wide_tiles) { return wide_tiles < compute_units(); }
+inline bool gemm_few_tiles(int wide_tiles, int compute_units) { return wide_tiles < compute_units; }
 
 constexpr int gemm_grid(const GemmShape& sh) { return (sh.gx * sh.gy * sh.gz + GEMM_XCDS - 1) / GEMM_XCDS * GEMM_XCDS; }
 
@@ -600,7 +600,7 @@ void gemm_launch(int M, int N, int K, int lda, int ldb, int batch, const Epi& ep
 }
 
 // Whether every tile of 32 x 32 finds a compute unit of its own (both sides measured: gemm_split_roles).
-inline bool gemm_roles_fit(int M, int N, int batch) { return (M + 31) / 32 * ((N + 31) / 32) * batch <= compute_units(); }
+inline bool gemm_roles_fit(int M, int N, int batch, int compute_units) { return (M + 31) / 32 * ((N + 31) / 32) * batch <= compute_units; }
 
 // K: at least 64, a multiple of 16.
 template <bool A_KC, bool B_KC, class Epi>
@@ -614,11 +614,11 @@ void gemm_launch_roles(int M, int N, int K, int lda, int ldb, int batch, const E
 // One problem per batch index in tiles of 32 x 32, or 32 x 64 if those alone give every compute unit a block; K =
 // CHUNKS * CHUNK MFMA steps.
 template <bool A_KC, bool B_KC, int CHUNKS, int CHUNK, class Epi>
-void gemm_launch_chunks(int M, int N, int lda, int ldb, int batch, const Epi& epi, hipStream_t s)
+void gemm_launch_chunks(int M, int N, int lda, int ldb, int batch, int compute_units, const Epi& epi, hipStream_t s)
 {
     if (M <= 0 || N <= 0 || batch <= 0) return;
     GemmShape sh{M, N, CHUNKS * CHUNK * GEMM_K, lda, ldb, (M + 31) / 32, (N + 31) / 32, batch, 0, 0};
-    if (N <= 32 || sh.gx * sh.gy * batch <= compute_units()) {
+    if (N <= 32 || sh.gx * sh.gy * batch <= compute_units) {
         hipLaunchKernelGGL((gemm_split_chunks<A_KC, B_KC, 1, CHUNKS, CHUNK, Epi>), dim3(gemm_grid(sh)), dim3(64 * CHUNKS), 0, s, sh, epi);
     } else {
         sh.gy = (N + 63) / 64;

@@ -92,31 +92,20 @@ __global__ __launch_bounds__(256) void keep_mask_kernel(uint8_t* keep, int B, ui
 
 }  // namespace
 
-int compute_units()
-{
-    static int cus = 0;
-    if (cus == 0) {
-        int dev = 0;
-        if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
-            cus = 256;
-    }
-    return cus;
-}
-
 // As many (up to `most`) as leave two wavefronts for every SIMD: what a wavefront does once per launch, reading
 // and splitting a filter bank above all, takes up to a quarter of an image's time.
-int images_per_wavefront(int n, int batch, int most)
+int images_per_wavefront(const WorkerBuffers& wb, int most)
 {
     int ipw = most;
-    while (ipw > 1 && n * ((batch + ipw - 1) / ipw) < 2 * 4 * compute_units()) ipw /= 2;
+    while (ipw > 1 && wb.n * ((wb.B + ipw - 1) / ipw) < 2 * 4 * wb.compute_units) ipw /= 2;
     return ipw;
 }
 
 // How many wavefronts (1, 2 or 4, up to `most`) can share an image and still find SIMDs to run on, one each.
-int wavefronts_per_image(int n, int batch, int most)
+int wavefronts_per_image(const WorkerBuffers& wb, int most)
 {
     int parts = 1;
-    while (parts < most && 2 * parts * n * batch <= 4 * compute_units()) parts *= 2;
+    while (parts < most && 2 * parts * wb.n * wb.B <= 4 * wb.compute_units) parts *= 2;
     return parts;
 }
 
@@ -147,11 +136,11 @@ hipError_t launch_worker_backward(const WorkerBuffers& wb, hipStream_t s, Profil
 {
     if (wb.n * wb.B <= 0) return hipSuccess;
     PS_TIMED(K_FC2, launch_fc2(wb, s));
-    if (!fc1_dw_is_few(wb.n)) PS_TIMED(K_FC1_DW, launch_fc1_dw(wb, s));
+    if (!fc1_dw_is_few(wb)) PS_TIMED(K_FC1_DW, launch_fc1_dw(wb, s));
     PS_TIMED(K_FC1_DX, launch_fc1_dx(wb, s));
-    PS_TIMED(fc1_dw_is_few(wb.n) ? K_BACKWARD_FC1 : K_BACKWARD, launch_backward(wb, s));
+    PS_TIMED(fc1_dw_is_few(wb) ? K_BACKWARD_FC1 : K_BACKWARD, launch_backward(wb, s));
     // one value per thread while the chip has room, at least the blocks that the conv1 values take
-    const int reduce_y = wb.n * (REDUCE_ITEMS / 256 + 1) <= 8 * compute_units() ? REDUCE_ITEMS / 256 + 1 : 8;
+    const int reduce_y = wb.n * (REDUCE_ITEMS / 256 + 1) <= 8 * wb.compute_units ? REDUCE_ITEMS / 256 + 1 : 8;
     PS_TIMED(K_GRAD_REDUCE, hipLaunchKernelGGL(grad_reduce_kernel, dim3(wb.n, reduce_y), dim3(256), 0, s, wb, fc2_split(wb.n),
                                                 conv1_part_slots(wb.B), conv2_part_slots(wb.B)));
     return hipGetLastError();
