@@ -106,9 +106,12 @@ int conv2_part_slots(int batch);  // conv2 partial slots per worker (one per blo
 int conv1_part_slots(int batch);  // conv1 partial slots per worker (one per image, written by conv2's input-gradient kernel)
 
 // For the kernels in which a wavefront works on whole images, or several share one in small launches.
-int images_per_wavefront(const WorkerBuffers& wb, int most);
-int wavefronts_per_image(const WorkerBuffers& wb, int most);
-int blocks_per_worker(int batch, int images_per_wavefront, int wavefronts_per_image, int wavefronts);
+struct ImageSplit {
+    int images;      // per wavefront: 1 if several share an image
+    int wavefronts;  // per image
+    int blocks;      // per worker
+};
+ImageSplit split_images(const WorkerBuffers& wb, int most_images, int most_wavefronts, int wavefronts_per_block);
 
 void launch_conv1_fwd(const WorkerBuffers& wb, hipStream_t s);
 void launch_fc1_fwd(const WorkerBuffers& wb, hipStream_t s);

@@ -103,11 +103,10 @@ __global__ __launch_bounds__(CONV1_NT) void conv1_fwd_kernel(WorkerBuffers wb, i
 template <int N_META>
 static void start_conv1_fwd(const WorkerBuffers& wb, hipStream_t s)
 {
-    const int ipw = images_per_wavefront(wb, CONV1_IPW), parts = wavefronts_per_image(wb, 4);
-    const int bpw = blocks_per_worker(wb.B, ipw, parts, CONV1_NW);
+    const ImageSplit sp = split_images(wb, CONV1_IPW, 4, CONV1_NW);
     MetaArgs<N_META> args;
     if (N_META > 0) std::copy(wb.meta_host, wb.meta_host + wb.n, args.m);
-    hipLaunchKernelGGL(conv1_fwd_kernel<N_META>, dim3(wb.n * bpw), dim3(CONV1_NT), 0, s, wb, bpw, ipw, parts, args);
+    hipLaunchKernelGGL(conv1_fwd_kernel<N_META>, dim3(wb.n * sp.blocks), dim3(CONV1_NT), 0, s, wb, sp.blocks, sp.images, sp.wavefronts, args);
 }
 
 void launch_conv1_fwd(const WorkerBuffers& wb, hipStream_t s)

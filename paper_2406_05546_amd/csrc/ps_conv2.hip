@@ -723,9 +723,8 @@ __global__ __launch_bounds__(256, 2) void backward_kernel(WorkerBuffers wb, BwdS
 
 void launch_conv2_fwd(const WorkerBuffers& wb, hipStream_t s)
 {
-    const int ipw = images_per_wavefront(wb, FWD_IPW), parts = wavefronts_per_image(wb, 4);
-    const int bpw = blocks_per_worker(wb.B, ipw, parts, FWD_NW);
-    hipLaunchKernelGGL(conv2_fwd_kernel, dim3(wb.n * bpw), dim3(FWD_NT), 0, s, wb, bpw, ipw, parts);
+    const ImageSplit sp = split_images(wb, FWD_IPW, 4, FWD_NW);
+    hipLaunchKernelGGL(conv2_fwd_kernel, dim3(wb.n * sp.blocks), dim3(FWD_NT), 0, s, wb, sp.blocks, sp.images, sp.wavefronts);
 }
 
 int conv1_part_slots(int batch) { return batch; }
@@ -741,9 +740,10 @@ int conv2_part_slots(int batch)
 void launch_backward(const WorkerBuffers& wb, hipStream_t s)
 {
     BwdShape sh;
-    sh.dx_ipw = images_per_wavefront(wb, DX_IPW);
-    sh.dx_parts = wavefronts_per_image(wb, 2);
-    sh.dx_blocks_per_worker = blocks_per_worker(wb.B, sh.dx_ipw, sh.dx_parts, DX_NW);
+    const ImageSplit dx = split_images(wb, DX_IPW, 2, DX_NW);
+    sh.dx_ipw = dx.images;
+    sh.dx_parts = dx.wavefronts;
+    sh.dx_blocks_per_worker = dx.blocks;
     sh.dx_blocks = wb.n * sh.dx_blocks_per_worker;
     sh.dw_slots = conv2_part_slots(wb.B);
     sh.dw_ipw = conv2_dw_ipw(wb.B);

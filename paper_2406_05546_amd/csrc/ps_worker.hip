@@ -92,28 +92,18 @@ __global__ __launch_bounds__(256) void keep_mask_kernel(uint8_t* keep, int B, ui
 
 }  // namespace
 
-// As many (up to `most`) as leave two wavefronts for every SIMD: what a wavefront does once per launch, reading
-// and splitting a filter bank above all, takes up to a quarter of an image's time.
-int images_per_wavefront(const WorkerBuffers& wb, int most)
+// Wavefronts take as many images (up to `most_images`) as leave two wavefronts for every SIMD: what one does once per
+// launch, reading and splitting a filter bank above all, takes up to a quarter of an image's time.  Where there is not
+// one for every SIMD, as many (1, 2 or 4, up to `most_wavefronts`) share an image as still find SIMDs to run on, one
+// each; the kernels count on those having that image alone.
+ImageSplit split_images(const WorkerBuffers& wb, int most_images, int most_wavefronts, int wavefronts_per_block)
 {
-    int ipw = most;
-    while (ipw > 1 && wb.n * ((wb.B + ipw - 1) / ipw) < 2 * 4 * wb.compute_units) ipw /= 2;
-    return ipw;
-}
-
-// How many wavefronts (1, 2 or 4, up to `most`) can share an image and still find SIMDs to run on, one each.
-int wavefronts_per_image(const WorkerBuffers& wb, int most)
-{
-    int parts = 1;
-    while (parts < most && 2 * parts * wb.n * wb.B <= 4 * wb.compute_units) parts *= 2;
-    return parts;
-}
-
-// Blocks of `wavefronts` for one worker; with several wavefronts per image every one takes (a part of) one image.
-int blocks_per_worker(int batch, int images_per_wavefront, int wavefronts_per_image, int wavefronts)
-{
-    const int units = (batch + images_per_wavefront - 1) / images_per_wavefront * wavefronts_per_image;
-    return (units + wavefronts - 1) / wavefronts;
+    ImageSplit sp{most_images, 1, 0};
+    while (sp.wavefronts < most_wavefronts && 2 * sp.wavefronts * wb.n * wb.B <= 4 * wb.compute_units) sp.wavefronts *= 2;
+    while (sp.images > 1 && (sp.wavefronts > 1 || wb.n * ((wb.B + sp.images - 1) / sp.images) < 2 * 4 * wb.compute_units)) sp.images /= 2;
+    const int units = (wb.B + sp.images - 1) / sp.images * sp.wavefronts;
+    sp.blocks = (units + wavefronts_per_block - 1) / wavefronts_per_block;
+    return sp;
 }
 
 #define PS_TIMED(id, ...)      \
