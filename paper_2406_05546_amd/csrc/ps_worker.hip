@@ -15,14 +15,15 @@ namespace {
 // per image (of conv2's input-gradient kernel), conv2 tensors one per block of its weight-gradient kernel, fc2
 // tensors, fc1 bias and the loss one per block of the fc2 kernel.  Nothing but memory latency at few workers:
 // the up to 16 slots of a conv2 or fc2 value are loaded together by one thread; the 160 conv1 values have a slot
-// per image and get C1_LANES threads each (thread j adds slots j, j + 8, ... in order, 16 loads in flight, and
-// the 8 sums are added in order), 32 values to each of the first 5 blocks of a worker.  How many blocks a worker
+// per image and get C1_LANES threads each (thread j adds slots j, j + 8, ..., 16 at a time, and the 8 sums
+// are added in order), 32 values to each of the first 5 blocks of a worker.  How many blocks a worker
 // gets does not change any sum.
 constexpr int REDUCE_SLOTS = 16, C1_LANES = 8, C1_VALUES = 32, C1_BLOCKS = OFF_W2 / C1_VALUES;
 static_assert(C1_VALUES * C1_BLOCKS == OFF_W2 && C1_VALUES * C1_LANES == 256, "conv1 values over the first blocks");
 constexpr int REDUCE_ITEMS = CONV2_PART + FC2_PART_LOSS + 1;  // conv2 values, then fc2's
 
-// p[0] + p[step] + ... in order, `count` values
+// p[0] + p[step] + ... in order, `count` values; of each REDUCE_SLOTS the sum first, which keeps the sums over a slot
+// per image as close to 64 bits as the others (batches of 4096: conv1's gradient off by 1.2e-7 in one chain, 0.56e-7 so)
 __device__ __forceinline__ float ordered_sum(const float* __restrict__ p, size_t step, int count)
 {
     float sum = 0.f;
@@ -30,9 +31,11 @@ __device__ __forceinline__ float ordered_sum(const float* __restrict__ p, size_t
         float v[REDUCE_SLOTS];
 #pragma unroll
         for (int c = 0; c < REDUCE_SLOTS; ++c) v[c] = p[(size_t)min(c0 + c, count - 1) * step];
+        float part = v[0];
 #pragma unroll
-        for (int c = 0; c < REDUCE_SLOTS; ++c)
-            if (c0 + c < count) sum += v[c];
+        for (int c = 1; c < REDUCE_SLOTS; ++c)
+            if (c0 + c < count) part += v[c];
+        sum += part;
     }
     return sum;
 }

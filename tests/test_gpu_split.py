@@ -59,6 +59,37 @@ def test_conv2_weight_gradient_error(ps, n, B, share, fp32):
         ps.ps_destroy(ctx)
 
 
+# the error of sums that are kept in registers over eight images
+@pytest.mark.parametrize("n,B,registers", [(8, 200, 7.92e-8), (8, 1024, 6.45e-8), (4, 4096, 7.16e-8)])
+def test_conv1_weight_gradient_error(ps, n, B, registers):
+    """conv1 has a partial sum per image; adding up those of a large batch must not lose what the sums had."""
+    import torch
+    theta = synth.he_uniform_theta(5)
+    W2 = torch.from_numpy(theta[OFF_W2:OFF_B2]).cuda().double().view(32, 144)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(7)
+    x = torch.rand(n, B, ps.IMAGE_PIXELS, device="cuda", generator=g)
+    y = torch.randint(0, 10, (n, B), device="cuda", generator=g, dtype=torch.int32)
+    ctx = ps.ps_init(ps.make_config(n, B, 1, n, DROP_SEED, P_DROP))
+    try:
+        ps.ps_set_weights(ctx, theta)
+        q = ps.worker_grads_batched(ctx, range(n), [0] * n, [synth.minibatch_id(w, 0) for w in range(n)], x, y)
+        ps.ps_sync(ctx)
+        want, err = [], []
+        for i in range(n):
+            d2, _ = _d2(ps, ctx, i)
+            code = torch.from_numpy(ps.ps_debug_last_batch(ctx, i)["pool1"]).cuda().long().view(B, 16, 196)
+            dp1 = torch.nn.functional.fold(torch.matmul(W2.t(), d2), (14, 14), 3, padding=1).view(B, 16, 196) * ((code & 4) > 0)
+            win = torch.zeros(B, 16, 196, 4, device="cuda", dtype=torch.float64).scatter_(-1, (code & 3).unsqueeze(-1), dp1.unsqueeze(-1))
+            d1 = win.view(B, 16, 14, 14, 2, 2).permute(0, 1, 2, 4, 3, 5).reshape(B, 16, 784)
+            pix = torch.nn.functional.unfold(x[i].double().view(B, 1, 28, 28), 3, padding=1)
+            want.append(torch.matmul(d1, pix.transpose(1, 2)).sum(0).flatten())
+            err.append(torch.from_numpy(ps.ps_get_grad(ctx, q[i])[:144]).cuda().double() - want[-1])
+        assert float(torch.cat(err).norm() / torch.cat(want).norm()) <= registers
+    finally:
+        ps.ps_destroy(ctx)
+
+
 @pytest.mark.parametrize("n,B", [(2, 32), (4, 130), (40, 64)])
 @pytest.mark.parametrize("what", ["nan", "infinite conv2 weight", "infinite fc1 weight"])
 def test_a_diverged_network_is_not_slow(ps, n, B, what):
