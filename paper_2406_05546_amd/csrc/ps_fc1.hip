@@ -53,8 +53,8 @@ struct Fc1DxEpi {
 // tile, and is cut up: into 64 x 64 tiles (32 x 32, with wavefronts that only multiply, where those find a compute unit
 // each), or, in the forward and the input gradient of batches up to 64, into
 // 32 x 32 tiles with a wavefront for every chunk of K (1568 = 7 x 14 stages, 512 = 4 x 8).  Whether a batch
-// is summed in chunks depends on its size alone, so that a worker's gradient has the same bits whatever else
-// is in the launch; beyond 64 the chunks' totals would not fit the registers of 64 x 64 wavefront tiles.
+// is summed in chunks depends on its size alone, so that these sums have the same bits whatever else is in the
+// launch; beyond 64 the chunks' totals would not fit the registers of 64 x 64 wavefront tiles.
 constexpr int FWD_CHUNKS = 7, FWD_CHUNK = 14, DX_CHUNKS = 4, DX_CHUNK = 8, CHUNKED_BATCH = 64;
 static_assert(FWD_CHUNKS * FWD_CHUNK * GEMM_K == P2_SIZE && DX_CHUNKS * DX_CHUNK * GEMM_K == FC1, "whole chunks");
 

@@ -296,6 +296,8 @@ void launch_fc2_eval(const WorkerBuffers& wb, float* loss_i, int32_t* correct, h
     hipLaunchKernelGGL(fc2_eval_kernel, dim3((wb.n * wb.B + 3) / 4), dim3(256), 0, s, wb, loss_i, correct);
 }
 
+// How a worker's images are shared out, and so in which order d W4, d b4, d b3 and the loss are added up, depends on
+// how many workers there are: the one place where that is so.
 int fc2_split(int n) { return std::min(16, std::max(1, (512 + n - 1) / n)); }
 
 void launch_fc2(const WorkerBuffers& wb, hipStream_t s)

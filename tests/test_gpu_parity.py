@@ -915,6 +915,37 @@ def test_gradient_bits_do_not_depend_on_the_launch(ps, n, B):
         ps.ps_destroy(ctx)
 
 
+@pytest.mark.parametrize("n,B", [(4, 256), (6, 100), (70, 250), (256, 256)])
+def test_gradient_bits_where_fc2_is_cut_differently(ps, n, B):
+    """fc2's blocks take ceil(512 / n) shares of a worker's images, up to 16, sixteen at a time.  Alone and among `n`
+    workers, conv1, conv2 and fc1's weights have the same gradient bytes; fc2's and fc1's bias only if the shares are the
+    same, and are otherwise the same sums in another order."""
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(9)
+    x = torch.rand(n, B, ps.IMAGE_PIXELS, device="cuda", generator=g)
+    y = torch.randint(0, 10, (n, B), device="cuda", generator=g, dtype=torch.int32)
+    mbs = [synth.minibatch_id(w, 7) for w in range(n)]
+    fc1_bias = synth.NetDims().segments()[5][1]
+    shares = [min((B + 15) // 16, 16, (512 + k - 1) // k) for k in (1, n)]
+    ctx = ps.ps_init(ps.make_config(n, B, 1, n + 1, DROP_SEED, P_DROP))
+    try:
+        ps.ps_set_weights(ctx, synth.he_uniform_theta(21))
+        entries = ps.worker_grads_batched(ctx, range(n), [0] * n, mbs, x, y)
+        for i in (0, n - 1):
+            (q,) = ps.worker_grads_batched(ctx, [i], [0], [mbs[i]], x[i:i + 1], y[i:i + 1])
+            ps.ps_sync(ctx)
+            among, alone = ps.ps_get_grad(ctx, entries[i]), ps.ps_get_grad(ctx, q)
+            assert np.array_equal(among[:fc1_bias], alone[:fc1_bias])
+            if shares[0] == shares[1]:
+                assert np.array_equal(among, alone)
+            else:   # sums of B products, each off by up to 2.5 u sqrt(B) of its tensor's largest
+                assert np.abs(among - alone)[fc1_bias:].max() <= 5 * 2.0 ** -24 * B ** 0.5 * np.abs(alone[fc1_bias:]).max()
+            ps.ps_apply_async(ctx, q, 0.0)
+    finally:
+        ps.ps_destroy(ctx)
+
+
 @pytest.mark.parametrize("extra", [1, 3])
 def test_evaluations_too_large_to_be_collected_on_the_gpu(ps, extra):
     """The results of up to 65,536 images are collected by a kernel, those of more are copied out: the same classes and

@@ -268,3 +268,38 @@ def test_tiny_operands_keep_their_bits(ps, n, B, what):
     assert 0 < max(np.abs(want).max() for _, want, _ in broken.values())
     _compare(broken)
     _compare(good)
+
+
+@pytest.mark.parametrize("n,B", [(20, 40), (80, 40), (70, 130), (4, 256)])
+@pytest.mark.parametrize("what", ["huge", "tiny", "some tiny"])
+def test_sums_formed_again_do_not_depend_on_the_launch(ps, n, B, what):
+    """Which sums are lost, and what they are then, is decided by tiles that all forms of a launch share: conv1's, conv2's
+    and fc1's weight gradients of a worker have the same bytes alone and among n."""
+    import torch
+    theta = synth.he_uniform_theta(5)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(19)
+    x = torch.rand(n, B, ps.IMAGE_PIXELS, device="cuda", generator=g)
+    y = torch.full((n, B), 3, device="cuda", dtype=torch.int32)
+    if what == "huge":
+        theta[144 + 13] = HUGE
+        theta[160:4768].reshape(32, 16, 9)[:, 13] *= 1e-5
+        theta[4800:807616] *= 1e-3
+    else:
+        theta[808128:813248] *= 0.01
+        theta[813248 + 3] = 80.0
+        if what == "some tiny":
+            y[:, ::3] = 5
+    ctx = ps.ps_init(ps.make_config(n, B, 1, n + 1, DROP_SEED, P_DROP))
+    try:
+        ps.ps_set_weights(ctx, theta)
+        mbs = [synth.minibatch_id(w, 7) for w in range(n)]
+        entries = ps.worker_grads_batched(ctx, range(n), [0] * n, mbs, x, y)
+        for i in (0, n - 1):
+            (q,) = ps.worker_grads_batched(ctx, [i], [0], [mbs[i]], x[i:i + 1], y[i:i + 1])
+            ps.ps_sync(ctx)
+            among, alone = ps.ps_get_grad(ctx, entries[i]), ps.ps_get_grad(ctx, q)
+            assert among[:OFF_B3].any() and np.array_equal(among[:OFF_B3].view(np.int32), alone[:OFF_B3].view(np.int32))
+            ps.ps_apply_async(ctx, q, 0.0)
+    finally:
+        ps.ps_destroy(ctx)
