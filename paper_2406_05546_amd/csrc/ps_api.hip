@@ -52,7 +52,7 @@ struct Carve {
 };
 
 struct Layout {
-    uint64_t theta, ring, queue, ada_g2, ada_dx2, meta, idx, slotq, st_state, st_stamp, st_entry, st_ringver, st_log, st_range, st_idx, st_wid, p1, am1, p2, am2, am2t, ht, z, pred, d3, dp2g, part, part1, fpart, normpart, scale, eval_loss, eval_ok, keep, total;
+    uint64_t theta, ring, queue, ada_g2, ada_dx2, meta, idx, slotq, st_state, st_stamp, st_entry, st_ringver, st_log, st_range, st_idx, st_wid, p1, am1, p2, am2, am2t, ht, z, pred, d3, dp2g, gscale, part, part1, fpart, normpart, scale, eval_loss, eval_ok, keep, total;
 };
 
 bool config_ok(const ps_config* c)
@@ -92,6 +92,7 @@ Layout make_layout(const ps_config& c)
     l.pred = k.take(n * 4);
     l.d3 = k.take(n * FC1 * 4);
     l.dp2g = k.take(n * P2_SIZE * 4 + 16);  // conv2's weight gradient reads rows of 7 in pieces of 4
+    l.gscale = k.take(n * 4);
     l.part = k.take((uint64_t)c.max_workers * conv2_part_slots(c.batch) * CONV2_PART * 4);
     l.part1 = k.take((uint64_t)c.max_workers * conv1_part_slots(c.batch) * OFF_W2 * 4);
     l.fpart = k.take((uint64_t)(512 + c.max_workers) * FC2_PART * 4);  // >= n * fc2_split(n) slots
@@ -250,6 +251,7 @@ WorkerBuffers buffers(const ps_ctx* c, int n, const float* x, const int32_t* y, 
     wb.pred = c->at<int32_t>(c->lay.pred);
     wb.d3 = c->at<float>(c->lay.d3);
     wb.dp2g = c->at<float>(c->lay.dp2g);
+    wb.grad_scale = c->at<float>(c->lay.gscale);
     wb.part = c->at<float>(c->lay.part);
     wb.part1 = c->at<float>(c->lay.part1);
     wb.fpart = c->at<float>(c->lay.fpart);

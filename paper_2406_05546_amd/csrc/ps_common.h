@@ -64,6 +64,9 @@ struct WorkerBuffers {
     int32_t* pred;       // [n*B]
     float* d3;           // [n*B][512]      d loss / d fc1 pre-activation
     float* dp2g;         // [n*B][1568]     d loss / d pool2 (its readers apply the ReLU gate of the window bytes)
+    float* grad_scale;   // [n*B]           2^64 for an image whose d loss / d logits are all below 2^-80 and not all 0, else 1: what
+                         //                 conv2's gradient kernels multiply its d loss / d pool2 by, and their sums by the
+                         //                 inverse.  Both are exact; the split (ps_split.h) would lose bits of such values.
     float* part;         // [n][conv2_part_slots(B)][CONV2_PART] partial sums of the conv2 weight gradient
     float* part1;        // [n][conv1_part_slots(B)][160] partial sums of the conv1 weight gradient
     float* fpart;        // [n][split][FC2_PART] partial sums of the fc2 kernel's blocks

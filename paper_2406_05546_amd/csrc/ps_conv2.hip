@@ -30,6 +30,9 @@ namespace {
 // sustains 1.8 PFLOP/s, this kernel 1.3); two workers of 32 images: 41 -> 13 us.
 constexpr int FWD_NW = 4, FWD_NT = 64 * FWD_NW, FWD_IPW = 8;  // wavefronts per block, most images per wavefront
 
+// Scale of the gradients of image g, as a scalar.
+__device__ __forceinline__ float image_scale(const WorkerBuffers& wb, size_t g) { return __int_as_float(uniform(__float_as_int(wb.grad_scale[g]))); }
+
 struct FwdImage {  // one wavefront's pooled image
     float p2[P2_SIZE];
     uint8_t am2[AM2_SIZE];
@@ -219,8 +222,9 @@ struct DxImage {  // one wavefront's image
     float xs[DX_XS];
 };
 
-// The same as conv2_fwd_again for d pool1 row Y of image g: lane (q, l16) holds channel l16 at X = 4q .. 4q + 3.
-__device__ __forceinline__ void conv2_dx_again(const WorkerBuffers& wb, size_t g, const float* __restrict__ W2, int Y, int lane, floatx4& sums)
+// The same as conv2_fwd_again for d pool1 row Y of image g, times `scale`: lane (q, l16) holds channel l16 at X = 4q
+// .. 4q + 3.
+__device__ __forceinline__ void conv2_dx_again(const WorkerBuffers& wb, size_t g, float scale, const float* __restrict__ W2, int Y, int lane, floatx4& sums)
 {
     const uint32_t which = lost_sums<4, 4>(sums);
     lane = rarely(lane);
@@ -236,7 +240,7 @@ __device__ __forceinline__ void conv2_dx_again(const WorkerBuffers& wb, size_t g
 #pragma unroll 2
         for (int k = 0; k < C2 / 4; ++k) {
             const int o = 4 * k + q;
-            const float d = dp[o * P2_POS + p];
+            const float d = scale * dp[o * P2_POS + p];
             const bool winner = inside & (codes[p * C2 + o] >> bit & 1);
             again = __builtin_amdgcn_mfma_f32_16x16x4f32(winner ? d : 0.f, W2[(o * C1 + l16) * 9 + tap], again, 0, 0, 0);
         }
@@ -251,13 +255,13 @@ struct Conv1Sums {
     float v[10];
 };
 
-// conv1's sums of image g, channel c: the first half's plus the second half's.
-__device__ __forceinline__ void store_conv1_sums(const WorkerBuffers& wb, size_t g, int c, const float* first, const float (&second)[10])
+// conv1's sums of image g, channel c: the first half's plus the second half's, without the image's scale.
+__device__ __forceinline__ void store_conv1_sums(const WorkerBuffers& wb, size_t g, int c, const float* first, const float (&second)[10], float unscale)
 {
     float* part = wb.part1 + g * OFF_W2;
 #pragma unroll
-    for (int i = 0; i < 9; ++i) part[OFF_W1 + c * 9 + i] = first[c * 10 + i] + second[i];
-    part[OFF_B1 + c] = first[c * 10 + 9] + second[9];
+    for (int i = 0; i < 9; ++i) part[OFF_W1 + c * 9 + i] = (first[c * 10 + i] + second[i]) * unscale;
+    part[OFF_B1 + c] = (first[c * 10 + 9] + second[9]) * unscale;
 }
 
 // How conv2's gradients are cut up: blocks of the input gradient, then blocks of the weight gradient.
@@ -298,6 +302,7 @@ __device__ __forceinline__ void conv2_dx_block(const WorkerBuffers& wb, const Bw
     const int o_in = lane >> 1, win_in = 25 * (lane & 1), last_in = o_in * P2_POS + (lane & 1 ? P2_POS - 1 : 24);
 
     Conv1Sums shared_sum{};
+    float unscale = 1.f;
     for (int s = s_begin; s < s_end; ++s) {
         const size_t g = (size_t)w * B + s;
         // the image's pooled gradients, window bytes (98 uint4), pool1 window bytes and pixels (196 of either;
@@ -305,6 +310,7 @@ __device__ __forceinline__ void conv2_dx_block(const WorkerBuffers& wb, const Bw
         float pv[26];
         floatx4 xv[4];
         uintx4 pc[2], bv[4];
+        const float scale = image_scale(wb, g);
         const float* dp = wb.dp2g + g * P2_SIZE;
 #pragma unroll
         for (int k = 0; k < 6; ++k) __builtin_memcpy(&pv[4 * k], dp + o_in * P2_POS + win_in + 4 * k, 16);
@@ -317,6 +323,11 @@ __device__ __forceinline__ void conv2_dx_block(const WorkerBuffers& wb, const Bw
             const int i = min(lane + 64 * k, IMG_PIX / 4 - 1);
             xv[k] = reinterpret_cast<const floatx4*>(wb.x + g * IMG_PIX)[i];
             bv[k] = reinterpret_cast<const uintx4*>(wb.am1 + g * P1_SIZE)[i];
+        }
+        unscale = scale == 1.f ? 1.f : 0x1p-64f;
+        if (__builtin_expect(scale != 1.f, 0)) {  // an image whose gradients are tiny: see grad_scale
+#pragma unroll
+            for (int k = 0; k < 26; ++k) pv[k] *= scale;
         }
         wave_lds_fence();  // the last image has been read
         const int at = win_in * DX_WIN + dx_place(o_in);
@@ -350,7 +361,7 @@ __device__ __forceinline__ void conv2_dx_block(const WorkerBuffers& wb, const Bw
 
         // conv1's gradient from d pool1 row Y: lane (q, l16) holds channel l16 at X = 4q .. 4q + 3
         auto finish_row = [&](int Y, floatx4 acc) {
-            if (any_lost<4, 4>(acc)) conv2_dx_again(wb, g, W2, Y, lane, acc);
+            if (any_lost<4, 4>(acc)) conv2_dx_again(wb, g, scale, W2, Y, lane, acc);
             const uint8_t* bytes = im.am1 + (P1_W * Y + 4 * q) * C1 + l16;
             const float* row = im.xs + 2 * Y * DX_XW + 8 * q;
 #pragma unroll
@@ -432,7 +443,7 @@ __device__ __forceinline__ void conv2_dx_block(const WorkerBuffers& wb, const Bw
         fold();
         wave_lds_fence();
         if (sh.dx_parts == 1) {
-            if (q == 0) store_conv1_sums(wb, g, l16, half_sum, g1);
+            if (q == 0) store_conv1_sums(wb, g, l16, half_sum, g1, unscale);
         } else {
             if (half == 0 && q == 0) {
 #pragma unroll
@@ -445,7 +456,7 @@ __device__ __forceinline__ void conv2_dx_block(const WorkerBuffers& wb, const Bw
     if (sh.dx_parts == 2) {  // one image (or none) per wavefront
         __syncthreads();
         if (half == 1 && s_begin < s_end && q == 0)
-            store_conv1_sums(wb, (size_t)w * B + s_begin, l16, reinterpret_cast<const float*>(images[wave - 1].am1), shared_sum.v);
+            store_conv1_sums(wb, (size_t)w * B + s_begin, l16, reinterpret_cast<const float*>(images[wave - 1].am1), shared_sum.v, unscale);
     }
 }
 
@@ -496,8 +507,8 @@ __device__ __forceinline__ ShiftedRow shifted_row(const float (&v)[10])
 }
 
 // The same as conv2_fwd_again for the sums over images [s_begin, s_end) of worker w: output channels 16 mt + 4q + i,
-// input channel l16, tap 0..8, or 9 for the bias.  The sums are times `sign`.
-__device__ __forceinline__ void conv2_dw_again(const WorkerBuffers& wb, int w, int s_begin, int s_end, int mt, int tap, float sign, int lane, floatx4& sums)
+// input channel l16, tap 0..8, or 9 for the bias.  The sums are times `scale`.
+__device__ __forceinline__ void conv2_dw_again(const WorkerBuffers& wb, int w, int s_begin, int s_end, int mt, int tap, float scale, int lane, floatx4& sums)
 {
     const uint32_t which = lost_sums<4, 4>(sums);
     lane = rarely(lane);
@@ -510,7 +521,7 @@ __device__ __forceinline__ void conv2_dw_again(const WorkerBuffers& wb, int w, i
         for (int k = 0; k < P1_POS / 4; ++k) {
             const int pos = 4 * k + q, y = pos / P1_W, x = pos % P1_W, r = o * P2_W + (y >> 1);
             const bool winner = wb.am2[g * AM2_SIZE + r * AM2_PITCH + (x >> 1)] >> (2 * (y & 1) + (x & 1)) & 1;
-            const float d = sign * wb.dp2g[g * P2_SIZE + r * P2_W + (x >> 1)];
+            const float d = scale * wb.dp2g[g * P2_SIZE + r * P2_W + (x >> 1)];
             const int yy = y + tap / 3 - 1, xx = x + tap % 3 - 1;
             const bool inside = yy >= 0 && yy < P1_W && xx >= 0 && xx < P1_W;
             const float v = wb.p1[g * P1_SIZE + (inside ? yy * P1_W + xx : 0) * C1 + l16];
@@ -531,7 +542,7 @@ typedef float DwSums[DW_NW][DW_REGS + 2][64];  // 75,776 B
 constexpr int DW_SHARES = 6;
 
 // Four pooled gradients and their window bytes -> the d2 operand of lane (q = 2e + xh, l16).
-__device__ __forceinline__ Split8 d2_operand(const floatx4& pooled, uint32_t bytes, int e, float sign)
+__device__ __forceinline__ Split8 d2_operand(const floatx4& pooled, uint32_t bytes, int e, float scale)
 {
     Split8 d2;
     const uint32_t bits = bytes >> (2 * e);  // bits 0, 1 of every byte: winner in this row, left or right
@@ -540,7 +551,7 @@ __device__ __forceinline__ Split8 d2_operand(const floatx4& pooled, uint32_t byt
         const uint32_t left = (uint32_t)__builtin_amdgcn_sbfe((int)bits, 8 * m, 1), right = (uint32_t)__builtin_amdgcn_sbfe((int)bits, 8 * m + 1, 1);
         const uint32_t mask = (left & 0xffffu) | (right & 0xffff0000u);
         uint32_t p0, p1, p2;
-        split2(sign * pooled[m], sign * pooled[m], p0, p1, p2);
+        split2(scale * pooled[m], scale * pooled[m], p0, p1, p2);
         d2.p[0][m] = p0 & mask;
         d2.p[1][m] = p1 & mask;
         d2.p[2][m] = p2 & mask;
@@ -559,7 +570,10 @@ __device__ __forceinline__ void conv2_dw_block(const WorkerBuffers& wb, const Bw
     const int w = block / slots, slot = block % slots;
     const int B = wb.B, s_begin = min(B, (slot * DW_NW + wave) * ipw), s_end = min(B, s_begin + ipw);
 
-    const float sign = wave & 1 ? -1.f : 1.f;
+    float unscale = s_begin < s_end ? 0x1p-64f : 1.f;  // of a wavefront's sums, if all its images have tiny gradients
+    for (int s = s_begin; s < s_end; ++s)
+        if (image_scale(wb, (size_t)w * B + s) == 1.f) unscale = 1.f;
+    const float scale = (wave & 1 ? -1.f : 1.f) * (unscale == 1.f ? 1.f : 0x1p64f);
     floatx4 acc[MTS][3 * DYS], acc_b[MTS];
 #pragma unroll
     for (int mt = 0; mt < MTS; ++mt) {
@@ -605,7 +619,7 @@ __device__ __forceinline__ void conv2_dw_block(const WorkerBuffers& wb, const Bw
         for (int py = 0; py < P2_W; ++py) {
             Split8 d2[MTS];
 #pragma unroll
-            for (int mt = 0; mt < MTS; ++mt) d2[mt] = d2_operand(pooled[mt], bytes[mt], e, sign);
+            for (int mt = 0; mt < MTS; ++mt) d2[mt] = d2_operand(pooled[mt], bytes[mt], e, scale);
             const ShiftedRow mid = shifted_row(raw[0]);
             if (!SHARED && py == 0) {  // rows -1 (zero) and 0: lanes 32..63 take what lanes 0..31 of `mid` hold
 #pragma unroll
@@ -660,27 +674,33 @@ __device__ __forceinline__ void conv2_dw_block(const WorkerBuffers& wb, const Bw
     bool lost = false;
 #pragma unroll
     for (int mt = 0; mt < MTS; ++mt) {
-        if (any_lost<4, 4>(acc_b[mt])) conv2_dw_again(wb, w, s_begin, s_end, mt0 + mt, 9, sign, lane, acc_b[mt]);
+        if (any_lost<4, 4>(acc_b[mt])) conv2_dw_again(wb, w, s_begin, s_end, mt0 + mt, 9, scale, lane, acc_b[mt]);
 #pragma unroll
         for (int j = 0; j < 3 * DYS; ++j) {
-            lost |= !split_holds(largest<4>(acc[mt][j]));
+            lost |= any_lost<4, 4>(acc[mt][j]);
 #pragma unroll
             for (int i = 0; i < 4; ++i) red[wave][((mt0 + mt) * 9 + 3 * dy0 + j) * 4 + i][lane] = acc[mt][j][i];
         }
         if (l16 == 0) *reinterpret_cast<floatx4*>(&red[wave][DW_REGS + mt0 + mt][4 * q]) = acc_b[mt];
     }
     const int r_begin = (mt0 * 9 + 3 * dy0) * 4;  // of this block's DYS * MTS * 12 registers
-    if (__builtin_expect(__any(lost), 0)) {
+    if (lost) {
 #pragma unroll 1
         for (int r = r_begin; r < r_begin + 12 * DYS * MTS; r += 4) {
             floatx4 sums;
 #pragma unroll
             for (int i = 0; i < 4; ++i) sums[i] = red[wave][r + i][lane];
             if (!any_lost<4, 4>(sums)) continue;
-            conv2_dw_again(wb, w, s_begin, s_end, r / 36, r % 36 / 4, sign, lane, sums);
+            conv2_dw_again(wb, w, s_begin, s_end, r / 36, r % 36 / 4, scale, lane, sums);
 #pragma unroll
             for (int i = 0; i < 4; ++i) red[wave][r + i][lane] = sums[i];
         }
+    }
+    if (__builtin_expect(unscale != 1.f, 0)) {
+        wave_lds_fence();
+#pragma unroll 1
+        for (int r = r_begin; r < r_begin + 12 * DYS * MTS; ++r) red[wave][r][lane] *= unscale;
+        if (lane < 16 * MTS) red[wave][DW_REGS + mt0 + lane / 16][lane % 16] *= unscale;
     }
     __syncthreads();
     float* part = wb.part + ((size_t)w * slots + slot) * CONV2_PART;

@@ -143,6 +143,10 @@ __global__ __launch_bounds__(256, 2) void fc2_kernel(WorkerBuffers wb)
                 if (img_ok && cls_ok) wb.z[(g0 + 4 * q + i) * NCLS + l16] = zi;
                 if (img_ok && l16 == 0) wb.pred[g0 + 4 * q + i] = (int)first;
             }
+            if (wave == 1) {
+                const float most = row16_reduce(fabsf(d4[i]), [](float a, float b) { return fmaxf(a, b); });
+                if (img_ok && l16 == 0) wb.grad_scale[g0 + 4 * q + i] = most > 0.f && most < 0x1p-80f ? 0x1p64f : 1.f;
+            }
         }
 
         // d4 with images along the lane rows, for the A operand of d3 (wavefront-private: no barrier)
