@@ -73,8 +73,8 @@ COUNTER_ROWS = {"conv1_fwd_kernel": "conv1_fwd_kernel", "conv2_fwd_kernel": "con
                 "gemm_split<Fc1DxEpi>": "gemm_split_edge<ps::GemmCfg<false, true", "backward_kernel": "backward_kernel",
                 "grad_reduce_kernel": "grad_reduce_kernel",
                 "grad_sqnorm_kernel": "grad_sqnorm_kernel", "apply_adadelta_kernel": "apply_adadelta_kernel",
-                "elastic_average_kernel": "elastic_average_kernel", "apply_kernel<0>": "apply_kernel<0, false, false>",
-                "apply_kernel<1>": "apply_kernel<1, false, false>", "apply_kernel<1, clip>": "apply_kernel<1, true, false>"}
+                "elastic_average_kernel": "elastic_average_kernel", "apply_kernel<0>": "apply_kernel<0, false, true>",
+                "apply_kernel<1>": "apply_kernel<1, false, true>", "apply_kernel<1, clip>": "apply_kernel<1, true, true>"}
 STALE_COUNTERS = ()
 
 

@@ -26,8 +26,7 @@ namespace {
 // In launches that would leave SIMDs idle, `parts` wavefronts share an image, two or four pooled rows each.
 // 14 of 16 columns are real: 378 MFMAs per image, 12,100 cycles of a SIMD's matrix pipe.
 // 65,536 images: 1.005 -> 0.61 ms against the fp32 MFMA kernel that staged padded planes in LDS (matrix pipe busy
-// 68 % of the cycles at the 2.0 GHz the chip then runs at; a loop of nothing but these MFMAs on random operands
-// sustains 1.8 PFLOP/s, this kernel 1.3); two workers of 32 images: 41 -> 13 us.
+// 71 % of the cycles); two workers of 32 images: 41 -> 13 us.
 constexpr int FWD_NW = 4, FWD_NT = 64 * FWD_NW, FWD_IPW = 8;  // wavefronts per block, most images per wavefront
 
 // Scale of the gradients of image g, as a scalar.
@@ -205,8 +204,9 @@ __global__ __launch_bounds__(FWD_NT, 2) void conv2_fwd_kernel(WorkerBuffers wb, 
 // image: the sum over rows 0-6 plus the sum over rows 7-13.  In launches that would leave SIMDs idle, two
 // wavefronts of a block share an image, a half each, and add up the same two sums: nothing depends on how a
 // launch is cut up.
-// 65,536 images: 1.146 -> 0.65 ms against the fp32 MFMA kernel in two-wavefront blocks; two workers of 32
-// images: 87 -> 16 us (a wavefront walked eight images there, now one).  Matrix pipe busy 58 % of the cycles.
+// 65,536 images, this and the weight gradient: 2.09 -> 1.35 ms against the fp32 MFMA kernels (this one in two-wavefront
+// blocks), matrix pipe busy 57 % of the cycles; two workers of 32 images: 87 -> 16 us (a wavefront walked eight images
+// there, now one).
 constexpr int DX_NW = 4, DX_NT = 64 * DX_NW, DX_IPW = 8;  // wavefronts per block, most images per wavefront
 constexpr int DX_XW = 30, DX_XS = 30 * DX_XW + 16;        // padded input image (and what lanes 14, 15 read past it)
 // A d2 operand lane holds eight output channels 8q + DX_CHANNEL(i); the order is the one in which a word of
@@ -468,14 +468,14 @@ __device__ __forceinline__ void conv2_dx_block(const WorkerBuffers& wb, const Bw
 // four pooled values, each split once into both halves of a register and masked by the window's bits; a
 // pool1 operand is ten values of a row, split once: columns from -1 (dx = 0) and +1 (dx = 2) on are the same
 // pairs, those from 0 on the pairs shifted by one value.  d b2 is the product with a column of ones.
-// A block's four wavefronts take DW_IPW images each at most, meet in LDS once, and write one partial slot;
+// A block's four wavefronts take conv2_dw_ipw(B) images each at most, meet in LDS once, and write one partial slot;
 // the slots depend on the batch alone, so that the order of a worker's sums does not depend on the launch.
 // The 72 registers of a second accumulator (ps_split.h) do not fit next to the operands: the five small terms of
 // a k-step are summed from zero and added on the vector ALU.  What is then cut off towards minus infinity is
 // -3.5e-9 to -7.5e-9 of the mean result, and the odd wavefronts take d2 negated and are subtracted, so that it
 // cancels in a slot.  Against 64 bits d W2 is off by 0.63-0.80e-7 (1.09-1.51e-7 with fp32 MFMAs; 0.91-1.74e-7, with a
 // mean error of -2.9e-8 to -1.2e-7, with all six terms in one accumulator), 4 % of the launch's time.
-// 65,536 images, this and the input gradient: 2.09 -> 1.31 ms against the fp32 MFMA kernels; one worker of 256
+// 65,536 images, this and the input gradient: 2.09 -> 1.35 ms against the fp32 MFMA kernels; one worker of 256
 // images 162 -> 45 us, two of 32 24 -> 14 us (more, smaller shares).
 constexpr int DW_NW = 4, DW_NT = 64 * DW_NW, DW_MAX_SLOTS = 16;
 constexpr int DW_REGS = 2 * 9 * 4;  // sums per lane without the bias

@@ -38,7 +38,8 @@ typedef GemmCfg<false, false, 1, 1, 2, 2, 4, 32> Fc1DwFew;
 
 // 64 x 64 tiles next to conv2's gradients (8 workers of 64 images: 34 us together) against a launch of wide ones, which
 // alone leave the compute units idle that conv2's gradients then have to themselves (16 + 22 us), up to two wide
-// tiles for a compute unit (16 of 64: 57 against 24 + 27 us).
+// tiles for a compute unit (16 of 64: 57 against 24 + 27 us).  Tiles are counted, which depend on the workers alone:
+// the batch is the contraction.
 inline bool fc1_dw_few(const WorkerBuffers& wb) { return gemm_few_tiles(FC1 / 128 * (FEAT_WIDE / 128) * wb.n / 2, wb.compute_units); }
 
 inline GemmShape fc1_dw_few_shape(int n, int B) { return gemm_shape<Fc1DwFew>(FC1, P2_SIZE, B, FC1, P2_SIZE, n, 0, FC1, 0, P2_SIZE); }

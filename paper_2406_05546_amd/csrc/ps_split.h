@@ -1,7 +1,8 @@
 // fp32 contractions on the bf16 matrix cores.  An fp32 value is the sum of three bf16 values,
 //   x = x0 + x1 + x2 (+ at most 2^-27 |x|),  x0 = bf16(x), x1 = bf16(x - x0), x2 = bf16(x - x0 - x1),
 // every difference exact, and a product a*b is taken as the six terms a0b0 + a0b1 + a1b0 + a0b2 + a2b0 +
-// a1b1; what is left out is below 2^-25 |a*b|, of either sign.  Products of two bf16 values are exact in
+// a1b1; what is left out (a1b2, a2b1, a2b2 and the tails) is at most about 2^-24 |a*b|, of either sign.
+// Products of two bf16 values are exact in
 // fp32, and the matrix cores add 16 or 32 of them per instruction to an fp32 accumulator, but cut off (towards
 // minus infinity) what a small addend has below the large one's last bit.  So a0b0 and the five small terms
 // are summed in accumulators of their own and meet at the end: measured against 64 bits such sums are off by
