@@ -461,53 +461,123 @@ __device__ __forceinline__ void conv2_dx_block(const WorkerBuffers& wb, const Bw
 }
 
 // ---------------------------------------------------------------------------------------------
-// Weight gradient (16x16x32): d W2[o][c][dy][dx] = sum over the worker's images and positions of
-// d2[o][y][x] * pool1pad[c][y+dy][x+dx];  d b2[o] = sum d2[o].  GEMM rows are the output channels (two
-// tiles), columns the 16 input channels of one tap (nine tiles), one k-step the two map rows of a pooled
-// row, 16 columns each: lane (q = 2e + xh, l16) holds columns 8xh .. 8xh + 7 of row 2py + e.  A d2 operand is
-// four pooled values, each split once into both halves of a register and masked by the window's bits; a
-// pool1 operand is ten values of a row, split once: columns from -1 (dx = 0) and +1 (dx = 2) on are the same
-// pairs, those from 0 on the pairs shifted by one value.  d b2 is the product with a column of ones.
+// Weight gradient (sparse 16x16x64): d W2[o][c][dy][dx] = sum over the worker's images and positions of
+// d2[o][y][x] * pool1pad[c][y+dy][x+dx];  d b2[o] = sum d2[o].  GEMM rows are the output channels (two tiles), columns
+// the 16 input channels of one tap (nine tiles).  Of the four values of a pooling window only the winner's is not zero, so
+// d2 is the operand of v_smfmac_f32_16x16x64_bf16, which holds two of every four consecutive k and says which: k = 4 window +
+// (map row, column), a k-step is 16 windows, which is a pooled row (seven and a pad) of each of two images, or of the
+// upper and the lower half of one.  Half the matrix instructions, and half the splits, that a dense k-step of 32 takes.
+// d2: lane (q, l16) holds channel l16, windows 4 (q % 2) .. + 3 of half q / 2; each pooled value is split once into both
+// halves of a register, and the winner's column says which of them stays, its row where the two are taken.
+// pool1: lane (q, l16) holds channel l16, the windows 2q and 2q + 1 of both halves.  A register is two columns of a map row;
+// tap row dy meets rows 2py - 1 + dy and 2py + dy, of which one is even and one odd: they have the even and the
+// odd registers of an operand, so that the next tap row needs one new row, in the place of the one before last.  (The
+// winner's row then takes the places of the other row in every other tap row: a second index.)
+// Bound by issue: next to 108 smfmac of 16 cycles, which leave room for one vector instruction each, a k-step has about
+// 430 (a third of them splits, a quarter adding and clearing the small terms' sums).
 // A block's four wavefronts take conv2_dw_ipw(B) images each at most, meet in LDS once, and write one partial slot;
 // the slots depend on the batch alone, so that the order of a worker's sums does not depend on the launch.
 // The 72 registers of a second accumulator (ps_split.h) do not fit next to the operands: the five small terms of
 // a k-step are summed from zero and added on the vector ALU.  What is then cut off towards minus infinity is
-// -3.5e-9 to -7.5e-9 of the mean result, and the odd wavefronts take d2 negated and are subtracted, so that it
-// cancels in a slot.  Against 64 bits d W2 is off by 0.63-0.80e-7 (1.09-1.51e-7 with fp32 MFMAs; 0.91-1.74e-7, with a
-// mean error of -2.9e-8 to -1.2e-7, with all six terms in one accumulator), 4 % of the launch's time.
-// 65,536 images, this and the input gradient: 2.09 -> 1.35 ms against the fp32 MFMA kernels; one worker of 256
-// images 162 -> 45 us, two of 32 24 -> 14 us (more, smaller shares).
+// of one sign, and the odd wavefronts take d2 negated and are subtracted, so that it cancels in a slot.  Against 64 bits
+// d W2 is off by 0.62-0.79e-7 (1.09-1.51e-7 with fp32 MFMAs), d b2, summed on the vector ALU, by 0.5-0.9e-7.
+// 65,536 images, this and the input gradient: 1.35 ms with dense 16x16x32, 1.07 with the sparse form (this alone 0.73 ->
+// 0.43); 64 workers of 128 images 172 -> 139 us, 16 of 64 27.8 -> 23.6, one of 256 24.7 -> 22.7.
 constexpr int DW_NW = 4, DW_NT = 64 * DW_NW, DW_MAX_SLOTS = 16;
 constexpr int DW_REGS = 2 * 9 * 4;  // sums per lane without the bias
 
-// eight columns of a pool1 row from each of the three starting columns
-struct ShiftedRow {
-    uint32_t pair[3][5], odd[3][4];
-    __device__ __forceinline__ Split8 columns(int dx) const
+typedef uint32_t uintx8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x16 __attribute__((ext_vector_type(16)));
+
+// Two map rows of pool1 as the dense operands of three tap columns, part by part: register 4 image + 2 window + (odd row).
+struct DwRows {
+    uintx8 t[3][3];  // [tap column][part]
+    // columns 4q - 1 .. 4q + 4 of a row of one of the two images
+    template <int ODD>
+    __device__ __forceinline__ void put(int image, const float (&v)[6])
     {
-        Split8 s;
+        uint32_t p[3][3];
 #pragma unroll
-        for (int i = 0; i < 3; ++i)
+        for (int j = 0; j < 3; ++j) split2(v[2 * j], v[2 * j + 1], p[0][j], p[1][j], p[2][j]);
+        const int at = 4 * image + ODD;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) s.p[i][j] = dx == 0 ? pair[i][j] : dx == 1 ? odd[i][j] : pair[i][j + 1];
-        return s;
+        for (int i = 0; i < 3; ++i) {
+            t[0][i][at] = p[i][0];
+            t[0][i][at + 2] = p[i][1];
+            t[1][i][at] = __builtin_amdgcn_alignbit(p[i][1], p[i][0], 16);
+            t[1][i][at + 2] = __builtin_amdgcn_alignbit(p[i][2], p[i][1], 16);
+            t[2][i][at] = p[i][1];
+            t[2][i][at + 2] = p[i][2];
+        }
+    }
+    template <int ODD>
+    __device__ __forceinline__ void clear()
+    {
+#pragma unroll
+        for (int dx = 0; dx < 3; ++dx)
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+#pragma unroll
+                for (int j = 0; j < 8; j += 2) t[dx][i][j + ODD] = 0;
     }
 };
 
-__device__ __forceinline__ ShiftedRow shifted_row(const float (&v)[10])
+// The parts of one value, each in both halves.
+__device__ __forceinline__ void split_twice(float x, uint32_t (&p)[3])
 {
-    ShiftedRow r;
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    typedef float floatx2 __attribute__((ext_vector_type(2)));
 #pragma unroll
-    for (int j = 0; j < 5; ++j) split2(v[2 * j], v[2 * j + 1], r.pair[0][j], r.pair[1][j], r.pair[2][j]);
+    for (int i = 0; i < 3; ++i) {
+        p[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(floatx2{x, x}, bf16x2));
+        x -= __uint_as_float(p[i] << 16);
+    }
+}
+
+// Zeros, made where they are wanted: the compiler would make them all at the top of the loop.
+__device__ __forceinline__ floatx4 cleared()
+{
+    floatx4 zero = {0.f, 0.f, 0.f, 0.f};
+    asm volatile("" : "+s"(zero));
+    return zero;
+}
+
+// Four pooled gradients of an output channel as the sparse operand.
+struct DwGrads {
+    Split8 value;   // window by window: in the low half if the winner is in the left column, in the high half if in the right one
+    int place[2];   // four bits a window: where in the window's four values they are taken; [1]: with the two map rows exchanged
+    float sum;      // of the values, for the bias
+};
+
+__device__ __forceinline__ DwGrads dw_grads(const floatx4& pooled, uint32_t bytes, float scale)
+{
+    DwGrads d;
+    // the winner's column: bits 0 and 2 of a byte the left one, bits 1 and 3 the right one; to the top of every byte
+    const uint32_t any = bytes | bytes >> 2, left = any << 7, right = any << 6;
+    const uint32_t mask[4] = {__builtin_amdgcn_perm(right << 8, left << 8, 0x0a0a0808u), __builtin_amdgcn_perm(right, left, 0x0a0a0808u),
+                              __builtin_amdgcn_perm(right << 8, left << 8, 0x0b0b0909u), __builtin_amdgcn_perm(right, left, 0x0b0b0909u)};
+    float v[4];
 #pragma unroll
-    for (int i = 0; i < 3; ++i)
+    for (int m = 0; m < 4; ++m) {
+        uint32_t p[3];
+        v[m] = scale * pooled[m];
+        split_twice(v[m], p);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) r.odd[i][j] = __builtin_amdgcn_alignbit(r.pair[i][j + 1], r.pair[i][j], 16);
-    return r;
+        for (int i = 0; i < 3; ++i) d.value.p[i][m] = p[i] & mask[m];
+        v[m] = mask[m] ? v[m] : 0.f;
+    }
+    d.sum = (v[0] + v[1]) + (v[2] + v[3]);
+    // the winner's row, bit 5 of a byte: its two places are 0, 1 (0b0100) or 2, 3 (0b1110)
+    uint32_t row = bytes >> 5 & 0x01010101u;
+    row = (row | row >> 4) & 0x00110011u;
+    row = (row | row >> 8) & 0x1111u;
+    d.place[0] = (int)(0x4444u + 10u * row);
+    d.place[1] = d.place[0] ^ 0xaaaa;
+    return d;
 }
 
 // The same as conv2_fwd_again for the sums over images [s_begin, s_end) of worker w: output channels 16 mt + 4q + i,
-// input channel l16, tap 0..8, or 9 for the bias.  The sums are times `scale`.
+// input channel l16, tap 0..8.  The sums are times `scale`.
 __device__ __forceinline__ void conv2_dw_again(const WorkerBuffers& wb, int w, int s_begin, int s_end, int mt, int tap, float scale, int lane, floatx4& sums)
 {
     const uint32_t which = lost_sums<4, 4>(sums);
@@ -525,7 +595,7 @@ __device__ __forceinline__ void conv2_dw_again(const WorkerBuffers& wb, int w, i
             const int yy = y + tap / 3 - 1, xx = x + tap % 3 - 1;
             const bool inside = yy >= 0 && yy < P1_W && xx >= 0 && xx < P1_W;
             const float v = wb.p1[g * P1_SIZE + (inside ? yy * P1_W + xx : 0) * C1 + l16];
-            again = __builtin_amdgcn_mfma_f32_16x16x4f32(winner ? d : 0.f, tap == 9 ? 1.f : inside ? v : 0.f, again, 0, 0, 0);
+            again = __builtin_amdgcn_mfma_f32_16x16x4f32(winner ? d : 0.f, inside ? v : 0.f, again, 0, 0, 0);
         }
         if (!worth_going_on<4>(which, again)) break;
     }
@@ -536,37 +606,30 @@ __device__ __forceinline__ void conv2_dw_again(const WorkerBuffers& wb, int w, i
 
 typedef float DwSums[DW_NW][DW_REGS + 2][64];  // 75,776 B
 
-// SHARES > 1: a launch that would leave SIMDs idle has six blocks for a slot, one for every (tap row, half of the
-// output channels); each sum is formed as in the one block, only fewer of them (one worker of 256 images: 45 us, or 22 us
-// with the input gradient and fc1's weight gradient in the same launch).
+// A wavefront's two images: pooled gradients and window bytes as they lie in memory, in whole KB.
+struct DwImages {
+    float dp2[2][7 * 256];
+    uint8_t am2[2][2048];
+};
+union DwShared {
+    DwImages images[DW_NW];
+    DwSums red;
+};
+
+// SHARED: a launch that would leave SIMDs idle has six blocks for a slot, one for every (tap row, half of the
+// output channels); each sum is formed as in the one block, only fewer of them.  Up to three wavefronts for four SIMDs
+// (two workers of 256 images, which has as many: 34 us shared, 39 not; one of 256: 23 and 36; with more, three of 64 20
+// and 18, three of 100 27 and 24, four of 256 53 and 44).
 constexpr int DW_SHARES = 6;
 
-// Four pooled gradients and their window bytes -> the d2 operand of lane (q = 2e + xh, l16).
-__device__ __forceinline__ Split8 d2_operand(const floatx4& pooled, uint32_t bytes, int e, float scale)
-{
-    Split8 d2;
-    const uint32_t bits = bytes >> (2 * e);  // bits 0, 1 of every byte: winner in this row, left or right
-#pragma unroll
-    for (int m = 0; m < 4; ++m) {
-        const uint32_t left = (uint32_t)__builtin_amdgcn_sbfe((int)bits, 8 * m, 1), right = (uint32_t)__builtin_amdgcn_sbfe((int)bits, 8 * m + 1, 1);
-        const uint32_t mask = (left & 0xffffu) | (right & 0xffff0000u);
-        uint32_t p0, p1, p2;
-        split2(scale * pooled[m], scale * pooled[m], p0, p1, p2);
-        d2.p[0][m] = p0 & mask;
-        d2.p[1][m] = p1 & mask;
-        d2.p[2][m] = p2 & mask;
-    }
-    return d2;
-}
-
 template <bool SHARED>
-__device__ __forceinline__ void conv2_dw_block(const WorkerBuffers& wb, const BwdShape& sh, int block, DwSums& red)
+__device__ __forceinline__ void conv2_dw_block(const WorkerBuffers& wb, const BwdShape& sh, int block, DwShared& lds)
 {
     constexpr int MTS = SHARED ? 1 : 2, DYS = SHARED ? 1 : 3;  // halves of the output channels and tap rows of this block
     const int share = SHARED ? block % DW_SHARES : 0, mt0 = share / 3, dy0 = share % 3;
     if (SHARED) block /= DW_SHARES;
     const int slots = sh.dw_slots, ipw = sh.dw_ipw;
-    const int lane = threadIdx.x & 63, wave = uniform(threadIdx.x >> 6), q = lane >> 4, l16 = lane & 15, e = q >> 1, xh = q & 1;
+    const int lane = threadIdx.x & 63, wave = uniform(threadIdx.x >> 6), q = lane >> 4, l16 = lane & 15;
     const int w = block / slots, slot = block % slots;
     const int B = wb.B, s_begin = min(B, (slot * DW_NW + wave) * ipw), s_end = min(B, s_begin + ipw);
 
@@ -574,114 +637,150 @@ __device__ __forceinline__ void conv2_dw_block(const WorkerBuffers& wb, const Bw
     for (int s = s_begin; s < s_end; ++s)
         if (image_scale(wb, (size_t)w * B + s) == 1.f) unscale = 1.f;
     const float scale = (wave & 1 ? -1.f : 1.f) * (unscale == 1.f ? 1.f : 0x1p64f);
-    floatx4 acc[MTS][3 * DYS], acc_b[MTS];
+    floatx4 acc[MTS][3 * DYS];
+    float acc_b[MTS];
 #pragma unroll
     for (int mt = 0; mt < MTS; ++mt) {
-        acc_b[mt] = floatx4{0.f, 0.f, 0.f, 0.f};
+        acc_b[mt] = 0.f;
 #pragma unroll
         for (int j = 0; j < 3 * DYS; ++j) acc[mt][j] = floatx4{0.f, 0.f, 0.f, 0.f};
     }
 
     constexpr uint32_t POS_BYTES = C1 * 4, ROW_BYTES = P1_W * POS_BYTES;
-    // columns 8xh - 1 .. 8xh + 8 of row e; of those outside the map only -1 and 14 ever meet a d2 value
-    const uint32_t at = (uint32_t)e * ROW_BYTES + (uint32_t)(8 * xh) * POS_BYTES + 4 * l16;  // column 8xh
-    const uint32_t at_first = xh == 0 ? BUFFER_NOWHERE : at - POS_BYTES, at_col14 = xh == 1 ? BUFFER_NOWHERE : at + 6 * POS_BYTES;
-    // rows R + e of the next pooled row: R = 2py and R = 2py + 1, or SHARED, R = 2py - 1 + dy0 alone
-    float raw[SHARED ? 1 : 2][10];
-    floatx4 pooled[MTS];  // pool2 gradients of windows px = 4xh .. 4xh + 3 (px = 7: whatever follows, masked) and their bytes
-    uint32_t bytes[MTS];
-    auto prefetch = [&](size_t g, int py) {
-        const Buffer b = buffer_of(wb.p1 + g * P1_SIZE, P1_SIZE * 4);
+    // columns 4q - 1 .. 4q + 4; the first of them, and the last three of the last quarter, are outside the map
+    const uint32_t at = (uint32_t)(4 * q) * POS_BYTES + 4 * l16, at_first = q == 0 ? BUFFER_NOWHERE : at - POS_BYTES;
+    const uint32_t at_last = q == 3 ? BUFFER_NOWHERE : at + 2 * POS_BYTES;
+    // What the two halves of a contraction are: two images, or, where a wavefront has but one, the upper four rows of
+    // windows of it and the lower three.
+    const bool one_image = ipw == 1;
+    const int steps = one_image ? 4 : P2_W, stride = one_image ? 1 : 2;
+    auto load_row = [&](int s, int set, int R, float (&v)[6]) {
+        const int image = one_image ? 0 : set;
+        if (one_image) R += 8 * set;
+        const bool here = s + image < s_end && R >= 0;
+        const Buffer b = buffer_of(wb.p1 + ((size_t)w * B + (here ? s + image : s_begin)) * P1_SIZE, here ? P1_SIZE * 4 : 0);
+        const uint32_t row = (uint32_t)max(R, 0) * ROW_BYTES;
+        v[0] = buffer_float(b, at_first, row);
 #pragma unroll
-        for (int i = 0; i < (SHARED ? 1 : 2); ++i) {
-            const int R = SHARED ? 2 * py - 1 + dy0 : 2 * py + i;
-            const bool above = SHARED && R + e < 0;  // row -1
-            const uint32_t row = (uint32_t)max(R, 0) * ROW_BYTES - (SHARED && R < 0 && e > 0 ? ROW_BYTES : 0u);
+        for (int k = 0; k < 2; ++k) v[1 + k] = buffer_float(b, at, row + k * POS_BYTES);
 #pragma unroll
-            for (int k = 0; k < 10; ++k) {
-                const uint32_t o = k == 0 ? at_first + row : k == 7 ? at_col14 + row : at + row + (k - 1) * POS_BYTES;
-                raw[i][k] = buffer_float(b, above ? BUFFER_NOWHERE : o);
-            }
-        }
+        for (int k = 0; k < 3; ++k) v[3 + k] = buffer_float(b, at_last, row + k * POS_BYTES);
+    };
+    // map rows of a step: 2py + 2 and 2py + 1; SHARED, the two that tap row dy0 meets
+    const int even_row = SHARED && dy0 < 2 ? 0 : 2, odd_row = SHARED && dy0 == 0 ? -1 : 1;
+    float even[2][6], odd[2][6];
+    DwImages& im = lds.images[wave];
+    // The images' gradients and bytes straight to LDS: by lanes, as they are used, each would touch 64 cache lines for a
+    // quarter KB.  An image that does not exist has no active windows.
+    auto bring_images = [&](int s) {
 #pragma unroll
-        for (int mt = 0; mt < MTS; ++mt) {
-            const int r = (16 * (mt0 + mt) + l16) * P2_W + py;
-            __builtin_memcpy(&pooled[mt], wb.dp2g + g * P2_SIZE + r * P2_W + 4 * xh, 16);
-            bytes[mt] = *reinterpret_cast<const uint32_t*>(wb.am2 + g * AM2_SIZE + r * AM2_PITCH + 4 * xh);
+        for (int image = 0; image < 2; ++image) {
+            if (one_image && image == 1) break;
+            const bool here = s + image < s_end;
+            const size_t g = (size_t)w * B + (here ? s + image : s_begin);
+            const Buffer d = buffer_of(wb.dp2g + g * P2_SIZE, P2_SIZE * 4);
+            const Buffer b = buffer_of(reinterpret_cast<const float*>(wb.am2 + g * AM2_SIZE), here ? AM2_SIZE : 0);
+#pragma unroll
+            for (int k = 0; k < 7; ++k) buffer_to_lds16(d, im.dp2[image] + 256 * k, 16 * lane, 1024 * k);
+#pragma unroll
+            for (int k = 0; k < 2; ++k) buffer_to_lds16(b, im.am2[image] + 1024 * k, 16 * lane, 1024 * k);
         }
     };
-    if (s_begin < s_end) prefetch((size_t)w * B + s_begin, 0);
+    // windows px = 4 (q % 2) .. + 3 of half q / 2 (px = 7: whatever follows, masked)
+    const int image_of = one_image ? 0 : q >> 1, py_of = one_image ? 4 * (q >> 1) : 0;
+    const float* const pooled = im.dp2[image_of] + (16 * mt0 + l16) * P2_POS + py_of * P2_W + 4 * (q & 1);
+    const uint8_t* const bytes = im.am2[image_of] + ((16 * mt0 + l16) * P2_W + py_of) * AM2_PITCH + 4 * (q & 1);
+    auto load_rows = [&](int s, int py) {
+#pragma unroll
+        for (int image = 0; image < 2; ++image) {
+            load_row(s, image, 2 * py + odd_row, odd[image]);
+            load_row(s, image, 2 * py + even_row, even[image]);
+        }
+    };
 
-    for (int s = s_begin; s < s_end; ++s) {
-        const size_t g = (size_t)w * B + s;
-        ShiftedRow up;  // rows 2py - 1 + e
+    if (s_begin < s_end) {
+        bring_images(s_begin);
+        load_rows(s_begin, 0);
+    }
+    for (int s = s_begin; s < s_end; s += stride) {
+        DwRows rows;
+        rows.clear<1>();  // row -1
+        if (!SHARED) {
+            float first[2][6];
+#pragma unroll
+            for (int set = 0; set < 2; ++set) load_row(s, set, 0, first[set]);
+#pragma unroll
+            for (int set = 0; set < 2; ++set) rows.put<0>(set, first[set]);
+            if (one_image) {
+                load_row(s, 1, -1, first[1]);
+                rows.put<1>(1, first[1]);
+            }
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the images are in LDS
 #pragma unroll 1
-        for (int py = 0; py < P2_W; ++py) {
-            Split8 d2[MTS];
-#pragma unroll
-            for (int mt = 0; mt < MTS; ++mt) d2[mt] = d2_operand(pooled[mt], bytes[mt], e, scale);
-            const ShiftedRow mid = shifted_row(raw[0]);
-            if (!SHARED && py == 0) {  // rows -1 (zero) and 0: lanes 32..63 take what lanes 0..31 of `mid` hold
-#pragma unroll
-                for (int i = 0; i < 3; ++i) {
-#pragma unroll
-                    for (int j = 0; j < 5; ++j) up.pair[i][j] = __builtin_amdgcn_permlane32_swap(0u, mid.pair[i][j], false, false)[0];
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) up.odd[i][j] = __builtin_amdgcn_permlane32_swap(0u, mid.odd[i][j], false, false)[0];
-                }
-            }
-            const ShiftedRow low = shifted_row(raw[SHARED ? 0 : 1]);
-            const ShiftedRow* const rows[3] = {SHARED ? &mid : &up, &mid, &low};
-            const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int dy = 0; dy < DYS; ++dy) {
-                // the next pooled row's loads once the first tap row's operand is dead: in front of it they spill
-                if (!SHARED) __builtin_amdgcn_sched_barrier(0);
-                if (dy == 1 || SHARED) {
-                    if (py + 1 < P2_W)
-                        prefetch(g, py + 1);
-                    else if (s + 1 < s_end)
-                        prefetch(g + 1, 0);
-                }
-#pragma unroll
-                for (int dx = 0; dx < 3; ++dx) {
-                    const Split8 b = rows[dy]->columns(dx);
-                    floatx4 small[MTS];
-#pragma unroll
-                    for (int t = 0; t < SPLIT_SMALL; ++t)
-#pragma unroll
-                        for (int mt = 0; mt < MTS; ++mt)
-                            small[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(d2[mt].part(TERM_A[t]), b.part(TERM_B[t]), t == 0 ? zero : small[mt], 0, 0, 0);
-#pragma unroll
-                    for (int mt = 0; mt < MTS; ++mt) {
-                        floatx4& sum = acc[mt][3 * dy + dx];
-                        sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(d2[mt].part(0), b.part(0), sum, 0, 0, 0) + small[mt];
-                    }
-                }
-            }
-            const bf16x8 ones = __builtin_bit_cast(bf16x8, uintx4{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u});
+        for (int py = 0; py < steps; ++py) {
+            const int next_s = py + 1 < steps ? s : s + stride, next_py = py + 1 < steps ? py + 1 : 0;
+            DwGrads d2[MTS];
 #pragma unroll
             for (int mt = 0; mt < MTS; ++mt) {
-                floatx4 small = __builtin_amdgcn_mfma_f32_16x16x32_bf16(d2[mt].part(2), ones, zero, 0, 0, 0);
-                small = __builtin_amdgcn_mfma_f32_16x16x32_bf16(d2[mt].part(1), ones, small, 0, 0, 0);
-                acc_b[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(d2[mt].part(0), ones, acc_b[mt], 0, 0, 0) + small;
+                const float* p = pooled + 16 * mt * P2_POS + py * P2_W;
+                uint32_t b = *reinterpret_cast<const uint32_t*>(bytes + (16 * mt * P2_W + py) * AM2_PITCH);
+                if (py + py_of >= P2_W) b = 0;
+                d2[mt] = dw_grads(floatx4{p[0], p[1], p[2], p[3]}, b, scale);
+                acc_b[mt] += d2[mt].sum;
             }
-            if (!SHARED) up = low;
+            if (py + 1 == steps) {  // these were the last values of the images: the next ones take their place
+                wave_lds_fence();
+                if (s + stride < s_end) bring_images(s + stride);
+            }
+#pragma unroll
+            for (int dy = 0; dy < DYS; ++dy) {
+                if (SHARED || dy == 1) {
+#pragma unroll
+                    for (int image = 0; image < 2; ++image) rows.put<1>(image, odd[image]);
+                }
+                if (SHARED || dy == 2) {
+#pragma unroll
+                    for (int image = 0; image < 2; ++image) rows.put<0>(image, even[image]);
+                    load_rows(next_s, next_py);
+                }
+                if (!SHARED) __builtin_amdgcn_sched_barrier(0);
+                const bool exchanged = SHARED ? dy0 != 1 : dy != 1;
+                // tile by tile; a tile's small terms are added to its sums under the next one's products
+                floatx4 small[2];
+                auto settle = [&](int n) { acc[n % MTS][3 * dy + n / MTS] += small[n % 2]; };
+#pragma unroll
+                for (int n = 0; n < 3 * MTS; ++n) {
+                    const int mt = n % MTS, dx = n / MTS, place = exchanged ? d2[mt].place[1] : d2[mt].place[0];
+                    const auto product = [&](int ta, int tb, floatx4 sum) {
+                        return __builtin_amdgcn_smfmac_f32_16x16x64_bf16(d2[mt].value.part(ta), __builtin_bit_cast(bf16x16, rows.t[dx][tb]), sum, place, 0, 0);
+                    };
+                    small[n % 2] = cleared();
+#pragma unroll
+                    for (int t = 0; t < SPLIT_SMALL; ++t) small[n % 2] = product(TERM_A[t], TERM_B[t], small[n % 2]);
+                    acc[mt][3 * dy + dx] = product(0, 0, acc[mt][3 * dy + dx]);
+                    if (n > 0) settle(n - 1);
+                }
+                settle(3 * MTS - 1);
+            }
         }
     }
 
-    // register i of tile (mt, j): output channel 16 mt + 4q + i, input channel l16, tap j (every column of the bias tile alike)
+    DwSums& red = lds.red;
+    __syncthreads();  // everybody has read its images, whose place the sums take
+    // register i of tile (mt, j): output channel 16 mt + 4q + i, input channel l16, tap j
     bool lost = false;
 #pragma unroll
     for (int mt = 0; mt < MTS; ++mt) {
-        if (any_lost<4, 4>(acc_b[mt])) conv2_dw_again(wb, w, s_begin, s_end, mt0 + mt, 9, scale, lane, acc_b[mt]);
 #pragma unroll
         for (int j = 0; j < 3 * DYS; ++j) {
             lost |= any_lost<4, 4>(acc[mt][j]);
 #pragma unroll
             for (int i = 0; i < 4; ++i) red[wave][((mt0 + mt) * 9 + 3 * dy0 + j) * 4 + i][lane] = acc[mt][j][i];
         }
-        if (l16 == 0) *reinterpret_cast<floatx4*>(&red[wave][DW_REGS + mt0 + mt][4 * q]) = acc_b[mt];
+        acc_b[mt] += __shfl_xor(acc_b[mt], 16, 64);
+        acc_b[mt] += __shfl_xor(acc_b[mt], 32, 64);
+        if (q == 0) red[wave][DW_REGS + mt0 + mt][l16] = acc_b[mt];
     }
     const int r_begin = (mt0 * 9 + 3 * dy0) * 4;  // of this block's DYS * MTS * 12 registers
     if (lost) {
@@ -725,13 +824,13 @@ __global__ __launch_bounds__(256, 2) void backward_kernel(WorkerBuffers wb, BwdS
     static_assert(DX_NT == 256 && DW_NT == 256, "one block size");
     __shared__ __attribute__((aligned(16))) union {
         DxImage images[DX_NW];
-        DwSums red;
+        DwShared dw;
         char stages[FC1_DW ? 2 * Fc1DwFew::STAGE : 1];
     } lds;
     int block = blockIdx.x;
     if (block < sh.dx_blocks) return conv2_dx_block(wb, sh, block, lds.images);
     block -= sh.dx_blocks;
-    if (block < sh.dw_blocks) return sh.dw_shared ? conv2_dw_block<true>(wb, sh, block, lds.red) : conv2_dw_block<false>(wb, sh, block, lds.red);
+    if (block < sh.dw_blocks) return sh.dw_shared ? conv2_dw_block<true>(wb, sh, block, lds.dw) : conv2_dw_block<false>(wb, sh, block, lds.dw);
     // fc1's blocks start at a multiple of 8: block number mod 8 says which XCD a tile runs on
     if constexpr (FC1_DW > 0) {
         block = blockIdx.x - (sh.dx_blocks + sh.dw_blocks + 7) / 8 * 8;
@@ -749,7 +848,13 @@ void launch_conv2_fwd(const WorkerBuffers& wb, hipStream_t s)
 
 int conv1_part_slots(int batch) { return batch; }
 
-static int conv2_dw_ipw(int batch) { return (batch + DW_NW * DW_MAX_SLOTS - 1) / (DW_NW * DW_MAX_SLOTS); }
+// Images per wavefront: one, or an even number, which are then taken in pairs.  One image in halves takes four k-steps,
+// two in a pair seven: for up to 64 images, wavefronts of one each are more in number and done sooner (16 workers of 64
+// images: 23.6 us against 28.7 with pairs, of which there are half as many).
+static int conv2_dw_ipw(int batch)
+{
+    return batch <= DW_NW * DW_MAX_SLOTS ? 1 : 2 * ((batch + 2 * DW_NW * DW_MAX_SLOTS - 1) / (2 * DW_NW * DW_MAX_SLOTS));
+}
 
 int conv2_part_slots(int batch)
 {
@@ -767,7 +872,7 @@ void launch_backward(const WorkerBuffers& wb, hipStream_t s)
     sh.dx_blocks = wb.n * sh.dx_blocks_per_worker;
     sh.dw_slots = conv2_part_slots(wb.B);
     sh.dw_ipw = conv2_dw_ipw(wb.B);
-    sh.dw_shared = DW_SHARES * DW_NW * wb.n * sh.dw_slots <= 2 * 4 * wb.compute_units;
+    sh.dw_shared = DW_SHARES * DW_NW * wb.n * sh.dw_slots <= 3 * wb.compute_units;
     sh.dw_blocks = wb.n * sh.dw_slots * (sh.dw_shared ? DW_SHARES : 1);
     const GemmShape fc1 = fc1_dw_few_shape(wb.n, wb.B);
     const int conv_blocks = (sh.dx_blocks + sh.dw_blocks + 7) / 8 * 8;

@@ -59,6 +59,31 @@ def test_conv2_weight_gradient_error(ps, n, B, share, fp32):
         ps.ps_destroy(ctx)
 
 
+# wavefronts of one image, and of pairs of which the last is incomplete; few blocks for a tap row each, and many for all
+@pytest.mark.parametrize("n,B", [(1, 1), (2, 3), (3, 64), (1, 65), (2, 129), (30, 7), (40, 66), (40, 130)])
+def test_conv2_weight_gradient_forms(ps, n, B):
+    """d W2 within the error of fp32 matrix instructions (1.5e-7, above), d b2 within four roundings of 2^-24: a lane
+    adds a value for a row of windows, seven of an image."""
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(11 * n + B)
+    x = torch.rand(n, B, ps.IMAGE_PIXELS, device="cuda", generator=g)
+    y = torch.randint(0, 10, (n, B), device="cuda", generator=g, dtype=torch.int32)
+    ctx = ps.ps_init(ps.make_config(n, B, 1, n, DROP_SEED, P_DROP))
+    try:
+        ps.ps_set_weights(ctx, synth.he_uniform_theta(5))
+        q = ps.worker_grads_batched(ctx, range(n), [0] * n, [synth.minibatch_id(w, 0) for w in range(n)], x, y)
+        ps.ps_sync(ctx)
+        for i in {0, n // 2, n - 1}:
+            d2, u = _d2(ps, ctx, i)
+            got = torch.from_numpy(ps.ps_get_grad(ctx, q[i])).cuda().double()
+            want, want_b = torch.matmul(d2, u.transpose(1, 2)).sum(0).flatten(), d2.sum((0, 2))
+            assert float((got[OFF_W2:OFF_B2] - want).norm() / want.norm()) <= 1.5e-7
+            assert float((got[OFF_B2:OFF_B2 + 32] - want_b).norm() / want_b.norm()) <= 4 * 2.0 ** -24
+    finally:
+        ps.ps_destroy(ctx)
+
+
 # the error of sums that are kept in registers over eight images
 @pytest.mark.parametrize("n,B,registers", [(8, 200, 7.92e-8), (8, 1024, 6.45e-8), (4, 4096, 7.16e-8)])
 def test_conv1_weight_gradient_error(ps, n, B, registers):
