@@ -134,7 +134,7 @@ hipError_t launch_eval_collect(int n_images, const float* loss_i, const int32_t*
 
 void launch_conv2_fwd(const WorkerBuffers& wb, hipStream_t s);
 void launch_fc1_dw(const WorkerBuffers& wb, hipStream_t s);
-bool fc1_dw_is_few(const WorkerBuffers& wb);  // whether fc1's weight gradient runs in launch_backward's launch instead of one of its own
+bool fc1_dw_in_backward(const WorkerBuffers& wb);  // whether fc1's weight gradient runs in launch_backward's launch instead of one of its own
 void launch_backward(const WorkerBuffers& wb, hipStream_t s);  // conv2's gradients (and conv1's)
 
 // Kernels of the path, in launch order; ids index the per-kernel timing table.

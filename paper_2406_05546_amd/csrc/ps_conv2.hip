@@ -814,27 +814,28 @@ __device__ __forceinline__ void conv2_dw_block(const WorkerBuffers& wb, const Bw
     }
 }
 
-// conv2's two gradients in one launch, and in small launches (FC1 > 0) fc1's weight gradient with them: none needs
-// another, the one fills the SIMDs that the others leave idle, and one or two launches are saved.  In large ones
-// fc1's blocks only get in the way: sharing the compute units with conv2's, 256 workers of 256 images took 2.11 ms
-// instead of 1.29 + 0.73.
-template <int FC1_DW>  // 0: without fc1, 1: with, 2: with, and a batch that is not a multiple of its stages
+// conv2's two gradients in one launch, and with up to 42 workers fc1's weight gradient (ps_fc1_dw.h) with them: none needs
+// another, the one fills the SIMDs that the others leave idle, and one or two launches are saved.
+struct NoFc1Dw {
+    static constexpr int STAGE = 0;
+};
+template <class Fc1Dw, bool RAGGED>  // fc1's tiles, and whether the batch is not a multiple of their stages
 __global__ __launch_bounds__(256, 2) void backward_kernel(WorkerBuffers wb, BwdShape sh, GemmShape fc1)
 {
     static_assert(DX_NT == 256 && DW_NT == 256, "one block size");
     __shared__ __attribute__((aligned(16))) union {
         DxImage images[DX_NW];
         DwShared dw;
-        char stages[FC1_DW ? 2 * Fc1DwFew::STAGE : 1];
+        char stages[2 * Fc1Dw::STAGE + 1];
     } lds;
     int block = blockIdx.x;
     if (block < sh.dx_blocks) return conv2_dx_block(wb, sh, block, lds.images);
     block -= sh.dx_blocks;
     if (block < sh.dw_blocks) return sh.dw_shared ? conv2_dw_block<true>(wb, sh, block, lds.dw) : conv2_dw_block<false>(wb, sh, block, lds.dw);
     // fc1's blocks start at a multiple of 8: block number mod 8 says which XCD a tile runs on
-    if constexpr (FC1_DW > 0) {
+    if constexpr (Fc1Dw::STAGE > 0) {
         block = blockIdx.x - (sh.dx_blocks + sh.dw_blocks + 7) / 8 * 8;
-        if (block >= 0) fc1_dw_few_block<FC1_DW == 2>(wb, fc1, block, lds.stages);
+        if (block >= 0) fc1_dw_block<Fc1Dw, RAGGED>(wb, fc1, block, lds.stages);
     }
 }
 
@@ -862,6 +863,19 @@ int conv2_part_slots(int batch)
     return (batch + per_slot - 1) / per_slot;
 }
 
+template <class Fc1Dw>
+static void start_backward(const WorkerBuffers& wb, const BwdShape& sh, const GemmShape& fc1, hipStream_t s)
+{
+    const int conv_blocks = (sh.dx_blocks + sh.dw_blocks + 7) / 8 * 8;
+    auto kernel = backward_kernel<Fc1Dw, false>;
+    int blocks = conv_blocks;
+    if constexpr (Fc1Dw::STAGE > 0) {
+        if (wb.B % Fc1Dw::KS != 0) kernel = backward_kernel<Fc1Dw, true>;
+        blocks += gemm_grid(fc1);
+    }
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), 0, s, wb, sh, fc1);
+}
+
 void launch_backward(const WorkerBuffers& wb, hipStream_t s)
 {
     BwdShape sh;
@@ -874,14 +888,15 @@ void launch_backward(const WorkerBuffers& wb, hipStream_t s)
     sh.dw_ipw = conv2_dw_ipw(wb.B);
     sh.dw_shared = DW_SHARES * DW_NW * wb.n * sh.dw_slots <= 3 * wb.compute_units;
     sh.dw_blocks = wb.n * sh.dw_slots * (sh.dw_shared ? DW_SHARES : 1);
-    const GemmShape fc1 = fc1_dw_few_shape(wb.n, wb.B);
-    const int conv_blocks = (sh.dx_blocks + sh.dw_blocks + 7) / 8 * 8;
-    if (!fc1_dw_few(wb))
-        hipLaunchKernelGGL(backward_kernel<0>, dim3(conv_blocks), dim3(256), 0, s, wb, sh, fc1);
+    const Fc1DwWhere where = fc1_dw_where(wb);
+    if (where == FC1_DW_FEW)
+        start_backward<Fc1DwFew>(wb, sh, fc1_dw_shape<Fc1DwFew>(wb), s);
+    else if (where == FC1_DW_SEVERAL)
+        start_backward<Fc1DwSeveral>(wb, sh, fc1_dw_shape<Fc1DwSeveral>(wb), s);
     else
-        hipLaunchKernelGGL((wb.B % Fc1DwFew::KS == 0 ? backward_kernel<1> : backward_kernel<2>), dim3(conv_blocks + gemm_grid(fc1)), dim3(256), 0, s, wb, sh, fc1);
+        start_backward<NoFc1Dw>(wb, sh, GemmShape{}, s);
 }
 
-bool fc1_dw_is_few(const WorkerBuffers& wb) { return fc1_dw_few(wb); }
+bool fc1_dw_in_backward(const WorkerBuffers& wb) { return fc1_dw_where(wb) != FC1_DW_ALONE; }
 
 }  // namespace ps

@@ -77,7 +77,7 @@ void launch_fc1_fwd(const WorkerBuffers& wb, hipStream_t s)
     }
 }
 
-// weight gradient of a launch that is not FEW (see ps_fc1_dw.h)
+// weight gradient in a launch of its own (see ps_fc1_dw.h)
 void launch_fc1_dw(const WorkerBuffers& wb, hipStream_t s)
 {
     gemm_launch_edge<Fc1DwMain, Fc1DwEdge, true, 0, 2>(FC1, P2_SIZE, wb.B, FC1, P2_SIZE, wb.n, FC1, FEAT_WIDE, Fc1DwEpi<true>{wb}, s);

@@ -129,9 +129,9 @@ hipError_t launch_worker_backward(const WorkerBuffers& wb, hipStream_t s, Profil
 {
     if (wb.n * wb.B <= 0) return hipSuccess;
     PS_TIMED(K_FC2, launch_fc2(wb, s));
-    if (!fc1_dw_is_few(wb)) PS_TIMED(K_FC1_DW, launch_fc1_dw(wb, s));
+    if (!fc1_dw_in_backward(wb)) PS_TIMED(K_FC1_DW, launch_fc1_dw(wb, s));
     PS_TIMED(K_FC1_DX, launch_fc1_dx(wb, s));
-    PS_TIMED(fc1_dw_is_few(wb) ? K_BACKWARD_FC1 : K_BACKWARD, launch_backward(wb, s));
+    PS_TIMED(fc1_dw_in_backward(wb) ? K_BACKWARD_FC1 : K_BACKWARD, launch_backward(wb, s));
     // one value per thread while the chip has room, at least the blocks that the conv1 values take
     const int reduce_y = wb.n * (REDUCE_ITEMS / 256 + 1) <= 8 * wb.compute_units ? REDUCE_ITEMS / 256 + 1 : 8;
     PS_TIMED(K_GRAD_REDUCE, hipLaunchKernelGGL(grad_reduce_kernel, dim3(wb.n, reduce_y), dim3(256), 0, s, wb, fc2_split(wb.n),

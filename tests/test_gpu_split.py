@@ -84,6 +84,34 @@ def test_conv2_weight_gradient_forms(ps, n, B):
         ps.ps_destroy(ctx)
 
 
+# both sides of the lines between 128 x 64 and 128 x 128 tiles next to conv2's gradients, and between those and a launch of
+# their own; whole stages and a remainder
+@pytest.mark.parametrize("n", [10, 11, 42, 43])
+@pytest.mark.parametrize("B", [5, 16, 48, 51])
+def test_fc1_weight_gradient_tiles(ps, n, B):
+    """Every row of d fc1.W against 64 bits: within the error of fp32 matrix instructions (1.5e-7, above)."""
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(13 * n + B)
+    x = torch.rand(n, B, ps.IMAGE_PIXELS, device="cuda", generator=g)
+    y = torch.randint(0, 10, (n, B), device="cuda", generator=g, dtype=torch.int32)
+    ctx = ps.ps_init(ps.make_config(n, B, 1, n, DROP_SEED, P_DROP))
+    try:
+        ps.ps_set_weights(ctx, synth.he_uniform_theta(5))
+        q = ps.worker_grads_batched(ctx, range(n), [0] * n, [synth.minibatch_id(w, 0) for w in range(n)], x, y)
+        ps.ps_sync(ctx)
+        for i in (0, n - 1):
+            act = ps.ps_debug_last_activations(ctx, i)
+            d3, p2 = (torch.from_numpy(act[k]).cuda().double().view(B, -1) for k in ("d3", "pool2_val"))
+            want = d3.t() @ p2
+            got = torch.from_numpy(ps.ps_get_grad(ctx, q[i])[4800:807616]).cuda().double().view(512, 1568)
+            some = want.norm(dim=1) > 0
+            assert float(((got - want).norm(dim=1)[some] / want.norm(dim=1)[some]).max()) <= 1.5e-7
+            assert not bool(got[~some].any())
+    finally:
+        ps.ps_destroy(ctx)
+
+
 # the error of sums that are kept in registers over eight images
 @pytest.mark.parametrize("n,B,registers", [(8, 200, 7.92e-8), (8, 1024, 6.45e-8), (4, 4096, 7.16e-8)])
 def test_conv1_weight_gradient_error(ps, n, B, registers):
