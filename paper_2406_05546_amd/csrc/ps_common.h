@@ -114,7 +114,7 @@ struct ImageSplit {
     int wavefronts;  // per image
     int blocks;      // per worker
 };
-ImageSplit split_images(const WorkerBuffers& wb, int most_images, int most_wavefronts, int wavefronts_per_block);
+ImageSplit split_images(const WorkerBuffers& wb, int most_images, int most_wavefronts, int wavefronts_per_block, bool alone);
 
 void launch_conv1_fwd(const WorkerBuffers& wb, hipStream_t s);
 void launch_fc1_fwd(const WorkerBuffers& wb, hipStream_t s);

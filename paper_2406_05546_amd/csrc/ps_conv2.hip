@@ -843,7 +843,7 @@ __global__ __launch_bounds__(256, 2) void backward_kernel(WorkerBuffers wb, BwdS
 
 void launch_conv2_fwd(const WorkerBuffers& wb, hipStream_t s)
 {
-    const ImageSplit sp = split_images(wb, FWD_IPW, 4, FWD_NW);
+    const ImageSplit sp = split_images(wb, FWD_IPW, 4, FWD_NW, true);
     hipLaunchKernelGGL(conv2_fwd_kernel, dim3(wb.n * sp.blocks), dim3(FWD_NT), 0, s, wb, sp.blocks, sp.images, sp.wavefronts);
 }
 
@@ -879,7 +879,7 @@ static void start_backward(const WorkerBuffers& wb, const BwdShape& sh, const Ge
 void launch_backward(const WorkerBuffers& wb, hipStream_t s)
 {
     BwdShape sh;
-    const ImageSplit dx = split_images(wb, DX_IPW, 2, DX_NW);
+    const ImageSplit dx = split_images(wb, DX_IPW, 2, DX_NW, false);
     sh.dx_ipw = dx.images;
     sh.dx_parts = dx.wavefronts;
     sh.dx_blocks_per_worker = dx.blocks;

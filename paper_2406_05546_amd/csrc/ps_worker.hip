@@ -99,13 +99,21 @@ __global__ __launch_bounds__(256) void keep_mask_kernel(uint8_t* keep, int B, ui
 // launch, reading and splitting a filter bank above all, takes up to a quarter of an image's time.  Where there is not
 // one for every SIMD, as many (1, 2 or 4, up to `most_wavefronts`) share an image as still find SIMDs to run on, one
 // each; the kernels count on those having that image alone.
-ImageSplit split_images(const WorkerBuffers& wb, int most_images, int most_wavefronts, int wavefronts_per_block)
+// A launch of nothing else (`alone`) lasts as long as the compute unit with the most blocks: it takes fewer images at a time
+// where that makes its share smaller.  100 workers of 128 images: conv1 70 -> 60 us, conv2's forward pass 142 -> 128
+// (eight images: 400 blocks, two on some compute units; one: 3200, thirteen at most); 200 of 30 37 -> 33 and 74 -> 70.  What
+// a wavefront of these does once is a sixteenth of an image's time (64 of 128, four, two and one image: 79.6, 80.8, 83.3 us).
+ImageSplit split_images(const WorkerBuffers& wb, int most_images, int most_wavefronts, int wavefronts_per_block, bool alone)
 {
     ImageSplit sp{most_images, 1, 0};
     while (sp.wavefronts < most_wavefronts && 2 * sp.wavefronts * wb.n * wb.B <= 4 * wb.compute_units) sp.wavefronts *= 2;
     while (sp.images > 1 && (sp.wavefronts > 1 || wb.n * ((wb.B + sp.images - 1) / sp.images) < 2 * 4 * wb.compute_units)) sp.images /= 2;
-    const int units = (wb.B + sp.images - 1) / sp.images * sp.wavefronts;
-    sp.blocks = (units + wavefronts_per_block - 1) / wavefronts_per_block;
+    auto blocks = [&](int images) { return ((wb.B + images - 1) / images * sp.wavefronts + wavefronts_per_block - 1) / wavefronts_per_block; };
+    auto longest = [&](int images) { return (int64_t)((wb.n * blocks(images) + wb.compute_units - 1) / wb.compute_units) * (16 * images + 1); };
+    if (alone)
+        for (int images = sp.images / 2; images > 0; images /= 2)
+            if (longest(images) < longest(sp.images)) sp.images = images;
+    sp.blocks = blocks(sp.images);
     return sp;
 }
 
