@@ -730,7 +730,9 @@ __device__ __forceinline__ void conv2_dw_block(const WorkerBuffers& wb, const Bw
                 acc_b[mt] += d2[mt].sum;
             }
             if (py + 1 == steps) {  // these were the last values of the images: the next ones take their place
-                wave_lds_fence();
+                // what comes straight to LDS does not wait for reads that are on their way: with fc1's blocks next to this one
+                // they were late enough, now and then, to find the next image
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
                 if (s + stride < s_end) bring_images(s + stride);
             }
 #pragma unroll

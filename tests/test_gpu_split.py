@@ -84,6 +84,30 @@ def test_conv2_weight_gradient_forms(ps, n, B):
         ps.ps_destroy(ctx)
 
 
+# several pairs of images for a wavefront, with fc1's blocks next to them and without
+@pytest.mark.parametrize("n,B", [(22, 166), (19, 176), (50, 166)])
+def test_gradients_repeat_bit_for_bit(ps, n, B):
+    """The next images must not take the place of those that a wavefront still reads."""
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(19 * n + B)
+    x = torch.rand(n, B, ps.IMAGE_PIXELS, device="cuda", generator=g)
+    y = torch.randint(0, 10, (n, B), device="cuda", generator=g, dtype=torch.int32)
+    ctx = ps.ps_init(ps.make_config(n, B, 1, n, DROP_SEED, P_DROP))
+    try:
+        ps.ps_set_weights(ctx, synth.he_uniform_theta(5))
+        rows = ctx.workspace[:(2 + n) * ps.ROW_FLOATS * 4].view(torch.float32).view(-1, ps.ROW_FLOATS)[2:]
+        first = None
+        for _ in range(200):
+            q = ps.worker_grads_batched(ctx, range(n), [0] * n, [synth.minibatch_id(w, 0) for w in range(n)], x, y)
+            got = rows[:, :ps.P].clone()
+            first = got if first is None else first
+            assert bool((got == first).all())
+            ps.ps_apply_sync(ctx, q, 0.0)
+    finally:
+        ps.ps_destroy(ctx)
+
+
 # both sides of the lines between 128 x 64 and 128 x 128 tiles next to conv2's gradients, and between those and a launch of
 # their own; whole stages and a remainder
 @pytest.mark.parametrize("n", [10, 11, 42, 43])
