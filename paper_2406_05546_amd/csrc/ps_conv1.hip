@@ -18,7 +18,10 @@ namespace {
 // and stored [channel][position] (0.37 ms when that kernel stored [position][channel], 16 bytes at a time 64
 // bytes apart); two workers of 32 images: 11 -> 8 us.  Two images at most: with eight 262 us instead of 254, 64 workers of 128
 // images 43.6 instead of 41.
-constexpr int CONV1_NW = 4, CONV1_NT = 64 * CONV1_NW, CONV1_IPW = 2;  // wavefronts per block, most images per wavefront
+// Up to eight wavefronts share an image: two workers of 32 images, whole step 61.7 -> 59.9 us with eight, one of 16 59.0 -> 58.1.
+// Each as a block of its own, two to a SIMD, gained 1 % more on images that the caches held, and lost as much on others, which
+// each of them then fetched.
+constexpr int CONV1_NW = 4, CONV1_NT = 64 * CONV1_NW, CONV1_IPW = 2, CONV1_PARTS = 8;  // wavefronts per block, most images per wavefront, most wavefronts per image
 constexpr int CONV1_XW = 30;
 
 // N_META > 0: the workers' metadata are in the arguments, and the first block of a worker puts its own where the
@@ -104,7 +107,7 @@ __global__ __launch_bounds__(CONV1_NT) void conv1_fwd_kernel(WorkerBuffers wb, i
 template <int N_META>
 static void start_conv1_fwd(const WorkerBuffers& wb, hipStream_t s)
 {
-    const ImageSplit sp = split_images(wb, CONV1_IPW, 4, CONV1_NW, true);
+    const ImageSplit sp = split_images(wb, CONV1_IPW, CONV1_PARTS, CONV1_NW, true);
     MetaArgs<N_META> args;
     if (N_META > 0) std::copy(wb.meta_host, wb.meta_host + wb.n, args.m);
     hipLaunchKernelGGL(conv1_fwd_kernel<N_META>, dim3(wb.n * sp.blocks), dim3(CONV1_NT), 0, s, wb, sp.blocks, sp.images, sp.wavefronts, args);

@@ -23,11 +23,15 @@ namespace {
 // same operand moved by 0, 1, 2 lanes, and the pair of dy = 2 is that of dy = 0 one pooled row further on.
 // A lane ends up with both rows of four windows of one output channel, so pooling stays in its registers;
 // the pooled image is turned to [channel][position] in LDS and leaves in 16-byte stores.
-// In launches that would leave SIMDs idle, `parts` wavefronts share an image, two or four pooled rows each.
+// In launches that would leave SIMDs idle, `parts` wavefronts share an image: four, two or one pooled rows each.
 // 14 of 16 columns are real: 378 MFMAs per image, 12,100 cycles of a SIMD's matrix pipe.
 // 65,536 images: 1.005 -> 0.61 ms against the fp32 MFMA kernel that staged padded planes in LDS (matrix pipe busy
 // 71 % of the cycles); two workers of 32 images: 41 -> 13 us.
 constexpr int FWD_NW = 4, FWD_NT = 64 * FWD_NW, FWD_IPW = 8;  // wavefronts per block, most images per wavefront
+// Most wavefronts per image, seven of which have a row.  Whole steps with eight against four: one worker of three images
+// 58.8 -> 57.3 us, two of 32 62.8 -> 61.6; where two of them would share a SIMD they split the filter bank twice as often: ten of
+// 100 145.9 -> 148.9.
+constexpr int FWD_PARTS = 8;
 
 // Scale of the gradients of image g, as a scalar.
 __device__ __forceinline__ float image_scale(const WorkerBuffers& wb, size_t g) { return __int_as_float(uniform(__float_as_int(wb.grad_scale[g]))); }
@@ -74,7 +78,7 @@ __global__ __launch_bounds__(FWD_NT, 2) void conv2_fwd_kernel(WorkerBuffers wb, 
     const int w = blockIdx.x / blocks_per_worker, chunk = blockIdx.x % blocks_per_worker;
     const int unit = chunk * FWD_NW + wave, t_begin = unit % parts * 8 / parts, t_end = min(P2_W, t_begin + 8 / parts);
     const int B = wb.B, s_begin = unit / parts * ipw, s_end = min(B, s_begin + ipw);
-    if (s_begin >= s_end) return;
+    if (s_begin >= s_end || t_begin >= t_end) return;
     FwdImage& im = images[wave];
     const float* __restrict__ W2 = worker_theta(wb, w) + OFF_W2;
 
@@ -845,7 +849,7 @@ __global__ __launch_bounds__(256, 2) void backward_kernel(WorkerBuffers wb, BwdS
 
 void launch_conv2_fwd(const WorkerBuffers& wb, hipStream_t s)
 {
-    const ImageSplit sp = split_images(wb, FWD_IPW, 4, FWD_NW, true);
+    const ImageSplit sp = split_images(wb, FWD_IPW, FWD_PARTS, FWD_NW, true);
     hipLaunchKernelGGL(conv2_fwd_kernel, dim3(wb.n * sp.blocks), dim3(FWD_NT), 0, s, wb, sp.blocks, sp.images, sp.wavefronts);
 }
 

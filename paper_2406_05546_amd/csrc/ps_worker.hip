@@ -97,7 +97,7 @@ __global__ __launch_bounds__(256) void keep_mask_kernel(uint8_t* keep, int B, ui
 
 // Wavefronts take as many images (up to `most_images`) as leave two wavefronts for every SIMD: what one does once per
 // launch, reading and splitting a filter bank above all, takes up to a quarter of an image's time.  Where there is not
-// one for every SIMD, as many (1, 2 or 4, up to `most_wavefronts`) share an image as still find SIMDs to run on, one
+// one for every SIMD, as many (a power of two up to `most_wavefronts`) share an image as still find SIMDs to run on, one
 // each; the kernels count on those having that image alone.
 // A launch of nothing else (`alone`) lasts as long as the compute unit with the most blocks: it takes fewer images at a time
 // where that makes its share smaller.  100 workers of 128 images: conv1 70 -> 60 us, conv2's forward pass 142 -> 128

@@ -108,6 +108,35 @@ def test_gradients_repeat_bit_for_bit(ps, n, B):
         ps.ps_destroy(ctx)
 
 
+# both sides of the lines at which eight, four and two wavefronts share an image: 128, 256 and 512 images
+@pytest.mark.parametrize("n,B", [(1, 1), (2, 64), (1, 129), (2, 128), (1, 257), (4, 128), (1, 513), (2, 256), (1, 1025)])
+def test_images_that_wavefronts_share(ps, n, B):
+    """The maps and winners of conv1 and conv2 have the same bytes in a launch of n workers and among so many that no image is shared."""
+    import torch
+    many = n + 1024 // B + 1
+    g = torch.Generator(device="cuda")
+    g.manual_seed(17 * n + B)
+    x = torch.rand(many, B, ps.IMAGE_PIXELS, device="cuda", generator=g)
+    y = torch.randint(0, 10, (many, B), device="cuda", generator=g, dtype=torch.int32)
+    seen = []
+    ctx = ps.ps_init(ps.make_config(many, B, 1, many, DROP_SEED, P_DROP))
+    try:
+        ps.ps_set_weights(ctx, synth.he_uniform_theta(5))
+        for k in (many, n):
+            q = ps.worker_grads_batched(ctx, range(k), [0] * k, [synth.minibatch_id(w, 0) for w in range(k)], x[:k], y[:k])
+            ps.ps_sync(ctx)
+            seen.append([])
+            for i in (0, n - 1):
+                act, dbg = ps.ps_debug_last_activations(ctx, i), ps.ps_debug_last_batch(ctx, i)
+                seen[-1] += [act["pool1_val"].copy(), act["pool2_val"].copy(), dbg["pool1"].copy(), dbg["pool2"].copy()]
+            for e in q:
+                ps.ps_apply_async(ctx, e, 0.0)
+        for one, other in zip(*seen):
+            np.testing.assert_array_equal(one, other)
+    finally:
+        ps.ps_destroy(ctx)
+
+
 # both sides of the lines between 128 x 64 and 128 x 128 tiles next to conv2's gradients, and between those and a launch of
 # their own; whole stages and a remainder
 @pytest.mark.parametrize("n", [10, 11, 42, 43])
