@@ -661,14 +661,16 @@ __device__ __forceinline__ void conv2_dw_block(const WorkerBuffers& wb, const Bw
     auto load_row = [&](int s, int set, int R, float (&v)[6]) {
         const int image = one_image ? 0 : set;
         if (one_image) R += 8 * set;
-        const bool here = s + image < s_end && R >= 0;
-        const Buffer b = buffer_of(wb.p1 + ((size_t)w * B + (here ? s + image : s_begin)) * P1_SIZE, here ? P1_SIZE * 4 : 0);
-        const uint32_t row = (uint32_t)max(R, 0) * ROW_BYTES;
-        v[0] = buffer_float(b, at_first, row);
+        // a descriptor of the row alone: a map's own would have to take the row as the scalar offset, of which the compiler's
+        // definition says that bounds do not count it, and rows 14 to 16 are the next image's
+        const bool here = s + image < s_end && R >= 0 && R < P1_W;
+        const float* row = wb.p1 + ((size_t)w * B + (here ? s + image : s_begin)) * P1_SIZE + (here ? R * P1_W * C1 : 0);
+        const Buffer b = buffer_of(row, here ? ROW_BYTES : 0);
+        v[0] = buffer_float(b, at_first);
 #pragma unroll
-        for (int k = 0; k < 2; ++k) v[1 + k] = buffer_float(b, at, row + k * POS_BYTES);
+        for (int k = 0; k < 2; ++k) v[1 + k] = buffer_float(b, at + k * POS_BYTES);
 #pragma unroll
-        for (int k = 0; k < 3; ++k) v[3 + k] = buffer_float(b, at_last, row + k * POS_BYTES);
+        for (int k = 0; k < 3; ++k) v[3 + k] = buffer_float(b, at_last + k * POS_BYTES);
     };
     // map rows of a step: 2py + 2 and 2py + 1; SHARED, the two that tap row dy0 meets
     const int even_row = SHARED && dy0 < 2 ? 0 : 2, odd_row = SHARED && dy0 == 0 ? -1 : 1;
@@ -685,9 +687,9 @@ __device__ __forceinline__ void conv2_dw_block(const WorkerBuffers& wb, const Bw
             const Buffer d = buffer_of(wb.dp2g + g * P2_SIZE, P2_SIZE * 4);
             const Buffer b = buffer_of(reinterpret_cast<const float*>(wb.am2 + g * AM2_SIZE), here ? AM2_SIZE : 0);
 #pragma unroll
-            for (int k = 0; k < 7; ++k) buffer_to_lds16(d, im.dp2[image] + 256 * k, 16 * lane, 1024 * k);
+            for (int k = 0; k < 7; ++k) buffer_to_lds16(d, im.dp2[image] + 256 * k, 16 * lane + 1024 * k);
 #pragma unroll
-            for (int k = 0; k < 2; ++k) buffer_to_lds16(b, im.am2[image] + 1024 * k, 16 * lane, 1024 * k);
+            for (int k = 0; k < 2; ++k) buffer_to_lds16(b, im.am2[image] + 1024 * k, 16 * lane + 1024 * k);
         }
     };
     // windows px = 4 (q % 2) .. + 3 of half q / 2 (px = 7: whatever follows, masked)

@@ -188,9 +188,9 @@ __device__ __forceinline__ Buffer buffer_of(const float* base, uint32_t bytes)
 {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), 0, (int)bytes, 0x00020000);
 }
-__device__ __forceinline__ float buffer_float(Buffer b, uint32_t offset, uint32_t uniform_offset = 0)
+__device__ __forceinline__ float buffer_float(Buffer b, uint32_t offset)
 {
-    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(b, (int)offset, (int)uniform_offset, 0));
+    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(b, (int)offset, 0, 0));
 }
 __device__ __forceinline__ floatx4 buffer_float4(Buffer b, uint32_t offset)
 {
@@ -198,9 +198,9 @@ __device__ __forceinline__ floatx4 buffer_float4(Buffer b, uint32_t offset)
 }
 
 // 16 bytes for every lane straight to LDS, one behind the other from `lds` (uniform) on; there once vmcnt says so.
-__device__ __forceinline__ void buffer_to_lds16(Buffer b, void* lds, uint32_t offset, uint32_t uniform_offset)
+__device__ __forceinline__ void buffer_to_lds16(Buffer b, void* lds, uint32_t offset)
 {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(b, (__attribute__((address_space(3))) void*)lds, 16, (int)offset, (int)uniform_offset, 0, 0);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(b, (__attribute__((address_space(3))) void*)lds, 16, (int)offset, 0, 0, 0);
 }
 
 // LDS written by some lanes of a wavefront and read by others of the same wavefront.

@@ -84,6 +84,37 @@ def test_conv2_weight_gradient_forms(ps, n, B):
         ps.ps_destroy(ctx)
 
 
+# the forms above, with a worker behind every worker
+@pytest.mark.parametrize("n,B", [(2, 1), (2, 3), (4, 64), (2, 65), (2, 129), (30, 7), (40, 66)])
+def test_rows_below_a_map_are_zero(ps, n, B):
+    """Rows 14 to 16 of a worker's last map are the first of the next worker's: whether those are infinite must not show."""
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(23 * n + B)
+    x = torch.rand(n, B, ps.IMAGE_PIXELS, device="cuda", generator=g)
+    y = torch.randint(0, 10, (n, B), device="cuda", generator=g, dtype=torch.int32)
+    theta = synth.he_uniform_theta(5)
+    broken = theta.copy()
+    broken[144:160] = np.inf  # conv1's bias
+    ctx = ps.ps_init(ps.make_config(n, B, 2, n, DROP_SEED, P_DROP))
+    try:
+        ps.ps_set_weights(ctx, theta)
+        ps.ps_load_snapshot(ctx, 1, broken, 0)
+        seen = []
+        for other in (0, 1):
+            q = ps.worker_grads_batched(ctx, range(n), [0, other] * (n // 2), [synth.minibatch_id(w, 0) for w in range(n)], x, y)
+            ps.ps_sync(ctx)
+            assert np.isinf(ps.ps_debug_last_activations(ctx, 1)["pool1_val"]).all() == (other == 1)
+            seen.append([ps.ps_get_grad(ctx, q[i]) for i in (0, n - 2)])
+            for e in q:
+                ps.ps_apply_async(ctx, e, 0.0)
+        for one, among in zip(*seen):
+            assert np.isfinite(one).all()
+            np.testing.assert_array_equal(one, among)
+    finally:
+        ps.ps_destroy(ctx)
+
+
 # several pairs of images for a wavefront, with fc1's blocks next to them and without
 @pytest.mark.parametrize("n,B", [(22, 166), (19, 176), (50, 166)])
 def test_gradients_repeat_bit_for_bit(ps, n, B):
