@@ -581,7 +581,10 @@ __device__ __forceinline__ DwGrads dw_grads(const floatx4& pooled, uint32_t byte
 }
 
 // The same as conv2_fwd_again for the sums over images [s_begin, s_end) of worker w: output channels 16 mt + 4q + i,
-// input channel l16, tap 0..8.  The sums are times `scale`.
+// input channel l16, tap 0..8.  The sums are times `scale`.  An infinite activation does not count: d2 is zero at every place that
+// sees it, whose products are left out (as where windows are multiplied, of which most places never meet an operand), or NaN,
+// which is in the sums without it.  Were it neither, an infinite pool2 value would have come of it, and with that an image
+// whose fc1 units are all off or whose logits are not numbers.
 __device__ __forceinline__ void conv2_dw_again(const WorkerBuffers& wb, int w, int s_begin, int s_end, int mt, int tap, float scale, int lane, floatx4& sums)
 {
     const uint32_t which = lost_sums<4, 4>(sums);
@@ -599,7 +602,7 @@ __device__ __forceinline__ void conv2_dw_again(const WorkerBuffers& wb, int w, i
             const int yy = y + tap / 3 - 1, xx = x + tap % 3 - 1;
             const bool inside = yy >= 0 && yy < P1_W && xx >= 0 && xx < P1_W;
             const float v = wb.p1[g * P1_SIZE + (inside ? yy * P1_W + xx : 0) * C1 + l16];
-            again = __builtin_amdgcn_mfma_f32_16x16x4f32(winner ? d : 0.f, inside ? v : 0.f, again, 0, 0, 0);
+            again = __builtin_amdgcn_mfma_f32_16x16x4f32(winner ? d : 0.f, inside && fabsf(v) < INFINITY ? v : 0.f, again, 0, 0, 0);
         }
         if (!worth_going_on<4>(which, again)) break;
     }

@@ -18,7 +18,8 @@
 // and so in every sum it enters; a0b0 can be infinite where a*b, within 2^-8 of the largest float, is not; and parts
 // are multiples of 2^-133, so that operands below 2^-110 lose bits.  The kernels look for sums that are not finite, and
 // for tiles whose sums are all below 2^-80 and not all zero, and form them again with fp32 matrix instructions, a
-// wavefront's tile at a time, until those are NaN.  What small operands take from the sums of another tile is below
+// wavefront's tile at a time, until those are NaN.  (They multiply zeros by infinities, all but conv2's weight gradient, whose
+// gradients of zero take nothing out of an infinite activation: its sparse products leave most zeros out.)  What small operands take from the sums of another tile is below
 // 2^-24 of its largest with up to 2^11 products and the other operands below 2^20.  Operands below 2^-134, which hold
 // at most 15 bits, count as zero in a tile that has no others (no weight that is a normal number is changed by such
 // gradients).  Images that are classified with margins of 60 and more have such gradients: conv2's gradient kernels

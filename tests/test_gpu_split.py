@@ -115,6 +115,38 @@ def test_rows_below_a_map_are_zero(ps, n, B):
         ps.ps_destroy(ctx)
 
 
+@pytest.mark.parametrize("n,B", [(1, 1), (2, 3), (3, 64), (1, 65), (2, 129), (30, 7), (40, 66)])
+def test_infinite_activations_that_no_gradient_meets(ps, n, B):
+    """A gradient of zero takes nothing out of an infinite pool1 value, wherever the winner of its window is.  (Channel 13
+    has two infinite values in an image; they make the outputs that see them minus infinity, which win nothing.)"""
+    import torch
+    theta = synth.he_uniform_theta(5)
+    theta[13 * 9:14 * 9] = 0
+    theta[13 * 9 + 4] = 5e37
+    theta[160:4768].reshape(32, 16, 9)[:, 13] = -1.2e-38
+    theta[4768:4800] = 1.0
+    g = torch.Generator(device="cuda")
+    g.manual_seed(29 * n + B)
+    x = torch.rand(n, B, ps.IMAGE_PIXELS, device="cuda", generator=g)
+    x.scatter_(-1, torch.randint(0, ps.IMAGE_PIXELS, (n, B, 2), device="cuda", generator=g), 8.0)
+    y = torch.randint(0, 10, (n, B), device="cuda", generator=g, dtype=torch.int32)
+    ctx = ps.ps_init(ps.make_config(n, B, 1, n, DROP_SEED, P_DROP))
+    try:
+        ps.ps_set_weights(ctx, theta)
+        q = ps.worker_grads_batched(ctx, range(n), [0] * n, [synth.minibatch_id(w, 0) for w in range(n)], x, y)
+        ps.ps_sync(ctx)
+        for i in {0, n - 1}:
+            d2, u = _d2(ps, ctx, i)
+            inf, finite = torch.isinf(u).double(), torch.where(torch.isinf(u), 0.0, u)
+            assert inf.any() and torch.isfinite(d2).all() and d2.any()
+            assert not torch.matmul((d2 != 0).double(), inf.transpose(1, 2)).any()
+            want, size = (torch.matmul(f(d2), f(finite).transpose(1, 2)).sum(0).flatten() for f in (lambda t: t, torch.abs))
+            got = torch.from_numpy(ps.ps_get_grad(ctx, q[i])[OFF_W2:OFF_B2]).cuda().double()
+            assert bool(((got - want).abs() <= 2.5 * 2.0 ** -24 * 1568 ** 0.5 * size + 1568 * 2.0 ** -150).all())
+    finally:
+        ps.ps_destroy(ctx)
+
+
 # several pairs of images for a wavefront, with fc1's blocks next to them and without
 @pytest.mark.parametrize("n,B", [(22, 166), (19, 176), (50, 166)])
 def test_gradients_repeat_bit_for_bit(ps, n, B):
