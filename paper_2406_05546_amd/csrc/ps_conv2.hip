@@ -624,9 +624,12 @@ union DwShared {
 };
 
 // SHARED: a launch that would leave SIMDs idle has six blocks for a slot, one for every (tap row, half of the
-// output channels); each sum is formed as in the one block, only fewer of them.  Up to three wavefronts for four SIMDs
-// (two workers of 256 images, which has as many: 34 us shared, 39 not; one of 256: 23 and 36; with more, three of 64 20
-// and 18, three of 100 27 and 24, four of 256 53 and 44).
+// output channels); each sum is formed as in the one block, only fewer of them.  A share repeats its images' splits, so what
+// it saves grows with the images of a wavefront.  Whole steps, shared and not: up to three wavefronts for four SIMDs one worker
+// of 64 images 56.0 and 56.9 us, of 128 71.7 and 77.3, of 256 86.6 and 101.6, two of 128 87.4 and 87.8, of 256 103.7 and
+// 113.6 (but two of 64 61.6 and 60.9).  With more, three of 64 68.4 and 67.2, of 100 95.4 and 93.4; but where a wavefront has three
+// images and more, up to four and a half for four SIMDs three of 160 104.8 and 108.2, of 192 126.3 and 126.0, of 288
+// 148.9 and 154.3, of 512 188.6 and 194.1, and beyond, four of 192 134.6 and 131.2, of 256 148.5 and 143.0.
 constexpr int DW_SHARES = 6;
 
 template <bool SHARED>
@@ -657,13 +660,12 @@ __device__ __forceinline__ void conv2_dw_block(const WorkerBuffers& wb, const Bw
     // columns 4q - 1 .. 4q + 4; the first of them, and the last three of the last quarter, are outside the map
     const uint32_t at = (uint32_t)(4 * q) * POS_BYTES + 4 * l16, at_first = q == 0 ? BUFFER_NOWHERE : at - POS_BYTES;
     const uint32_t at_last = q == 3 ? BUFFER_NOWHERE : at + 2 * POS_BYTES;
-    // What the two halves of a contraction are: two images, or, where a wavefront has but one, the upper four rows of
+    // What the two halves of a contraction are: two images, or, where a wavefront has but one left, the upper four rows of
     // windows of it and the lower three.
-    const bool one_image = ipw == 1;
-    const int steps = one_image ? 4 : P2_W, stride = one_image ? 1 : 2;
+    auto alone = [&](int s) { return s + 1 >= s_end; };
     auto load_row = [&](int s, int set, int R, float (&v)[6]) {
-        const int image = one_image ? 0 : set;
-        if (one_image) R += 8 * set;
+        const int image = alone(s) ? 0 : set;
+        if (alone(s)) R += 8 * set;
         // a descriptor of the row alone: a map's own would have to take the row as the scalar offset, of which the compiler's
         // definition says that bounds do not count it, and rows 14 to 16 are the next image's
         const bool here = s + image < s_end && R >= 0 && R < P1_W;
@@ -680,25 +682,20 @@ __device__ __forceinline__ void conv2_dw_block(const WorkerBuffers& wb, const Bw
     float even[2][6], odd[2][6];
     DwImages& im = lds.images[wave];
     // The images' gradients and bytes straight to LDS: by lanes, as they are used, each would touch 64 cache lines for a
-    // quarter KB.  An image that does not exist has no active windows.
+    // quarter KB.
     auto bring_images = [&](int s) {
 #pragma unroll
         for (int image = 0; image < 2; ++image) {
-            if (one_image && image == 1) break;
-            const bool here = s + image < s_end;
-            const size_t g = (size_t)w * B + (here ? s + image : s_begin);
+            if (alone(s) && image == 1) break;
+            const size_t g = (size_t)w * B + s + image;
             const Buffer d = buffer_of(wb.dp2g + g * P2_SIZE, P2_SIZE * 4);
-            const Buffer b = buffer_of(reinterpret_cast<const float*>(wb.am2 + g * AM2_SIZE), here ? AM2_SIZE : 0);
+            const Buffer b = buffer_of(reinterpret_cast<const float*>(wb.am2 + g * AM2_SIZE), AM2_SIZE);
 #pragma unroll
             for (int k = 0; k < 7; ++k) buffer_to_lds16(d, im.dp2[image] + 256 * k, 16 * lane + 1024 * k);
 #pragma unroll
             for (int k = 0; k < 2; ++k) buffer_to_lds16(b, im.am2[image] + 1024 * k, 16 * lane + 1024 * k);
         }
     };
-    // windows px = 4 (q % 2) .. + 3 of half q / 2 (px = 7: whatever follows, masked)
-    const int image_of = one_image ? 0 : q >> 1, py_of = one_image ? 4 * (q >> 1) : 0;
-    const float* const pooled = im.dp2[image_of] + (16 * mt0 + l16) * P2_POS + py_of * P2_W + 4 * (q & 1);
-    const uint8_t* const bytes = im.am2[image_of] + ((16 * mt0 + l16) * P2_W + py_of) * AM2_PITCH + 4 * (q & 1);
     auto load_rows = [&](int s, int py) {
 #pragma unroll
         for (int image = 0; image < 2; ++image) {
@@ -711,7 +708,13 @@ __device__ __forceinline__ void conv2_dw_block(const WorkerBuffers& wb, const Bw
         bring_images(s_begin);
         load_rows(s_begin, 0);
     }
-    for (int s = s_begin; s < s_end; s += stride) {
+    for (int s = s_begin; s < s_end; s += 2) {
+        const bool one_image = alone(s);
+        const int steps = one_image ? 4 : P2_W;
+        // windows px = 4 (q % 2) .. + 3 of half q / 2 (px = 7: whatever follows, masked)
+        const int image_of = one_image ? 0 : q >> 1, py_of = one_image ? 4 * (q >> 1) : 0;
+        const float* const pooled = im.dp2[image_of] + (16 * mt0 + l16) * P2_POS + py_of * P2_W + 4 * (q & 1);
+        const uint8_t* const bytes = im.am2[image_of] + ((16 * mt0 + l16) * P2_W + py_of) * AM2_PITCH + 4 * (q & 1);
         DwRows rows;
         rows.clear<1>();  // row -1
         if (!SHARED) {
@@ -728,7 +731,7 @@ __device__ __forceinline__ void conv2_dw_block(const WorkerBuffers& wb, const Bw
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the images are in LDS
 #pragma unroll 1
         for (int py = 0; py < steps; ++py) {
-            const int next_s = py + 1 < steps ? s : s + stride, next_py = py + 1 < steps ? py + 1 : 0;
+            const int next_s = py + 1 < steps ? s : s + 2, next_py = py + 1 < steps ? py + 1 : 0;
             DwGrads d2[MTS];
 #pragma unroll
             for (int mt = 0; mt < MTS; ++mt) {
@@ -742,7 +745,7 @@ __device__ __forceinline__ void conv2_dw_block(const WorkerBuffers& wb, const Bw
                 // what comes straight to LDS does not wait for reads that are on their way: with fc1's blocks next to this one
                 // they were late enough, now and then, to find the next image
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-                if (s + stride < s_end) bring_images(s + stride);
+                if (s + 2 < s_end) bring_images(s + 2);
             }
 #pragma unroll
             for (int dy = 0; dy < DYS; ++dy) {
@@ -860,13 +863,10 @@ void launch_conv2_fwd(const WorkerBuffers& wb, hipStream_t s)
 
 int conv1_part_slots(int batch) { return batch; }
 
-// Images per wavefront: one, or an even number, which are then taken in pairs.  One image in halves takes four k-steps,
-// two in a pair seven: for up to 64 images, wavefronts of one each are more in number and done sooner (16 workers of 64
-// images: 23.6 us against 28.7 with pairs, of which there are half as many).
-static int conv2_dw_ipw(int batch)
-{
-    return batch <= DW_NW * DW_MAX_SLOTS ? 1 : 2 * ((batch + 2 * DW_NW * DW_MAX_SLOTS - 1) / (2 * DW_NW * DW_MAX_SLOTS));
-}
+// Images per wavefront.  They are taken in pairs, seven k-steps each, and the last of an odd number in halves, in four.  (An even
+// number in its place is fewer and longer wavefronts: one worker of 160 images 76.7 against 80.9 us, five of 192 138 and 143, five of
+// 320 178 and 182; large launches, which lose the empty half of a k-step, 64 of 192 885 against 871, 256 of 160 3009 and 2969.)
+static int conv2_dw_ipw(int batch) { return (batch + DW_NW * DW_MAX_SLOTS - 1) / (DW_NW * DW_MAX_SLOTS); }
 
 int conv2_part_slots(int batch)
 {
@@ -897,7 +897,7 @@ void launch_backward(const WorkerBuffers& wb, hipStream_t s)
     sh.dx_blocks = wb.n * sh.dx_blocks_per_worker;
     sh.dw_slots = conv2_part_slots(wb.B);
     sh.dw_ipw = conv2_dw_ipw(wb.B);
-    sh.dw_shared = DW_SHARES * DW_NW * wb.n * sh.dw_slots <= 3 * wb.compute_units;
+    sh.dw_shared = 2 * DW_SHARES * DW_NW * wb.n * sh.dw_slots <= (sh.dw_ipw < 3 ? 6 : 9) * wb.compute_units;
     sh.dw_blocks = wb.n * sh.dw_slots * (sh.dw_shared ? DW_SHARES : 1);
     const Fc1DwWhere where = fc1_dw_where(wb);
     if (where == FC1_DW_FEW)

@@ -59,8 +59,8 @@ def test_conv2_weight_gradient_error(ps, n, B, share, fp32):
         ps.ps_destroy(ctx)
 
 
-# wavefronts of one image, and of pairs of which the last is incomplete; few blocks for a tap row each, and many for all
-@pytest.mark.parametrize("n,B", [(1, 1), (2, 3), (3, 64), (1, 65), (2, 129), (30, 7), (40, 66), (40, 130)])
+# wavefronts of one image, of pairs, and of pairs and one, and with fewer images than the others; few blocks for a tap row each, and many for all
+@pytest.mark.parametrize("n,B", [(1, 1), (2, 3), (3, 64), (1, 65), (2, 129), (3, 131), (3, 192), (4, 192), (2, 257), (30, 7), (40, 66), (40, 130)])
 def test_conv2_weight_gradient_forms(ps, n, B):
     """d W2 within the error of fp32 matrix instructions (1.5e-7, above), d b2 within four roundings of 2^-24: a lane
     adds a value for a row of windows, seven of an image."""

@@ -44,6 +44,19 @@ def test_workspace_bytes_and_argument_checks_without_a_gpu():
     assert len(names) == 17 and len(set(names)) == 17 and lib.ps_profile_kernel_name(99) == b""
 
 
+# odd and even numbers of images per wavefront, and batches that the last of them does not fill
+@pytest.mark.parametrize("B", [1, 16, 63, 65, 128, 129, 160, 192, 193, 256, 257, 320, 384, 448, 1024])
+def test_a_batch_is_cut_into_as_many_wavefronts_as_there_are_slots_for(B):
+    """A slot of conv2's weight gradient is four wavefronts of ceil(B / 64) images: an even number in its place, as pairs of
+    images would have it, leaves batches of 129-192, 257-320 and 385-448 with fewer and longer wavefronts, and one to five
+    workers of them 3-5 % slower.  The workspace says how many slots there are."""
+    def workspace(batch):
+        return ps.ps_workspace_bytes(ps.make_config(max_workers=64, batch=batch, n_versions=1, queue_capacity=64, seed=1))
+    image = workspace(64) - workspace(63)              # both have 16 slots of 4640 floats for each of the 64 workers
+    slots = 16 + (workspace(B) - workspace(64) - (B - 64) * image) / (64 * 4640 * 4)
+    assert slots == -(-B // (4 * -(-B // 64)))
+
+
 def test_minibatches_depend_only_on_logical_ids():
     x, y = synth.minibatch(3, synth.minibatch_id(2, 5), 8)
     assert x.dtype == np.float32 and y.dtype == np.int32 and x.shape == (8, 784)
