@@ -147,8 +147,8 @@ def test_infinite_activations_that_no_gradient_meets(ps, n, B):
         ps.ps_destroy(ctx)
 
 
-# several pairs of images for a wavefront, with fc1's blocks next to them and without
-@pytest.mark.parametrize("n,B", [(22, 166), (19, 176), (50, 166)])
+# several pairs of images for a wavefront, in shares, with fc1's blocks of either width next to them and without
+@pytest.mark.parametrize("n,B", [(1, 256), (10, 166), (22, 166), (19, 176), (50, 166)])
 def test_gradients_repeat_bit_for_bit(ps, n, B):
     """The next images must not take the place of those that a wavefront still reads."""
     import torch
@@ -196,6 +196,36 @@ def test_images_that_wavefronts_share(ps, n, B):
                 ps.ps_apply_async(ctx, e, 0.0)
         for one, other in zip(*seen):
             np.testing.assert_array_equal(one, other)
+    finally:
+        ps.ps_destroy(ctx)
+
+
+# one, two, four and eight images of a worker to a wavefront of conv2's forward pass, the last with fewer, and one or two of conv1's
+@pytest.mark.parametrize("n,B", [(100, 30), (99, 50), (39, 129), (109, 101), (113, 200), (128, 121)])
+def test_images_of_a_wavefront(ps, n, B):
+    """The maps and winners of conv1 and conv2 have the same bytes in a launch of n workers and in one of a worker alone."""
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(31 * n + B)
+    x = torch.rand(n, B, ps.IMAGE_PIXELS, device="cuda", generator=g)
+    y = torch.randint(0, 10, (n, B), device="cuda", generator=g, dtype=torch.int32)
+    ctx = ps.ps_init(ps.make_config(n, B, 1, n + 3, DROP_SEED, P_DROP))
+
+    def maps(i):
+        ps.ps_sync(ctx)
+        act, dbg = ps.ps_debug_last_activations(ctx, i), ps.ps_debug_last_batch(ctx, i)
+        return [act["pool1_val"].copy(), act["pool2_val"].copy(), dbg["pool1"].copy(), dbg["pool2"].copy()]
+
+    try:
+        ps.ps_set_weights(ctx, synth.he_uniform_theta(5))
+        mbs = [synth.minibatch_id(w, 0) for w in range(n)]
+        ps.worker_grads_batched(ctx, range(n), [0] * n, mbs, x, y)
+        workers = (0, n // 2, n - 1)
+        among = [maps(i) for i in workers]
+        for i, want in zip(workers, among):
+            ps.worker_grads_batched(ctx, [i], [0], [mbs[i]], x[i:i + 1], y[i:i + 1])
+            for one, other in zip(want, maps(0)):
+                np.testing.assert_array_equal(one, other)
     finally:
         ps.ps_destroy(ctx)
 
@@ -302,7 +332,8 @@ def test_a_diverged_network_is_not_slow(ps, n, B, what):
 # ------------------------------------------------------- every contraction against 64 bits on its own operands
 
 OFF_W3, OFF_B3 = 4800, 807616
-LAYERS = ("conv2 forward", "fc1 forward", "fc1 input gradient", "fc1 weight gradient", "conv2 input gradient", "conv2 weight gradient")
+LAYERS = ("conv2 forward", "fc1 forward", "fc1 input gradient", "fc1 weight gradient", "conv2 input gradient", "conv2 weight gradient",
+          "conv2 bias gradient")
 
 
 def _results(ps, ctx, i, q, theta, x):
@@ -325,10 +356,10 @@ def _results(ps, ctx, i, q, theta, x):
         w1 = torch.zeros(B, 16, 196, 4, device="cuda", dtype=torch.float64).scatter_(-1, (code1 & 3).unsqueeze(-1), dp1.unsqueeze(-1))
         d1 = w1.view(B, 16, 14, 14, 2, 2).permute(0, 1, 2, 4, 3, 5).reshape(B, 16, 784)
         out = (z, (p2 @ W3.t() + b3).clamp_min(0), d3 @ W3 * ((code2 & 4) > 0).view(B, 1568), d3.t() @ p2,
-               torch.matmul(d1, f(pix).transpose(1, 2)).sum(0), torch.matmul(f(d2), f(u).transpose(1, 2)).sum(0))
+               torch.matmul(d1, f(pix).transpose(1, 2)).sum(0), torch.matmul(f(d2), f(u).transpose(1, 2)).sum(0), f(d2).sum((0, 2)))
         return [t.flatten().cpu().numpy() for t in out]
 
-    got = (act["pool2_val"], dbg["hdrop"], act["dpool2"], grad[OFF_W3:OFF_B3], grad[:144], grad[OFF_W2:OFF_B2])
+    got = (act["pool2_val"], dbg["hdrop"], act["dpool2"], grad[OFF_W3:OFF_B3], grad[:144], grad[OFF_W2:OFF_B2], grad[OFF_B2:OFF_W3])
     return {k: (g.astype(np.float64).ravel(), w, m) for k, g, w, m in zip(LAYERS, got, layers(lambda t: t), layers(torch.abs))}
 
 
@@ -456,7 +487,7 @@ def test_tiny_gradients_among_others(ps, n, B):
     labels[:, ::3] = 3
     labels[:, 1] = 3
     broken, _ = _run(ps, theta, n, B, labels=labels)
-    _compare(broken, ("conv2 forward", "fc1 forward", "fc1 weight gradient", "conv2 input gradient", "conv2 weight gradient"), 2.0 ** -100)
+    _compare(broken, ("conv2 forward", "fc1 forward", "fc1 weight gradient", "conv2 input gradient", "conv2 weight gradient", "conv2 bias gradient"), 2.0 ** -100)
 
 
 @pytest.mark.parametrize("n,B", [(20, 40), (80, 40), (70, 130), (4, 256)])
