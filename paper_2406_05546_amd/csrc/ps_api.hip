@@ -91,7 +91,7 @@ Layout make_layout(const ps_config& c)
     l.z = k.take(n * NCLS * 4);
     l.pred = k.take(n * 4);
     l.d3 = k.take(n * FC1 * 4);
-    l.dp2g = k.take(n * P2_SIZE * 4 + 16);  // conv2's weight gradient reads rows of 7 in pieces of 4
+    l.dp2g = k.take(n * P2_SIZE * 4);
     l.gscale = k.take(n * 4);
     l.part = k.take((uint64_t)c.max_workers * conv2_part_slots(c.batch) * CONV2_PART * 4);
     l.part1 = k.take((uint64_t)c.max_workers * conv1_part_slots(c.batch) * OFF_W2 * 4);

@@ -26,7 +26,7 @@ namespace {
 // In launches that would leave SIMDs idle, `parts` wavefronts share an image: four, two or one pooled rows each.
 // 14 of 16 columns are real: 378 MFMAs per image, 12,100 cycles of a SIMD's matrix pipe.
 // 65,536 images: 1.005 -> 0.61 ms against the fp32 MFMA kernel that staged padded planes in LDS (matrix pipe busy
-// 71 % of the cycles); two workers of 32 images: 41 -> 13 us.
+// 69 % of the cycles); two workers of 32 images: 41 -> 13 us.
 constexpr int FWD_NW = 4, FWD_NT = 64 * FWD_NW, FWD_IPW = 8;  // wavefronts per block, most images per wavefront
 // Most wavefronts per image, seven of which have a row.  Whole steps with eight against four: one worker of three images
 // 58.8 -> 57.3 us, two of 32 62.8 -> 61.6; where two of them would share a SIMD they split the filter bank twice as often: ten of
@@ -208,9 +208,9 @@ __global__ __launch_bounds__(FWD_NT, 2) void conv2_fwd_kernel(WorkerBuffers wb, 
 // image: the sum over rows 0-6 plus the sum over rows 7-13.  In launches that would leave SIMDs idle, two
 // wavefronts of a block share an image, a half each, and add up the same two sums: nothing depends on how a
 // launch is cut up.
-// 65,536 images, this and the weight gradient: 2.09 -> 1.35 ms against the fp32 MFMA kernels (this one in two-wavefront
-// blocks), matrix pipe busy 57 % of the cycles; two workers of 32 images: 87 -> 16 us (a wavefront walked eight images
-// there, now one).
+// 65,536 images, this and the weight gradient when both were dense: 2.09 -> 1.35 ms against the fp32 MFMA kernels (this one in
+// two-wavefront blocks); two workers of 32 images: 87 -> 16 us (a wavefront walked eight images there, now one).  The
+// scratch that the compiler reports for the launch is a pair of registers, kept there outside the loops of products.
 constexpr int DX_NW = 4, DX_NT = 64 * DX_NW, DX_IPW = 8;  // wavefronts per block, most images per wavefront
 constexpr int DX_XW = 30, DX_XS = 30 * DX_XW + 16;        // padded input image (and what lanes 14, 15 read past it)
 // A d2 operand lane holds eight output channels 8q + DX_CHANNEL(i); the order is the one in which a word of
@@ -484,9 +484,11 @@ __device__ __forceinline__ void conv2_dx_block(const WorkerBuffers& wb, const Bw
 // The 72 registers of a second accumulator (ps_split.h) do not fit next to the operands: the five small terms of
 // a k-step are summed from zero and added on the vector ALU.  What is then cut off towards minus infinity is
 // of one sign, and the odd wavefronts take d2 negated and are subtracted, so that it cancels in a slot.  Against 64 bits
-// d W2 is off by 0.62-0.79e-7 (1.09-1.51e-7 with fp32 MFMAs), d b2, summed on the vector ALU, by 0.5-0.9e-7.
+// d W2 is off by 0.62-0.79e-7 (1.09-1.51e-7 with fp32 MFMAs), d b2, summed on the vector ALU, by 0.54-0.74e-7 (0.55-0.76e-7 as
+// a product with a column of ones).
 // 65,536 images, this and the input gradient: 1.35 ms with dense 16x16x32, 1.07 with the sparse form (this alone 0.73 ->
-// 0.43); 64 workers of 128 images 172 -> 139 us, 16 of 64 27.8 -> 23.6, one of 256 24.7 -> 22.7.
+// 0.43), matrix pipe busy 51 % of the cycles; 64 workers of 128 images 172 -> 139 us, 16 of 64 27.8 -> 23.6, one of 256
+// 24.7 -> 22.7.
 constexpr int DW_NW = 4, DW_NT = 64 * DW_NW, DW_MAX_SLOTS = 16;
 constexpr int DW_REGS = 2 * 9 * 4;  // sums per lane without the bias
 

@@ -12,8 +12,10 @@ constexpr int FEAT_WIDE = P2_SIZE / 128 * 128;  // 1536: features in whole 128-w
 
 // Per-worker d fc1.W[u][i] = sum_s d3[s][u] * pool2[s][i], written into the worker's queue entry.
 // Rows m are units, columns n features, so a wavefront's lanes run along contiguous memory.  STREAM: stored past the
-// caches, in launches that write more than those hold on to (64 workers of 128 images: 122 -> 112 us); in small
-// ones the update that follows reads the rows 0.4 us faster out of them.
+// caches, in launches that write more than those hold on to (64 workers of 128 images: 122 -> 112 us).  Next to conv2's
+// gradients, up to 56 workers, neither kind is ahead always, with the update that reads the rows: plain stores take 0.98-1.02 of the
+// time (16 of 64 132.8 and 132.6 us, 42 of 128 416 and 410, of 512 1306 and 1327), but for two to five workers of up to 32 images,
+// which store plainly and in wide tiles lose 1 us by it (2 of 32 58.8 and 57.5).
 template <bool STREAM>
 struct Fc1DwEpi {
     WorkerBuffers wb;
@@ -39,11 +41,20 @@ typedef GemmCfg<false, false, 1, 1, 4, 1, 2> Fc1DwEdge;
 
 // Next to conv2's gradients, which it needs as little as they need it: its blocks fill what those leave idle, and their stores
 // run under the others' products.  Tiles are counted, which depend on the workers alone: the batch is the contraction.
-// FEW workers (up to ten, less than two wide tiles for a compute unit) have 128 x 64 tiles: 8 workers of 64 images,
-// everything together, 28.5 us (64 x 64 tiles, four times as many loads and waits for them as products: 33; 128 x 128: 28.3), 5 of
-// 37 18.5 (23.5; 18.0), 1 of 256 21.9 (22.6; 25.4), 10 of 128 46.8 (53.7; 43.7).  SEVERAL (up to 42) have 128 x 128:
-// 16 of 64 44.8 us (128 x 64: 46; in a launch of its own 48-50), 20 of 64 52 (53; 66), 40 of 64 92 (97; 102), 40 of 250
-// 268 (288; 275).  With more its rows outgrow the caches: 64 of 128 243 us, in a launch of its own 229; 100 of 64 244 and 217.
+// FEW workers (up to ten, less than two wide tiles for a compute unit) have 128 x 64 tiles, SEVERAL 128 x 128.  Steps in us, with
+// the update that reads the rows:
+//   workers x images   1x64  1x256  2x100  2x256  3x192  4x256  5x37  8x64  8x256  10x128  11x64  12x256  16x64  20x256  40x128
+//   128 x 64           56.7   86.7   82.3  103.5  125.9  142.8  68.8  88.9  189.9   158.0  112.6   259.0  133.8   375.3   397.2
+//   128 x 128          57.3   91.0   86.3  109.3  129.4  145.2  68.9  89.1  188.2   156.6  113.4   260.3  132.8   368.8   388.8
+//   64 x 64            57.6   88.1   88.8  106.5  126.4  143.6  74.1  92.8  196.2   162.8  117.3   270.4
+// The narrow ones gain where a few long tiles would be what the launch waits for, the wide ones bring less for a product;
+// between eight and twelve workers either is ahead, by 1.5 % at most.
+// SEVERAL are up to 42 (eight wide tiles for a compute unit); with more, its blocks hold up conv2's in large batches, and in a
+// launch of its own the edge blocks run among the wide ones:
+//   workers x images   16x64  20x64  32x256  40x128  42x128  44x128  48x32  48x128  48x256  56x128  64x128  64x256  80x100  80x512
+//   here               132.6  168.0   551.7   385.7   410.3   433.1  220.5   463.4   804.8   548.7   594.7  1013.3   668.8  2428.2
+//   in its own         135.8  182.6   551.3   395.3   423.3   444.4  233.6   461.4   798.4   539.0   584.5  1006.0   649.9  2418.8
+// (Batches up to 64 gain here with more workers too, 2-5 %.)
 typedef GemmCfg<false, false, 2, 1, 2, 2, 2> Fc1DwFew;
 typedef Fc1DwMain Fc1DwSeveral;
 enum Fc1DwWhere { FC1_DW_FEW, FC1_DW_SEVERAL, FC1_DW_ALONE };

@@ -95,14 +95,15 @@ __global__ __launch_bounds__(256) void keep_mask_kernel(uint8_t* keep, int B, ui
 
 }  // namespace
 
-// Wavefronts take as many images (up to `most_images`) as leave two wavefronts for every SIMD: what one does once per
-// launch, reading and splitting a filter bank above all, takes up to a quarter of an image's time.  Where there is not
+// Wavefronts take as many images (up to `most_images`) as leave two wavefronts for every SIMD: each reads and splits a
+// filter bank (conv2) or reads its weights (conv1) once per launch.  Where there is not
 // one for every SIMD, as many (a power of two up to `most_wavefronts`) share an image as still find SIMDs to run on, one
 // each; the kernels count on those having that image alone.
 // A launch of nothing else (`alone`) lasts as long as the compute unit with the most blocks: it takes fewer images at a time
 // where that makes its share smaller.  100 workers of 128 images: conv1 70 -> 60 us, conv2's forward pass 142 -> 128
 // (eight images: 400 blocks, two on some compute units; one: 3200, thirteen at most); 200 of 30 37 -> 33 and 74 -> 70.  What
-// a wavefront of these does once is a sixteenth of an image's time (64 of 128, four, two and one image: 79.6, 80.8, 83.3 us).
+// a wavefront of conv2's forward pass does once is a sixteenth of an image's time (64 of 128, four, two and one image: 79.6,
+// 80.8, 83.3 us), and no more in conv1, for which the same figure serves.
 ImageSplit split_images(const WorkerBuffers& wb, int most_images, int most_wavefronts, int wavefronts_per_block, bool alone)
 {
     ImageSplit sp{most_images, 1, 0};
