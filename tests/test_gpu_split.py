@@ -150,7 +150,8 @@ def test_infinite_activations_that_no_gradient_meets(ps, n, B):
 # several pairs of images for a wavefront, in shares, with fc1's blocks of either width next to them and without
 @pytest.mark.parametrize("n,B", [(1, 256), (10, 166), (22, 166), (19, 176), (50, 166)])
 def test_gradients_repeat_bit_for_bit(ps, n, B):
-    """The next images must not take the place of those that a wavefront still reads."""
+    """The next images must not take the place of those that a wavefront still reads.  (Without the wait for those reads they
+    did now and then, at 22 workers of 166 and 19 of 176; not in every run, so that this can miss it.)"""
     import torch
     g = torch.Generator(device="cuda")
     g.manual_seed(19 * n + B)
