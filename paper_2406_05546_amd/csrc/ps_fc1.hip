@@ -54,26 +54,36 @@ struct Fc1DxEpi {
 // each), or, in the forward and the input gradient of batches up to 64, into
 // 32 x 32 tiles with a wavefront for every chunk of K (1568 = 7 x 14 stages, 512 = 4 x 8).  Whether a batch
 // is summed in chunks depends on its size alone, so that these sums have the same bits whatever else is in the
-// launch; beyond 64 the chunks' totals would not fit the registers of 64 x 64 wavefront tiles.
+// launch; beyond 64 the chunks' totals would not fit the registers of 64 x 64 wavefront tiles.  The forward pass of those
+// is summed in two parts of 784, which two sets of wavefronts form side by side wherever the wide tiles do not fill the chip twice.
 constexpr int FWD_CHUNKS = 7, FWD_CHUNK = 14, DX_CHUNKS = 4, DX_CHUNK = 8, CHUNKED_BATCH = 64;
 static_assert(FWD_CHUNKS * FWD_CHUNK * GEMM_K == P2_SIZE && DX_CHUNKS * DX_CHUNK * GEMM_K == FC1, "whole chunks");
 
 // forward: rows = 512 units (W3, k-contiguous), columns = the worker's samples (pool2, k-contiguous)
+// Beyond batches of 64, by how many tiles find a compute unit (the launch alone, us; all of K in one part: 1 x 256 23.7, 8 x 128
+// 39.8, 32 x 128 53.6, 48 x 128 74.3, 64 x 128 87.0):
+//   workers x images    1x256   8x128  16x128  16x200  24x80  32x128  24x200  40x128  48x128  56x128  64x128  72x128  256x256
+//   32 x 32, roles       18.0
+//   64 x 64, side by side        26.5    29.5    48.1   43.1    49.9    68.9    67.5    71.9    88.8
+//   128 x 128, side by side      59.2    59.4    59.5   59.1    60.3    62.3    61.0    64.3    69.5    75.6   128.1    587.9
+//   128 x 128, parts in turn                                                                            85.9   112.0    528.0
 void launch_fc1_fwd(const WorkerBuffers& wb, hipStream_t s)
 {
-    const bool few = gemm_few_tiles(FC1 / 128 * ((wb.B + 127) / 128) * wb.n, wb.compute_units);
+    const int wide_tiles = FC1 / 128 * ((wb.B + 127) / 128) * wb.n;
     const Fc1FwdEpi epi{wb};
     if (wb.B <= CHUNKED_BATCH) {
-        if (few)
+        if (gemm_few_tiles(wide_tiles, wb.compute_units))
             gemm_launch_chunks<true, true, FWD_CHUNKS, FWD_CHUNK>(FC1, wb.B, P2_SIZE, P2_SIZE, wb.n, wb.compute_units, epi, s);
         else
             gemm_launch<GemmCfg<true, true, 2, 1, 2, 2, 2>, FWD_CHUNK, 2>(FC1, wb.B, P2_SIZE, P2_SIZE, P2_SIZE, wb.n, epi, s);
     } else if (gemm_roles_fit(FC1, wb.B, wb.n, wb.compute_units)) {
-        gemm_launch_roles<true, true>(FC1, wb.B, P2_SIZE, P2_SIZE, P2_SIZE, wb.n, epi, s);
-    } else if (few) {
-        gemm_launch<GemmCfg<true, true, 1, 1, 2, 2, 4, 32>, 0, 2>(FC1, wb.B, P2_SIZE, P2_SIZE, P2_SIZE, wb.n, epi, s);
+        gemm_launch_roles<true, true, 2>(FC1, wb.B, P2_SIZE, P2_SIZE, P2_SIZE, wb.n, epi, s);
+    } else if (2 * wide_tiles <= wb.compute_units) {  // 64 x 64 tiles: two for a compute unit at most
+        gemm_launch_sides<GemmCfg<true, true, 1, 1, 2, 2, 4>>(FC1, wb.B, P2_SIZE, P2_SIZE, P2_SIZE, wb.n, epi, s);
+    } else if (wide_tiles <= wb.compute_units) {
+        gemm_launch_sides<GemmCfg<true, true, 2, 2, 2, 2, 2>>(FC1, wb.B, P2_SIZE, P2_SIZE, P2_SIZE, wb.n, epi, s);
     } else {
-        gemm_launch<GemmCfg<true, true, 2, 2, 2, 2, 2>, 0, 2>(FC1, wb.B, P2_SIZE, P2_SIZE, P2_SIZE, wb.n, epi, s);
+        gemm_launch_parts<GemmCfg<true, true, 2, 2, 2, 2, 2>, P2_SIZE>(FC1, wb.B, P2_SIZE, P2_SIZE, wb.n, epi, s);
     }
 }
 
@@ -99,7 +109,7 @@ void launch_fc1_dx(const WorkerBuffers& wb, hipStream_t s)
             gemm_launch_edge<GemmCfg<false, true, 2, 1, 2, 2, 2>, GemmCfg<false, true, 1, 1, 1, 4, 2>, false, DX_CHUNK, 2>(P2_SIZE, wb.B, FC1, P2_SIZE, FC1, wb.n,
                                                                                                           FEAT_WIDE, wb.B, epi, s);
     } else if (gemm_roles_fit(P2_SIZE, wb.B, wb.n, wb.compute_units)) {
-        gemm_launch_roles<false, true>(P2_SIZE, wb.B, FC1, P2_SIZE, FC1, wb.n, epi, s);
+        gemm_launch_roles<false, true, 1>(P2_SIZE, wb.B, FC1, P2_SIZE, FC1, wb.n, epi, s);
     } else if (few) {
         gemm_launch<GemmCfg<false, true, 1, 1, 2, 2, 4, 32>, 0, 2>(P2_SIZE, wb.B, FC1, P2_SIZE, FC1, wb.n, epi, s);
     } else {

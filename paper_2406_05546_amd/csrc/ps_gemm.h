@@ -339,6 +339,131 @@ __device__ __forceinline__ void gemm_block(const GemmShape& sh, const Epi& epi, 
             gemm_finish<Cfg::A_KC, Cfg::B_KC>(sh, epi, z, m0 + (wm * TM + a) * 32, n0 + (wn * TN + b) * 32, lane, CHUNK > 0 ? total[a][b] : acc[a][b].value());
 }
 
+// One block's tile with eight wavefronts, two to a SIMD: four form the sum over the first half of the contraction, the others
+// that over the rest, in one loop, and the sums meet in LDS.  For launches of up to one tile for a compute unit, which otherwise
+// leave every SIMD a single wavefront and its waits (64 workers of 128 images: 87 -> 76 us).  The loop is bound by issue: a stage
+// has about 100 vector instructions next to its 24 MFMAs, and the clock falls to 1.8-2.1 GHz under either.  The two fours
+// taking turns, one multiplying out of registers while the other reads, splits and writes, is slower (91 us): reads, splits and
+// writes after each other take 1,300 cycles of a SIMD to the products' 790.
+template <class Cfg, class Epi>
+__device__ __forceinline__ void gemm_sides_block(const GemmShape& sh, const Epi& epi, int block, char* __restrict__ lds)
+{
+    constexpr int TM = Cfg::TM, TN = Cfg::TN, WM = Cfg::WM, BM = Cfg::BM, BN = Cfg::BN, KS = Cfg::KS, AHEAD = Cfg::AHEAD;
+    constexpr bool HALVES = BM <= 64 && BN <= 64;  // the first two wavefronts of a four bring in A and the others B
+    using OpA = GemmOperand<BM, Cfg::A_KC, false, HALVES ? 128 : 256, KS>;
+    using OpB = GemmOperand<BN, Cfg::B_KC, false, HALVES ? 128 : 256, KS>;
+    static_assert(!HALVES || OpA::NV == OpB::NV, "one register set for either operand");
+    static_assert(AHEAD % 2 == 0, "the LDS buffer of an unrolled stage is fixed");
+
+    const int tid = threadIdx.x & 255, lane = tid & 63, wave = uniform(tid >> 6), half = uniform(threadIdx.x >> 8);
+    const int wm = wave % WM, wn = wave / WM;
+    const int v = gemm_tile(block, sh.gx * sh.gy * sh.gz);
+    if (v >= sh.gx * sh.gy * sh.gz) return;
+    const int m0 = sh.m_base + (v % sh.gx) * BM, n0 = sh.n_base + (v / sh.gx % sh.gy) * BN, z = v / (sh.gx * sh.gy);
+    const int k_first = half * (sh.K / 2), nk = sh.K / (2 * KS);
+    char* const stages = lds + half * 2 * Cfg::STAGE;
+
+    SplitSum<floatx16> acc[TM][TN];
+#pragma unroll
+    for (int a = 0; a < TM; ++a)
+#pragma unroll
+        for (int b = 0; b < TN; ++b) acc[a][b].clear();
+
+    floatx4 ra[AHEAD][OpA::NV], rb[HALVES ? 1 : AHEAD][OpB::NV];
+    const bool brings_b = HALVES && wave >= 2;
+    OpA opa;
+    OpB opb;
+    opa.init(epi.a_ptr(z), sh.lda, m0, sh.M, sh.K, HALVES ? tid & 127 : tid);
+    opb.init(epi.b_ptr(z), sh.ldb, n0, sh.N, sh.K, HALVES ? tid & 127 : tid);
+    auto load = [&](int kt, floatx4 (&a)[OpA::NV], floatx4 (&b)[OpB::NV]) {  // past the end the last stage again, which nobody reads
+        const int k = k_first + min(kt, nk - 1) * KS;
+        if (!brings_b) opa.load_at(k, a);
+        if constexpr (!HALVES)
+            opb.load_at(k, b);
+        else if (brings_b)
+            opb.load_at(k, a);
+    };
+    auto store = [&](char* stage, const floatx4 (&a)[OpA::NV], const floatx4 (&b)[OpB::NV]) {
+        if (!brings_b) OpA::store(stage, HALVES ? tid & 127 : tid, a);
+        if constexpr (!HALVES)
+            OpB::store(stage + OpA::BYTES, tid, b);
+        else if (brings_b)
+            OpB::store(stage + OpA::BYTES, tid & 127, a);
+    };
+    {
+        floatx4 ra0[OpA::NV], rb0[OpB::NV];
+        load(0, ra0, rb0);
+#pragma unroll
+        for (int i = 0; i < AHEAD; ++i) {
+            __builtin_amdgcn_sched_barrier(0);  // in this order, or the loop waits for younger loads than it needs
+            load(1 + i, ra[i], rb[HALVES ? 0 : i]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        store(stages, ra0, rb0);
+    }
+    __syncthreads();
+    auto multiply = [&](int u, int kt) __attribute__((always_inline)) {
+        const char* ta = stages + (u & 1) * Cfg::STAGE;
+        char* na = stages + (~u & 1) * Cfg::STAGE;
+#pragma unroll
+        for (int sub = 0; sub < KS / GEMM_K; ++sub) {
+            Split8 fa[TM], fb[TN];
+#pragma unroll
+            for (int a = 0; a < TM; ++a) fa[a] = OpA::fetch(ta, wm * TM + a, sub, lane);
+#pragma unroll
+            for (int b = 0; b < TN; ++b) fb[b] = OpB::fetch(ta + OpA::BYTES, wn * TN + b, sub, lane);
+            if (sub == 0) {
+                store(na, ra[u], rb[HALVES ? 0 : u]);
+                load(kt + 1 + AHEAD, ra[u], rb[HALVES ? 0 : u]);
+            }
+#pragma unroll
+            for (int t = 0; t <= SPLIT_SMALL; ++t)
+#pragma unroll
+                for (int a = 0; a < TM; ++a)
+#pragma unroll
+                    for (int b = 0; b < TN; ++b) acc[a][b].add(t, fa[a], fb[b]);
+        }
+        __syncthreads();
+    };
+    int kt0 = 0;
+    for (; kt0 + AHEAD <= nk; kt0 += AHEAD) {
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) multiply(u, kt0 + u);
+    }
+#pragma unroll
+    for (int u = 0; u < AHEAD - 1; ++u) {
+        if (kt0 + u >= nk) break;
+        multiply(u, kt0 + u);
+    }
+
+    // The parts meet in LDS, in the place of the stages; each four finish half of a wavefront's tiles, or the first all of one.
+    constexpr bool SHARED = TM % 2 == 0;
+    typedef float Meet[2][4][SHARED ? TM / 2 : TM][TN][16][64];  // [for which four]
+    static_assert(sizeof(Meet) <= 4 * Cfg::STAGE, "the sums fit where the stages were");
+    Meet& meet = *reinterpret_cast<Meet*>(lds);
+    auto finishes = [&](int a) { return SHARED ? (a >= TM / 2) == (half != 0) : half == 0; };
+#pragma unroll
+    for (int a = 0; a < TM; ++a)
+#pragma unroll
+        for (int b = 0; b < TN; ++b) {
+            if (finishes(a)) continue;
+            const floatx16 x = acc[a][b].value();
+#pragma unroll
+            for (int i = 0; i < 16; ++i) meet[!half][wave][SHARED ? a % (TM / 2) : a][b][i][lane] = x[i];
+        }
+    __syncthreads();
+#pragma unroll
+    for (int a = 0; a < TM; ++a)
+#pragma unroll
+        for (int b = 0; b < TN; ++b) {
+            if (!finishes(a)) continue;
+            floatx16 x = acc[a][b].value();
+#pragma unroll
+            for (int i = 0; i < 16; ++i) x[i] += meet[half][wave][SHARED ? a % (TM / 2) : a][b][i][lane];
+            gemm_finish<Cfg::A_KC, Cfg::B_KC>(sh, epi, z, m0 + (wm * TM + a) * 32, n0 + (wn * TN + b) * 32, lane, x);
+        }
+}
+
 // The same sums for a launch with too few tiles to fill the chip: a block owns one tile of 32 x 32 NT and its
 // wavefronts one CHUNK of MFMA steps each; the chunks' sums meet in LDS and are added up in order, so that a value is bit for
 // bit what gemm_block<..., CHUNK> makes of it.  A wavefront brings its operands through LDS of its own, 32
@@ -430,75 +555,82 @@ __global__ __launch_bounds__(64 * CHUNKS) void gemm_split_chunks(GemmShape sh, E
     }
 }
 
-// The sums of gemm_block<..., 0> for a launch with so few tiles that its time is that of one block's serial loop over K:
-// of five wavefronts one does nothing but multiply, a tile of 32 x 32, and four bring its operands in and split them,
-// 64 contraction indices at a time.  (A last stage of fewer begins earlier instead, and what comes twice is passed
-// over.)  Bound by the chain of the five small terms of a step, each of which waits for the one before: 190 ns for 16
-// contraction indices.  Forward of one worker of 256 images or four of 128 against 64 x 64 tiles, whose wavefronts do
-// everything: 38 -> 22 us, but eight of 128, two 32 x 32 tiles for a compute unit, 39 -> 44; input gradient of one of
-// 100 15.4 -> 9.4 us, of two 15.4 -> 16.3.
-template <bool A_KC, bool B_KC, class Epi>
-__global__ __launch_bounds__(320) void gemm_split_roles(GemmShape sh, Epi epi)
+// The same sums for a launch with so few tiles that its time is that of one block's serial loop over K: for each of PARTS
+// halves of the contraction (or all of it, the sums of gemm_block<..., 0>) a wavefront that does nothing but multiply, a tile of
+// 32 x 32, and four that bring its operands in and split them, 32 contraction indices at a time.  (A last stage of fewer begins
+// earlier instead, and what comes twice is passed over.)  Bound by the chain of the five small terms of a step, each of which
+// waits 66 cycles for the one before, 330 to a step of 16, and up to 200 more where splits are issued on the same SIMD.
+// Forward of one worker of 256 images or four of 128: 64 x 64 tiles, whose wavefronts do everything, 38 us, in one part 24, in
+// two 18.  Input gradient, one part, of one of 100 15.4 -> 9.4 us, of two 15.4 -> 16.3.
+template <bool A_KC, bool B_KC, int PARTS, class Epi>
+__global__ __launch_bounds__(320 * PARTS) void gemm_split_roles(GemmShape sh, Epi epi)
 {
-    constexpr int KS = 4 * GEMM_K, SUBS = KS / GEMM_K, AHEAD = 2;  // stages on their way in registers
+    constexpr int KS = 2 * GEMM_K, SUBS = KS / GEMM_K, AHEAD = 4;  // stages on their way in registers
     using OpA = GemmOperand<32, A_KC, false, 128, KS>;
     using OpB = GemmOperand<32, B_KC, false, 128, KS>;
     constexpr int STAGE = OpA::BYTES + OpB::BYTES;
     static_assert(OpA::NV == OpB::NV, "one register set for either operand");
-    static_assert(AHEAD == 2, "stage kt + 2 comes out of the registers of stage kt");
-    __shared__ __attribute__((aligned(16))) char lds[3 * STAGE];
-    const int lane = threadIdx.x & 63, wave = uniform(threadIdx.x >> 6), t = (threadIdx.x - 64) & 127;
+    __shared__ __attribute__((aligned(16))) char lds[PARTS][3 * STAGE];
+    __shared__ float meet[PARTS][16][64];
+    const int lane = threadIdx.x & 63, wave = uniform(threadIdx.x >> 6);
     const int v = gemm_tile(blockIdx.x, sh.gx * sh.gy * sh.gz);
     if (v >= sh.gx * sh.gy * sh.gz) return;
     const int m0 = v % sh.gx * 32, n0 = v / sh.gx % sh.gy * 32, z = v / (sh.gx * sh.gy);
-    const bool multiplies = wave == 0, brings_b = wave >= 3;
+    const bool multiplies = wave < PARTS;
+    const int half = multiplies ? wave : (wave - PARTS) >> 2, bringer = (wave - PARTS) & 3, t = (64 * bringer + lane) & 127;
+    const int K = sh.K / PARTS, k_first = half * K, nk = (K + KS - 1) / KS, tail = (nk * KS - K) / GEMM_K;  // MFMA steps that the last stage repeats
 
-    const int nk = (sh.K + KS - 1) / KS, tail = (nk * KS - sh.K) / GEMM_K;  // MFMA steps that the last stage repeats
-    OpA opa;
-    OpB opb;
-    if (brings_b)
-        opb.init(epi.b_ptr(z), sh.ldb, n0, sh.N, sh.K, t);
-    else
-        opa.init(epi.a_ptr(z), sh.lda, m0, sh.M, sh.K, t);
-    auto load = [&](int kt, floatx4 (&x)[OpA::NV]) {  // past the end the last stage again, which nobody reads
-        const int k = min(kt * KS, sh.K - KS);
-        if (brings_b)
-            opb.load_at(k, x);
-        else
-            opa.load_at(k, x);
-    };
-    auto store = [&](char* stage, const floatx4 (&x)[OpA::NV]) {
-        if (brings_b)
-            OpB::store(stage + OpA::BYTES, t, x);
-        else
-            OpA::store(stage, t, x);
-    };
     // While stage kt is multiplied, out of one buffer, stage kt + 1 lies in the second and stage kt + 2 comes into the
     // third: the multiplying wavefront reads one MFMA step ahead, also from one stage into the next.
-    // The two kinds of wavefronts run loops of their own: the same barriers (nk + 1), but in a common loop the compiler
-    // would wait for every load in flight where their ways meet.
-    char *now = lds, *next = lds + STAGE, *later = lds + 2 * STAGE;
+    // The two kinds of wavefronts run loops of their own: the same barriers (nk + 1, and one behind), but in a common loop
+    // the compiler would wait for every load in flight where their ways meet.
+    char *now = lds[half], *next = now + STAGE, *later = now + 2 * STAGE;
+    auto turn = [&]() __attribute__((always_inline)) {
+        char* const read = now;
+        now = next;
+        next = later;
+        later = read;
+    };
     if (!multiplies) {
-        floatx4 r[AHEAD][OpA::NV];
+        const bool brings_b = bringer >= 2;
+        OpA opa;
+        OpB opb;
+        if (brings_b)
+            opb.init(epi.b_ptr(z), sh.ldb, n0, sh.N, sh.K, t);
+        else
+            opa.init(epi.a_ptr(z), sh.lda, m0, sh.M, sh.K, t);
+        auto load = [&](int kt, floatx4 (&x)[OpA::NV]) {  // past the end the last stage again, which nobody reads
+            const int k = k_first + min(kt * KS, K - KS);
+            if (brings_b)
+                opb.load_at(k, x);
+            else
+                opa.load_at(k, x);
+        };
+        auto store = [&](char* stage, const floatx4 (&x)[OpA::NV]) {
+            if (brings_b)
+                OpB::store(stage + OpA::BYTES, t, x);
+            else
+                OpA::store(stage, t, x);
+        };
+        floatx4 r[AHEAD][OpA::NV];  // stage kt + 2 .. kt + 1 + AHEAD; stage s in r[s % AHEAD]
 #pragma unroll
         for (int i = 0; i < AHEAD; ++i) {
             load(i, r[i]);
             __builtin_amdgcn_sched_barrier(0);  // in this order
         }
-        store(now, r[0]);
-        load(AHEAD, r[0]);
-        store(next, r[1]);
-        load(AHEAD + 1, r[1]);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            store(i ? next : now, r[i]);
+            load(AHEAD + i, r[i]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
         __syncthreads();
         auto stage = [&](int u, int kt) __attribute__((always_inline)) {
-            store(later, r[u]);
-            load(kt + 2 + AHEAD, r[u]);
+            store(later, r[(u + 2) % AHEAD]);
+            load(kt + 2 + AHEAD, r[(u + 2) % AHEAD]);
             __syncthreads();
             __builtin_amdgcn_sched_barrier(0);  // or the next stages are split, and so waited for, up here
-            char* const read = now;
-            now = next;
-            next = later;
-            later = read;
+            turn();
         };
         int kt0 = 0;
         for (; kt0 + AHEAD <= nk; kt0 += AHEAD) {
@@ -510,6 +642,7 @@ __global__ __launch_bounds__(320) void gemm_split_roles(GemmShape sh, Epi epi)
             if (kt0 + u >= nk) break;
             stage(u, kt0 + u);
         }
+        __syncthreads();
         return;
     }
     __syncthreads();
@@ -534,12 +667,20 @@ __global__ __launch_bounds__(320) void gemm_split_roles(GemmShape sh, Epi epi)
             acc.add(a, b);
         }
         __syncthreads();
-        char* const read = now;
-        now = next;
-        next = later;
-        later = read;
+        turn();
     }
-    gemm_finish<A_KC, B_KC>(sh, epi, z, m0, n0, lane, acc.value());
+    floatx16 sums = acc.value();
+    if (half > 0) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) meet[half][i][lane] = sums[i];
+    }
+    __syncthreads();
+    if (half > 0) return;
+#pragma unroll
+    for (int p = 1; p < PARTS; ++p)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) sums[i] += meet[p][i][lane];
+    gemm_finish<A_KC, B_KC>(sh, epi, z, m0, n0, lane, sums);
 }
 
 // Whether a launch over this many 128 x 128 tiles leaves compute units idle.
@@ -552,6 +693,109 @@ __global__ __launch_bounds__(256, MINW) void gemm_split(GemmShape sh, Epi epi)
 {
     __shared__ __attribute__((aligned(16))) char lds[2 * Cfg::STAGE];
     gemm_block<Cfg, false, CHUNK>(sh, epi, blockIdx.x, lds);
+}
+
+template <class Cfg, class Epi>
+__global__ __launch_bounds__(512, 2) void gemm_split_sides(GemmShape sh, Epi epi)
+{
+    __shared__ __attribute__((aligned(16))) char lds[4 * Cfg::STAGE];
+    gemm_sides_block<Cfg>(sh, epi, blockIdx.x, lds);
+}
+
+// The same sums for launches of many tiles: four wavefronts to a block, two blocks to a compute unit, which need not keep in
+// step, one half after the other.  The first half's sums, 64 a lane, wait in LDS (28) and in registers (36), for which loads run
+// one stage ahead instead of two.  256 workers of 256 images 558 us (all of K in one chain 557; 28, 20 and the rest in
+// the tile's own place in C 4 us more, all of them there 37 more; gemm_sides_block 38 more).
+template <class Cfg, class Epi>
+__global__ __launch_bounds__(256, 2) void gemm_split_parts(GemmShape sh, Epi epi)
+{
+    constexpr int TM = Cfg::TM, TN = Cfg::TN, WM = Cfg::WM, BM = Cfg::BM, BN = Cfg::BN, KS = Cfg::KS;
+    using OpA = GemmOperand<BM, Cfg::A_KC, false, 256, KS>;
+    using OpB = GemmOperand<BN, Cfg::B_KC, false, 256, KS>;
+    static_assert(KS == GEMM_K, "one MFMA step to a stage");
+    constexpr int GROUPS = TM * TN * 4, IN_LDS = 7, IN_REGS = GROUPS - IN_LDS;  // groups of four sums: where those of the first part wait
+    __shared__ __attribute__((aligned(16))) char lds[2 * Cfg::STAGE];
+    __shared__ floatx4 waiting[IN_LDS][256];
+    const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6), wm = wave % WM, wn = wave / WM;
+    const int v = gemm_tile(blockIdx.x, sh.gx * sh.gy * sh.gz);
+    if (v >= sh.gx * sh.gy * sh.gz) return;
+    const int m0 = v % sh.gx * BM, n0 = v / sh.gx % sh.gy * BN, z = v / (sh.gx * sh.gy), nk = sh.K / KS;
+    OpA opa;
+    OpB opb;
+    opa.init(epi.a_ptr(z), sh.lda, m0, sh.M, sh.K, tid);
+    opb.init(epi.b_ptr(z), sh.ldb, n0, sh.N, sh.K, tid);
+    SplitSum<floatx16> acc[TM][TN];
+    auto clear = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int a = 0; a < TM; ++a)
+#pragma unroll
+            for (int b = 0; b < TN; ++b) acc[a][b].clear();
+    };
+    clear();
+    floatx4 held[IN_REGS] = {};
+    floatx4 ra[OpA::NV], rb[OpB::NV];  // of the stage after the next
+    {
+        floatx4 ra0[OpA::NV], rb0[OpB::NV];
+        opa.load(0, ra0);
+        opb.load(0, rb0);
+        opa.load(min(1, nk - 1), ra);
+        opb.load(min(1, nk - 1), rb);
+        OpA::store(lds, tid, ra0);
+        OpB::store(lds + OpA::BYTES, tid, rb0);
+    }
+    __syncthreads();
+    for (int kt0 = 0; kt0 < nk; kt0 += 2) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int kt = kt0 + u;
+            if (u > 0 && kt >= nk) break;
+            const char* ta = lds + (u & 1) * Cfg::STAGE;
+            char* na = lds + (~u & 1) * Cfg::STAGE;
+            Split8 fa[TM], fb[TN];
+#pragma unroll
+            for (int a = 0; a < TM; ++a) fa[a] = OpA::fetch(ta, wm * TM + a, 0, lane);
+#pragma unroll
+            for (int b = 0; b < TN; ++b) fb[b] = OpB::fetch(ta + OpA::BYTES, wn * TN + b, 0, lane);
+            OpA::store(na, tid, ra);
+            OpB::store(na + OpA::BYTES, tid, rb);
+            opa.load(min(kt + 2, nk - 1), ra);
+            opb.load(min(kt + 2, nk - 1), rb);
+#pragma unroll
+            for (int t = 0; t <= SPLIT_SMALL; ++t)
+#pragma unroll
+                for (int a = 0; a < TM; ++a)
+#pragma unroll
+                    for (int b = 0; b < TN; ++b) acc[a][b].add(t, fa[a], fb[b]);
+            __syncthreads();
+            if (u == 0 && __builtin_expect(kt == nk / 2 - 1, 0)) {  // the first part is done
+#pragma unroll
+                for (int i = 0; i < GROUPS; ++i) {
+                    const int a = i / (4 * TN), b = i / 4 % TN, g = i % 4;
+                    const SplitSum<floatx16>& x = acc[a][b];
+                    const floatx4 first = {x.big[4 * g] + x.small[4 * g], x.big[4 * g + 1] + x.small[4 * g + 1], x.big[4 * g + 2] + x.small[4 * g + 2],
+                                           x.big[4 * g + 3] + x.small[4 * g + 3]};
+                    if (i < IN_LDS)
+                        waiting[i][tid] = first;
+                    else
+                        held[i - IN_LDS] = first;
+                }
+                clear();
+            }
+        }
+    }
+#pragma unroll
+    for (int a = 0; a < TM; ++a)
+#pragma unroll
+        for (int b = 0; b < TN; ++b) {
+            floatx16 x = acc[a][b].value();
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const floatx4 first = (a * TN + b) * 4 + g < IN_LDS ? waiting[(a * TN + b) * 4 + g][tid] : held[(a * TN + b) * 4 + g - IN_LDS];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) x[4 * g + k] += first[k];
+            }
+            gemm_finish<Cfg::A_KC, Cfg::B_KC>(sh, epi, z, m0 + (wm * TM + a) * 32, n0 + (wn * TN + b) * 32, lane, x);
+        }
 }
 
 // Two tile shapes in one launch: `main_blocks` blocks cover the main part of C with Main tiles, the rest cover an
@@ -599,16 +843,33 @@ void gemm_launch(int M, int N, int K, int lda, int ldb, int batch, const Epi& ep
     hipLaunchKernelGGL((gemm_split<Cfg, CHUNK, MINW, Epi>), dim3(gemm_grid(sh)), dim3(256), 0, s, sh, epi);
 }
 
+template <class Cfg, class Epi>
+void gemm_launch_sides(int M, int N, int K, int lda, int ldb, int batch, const Epi& epi, hipStream_t s)
+{
+    if (M <= 0 || N <= 0 || batch <= 0) return;
+    const GemmShape sh = gemm_shape<Cfg>(M, N, K, lda, ldb, batch, 0, M, 0, N);
+    hipLaunchKernelGGL((gemm_split_sides<Cfg, Epi>), dim3(gemm_grid(sh)), dim3(512), 0, s, sh, epi);
+}
+
+template <class Cfg, int K, class Epi>
+void gemm_launch_parts(int M, int N, int lda, int ldb, int batch, const Epi& epi, hipStream_t s)
+{
+    static_assert(K % (4 * Cfg::KS) == 2 * Cfg::KS, "the first half's last stage is an even one");
+    if (M <= 0 || N <= 0 || batch <= 0) return;
+    const GemmShape sh = gemm_shape<Cfg>(M, N, K, lda, ldb, batch, 0, M, 0, N);
+    hipLaunchKernelGGL((gemm_split_parts<Cfg, Epi>), dim3(gemm_grid(sh)), dim3(256), 0, s, sh, epi);
+}
+
 // Whether every tile of 32 x 32 finds a compute unit of its own (both sides measured: gemm_split_roles).
 inline bool gemm_roles_fit(int M, int N, int batch, int compute_units) { return (M + 31) / 32 * ((N + 31) / 32) * batch <= compute_units; }
 
-// K: at least 64, a multiple of 16.
-template <bool A_KC, bool B_KC, class Epi>
+// K / PARTS: at least 32, a multiple of 16.
+template <bool A_KC, bool B_KC, int PARTS, class Epi>
 void gemm_launch_roles(int M, int N, int K, int lda, int ldb, int batch, const Epi& epi, hipStream_t s)
 {
     if (M <= 0 || N <= 0 || batch <= 0) return;
     const GemmShape sh{M, N, K, lda, ldb, (M + 31) / 32, (N + 31) / 32, batch, 0, 0};
-    hipLaunchKernelGGL((gemm_split_roles<A_KC, B_KC, Epi>), dim3(gemm_grid(sh)), dim3(320), 0, s, sh, epi);
+    hipLaunchKernelGGL((gemm_split_roles<A_KC, B_KC, PARTS, Epi>), dim3(gemm_grid(sh)), dim3(320 * PARTS), 0, s, sh, epi);
 }
 
 // One problem per batch index in tiles of 32 x 32, or 32 x 64 if those alone give every compute unit a block; K =
