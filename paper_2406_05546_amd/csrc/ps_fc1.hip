@@ -52,10 +52,19 @@ struct Fc1DxEpi {
 // tiles.  A launch with fewer wide tiles than compute units takes as long as the serial loop over K of one
 // tile, and is cut up: into 64 x 64 tiles (32 x 32, with wavefronts that only multiply, where those find a compute unit
 // each), or, in the forward and the input gradient of batches up to 64, into
-// 32 x 32 tiles with a wavefront for every chunk of K (1568 = 7 x 14 stages, 512 = 4 x 8).  Whether a batch
+// 32 x 32 or 32 x 64 tiles with a wavefront for every chunk of K (1568 = 7 x 14 stages, 512 = 4 x 8).  Whether a batch
 // is summed in chunks depends on its size alone, so that these sums have the same bits whatever else is in the
-// launch; beyond 64 the chunks' totals would not fit the registers of 64 x 64 wavefront tiles.  The forward pass of those
-// is summed in two parts of 784, which two sets of wavefronts form side by side wherever the wide tiles do not fill the chip twice.
+// launch; beyond 64 the chunks' totals would not fit the registers of 64 x 64 wavefront tiles.
+// Those tiles serve larger launches too (us, in 32 x 32, 32 x 64 and 128 x 64 tiles; of batches up to 32 only the first are full):
+//   workers x images     4x64  8x64  12x64  16x64  20x40  40x64  48x64  64x32  64x64  100x64  128x32  256x32  256x64
+//   forward, 32 x 32     11.9  12.6   18.4   19.8   24.4   38.9   52.6   34.2   65.4    93.1    65.0   116.6   230.3
+//            32 x 64           12.6   17.8   18.8   30.0   44.3
+//            128 x 64                                       51     55.6   57.4   58.2    80.4    83.7   159.7   174.1
+//   backward, 32 x 32     9.3  13.1   15.8   20.0   21.2   38.5   45.7   33.1                    57.3   107.2
+//             32 x 64     9.9  12.5   16.0   19.9   20.0   36.9   43.9          54.9    78.9                   185.7
+//             128 x 64                                      41.8   48.0   53.9   55.2    79.9    91.7   167.9   181.6
+// Beyond batches of 64 the forward pass is summed in two parts of 784, which two sets of wavefronts form side by side where there
+// are no more wide tiles than compute units.
 constexpr int FWD_CHUNKS = 7, FWD_CHUNK = 14, DX_CHUNKS = 4, DX_CHUNK = 8, CHUNKED_BATCH = 64;
 static_assert(FWD_CHUNKS * FWD_CHUNK * GEMM_K == P2_SIZE && DX_CHUNKS * DX_CHUNK * GEMM_K == FC1, "whole chunks");
 
@@ -72,8 +81,10 @@ void launch_fc1_fwd(const WorkerBuffers& wb, hipStream_t s)
     const int wide_tiles = FC1 / 128 * ((wb.B + 127) / 128) * wb.n;
     const Fc1FwdEpi epi{wb};
     if (wb.B <= CHUNKED_BATCH) {
-        if (gemm_few_tiles(wide_tiles, wb.compute_units))
-            gemm_launch_chunks<true, true, FWD_CHUNKS, FWD_CHUNK>(FC1, wb.B, P2_SIZE, P2_SIZE, wb.n, wb.compute_units, epi, s);
+        const int tiles = FC1 / 32 * wb.n;  // of a worker's samples 32 or 64 at a time
+        const bool narrow = wb.B <= 32 || 2 * tiles <= wb.compute_units || tiles > wb.compute_units;
+        if (wb.B <= 32 || gemm_few_tiles(wide_tiles, wb.compute_units))
+            gemm_launch_chunks<true, true, FWD_CHUNKS, FWD_CHUNK>(FC1, wb.B, P2_SIZE, P2_SIZE, wb.n, narrow, epi, s);
         else
             gemm_launch<GemmCfg<true, true, 2, 1, 2, 2, 2>, FWD_CHUNK, 2>(FC1, wb.B, P2_SIZE, P2_SIZE, P2_SIZE, wb.n, epi, s);
     } else if (gemm_roles_fit(FC1, wb.B, wb.n, wb.compute_units)) {
@@ -100,11 +111,12 @@ void launch_fc1_dx(const WorkerBuffers& wb, hipStream_t s)
     // 64 x 64 tiles already fall behind where there is a wide tile for two compute units (8 workers of 128 images, 96
     // tiles: 22 against 28 us; 16 of 128: 37 against 31)
     const int wide_tiles = FEAT_WIDE / 128 * ((wb.B + 127) / 128) * wb.n;
-    const bool few = gemm_few_tiles(wb.B <= CHUNKED_BATCH ? wide_tiles : 2 * wide_tiles, wb.compute_units);
+    const bool few = gemm_few_tiles(2 * wide_tiles, wb.compute_units);
     const Fc1DxEpi epi{wb};
     if (wb.B <= CHUNKED_BATCH) {
-        if (few)
-            gemm_launch_chunks<false, true, DX_CHUNKS, DX_CHUNK>(P2_SIZE, wb.B, P2_SIZE, FC1, wb.n, wb.compute_units, epi, s);
+        const bool narrow = wb.B <= 32 || 4 * (P2_SIZE / 32) * wb.n <= 5 * wb.compute_units;
+        if (wb.B <= 32 || wide_tiles < 5 * wb.compute_units)
+            gemm_launch_chunks<false, true, DX_CHUNKS, DX_CHUNK>(P2_SIZE, wb.B, P2_SIZE, FC1, wb.n, narrow, epi, s);
         else
             gemm_launch_edge<GemmCfg<false, true, 2, 1, 2, 2, 2>, GemmCfg<false, true, 1, 1, 1, 4, 2>, false, DX_CHUNK, 2>(P2_SIZE, wb.B, FC1, P2_SIZE, FC1, wb.n,
                                                                                                           FEAT_WIDE, wb.B, epi, s);

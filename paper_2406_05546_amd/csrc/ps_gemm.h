@@ -167,7 +167,7 @@ __device__ __forceinline__ floatx4 gemm_operand4(const float* __restrict__ base,
 }
 
 // The sums `which` of a 32x32 tile at (m0, n0), for which the split does not hold (ps_split.h), formed again with fp32 matrix
-// instructions, whose registers lie as those of the bf16 ones do.  Operands come straight from memory, so it takes
+// instructions, whose registers lie as those of the bf16 ones do.  Operands come straight from memory, 32 k ahead, so it takes
 // about four times as long as the tile did, unless the sums turn out NaN anyway: a network of NaN weights is not
 // slowed down by more than that first look.
 template <bool A_KC, bool B_KC, class Epi>
@@ -180,15 +180,30 @@ __device__ __forceinline__ void gemm_again(const GemmShape& sh, const Epi& epi, 
     floatx16 again;
 #pragma unroll
     for (int i = 0; i < 16; ++i) again[i] = 0.f;
+    floatx4 a[4], b[4];  // of the next 32 k; past K, a multiple of 8 where an operand does not read as zero there, the last ones
+    auto load = [&](int k0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int k = (A_KC || B_KC ? min(k0 + 8 * i, sh.K - 8) : k0 + 8 * i) + 4 * h;
+            a[i] = gemm_operand4<A_KC>(A, sh.lda, row, k, sh.K);
+            b[i] = gemm_operand4<B_KC>(B, sh.ldb, col, k, sh.K);
+        }
+    };
+    load(0);
 #pragma unroll 1
     for (int k0 = 0; k0 < sh.K; k0 += 32) {
+        floatx4 x[4], y[4];
 #pragma unroll
-        for (int k = 0; k < 32; k += 8) {
-            if (k0 + k >= sh.K) break;  // K is a multiple of 8, or the operands read as zero past it
-            const floatx4 a = gemm_operand4<A_KC>(A, sh.lda, row, k0 + k + 4 * h, sh.K);
-            const floatx4 b = gemm_operand4<B_KC>(B, sh.ldb, col, k0 + k + 4 * h, sh.K);
+        for (int i = 0; i < 4; ++i) {
+            x[i] = a[i];
+            y[i] = b[i];
+        }
+        load(k0 + 32);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) again = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[i], again, 0, 0, 0);
+        for (int i = 0; i < 4; ++i) {
+            if (k0 + 8 * i >= sh.K) break;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) again = __builtin_amdgcn_mfma_f32_32x32x2f32(x[i][j], y[i][j], again, 0, 0, 0);
         }
         if (!worth_going_on<16>(which, again)) break;
     }
@@ -464,65 +479,119 @@ __device__ __forceinline__ void gemm_sides_block(const GemmShape& sh, const Epi&
         }
 }
 
-// The same sums for a launch with too few tiles to fill the chip: a block owns one tile of 32 x 32 NT and its
-// wavefronts one CHUNK of MFMA steps each; the chunks' sums meet in LDS and are added up in order, so that a value is bit for
-// bit what gemm_block<..., CHUNK> makes of it.  A wavefront brings its operands through LDS of its own, 32
-// contraction indices at a time, so that a load touches whole cache lines: straight into the MFMA layout a load
-// touched 32 lines, which took all of the 14 us of the forward pass of two workers of 32 images and of the 30 us of
-// 16 of 64.
+// An operand that a wavefront brings for itself alone: 32 contraction indices at a time, straight to LDS as they are, and split
+// on their way from there into the MFMA layout.  KC: a row of the stage is 128 bytes, whose 16-byte pieces are exchanged by bits
+// 1-3 of the row, so that 16 rows read the same piece from different banks.  RC: one k is 128 bytes.
+template <int ROWS, bool KC>
+struct GemmOwnOperand {
+    static constexpr int KS = 2 * GEMM_K, BYTES = ROWS * KS * 4, LOADS = BYTES / 1024;
+    static_assert(KC || ROWS == 32, "a k of an RC operand is one line");
+    Buffer buffer;
+    uint32_t off[LOADS];  // of this lane's 16 bytes in stage 0
+    uint32_t stage_step;
+
+    __device__ __forceinline__ void init(const float* base, int ld, int row0, int nrows, int K, int k_first, int lane)
+    {
+        buffer = buffer_of(base, (uint32_t)(KC ? nrows : K) * ld * 4);
+        stage_step = (KC ? KS : KS * ld) * 4;
+#pragma unroll
+        for (int i = 0; i < LOADS; ++i) {
+            const int r = 8 * i + lane / 8, piece = KC ? lane % 8 ^ (r >> 1 & 7) : lane % 8;  // r: row, or k
+            if (KC)
+                off[i] = ((uint32_t)min(row0 + r, nrows - 1) * ld + k_first + 4 * piece) * 4;
+            else
+                off[i] = ((uint32_t)(k_first + r) * ld + min(row0 + 4 * piece, nrows - 4)) * 4;
+        }
+    }
+    __device__ __forceinline__ void bring(int kt, char* tile) const
+    {
+#pragma unroll
+        for (int i = 0; i < LOADS; ++i) buffer_to_lds16(buffer, tile + 1024 * i, off[i] + (uint32_t)kt * stage_step);
+    }
+    // The operand of rows 32 * rt .. +31 in the `sub`-th MFMA of the stage: lane (h, l32) gets k = 16 sub + 8h + 0..7 of row l32.
+    static __device__ __forceinline__ void read(const char* tile, int rt, int sub, int lane, float (&v)[8])
+    {
+        const int h = lane >> 5, l32 = lane & 31;
+        if (KC) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const floatx4 x = *reinterpret_cast<const floatx4*>(tile + (32 * rt + l32) * 128 + ((4 * sub + 2 * h + i) ^ (l32 >> 1 & 7)) * 16);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) v[4 * i + j] = x[j];
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] = *reinterpret_cast<const float*>(tile + (16 * sub + 8 * h + j) * 128 + l32 * 4);
+        }
+    }
+};
+
+// The same sums for small batches: a block owns one tile of 32 x 32 NT and its wavefronts one CHUNK of MFMA steps each; the
+// chunks' sums meet in LDS and are added up in order, so that a value is bit for bit what gemm_block<..., CHUNK> makes of it.
+// A wavefront brings its operands to LDS of its own, 32 contraction indices at a time, so that a load touches whole cache
+// lines (straight into the MFMA layout it touches 32, which took all of the 14 us of the forward pass of two workers of 32 images),
+// and without a way through registers: next to matrix instructions of the other wavefronts of its SIMD a load into registers gets
+// 32 bytes a cycle of a compute unit, one into LDS 64, and the parts need not be written to LDS.  Through registers and split
+// before LDS, and so (us): forward 2 x 32 13.5 -> 11.7, 8 x 64 14.5 -> 12.6, 40 x 64 51 -> 39; input gradient 8.4 -> 7.8, 14.2 -> 12.5,
+// 40 -> 37.  Two stages on their way are no faster (forward 2 x 32 12.2) and leave room for fewer blocks.
 template <bool A_KC, bool B_KC, int NT, int CHUNKS, int CHUNK, class Epi>
-__global__ __launch_bounds__(64 * CHUNKS) void gemm_split_chunks(GemmShape sh, Epi epi)
+__global__ __launch_bounds__(64 * CHUNKS, NT == 1 ? 4 : CHUNKS == 4 ? 3 : 2) void gemm_split_chunks(GemmShape sh, Epi epi)
 {
-    static_assert(CHUNKS >= 4, "four wavefronts store the tile");
-    constexpr int KS = 2 * GEMM_K, STAGES = CHUNK / 2;
-    static_assert(CHUNK % 2 == 0, "whole stages");
-    using OpA = GemmOperand<32, A_KC, false, 64, KS>;
-    using OpB = GemmOperand<32 * NT, B_KC, false, 64, KS>;
+    static_assert(CHUNKS >= 4 && NT <= 2, "four wavefronts store the tile");
+    using OpA = GemmOwnOperand<32, A_KC>;
+    using OpB = GemmOwnOperand<32 * NT, B_KC>;
+    constexpr int SUBS = OpA::KS / GEMM_K, STAGES = CHUNK / SUBS;
+    static_assert(CHUNK % SUBS == 0, "whole stages");
     __shared__ __attribute__((aligned(16))) union {
         char stage[CHUNKS][OpA::BYTES + OpB::BYTES];
         float part[CHUNKS][NT][16][64];
     } lds;
+    __shared__ int lost[NT];
     const int lane = threadIdx.x & 63, wave = uniform(threadIdx.x >> 6);
     const int t = gemm_tile(blockIdx.x, sh.gx * sh.gy * sh.gz);
     if (t >= sh.gx * sh.gy * sh.gz) return;
+    if (threadIdx.x < NT) lost[threadIdx.x] = 0;
     const int m0 = t % sh.gx * 32, n0 = t / sh.gx % sh.gy * 32 * NT, z = t / (sh.gx * sh.gy);
     OpA opa;
     OpB opb;
-    opa.init(epi.a_ptr(z), sh.lda, m0, sh.M, sh.K, lane);
-    opb.init(epi.b_ptr(z), sh.ldb, n0, sh.N, sh.K, lane);
-    char* tile = lds.stage[wave];
-    const int k0 = wave * STAGES;
-    constexpr int AHEAD = 2;  // stages in flight
-    floatx4 a[AHEAD][OpA::NV], b[AHEAD][OpB::NV];
-#pragma unroll
-    for (int i = 0; i < AHEAD; ++i) {
-        opa.load(k0 + i, a[i]);
-        opb.load(k0 + i, b[i]);
-    }
+    opa.init(epi.a_ptr(z), sh.lda, m0, sh.M, sh.K, wave * CHUNK * GEMM_K, lane);
+    opb.init(epi.b_ptr(z), sh.ldb, n0, sh.N, sh.K, wave * CHUNK * GEMM_K, lane);
+    char* const tile_a = lds.stage[wave];
+    char* const tile_b = tile_a + OpA::BYTES;
+    opa.bring(0, tile_a);
+    opb.bring(0, tile_b);
     SplitSum<floatx16> sum[NT];
 #pragma unroll
     for (int i = 0; i < NT; ++i) sum[i].clear();
 #pragma unroll
     for (int kt = 0; kt < STAGES; ++kt) {
-        wave_lds_fence();  // the last stage has been read
-        OpA::store(tile, lane, a[kt % AHEAD]);
-        OpB::store(tile + OpA::BYTES, lane, b[kt % AHEAD]);
-        if (kt + AHEAD < STAGES) {
-            opa.load(k0 + kt + AHEAD, a[kt % AHEAD]);
-            opb.load(k0 + kt + AHEAD, b[kt % AHEAD]);
-        }
-        wave_lds_fence();
+        float a[SUBS][8], b[SUBS][NT][8];
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the stage is in LDS
 #pragma unroll
-        for (int sub = 0; sub < KS / GEMM_K; ++sub) {
-            const Split8 fa = OpA::fetch(tile, 0, sub, lane);
+        for (int sub = 0; sub < SUBS; ++sub) {
+            OpA::read(tile_a, 0, sub, lane, a[sub]);
+#pragma unroll
+            for (int i = 0; i < NT; ++i) OpB::read(tile_b, i, sub, lane, b[sub][i]);
+        }
+        if (kt + 1 < STAGES) {
+            // what comes straight to LDS does not wait for reads that are on their way
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            opa.bring(kt + 1, tile_a);
+            opb.bring(kt + 1, tile_b);
+        }
+        __builtin_amdgcn_sched_barrier(0);  // the next stage is on its way before this one is split
+#pragma unroll
+        for (int sub = 0; sub < SUBS; ++sub) {
+            const Split8 fa = split8(a[sub]);
             Split8 fb[NT];
 #pragma unroll
-            for (int i = 0; i < NT; ++i) fb[i] = OpB::fetch(tile + OpA::BYTES, i, sub, lane);
+            for (int i = 0; i < NT; ++i) fb[i] = split8(b[sub][i]);
 #pragma unroll
             for (int t = 0; t <= SPLIT_SMALL; ++t)
 #pragma unroll
                 for (int i = 0; i < NT; ++i) sum[i].add(t, fa, fb[i]);
         }
+        __builtin_amdgcn_sched_barrier(0);  // and is not waited for in front of that
     }
     __syncthreads();  // everybody has read its stages, whose place the sums take
 #pragma unroll
@@ -532,26 +601,56 @@ __global__ __launch_bounds__(64 * CHUNKS) void gemm_split_chunks(GemmShape sh, E
         for (int i = 0; i < 16; ++i) lds.part[wave][j][i][lane] = acc[i];
     }
     __syncthreads();
+    floatx4 v[NT];  // wavefront g stores rows 8g + 4h .. +3
+    if (wave < 4) {
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                v[j][i] = lds.part[0][j][4 * wave + i][lane];
+#pragma unroll
+                for (int c = 1; c < CHUNKS; ++c) v[j][i] += lds.part[c][j][4 * wave + i][lane];
+            }
+            if (any_lost<4, 4>(v[j])) lost[j] = 1;
+        }
+    }
+    __syncthreads();
+    int again[NT], redo = 0;
+#pragma unroll
+    for (int j = 0; j < NT; ++j) redo |= again[j] = uniform(lost[j]);
+    if (__builtin_expect(redo, 0)) {  // a tile's lost sums are formed again by one wavefront for all four
+        uint32_t(*which)[4][64] = reinterpret_cast<uint32_t(*)[4][64]>(lds.part[1]);
+        float(*sums)[16][64] = lds.part[0];
+        if (wave < 4) {
+#pragma unroll
+            for (int j = 0; j < NT; ++j) which[j][wave][lane] = lost_sums<4, 4>(v[j]);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+            if (!again[j] || wave != j) continue;
+            uint32_t all = 0;
+#pragma unroll
+            for (int g = 0; g < 4; ++g) all |= which[j][g][lane] << (4 * g);
+            floatx16 x;
+            gemm_again<A_KC, B_KC>(sh, epi, z, m0, n0 + 32 * j, lane, all, x);
+#pragma unroll
+            for (int i = 0; i < 16; ++i) sums[j][i][lane] = x[i];
+        }
+        __syncthreads();
+        if (wave < 4) {
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (which[j][wave][lane] >> i & 1) v[j][i] = sums[j][4 * wave + i][lane];
+        }
+    }
     if (wave >= 4) return;
 #pragma unroll
     for (int j = 0; j < NT; ++j) {
-        floatx4 v;  // wavefront g stores rows 8g + 4h .. +3
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            v[i] = lds.part[0][j][4 * wave + i][lane];
-#pragma unroll
-            for (int c = 1; c < CHUNKS; ++c) v[i] += lds.part[c][j][4 * wave + i][lane];
-        }
-        if (any_lost<4, 4>(v)) {
-            const uint32_t which = lost_sums<4, 4>(v);
-            floatx16 sums;
-            gemm_again<A_KC, B_KC>(sh, epi, z, m0, n0 + 32 * j, lane, which << (4 * wave), sums);
-#pragma unroll
-            for (int i = 0; i < 16; ++i)
-                if (i / 4 == wave && (which >> (i % 4) & 1)) v[i % 4] = sums[i];
-        }
         const int m = m0 + 8 * wave + 4 * (lane >> 5), n = n0 + 32 * j + (lane & 31);
-        if (m < sh.M && n < sh.N) epi(z, m, n, make_float4(v[0], v[1], v[2], v[3]));
+        if (m < sh.M && n < sh.N) epi(z, m, n, make_float4(v[j][0], v[j][1], v[j][2], v[j][3]));
     }
 }
 
@@ -872,19 +971,14 @@ void gemm_launch_roles(int M, int N, int K, int lda, int ldb, int batch, const E
     hipLaunchKernelGGL((gemm_split_roles<A_KC, B_KC, PARTS, Epi>), dim3(gemm_grid(sh)), dim3(320 * PARTS), 0, s, sh, epi);
 }
 
-// One problem per batch index in tiles of 32 x 32, or 32 x 64 if those alone give every compute unit a block; K =
-// CHUNKS * CHUNK MFMA steps.
+// One problem per batch index in tiles of 32 x 32 (narrow) or 32 x 64; K = CHUNKS * CHUNK MFMA steps.
 template <bool A_KC, bool B_KC, int CHUNKS, int CHUNK, class Epi>
-void gemm_launch_chunks(int M, int N, int lda, int ldb, int batch, int compute_units, const Epi& epi, hipStream_t s)
+void gemm_launch_chunks(int M, int N, int lda, int ldb, int batch, bool narrow, const Epi& epi, hipStream_t s)
 {
     if (M <= 0 || N <= 0 || batch <= 0) return;
-    GemmShape sh{M, N, CHUNKS * CHUNK * GEMM_K, lda, ldb, (M + 31) / 32, (N + 31) / 32, batch, 0, 0};
-    if (N <= 32 || sh.gx * sh.gy * batch <= compute_units) {
-        hipLaunchKernelGGL((gemm_split_chunks<A_KC, B_KC, 1, CHUNKS, CHUNK, Epi>), dim3(gemm_grid(sh)), dim3(64 * CHUNKS), 0, s, sh, epi);
-    } else {
-        sh.gy = (N + 63) / 64;
-        hipLaunchKernelGGL((gemm_split_chunks<A_KC, B_KC, 2, CHUNKS, CHUNK, Epi>), dim3(gemm_grid(sh)), dim3(64 * CHUNKS), 0, s, sh, epi);
-    }
+    const GemmShape sh{M, N, CHUNKS * CHUNK * GEMM_K, lda, ldb, (M + 31) / 32, narrow ? (N + 31) / 32 : (N + 63) / 64, batch, 0, 0};
+    auto kernel = narrow ? gemm_split_chunks<A_KC, B_KC, 1, CHUNKS, CHUNK, Epi> : gemm_split_chunks<A_KC, B_KC, 2, CHUNKS, CHUNK, Epi>;
+    hipLaunchKernelGGL(kernel, dim3(gemm_grid(sh)), dim3(64 * CHUNKS), 0, s, sh, epi);
 }
 
 // Rows [0, m_split) x columns [0, n_split) of C with Main tiles and the rest with Edge tiles, where exactly

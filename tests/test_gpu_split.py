@@ -231,13 +231,16 @@ def test_images_of_a_wavefront(ps, n, B):
         ps.ps_destroy(ctx)
 
 
-# fc1's forward pass beyond batches of 64: 32 x 32 tiles, 64 x 64, 128 x 128 with either half of the sums side by side, and with
-# one after the other, on both sides of the lines between them; whole tiles and remainders down to a column
-@pytest.mark.parametrize("n,B", [(1, 65), (1, 512), (3, 193), (32, 100), (33, 97), (64, 128), (65, 90), (40, 257)])
-def test_fc1_forward_forms(ps, n, B):
-    """Activations of every image within what an fp32 sum may be off, and with the same bytes when their worker is alone.
-    The partial sums of K terms of size 1 are sqrt(k) large, each rounded by 2^-24 / sqrt(3) of that, and the result is
-    sqrt(K) large: 2^-24 sqrt(K / 6) of it, here for halves of K = 1568.  (A term of the split left out gives 1e-6 and more.)"""
+# fc1's forward pass and input gradient on both sides of the lines between their forms.  Batches up to 64: 32 x 32, 32 x 64 and
+# 128 x 64 tiles; beyond: 32 x 32 tiles, 64 x 64, and 128 x 128 with either half of the forward sums side by side or one after the
+# other.  Whole tiles and remainders down to a column.
+@pytest.mark.parametrize("n,B", [(1, 1), (6, 64), (7, 33), (9, 64), (17, 64), (64, 32), (64, 33), (63, 64), (107, 40),
+                                 (1, 65), (1, 512), (3, 193), (32, 100), (33, 97), (64, 128), (65, 90), (40, 257)])
+def test_fc1_forms(ps, n, B):
+    """Activations and gradients of every image within what an fp32 sum may be off, and with the same bytes when their worker is
+    alone.  The partial sums of K terms of size 1 are sqrt(k) large, each rounded by 2^-24 / sqrt(3) of that, and the result is
+    sqrt(K) large: 2^-24 sqrt(K / 6) of it, here for halves of K = 1568 and for K = 512.  (A term of the split left out gives
+    1e-6 and more.)"""
     import torch
     theta = synth.he_uniform_theta(5)
     g = torch.Generator(device="cuda")
@@ -245,21 +248,30 @@ def test_fc1_forward_forms(ps, n, B):
     x = torch.rand(n, B, ps.IMAGE_PIXELS, device="cuda", generator=g)
     y = torch.randint(0, 10, (n, B), device="cuda", generator=g, dtype=torch.int32)
     ctx = ps.ps_init(ps.make_config(n, B, 1, n + 2, DROP_SEED, P_DROP))
+
+    def layer(i):
+        ps.ps_sync(ctx)
+        dbg, act = ps.ps_debug_last_batch(ctx, i), ps.ps_debug_last_activations(ctx, i)
+        return {k: v.copy() for k, v in (*dbg.items(), *act.items()) if k in ("keep", "hdrop", "pool2_val", "d3", "dpool2")}
+
+    def off(got, want):
+        return float((torch.from_numpy(got).cuda().double() - want).norm(dim=1).div(want.norm(dim=1)).nan_to_num(0.0).max())
+
     try:
         ps.ps_set_weights(ctx, theta)
         w3, b3 = (torch.from_numpy(theta[a:b]).cuda().double() for a, b in ((4800, 807616), (807616, 808128)))
+        w3 = w3.view(512, 1568)
         mbs = [synth.minibatch_id(w, 0) for w in range(n)]
         ps.worker_grads_batched(ctx, range(n), [0] * n, mbs, x, y)
-        ps.ps_sync(ctx)
-        among = {i: (ps.ps_debug_last_batch(ctx, i), ps.ps_debug_last_activations(ctx, i)["pool2_val"].copy()) for i in {0, n - 1}}
-        for i, (dbg, p2) in among.items():
-            h = (torch.from_numpy(p2).cuda().double() @ w3.view(512, 1568).t() + b3).clamp_min(0)
-            want = h * torch.from_numpy(dbg["keep"]).cuda() / (1 - P_DROP)
-            got = torch.from_numpy(dbg["hdrop"]).cuda().double()
-            assert float((got - want).norm(dim=1).div(want.norm(dim=1)).max()) <= 2.0 ** -24 * (784 / 6) ** 0.5
+        among = {i: layer(i) for i in {0, n - 1}}
+        for i, seen in among.items():
+            p2, keep, d3 = (torch.from_numpy(seen[k]).cuda().double() for k in ("pool2_val", "keep", "d3"))
+            assert off(seen["hdrop"], (p2 @ w3.t() + b3).clamp_min(0) * keep / (1 - P_DROP)) <= 2.0 ** -24 * (784 / 6) ** 0.5
+            assert off(seen["dpool2"], (d3 @ w3) * (p2 > 0)) <= 2.0 ** -24 * (512 / 6) ** 0.5
             ps.worker_grads_batched(ctx, [i], [0], [mbs[i]], x[i:i + 1], y[i:i + 1])
-            ps.ps_sync(ctx)
-            np.testing.assert_array_equal(ps.ps_debug_last_batch(ctx, 0)["hdrop"], dbg["hdrop"])
+            alone = layer(0)
+            for k in ("hdrop", "d3", "dpool2"):
+                np.testing.assert_array_equal(alone[k], seen[k])
     finally:
         ps.ps_destroy(ctx)
 
