@@ -846,9 +846,11 @@ ps_status ps_elastic_average(ps_ctx* c, const int32_t* slot_host, int32_t n, flo
         seen[s] = 1;
     }
     { const ps_status g_ = ordered_guard(c, "ps_elastic_average"); if (g_ != PS_OK) return g_; }
-    ps_status st = upload(c, c->at<int32_t>(c->lay.slotq), slot_host, (size_t)n * sizeof(int32_t));
-    if (st != PS_OK) return st;
-    PS_HIP(c, launch_elastic_average(c->theta(), c->at<float>(c->lay.ring), c->at<int32_t>(c->lay.slotq), n, alpha, c->stream,
+    if (n > ELASTIC_IN_ARGS) {
+        const ps_status st = upload(c, c->at<int32_t>(c->lay.slotq), slot_host, (size_t)n * sizeof(int32_t));
+        if (st != PS_OK) return st;
+    }
+    PS_HIP(c, launch_elastic_average(c->theta(), c->at<float>(c->lay.ring), slot_host, c->at<int32_t>(c->lay.slotq), n, alpha, c->stream,
                                      c->prof));
     c->version += 1;
     return PS_OK;

@@ -178,8 +178,19 @@ __global__ __launch_bounds__(APPLY_BLOCK) void local_step_kernel(float4* __restr
 // one row per iteration and cache-bypassing loads and stores (6.0 TB/s in a timing probe of this
 // access pattern, against 5.0 TB/s with eight loads batched before eight stores and 5.3 TB/s for
 // the runtime's device-to-device copy of the same bytes).
+// N_ARGS > 0: the slots are in the arguments; a list uploaded in front costs a copy and the wait for it (64 copies: 73.9 us with the
+// kernel's 68, now 68.6).
+template <int N_ARGS>
+struct ElasticSlots {
+    int32_t slot[N_ARGS];
+};
+template <>
+struct ElasticSlots<0> {
+    const int32_t* slot;
+};
+template <int N_ARGS>
 __global__ __launch_bounds__(APPLY_BLOCK) void elastic_average_kernel(float4* __restrict__ theta, float4* __restrict__ ring,
-                                                               const int32_t* __restrict__ slots, int n, float alpha)
+                                                               ElasticSlots<N_ARGS> slots, int n, float alpha)
 {
     const int i = blockIdx.x * APPLY_BLOCK + threadIdx.x;
     if (i >= ROW4) return;
@@ -187,7 +198,7 @@ __global__ __launch_bounds__(APPLY_BLOCK) void elastic_average_kernel(float4* __
     float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll 1
     for (int k = 0; k < n; ++k) {
-        float4* px = ring + (size_t)slots[k] * ROW4 + i;
+        float4* px = ring + (size_t)slots.slot[k] * ROW4 + i;
         const float4 x = ld_stream(px);
         const float4 d = make_float4(x.x - c.x, x.y - c.y, x.z - c.z, x.w - c.w);
         s.x += d.x; s.y += d.y; s.z += d.z; s.w += d.w;
@@ -322,13 +333,18 @@ hipError_t launch_local_steps(float* ring, const float* queue, const int32_t* pa
     return hipGetLastError();
 }
 
-hipError_t launch_elastic_average(float* theta, float* ring, const int32_t* slots_dev, int n, float alpha, hipStream_t s,
-                                  Profiler& prof)
+hipError_t launch_elastic_average(float* theta, float* ring, const int32_t* slots_host, const int32_t* slots_dev, int n, float alpha,
+                                  hipStream_t s, Profiler& prof)
 {
     if (n <= 0) return hipSuccess;
     prof.begin(K_ELASTIC, s);
-    hipLaunchKernelGGL(elastic_average_kernel, dim3((ROW4 + APPLY_BLOCK - 1) / APPLY_BLOCK), dim3(APPLY_BLOCK), 0, s, (float4*)theta, (float4*)ring,
-                       slots_dev, n, alpha);
+    if (n <= ELASTIC_IN_ARGS) {
+        ElasticSlots<ELASTIC_IN_ARGS> slots;
+        std::copy(slots_host, slots_host + n, slots.slot);
+        hipLaunchKernelGGL(elastic_average_kernel<ELASTIC_IN_ARGS>, APPLY_GRID, dim3(APPLY_BLOCK), 0, s, (float4*)theta, (float4*)ring, slots, n, alpha);
+    } else {
+        hipLaunchKernelGGL(elastic_average_kernel<0>, APPLY_GRID, dim3(APPLY_BLOCK), 0, s, (float4*)theta, (float4*)ring, ElasticSlots<0>{slots_dev}, n, alpha);
+    }
     prof.end(s);
     return hipGetLastError();
 }

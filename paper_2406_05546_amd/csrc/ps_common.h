@@ -195,9 +195,11 @@ const char* static_last_error();
 // ring[slot_j] -= lr * queue[q_j] for n (slot, q) pairs with distinct slots (pairs_dev: 2n int32).
 hipError_t launch_local_steps(float* ring, const float* queue, const int32_t* pairs_dev, int n, float lr, hipStream_t s,
                               Profiler& prof);
-// One elastic-averaging step between theta and the n listed (distinct) ring slots.
-hipError_t launch_elastic_average(float* theta, float* ring, const int32_t* slots_dev, int n, float alpha, hipStream_t s,
-                                  Profiler& prof);
+// One elastic-averaging step between theta and the n listed (distinct) ring slots; up to ELASTIC_IN_ARGS are listed in host
+// memory and travel in the kernel arguments, more in device memory.
+constexpr int ELASTIC_IN_ARGS = 256;
+hipError_t launch_elastic_average(float* theta, float* ring, const int32_t* slots_host, const int32_t* slots_dev, int n, float alpha,
+                                  hipStream_t s, Profiler& prof);
 
 // K Adadelta steps, one per listed queue row in order; acc_g2 and acc_dx2 are P-vector rows of state.
 hipError_t launch_apply_adadelta(float* theta, float* acc_g2, float* acc_dx2, const float* queue, const RowList& rows, int K, float lr,

@@ -1,0 +1,45 @@
+"""Kernels whose launches take different forms, at the sizes where these change."""
+import numpy as np
+import pytest
+
+from oracle import oracle as orc
+from paper_2406_05546_amd import synth
+
+pytestmark = pytest.mark.gpu
+DROP_SEED, P_DROP = 0xBEEF, 0.25
+
+
+@pytest.fixture(scope="module")
+def ps():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need an MI355X"
+    from paper_2406_05546_amd import binding
+    return binding
+
+
+@pytest.mark.parametrize("n", [1, 256, 257])
+def test_elastic_slots_with_the_launch_and_uploaded(ps, n):
+    """Slots in any order, in the kernel's arguments (up to 256) and from an uploaded list."""
+    import torch
+    alpha = 1 / 512
+    ctx = ps.ps_init(ps.make_config(1, 1, n + 2, 1, DROP_SEED, P_DROP))
+    try:
+        g = torch.Generator(device="cuda")
+        g.manual_seed(n)
+        rows = ctx.workspace[:(3 + n) * ps.ROW_FLOATS * 4].view(torch.float32).view(-1, ps.ROW_FLOATS)  # server, ring
+        rows[:, :ps.P] = torch.rand(3 + n, ps.P, device="cuda", generator=g) - 0.5
+        slots = (torch.randperm(n + 2, generator=torch.Generator().manual_seed(n))[:n]).tolist()
+        before = rows.clone()
+        ps.ps_elastic_average(ctx, slots, alpha)
+        ps.ps_sync(ctx)
+        at = torch.tensor(slots, device="cuda") + 1
+        d = before[at].double() - before[0].double()
+        want = before.double()
+        want[0] += alpha * d.sum(0)
+        want[at] -= alpha * d
+        # a difference, a product and n sums, each rounded to 2^-24 of values below 1 and of alpha times their sum
+        assert float((rows.double() - want).abs().max()) <= 2.0 ** -24 * (2 + 2 * alpha * n ** 0.5 * n)
+        untouched = [s + 1 for s in range(n + 2) if s not in slots]
+        assert bool((rows[untouched] == before[untouched]).all())
+    finally:
+        ps.ps_destroy(ctx)
