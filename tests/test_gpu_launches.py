@@ -43,3 +43,38 @@ def test_elastic_slots_with_the_launch_and_uploaded(ps, n):
         assert bool((rows[untouched] == before[untouched]).all())
     finally:
         ps.ps_destroy(ctx)
+
+
+@pytest.mark.parametrize("n,B", [(1, 1), (3, 15), (2, 17), (5, 40)])
+def test_evaluation_of_odd_numbers_of_images(ps, n, B):
+    """Groups of 16 images and what is left of them."""
+    import torch
+    theta = synth.he_uniform_theta(9)
+    x, y = synth.minibatches(9, [synth.minibatch_id(w, 0) for w in range(n)], B)
+    ctx = ps.ps_init(ps.make_config(n, B, 1, 1, DROP_SEED, P_DROP))
+    try:
+        ps.ps_set_weights(ctx, theta)
+        x, y = x.reshape(n * B, -1), y.reshape(-1)
+        loss, accuracy, pred = ps.ps_evaluate(ctx, -1, torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda())
+        want, want_accuracy, want_pred, z = orc.evaluate(orc.Dims(), theta.astype(np.float64), x, y)
+        assert abs(loss - want) <= 1e-6 * want  # 2^-24 sqrt(1568 / 6) of a logit, and the others' sums
+        top = np.sort(np.asarray(z), axis=1)
+        clear = top[:, -1] - top[:, -2] > 1e-5 * np.abs(z).max()
+        np.testing.assert_array_equal(np.asarray(pred)[clear], np.asarray(want_pred)[clear])
+        assert abs(accuracy - want_accuracy) <= (~clear).mean()
+    finally:
+        ps.ps_destroy(ctx)
+
+
+def test_evaluation_of_nan(ps):
+    """Weights that are all NaN predict class 0, with a loss that is not a number."""
+    import torch
+    ctx = ps.ps_init(ps.make_config(1, 20, 1, 1, DROP_SEED, P_DROP))
+    try:
+        ps.ps_set_weights(ctx, np.full(ps.P, np.nan, np.float32))
+        x, y = synth.minibatches(9, [synth.minibatch_id(0, 0)], 20)
+        loss, accuracy, pred = ps.ps_evaluate(ctx, -1, torch.from_numpy(x[0]).cuda(), torch.from_numpy(y[0]).cuda())
+        assert np.isnan(loss) and not np.asarray(pred).any()
+        assert abs(accuracy - float((y[0] == 0).mean())) < 1e-9
+    finally:
+        ps.ps_destroy(ctx)
