@@ -78,3 +78,75 @@ def test_evaluation_of_nan(ps):
         assert abs(accuracy - float((y[0] == 0).mean())) < 1e-9
     finally:
         ps.ps_destroy(ctx)
+
+
+def _clipped(theta, rows, mode, lr, clip):
+    """In 64 bits: what a clipped drain of `rows` [K, P] makes of theta, on the GPU."""
+    import torch
+    rows = rows.double()
+    c = torch.clamp(clip / rows.norm(dim=1), max=1.0)
+    return theta.double() - lr * (c[:, None] * rows).sum(0)
+
+
+# rows that a block keeps in registers (18), in LDS (11), and reads again, in sixes; the most that one pass takes and one more
+@pytest.mark.parametrize("K", [1, 17, 18, 19, 29, 30, 35, 36, 112, 113])
+@pytest.mark.parametrize("mode", [0, 1])
+def test_clipped_drain_in_one_pass(ps, K, mode):
+    """Rows on both sides of the clipping limit, consecutive ones and, in a context, in another order; a second drain over
+    other rows, which must not see anything of the first."""
+    import torch
+    lr, clip = 0.01, 4.0
+    g = torch.Generator(device="cuda")
+    g.manual_seed(K)
+    rows = torch.zeros(2 * K, ps.ROW_FLOATS, device="cuda")
+    size = torch.tensor([1e-2, 5e-3, 2e-2], device="cuda")[torch.arange(2 * K, device="cuda") % 3]
+    rows[:, :ps.P] = (torch.rand(2 * K, ps.P, device="cuda", generator=g) * 2 - 1) * size[:, None]
+    theta = torch.zeros(ps.ROW_FLOATS, device="cuda")
+    theta[:ps.P] = torch.rand(ps.P, device="cuda", generator=g) - 0.5
+    want = theta
+    for part in (rows[:K], rows[K:]):
+        want = _clipped(want, part, mode, lr, clip)
+        ps.ps_drain_rows_mitigated(theta, part, mode, lr, 0.0, clip)
+        # K roundings of weights below 1, and of a sum of K gradients below lr * 0.02 each
+        assert float((theta.double() - want).abs().max()) <= 2.0 ** -24 * (2 + K)
+        want = theta.double()
+    ctx = ps.ps_init(ps.make_config(1, 1, 1, K + 2, DROP_SEED, P_DROP))
+    try:
+        start = np.linspace(-0.5, 0.5, ps.P, dtype=np.float32)
+        ps.ps_set_weights(ctx, start)
+        host = rows[:K + 1, :ps.P].cpu().numpy()
+        first = ps.ps_queue_push_host(ctx, host[K], 0, 0, 0)
+        for k in range(K - 1):
+            ps.ps_queue_push_host(ctx, host[k], 0, 0, k)
+        ps.ps_apply_async(ctx, first, 0.0)  # its place, in front of the others, is the next one handed out
+        ps.ps_queue_push_host(ctx, host[K - 1], 0, 0, K)
+        ps.ps_drain_buffered_mitigated(ctx, mode, lr, 0.0, clip)
+        want = _clipped(torch.from_numpy(start).cuda(), rows[:K, :ps.P], mode, lr, clip)
+        assert float((torch.from_numpy(ps.ps_get_weights(ctx)).cuda().double() - want).abs().max()) <= 2.0 ** -24 * (2 + K)
+    finally:
+        ps.ps_destroy(ctx)
+
+
+@pytest.mark.parametrize("K", [5, 40])
+def test_clipped_drain_beside_other_work(ps, K):
+    """Blocks that find no compute unit while others wait for them: whoever applies a column, the bytes are the same."""
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(K)
+    rows = torch.zeros(K, ps.ROW_FLOATS, device="cuda")
+    rows[:, :ps.P] = (torch.rand(K, ps.P, device="cuda", generator=g) * 2 - 1) * 1e-2
+    a = torch.rand(4096, 4096, device="cuda", generator=g)
+    side, first = torch.cuda.Stream(), None
+    torch.cuda.synchronize()
+    for busy in [False] + [True] * 12:
+        if busy:
+            with torch.cuda.stream(side):
+                for _ in range(3):
+                    b = a @ a
+        theta = torch.full((ps.ROW_FLOATS,), 0.25, device="cuda")
+        for mode in (0, 1):
+            ps.ps_drain_rows_mitigated(theta, rows, mode, 0.01, 0.0, 4.0)
+        torch.cuda.synchronize()
+        first = theta if first is None else first
+        assert bool((theta == first).all())
+    del b
