@@ -638,12 +638,17 @@ ps_status worker_grads_append(ps_ctx* c, int32_t n, const int32_t* worker_id_hos
     if (st != PS_OK) return st;
     const uint64_t cap = (uint64_t)c->cfg.queue_capacity;
     poll_consumed(c);
-    if (c->store_claimed + (uint64_t)n - c->store_confirmed > cap) {
-        PS_HIP(c, hipStreamSynchronize(c->server));  // let enqueued server steps finish, then look again
-        poll_consumed(c);
-        if (c->store_claimed + (uint64_t)n - c->store_confirmed > cap)
-            return fail(c, PS_EFULL, "worker_grads_append: gradient store full");
+    // Server steps finish in order: the oldest one in flight first, and no more of them than make room, so that the GPU goes on
+    // with the others while this append is put together.
+    for (int i = 0; i < N_HEADRB && c->store_claimed + (uint64_t)n - c->store_confirmed > cap; ++i) {
+        const int at = (c->next_headrb + i) % N_HEADRB;
+        HeadReadback& r = c->headrb[at];
+        if (!r.in_flight) continue;
+        PS_HIP(c, hipEventSynchronize(r.done));
+        c->store_confirmed = std::max<uint64_t>(c->store_confirmed, c->headrb_host[at]);
+        r.in_flight = false;
     }
+    if (c->store_claimed + (uint64_t)n - c->store_confirmed > cap) return fail(c, PS_EFULL, "worker_grads_append: gradient store full");
 
     std::vector<int32_t> slots(version_slot_host, version_slot_host + n);
     std::sort(slots.begin(), slots.end());
@@ -692,7 +697,6 @@ ps_status ps_store_consume(ps_ctx* c, int32_t mode, float lr, int32_t max_entrie
     const StoreBuffers sb = store_buffers(c);
     PS_HIP(c, launch_store_take(sb, limit, c->server));
     PS_HIP(c, launch_apply(c->theta(), c->at<float>(c->lay.queue), RowList{sb.idx, 0, nullptr}, limit, lr, mode, c->server, c->prof, &sb.range->count));
-    PS_HIP(c, launch_store_release(sb, mode, c->server));
     HeadReadback& r = c->headrb[c->next_headrb];
     unsigned long long* dst = c->headrb_host + c->next_headrb;
     c->next_headrb = (c->next_headrb + 1) % N_HEADRB;
@@ -701,7 +705,7 @@ ps_status ps_store_consume(ps_ctx* c, int32_t mode, float lr, int32_t max_entrie
         c->store_confirmed = std::max<uint64_t>(c->store_confirmed, *dst);
         r.in_flight = false;
     }
-    PS_HIP(c, hipMemcpyAsync(dst, &sb.state->head, sizeof(unsigned long long), hipMemcpyDeviceToHost, c->server));
+    PS_HIP(c, launch_store_release(sb, mode, dst, c->server));
     PS_HIP(c, hipEventRecord(r.done, c->server));
     r.in_flight = true;
     c->server_dirty = true;
@@ -715,8 +719,7 @@ ps_status ps_store_publish(ps_ctx* c, int32_t slot)
     ps_status st = store_begin(c, "ps_store_publish");
     if (st != PS_OK) return st;
     if (c->slot_read_valid[slot]) PS_HIP(c, hipStreamWaitEvent(c->server, c->ev_slot_read[slot], 0));
-    PS_HIP(c, hipMemcpyAsync(c->ring(slot), c->theta(), sizeof(float) * PSTRIDE, hipMemcpyDeviceToDevice, c->server));
-    PS_HIP(c, launch_store_stamp_version(store_buffers(c), slot, c->server));
+    PS_HIP(c, launch_store_snapshot(store_buffers(c), slot, c->theta(), c->ring(slot), c->server));
     PS_HIP(c, hipEventRecord(c->ev_slot_written[slot], c->server));
     c->slot_written_valid[slot] = 1;
     c->server_dirty = true;

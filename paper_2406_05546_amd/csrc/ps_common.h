@@ -252,7 +252,7 @@ struct StoreBuffers {
 hipError_t launch_store_reset(const StoreBuffers& sb, unsigned long long version, hipStream_t s);
 hipError_t launch_store_publish(const StoreBuffers& sb, const WorkerMeta* meta, const int32_t* worker_id_host, int n, hipStream_t s);
 hipError_t launch_store_take(const StoreBuffers& sb, int max_entries, hipStream_t s);
-hipError_t launch_store_release(const StoreBuffers& sb, int mode, hipStream_t s);
-hipError_t launch_store_stamp_version(const StoreBuffers& sb, int slot, hipStream_t s);
+hipError_t launch_store_release(const StoreBuffers& sb, int mode, unsigned long long* head_host, hipStream_t s);
+hipError_t launch_store_snapshot(const StoreBuffers& sb, int slot, const float* theta, float* to, hipStream_t s);
 
 }  // namespace ps

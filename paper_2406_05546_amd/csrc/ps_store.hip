@@ -75,9 +75,11 @@ __global__ __launch_bounds__(64) void store_take_kernel(StoreBuffers sb, int max
     }
 }
 
-__global__ void store_release_kernel(StoreBuffers sb, int mode)
+// head_out: host memory that the new consumed count goes to as well, in place of a copy behind this launch.
+__global__ void store_release_kernel(StoreBuffers sb, int mode, u64* head_out)
 {
     const uint32_t k = sb.range->count;
+    __hip_atomic_store(head_out, sb.range->first + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     if (k == 0) return;
     StoreState* st = sb.state;
     const u64 v = st->version + (mode == 0 ? 1ull : (u64)k);
@@ -92,7 +94,13 @@ __global__ void store_release_kernel(StoreBuffers sb, int mode)
     __hip_atomic_store(&st->head, r.first + k, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__global__ void store_stamp_version_kernel(StoreBuffers sb, int slot) { sb.ring_version[slot] = sb.state->version; }
+// The server's weights into a ring slot, and the slot's version: one launch instead of the runtime's copy and another.
+__global__ __launch_bounds__(256) void store_snapshot_kernel(StoreBuffers sb, int slot, const float4* __restrict__ theta, float4* __restrict__ to)
+{
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i == 0) sb.ring_version[slot] = sb.state->version;
+    if (i < PSTRIDE / 4) to[i] = theta[i];
+}
 
 }  // namespace
 
@@ -116,15 +124,15 @@ hipError_t launch_store_take(const StoreBuffers& sb, int max_entries, hipStream_
     return hipGetLastError();
 }
 
-hipError_t launch_store_release(const StoreBuffers& sb, int mode, hipStream_t s)
+hipError_t launch_store_release(const StoreBuffers& sb, int mode, unsigned long long* head_host, hipStream_t s)
 {
-    hipLaunchKernelGGL(store_release_kernel, dim3(1), dim3(1), 0, s, sb, mode);
+    hipLaunchKernelGGL(store_release_kernel, dim3(1), dim3(1), 0, s, sb, mode, head_host);
     return hipGetLastError();
 }
 
-hipError_t launch_store_stamp_version(const StoreBuffers& sb, int slot, hipStream_t s)
+hipError_t launch_store_snapshot(const StoreBuffers& sb, int slot, const float* theta, float* to, hipStream_t s)
 {
-    hipLaunchKernelGGL(store_stamp_version_kernel, dim3(1), dim3(1), 0, s, sb, slot);
+    hipLaunchKernelGGL(store_snapshot_kernel, dim3((PSTRIDE / 4 + 255) / 256), dim3(256), 0, s, sb, slot, (const float4*)theta, (float4*)to);
     return hipGetLastError();
 }
 

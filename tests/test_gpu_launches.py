@@ -150,3 +150,36 @@ def test_clipped_drain_beside_other_work(ps, K):
         first = theta if first is None else first
         assert bool((theta == first).all())
     del b
+
+
+def test_store_runs_ahead_of_the_gpu(ps):
+    """Forty appends into a store of two appends' size without a look at the GPU in between: each waits for no more than the
+    oldest server step, and the updates are those of the ordered queue."""
+    import torch
+    n, B, lr = 3, 20, 0.01
+    theta = synth.he_uniform_theta(4)
+    mbs = [[synth.minibatch_id(w, r) for w in range(n)] for r in range(40)]
+    x, y = (torch.from_numpy(a).cuda() for a in synth.minibatches(4, mbs[0], B))
+    seen = []
+    for lock_free in (True, False):
+        ctx = ps.ps_init(ps.make_config(n, B, 2, 2 * n, DROP_SEED, P_DROP))
+        try:
+            ps.ps_set_weights(ctx, theta)
+            for r in range(40):
+                if lock_free:
+                    ps.worker_grads_append(ctx, range(n), [0] * n, mbs[r], x, y)
+                    ps.ps_store_consume(ctx, ps.DRAIN_SEQ, lr)
+                    ps.ps_store_publish(ctx, 1)
+                else:
+                    ps.worker_grads_batched(ctx, range(n), [0] * n, mbs[r], x, y)
+                    ps.ps_drain_buffered(ctx, ps.DRAIN_SEQ, lr)
+                    ps.ps_snapshot_weights(ctx, 1)
+            if lock_free:
+                state = ps.ps_store_state(ctx)
+                assert (state["claimed"], state["consumed"], state["version"]) == (40 * n, 40 * n, 40 * n)
+            seen.append([ps.ps_get_weights(ctx), ps.ps_get_weights(ctx, 1)])
+        finally:
+            ps.ps_destroy(ctx)
+    for one, other in zip(*seen):
+        np.testing.assert_array_equal(one, other)
+    np.testing.assert_array_equal(seen[0][0], seen[0][1])
