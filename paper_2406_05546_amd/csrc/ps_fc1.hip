@@ -101,7 +101,10 @@ void launch_fc1_fwd(const WorkerBuffers& wb, hipStream_t s)
 // weight gradient in a launch of its own (see ps_fc1_dw.h)
 void launch_fc1_dw(const WorkerBuffers& wb, hipStream_t s)
 {
-    gemm_launch_edge<Fc1DwMain, Fc1DwEdge, true, 0, 2>(FC1, P2_SIZE, wb.B, FC1, P2_SIZE, wb.n, FC1, FEAT_WIDE, Fc1DwEpi<true>{wb}, s);
+    if (fc1_dw_short(wb))
+        gemm_launch_edge<Fc1DwShort, Fc1DwEdge, false, 0, 3>(FC1, P2_SIZE, wb.B, FC1, P2_SIZE, wb.n, FC1, FEAT_WIDE, Fc1DwEpi<true>{wb}, s);
+    else
+        gemm_launch_edge<Fc1DwMain, Fc1DwEdge, true, 0, 2>(FC1, P2_SIZE, wb.B, FC1, P2_SIZE, wb.n, FC1, FEAT_WIDE, Fc1DwEpi<true>{wb}, s);
 }
 
 // input gradient: rows = 1568 features (W3, row-contiguous), columns = samples (d3, k-contiguous),

@@ -304,6 +304,32 @@ def test_fc1_weight_gradient_tiles(ps, n, B):
         ps.ps_destroy(ctx)
 
 
+# both sides of the lines between 64 x 128 and 128 x 128 tiles in a launch of their own; whole stages and a remainder
+@pytest.mark.parametrize("n,B", [(43, 1), (43, 17), (170, 96), (170, 97), (160, 97), (160, 128), (161, 128), (43, 128), (43, 129)])
+def test_fc1_weight_gradient_alone(ps, n, B):
+    """A sum's order depends on the batch alone: the same bytes as next to conv2's gradients, in 128 x 64 tiles, which are held
+    to 64 bits above."""
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(13 * n + B)
+    x = torch.rand(n, B, ps.IMAGE_PIXELS, device="cuda", generator=g)
+    y = torch.randint(0, 10, (n, B), device="cuda", generator=g, dtype=torch.int32)
+    ctx = ps.ps_init(ps.make_config(n, B, 1, n + 2, DROP_SEED, P_DROP))
+    try:
+        ps.ps_set_weights(ctx, synth.he_uniform_theta(5))
+        mbs = [synth.minibatch_id(w, 0) for w in range(n)]
+        q = ps.worker_grads_batched(ctx, range(n), [0] * n, mbs, x, y)
+        for i in (0, n - 1):
+            q += ps.worker_grads_batched(ctx, [i], [0], [mbs[i]], x[i:i + 1], y[i:i + 1])
+        ps.ps_sync(ctx)
+        for i, alone in ((0, q[n]), (n - 1, q[n + 1])):
+            among = ps.ps_get_grad(ctx, q[i])[4800:807616]
+            assert among.any()
+            np.testing.assert_array_equal(among, ps.ps_get_grad(ctx, alone)[4800:807616])
+    finally:
+        ps.ps_destroy(ctx)
+
+
 # the error of sums that are kept in registers over eight images
 @pytest.mark.parametrize("n,B,registers", [(8, 200, 7.92e-8), (8, 1024, 6.45e-8), (4, 4096, 7.16e-8)])
 def test_conv1_weight_gradient_error(ps, n, B, registers):
