@@ -87,8 +87,8 @@ void launch_fc1_fwd(const WorkerBuffers& wb, hipStream_t s)
             gemm_launch_chunks<true, true, FWD_CHUNKS, FWD_CHUNK>(FC1, wb.B, P2_SIZE, P2_SIZE, wb.n, narrow, epi, s);
         else
             gemm_launch<GemmCfg<true, true, 2, 1, 2, 2, 2>, FWD_CHUNK, 2>(FC1, wb.B, P2_SIZE, P2_SIZE, P2_SIZE, wb.n, epi, s);
-    } else if (gemm_roles_fit(FC1, wb.B, wb.n, wb.compute_units)) {
-        gemm_launch_roles<true, true, 2>(FC1, wb.B, P2_SIZE, P2_SIZE, P2_SIZE, wb.n, epi, s);
+    } else if (gemm_roles_fit<1>(FC1, wb.B, wb.n, wb.compute_units)) {
+        gemm_launch_roles<true, true, 2, 1>(FC1, wb.B, P2_SIZE, P2_SIZE, P2_SIZE, wb.n, epi, s);
     } else if (2 * wide_tiles <= wb.compute_units) {  // 64 x 64 tiles: two for a compute unit at most
         gemm_launch_sides<GemmCfg<true, true, 1, 1, 2, 2, 4>>(FC1, wb.B, P2_SIZE, P2_SIZE, P2_SIZE, wb.n, epi, s);
     } else if (wide_tiles <= wb.compute_units) {
@@ -112,7 +112,8 @@ void launch_fc1_dw(const WorkerBuffers& wb, hipStream_t s)
 void launch_fc1_dx(const WorkerBuffers& wb, hipStream_t s)
 {
     // 64 x 64 tiles already fall behind where there is a wide tile for two compute units (8 workers of 128 images, 96
-    // tiles: 22 against 28 us; 16 of 128: 37 against 31)
+    // tiles: 22 against 28 us; 16 of 128: 37 against 31); where each finds a compute unit, some wavefronts only multiply (two of
+    // 128: 16.6 -> 13.4 us)
     const int wide_tiles = FEAT_WIDE / 128 * ((wb.B + 127) / 128) * wb.n;
     const bool few = gemm_few_tiles(2 * wide_tiles, wb.compute_units);
     const Fc1DxEpi epi{wb};
@@ -123,8 +124,10 @@ void launch_fc1_dx(const WorkerBuffers& wb, hipStream_t s)
         else
             gemm_launch_edge<GemmCfg<false, true, 2, 1, 2, 2, 2>, GemmCfg<false, true, 1, 1, 1, 4, 2>, false, DX_CHUNK, 2>(P2_SIZE, wb.B, FC1, P2_SIZE, FC1, wb.n,
                                                                                                           FEAT_WIDE, wb.B, epi, s);
-    } else if (gemm_roles_fit(P2_SIZE, wb.B, wb.n, wb.compute_units)) {
-        gemm_launch_roles<false, true, 1>(P2_SIZE, wb.B, FC1, P2_SIZE, FC1, wb.n, epi, s);
+    } else if (gemm_roles_fit<1>(P2_SIZE, wb.B, wb.n, wb.compute_units)) {
+        gemm_launch_roles<false, true, 1, 1>(P2_SIZE, wb.B, FC1, P2_SIZE, FC1, wb.n, epi, s);
+    } else if (gemm_roles_fit<2>(P2_SIZE, wb.B, wb.n, wb.compute_units)) {
+        gemm_launch_roles<false, true, 1, 2>(P2_SIZE, wb.B, FC1, P2_SIZE, FC1, wb.n, epi, s);
     } else if (few) {
         gemm_launch<GemmCfg<false, true, 1, 1, 2, 2, 4, 32>, 0, 2>(P2_SIZE, wb.B, FC1, P2_SIZE, FC1, wb.n, epi, s);
     } else {

@@ -655,18 +655,24 @@ __global__ __launch_bounds__(64 * CHUNKS, NT == 1 ? 4 : CHUNKS == 4 ? 3 : 2) voi
 }
 
 // The same sums for a launch with so few tiles that its time is that of one block's serial loop over K: for each of PARTS
-// halves of the contraction (or all of it, the sums of gemm_block<..., 0>) a wavefront that does nothing but multiply, a tile of
-// 32 x 32, and four that bring its operands in and split them, 32 contraction indices at a time.  (A last stage of fewer begins
-// earlier instead, and what comes twice is passed over.)  Bound by the chain of the five small terms of a step, each of which
+// halves of the contraction (or all of it, the sums of gemm_block<..., 0>) T x T wavefronts that do nothing but multiply, a tile of
+// 32 x 32 each, and four T that bring their operands in and split them, 32 contraction indices at a time.  (A last stage of fewer
+// begins earlier instead, and what comes twice is passed over.)  Bound by the chain of the five small terms of a step, each of which
 // waits 66 cycles for the one before, 330 to a step of 16, and up to 200 more where splits are issued on the same SIMD.
 // Forward of one worker of 256 images or four of 128: 64 x 64 tiles, whose wavefronts do everything, 38 us, in one part 24, in
-// two 18.  Input gradient, one part, of one of 100 15.4 -> 9.4 us, of two 15.4 -> 16.3.
-template <bool A_KC, bool B_KC, int PARTS, class Epi>
-__global__ __launch_bounds__(320 * PARTS) void gemm_split_roles(GemmShape sh, Epi epi)
+// two 18.  Input gradient, one part, of one of 100 15.4 -> 9.4 us, of two 15.4 -> 16.3.  T = 2, a multiplying wavefront on each
+// SIMD, input gradient of two of 100 to one of 512 16.6 -> 13.4 us (events included; with four that bring 15.2, and two such
+// blocks to a compute unit, eight of 128, 25.6 against 21.3 in 64 x 64 tiles).  In two parts there is room for four of them to a part
+// only: forward of five to ten of 128 32.4 against 26.4 us side by side.
+constexpr int roles_bring(int T) { return 4 * T; }  // wavefronts of a part that bring operands; T * T multiply
+template <bool A_KC, bool B_KC, int PARTS, int T, class Epi>
+__global__ __launch_bounds__(64 * PARTS * (T * T + roles_bring(T))) void gemm_split_roles(GemmShape sh, Epi epi)
 {
     constexpr int KS = 2 * GEMM_K, SUBS = KS / GEMM_K, AHEAD = 4;  // stages on their way in registers
-    using OpA = GemmOperand<32, A_KC, false, 128, KS>;
-    using OpB = GemmOperand<32, B_KC, false, 128, KS>;
+    constexpr int MULT = T * T, BRING = roles_bring(T), NT = 64 * BRING / 2;
+    static_assert(T == 1 || (T == 2 && PARTS == 1), "the parts of one tile meet");
+    using OpA = GemmOperand<32 * T, A_KC, false, NT, KS>;
+    using OpB = GemmOperand<32 * T, B_KC, false, NT, KS>;
     constexpr int STAGE = OpA::BYTES + OpB::BYTES;
     static_assert(OpA::NV == OpB::NV, "one register set for either operand");
     __shared__ __attribute__((aligned(16))) char lds[PARTS][3 * STAGE];
@@ -674,9 +680,10 @@ __global__ __launch_bounds__(320 * PARTS) void gemm_split_roles(GemmShape sh, Ep
     const int lane = threadIdx.x & 63, wave = uniform(threadIdx.x >> 6);
     const int v = gemm_tile(blockIdx.x, sh.gx * sh.gy * sh.gz);
     if (v >= sh.gx * sh.gy * sh.gz) return;
-    const int m0 = v % sh.gx * 32, n0 = v / sh.gx % sh.gy * 32, z = v / (sh.gx * sh.gy);
-    const bool multiplies = wave < PARTS;
-    const int half = multiplies ? wave : (wave - PARTS) >> 2, bringer = (wave - PARTS) & 3, t = (64 * bringer + lane) & 127;
+    const int m0 = v % sh.gx * (32 * T), n0 = v / sh.gx % sh.gy * (32 * T), z = v / (sh.gx * sh.gy);
+    const bool multiplies = wave < PARTS * MULT;
+    const int half = multiplies ? wave / MULT : (int)((uint32_t)(wave - PARTS * MULT) / BRING), bringer = (wave - PARTS * MULT) & (BRING - 1), t = (64 * bringer + lane) & (NT - 1);
+    const int mt = wave & (T - 1), nt = wave / T & (T - 1);  // tile of a multiplying wavefront
     const int K = sh.K / PARTS, k_first = half * K, nk = (K + KS - 1) / KS, tail = (nk * KS - K) / GEMM_K;  // MFMA steps that the last stage repeats
 
     // While stage kt is multiplied, out of one buffer, stage kt + 1 lies in the second and stage kt + 2 comes into the
@@ -691,7 +698,7 @@ __global__ __launch_bounds__(320 * PARTS) void gemm_split_roles(GemmShape sh, Ep
         later = read;
     };
     if (!multiplies) {
-        const bool brings_b = bringer >= 2;
+        const bool brings_b = bringer >= BRING / 2;
         OpA opa;
         OpB opb;
         if (brings_b)
@@ -750,8 +757,8 @@ __global__ __launch_bounds__(320 * PARTS) void gemm_split_roles(GemmShape sh, Ep
     acc.clear();
     Split8 fa, fb;
     auto fetch = [&](const char* stage, int sub) {
-        fa = OpA::fetch(stage, 0, sub, lane);
-        fb = OpB::fetch(stage + OpA::BYTES, 0, sub, lane);
+        fa = OpA::fetch(stage, mt, sub, lane);
+        fb = OpB::fetch(stage + OpA::BYTES, nt, sub, lane);
     };
     fetch(now, nk == 1 ? tail : 0);
     for (int kt = 0; kt < nk; ++kt) {
@@ -779,7 +786,7 @@ __global__ __launch_bounds__(320 * PARTS) void gemm_split_roles(GemmShape sh, Ep
     for (int p = 1; p < PARTS; ++p)
 #pragma unroll
         for (int i = 0; i < 16; ++i) sums[i] += meet[p][i][lane];
-    gemm_finish<A_KC, B_KC>(sh, epi, z, m0, n0, lane, sums);
+    gemm_finish<A_KC, B_KC>(sh, epi, z, m0 + 32 * mt, n0 + 32 * nt, lane, sums);
 }
 
 // Whether a launch over this many 128 x 128 tiles leaves compute units idle.
@@ -959,16 +966,20 @@ void gemm_launch_parts(int M, int N, int lda, int ldb, int batch, const Epi& epi
     hipLaunchKernelGGL((gemm_split_parts<Cfg, Epi>), dim3(gemm_grid(sh)), dim3(256), 0, s, sh, epi);
 }
 
-// Whether every tile of 32 x 32 finds a compute unit of its own (both sides measured: gemm_split_roles).
-inline bool gemm_roles_fit(int M, int N, int batch, int compute_units) { return (M + 31) / 32 * ((N + 31) / 32) * batch <= compute_units; }
+// Whether every tile of 32 T x 32 T finds a compute unit of its own (both sides measured: gemm_split_roles).
+template <int T>
+bool gemm_roles_fit(int M, int N, int batch, int compute_units)
+{
+    return (M + 32 * T - 1) / (32 * T) * ((N + 32 * T - 1) / (32 * T)) * batch <= compute_units;
+}
 
 // K / PARTS: at least 32, a multiple of 16.
-template <bool A_KC, bool B_KC, int PARTS, class Epi>
+template <bool A_KC, bool B_KC, int PARTS, int T, class Epi>
 void gemm_launch_roles(int M, int N, int K, int lda, int ldb, int batch, const Epi& epi, hipStream_t s)
 {
     if (M <= 0 || N <= 0 || batch <= 0) return;
-    const GemmShape sh{M, N, K, lda, ldb, (M + 31) / 32, (N + 31) / 32, batch, 0, 0};
-    hipLaunchKernelGGL((gemm_split_roles<A_KC, B_KC, PARTS, Epi>), dim3(gemm_grid(sh)), dim3(320 * PARTS), 0, s, sh, epi);
+    const GemmShape sh{M, N, K, lda, ldb, (M + 32 * T - 1) / (32 * T), (N + 32 * T - 1) / (32 * T), batch, 0, 0};
+    hipLaunchKernelGGL((gemm_split_roles<A_KC, B_KC, PARTS, T, Epi>), dim3(gemm_grid(sh)), dim3(64 * PARTS * (T * T + roles_bring(T))), 0, s, sh, epi);
 }
 
 // One problem per batch index in tiles of 32 x 32 (narrow) or 32 x 64; K = CHUNKS * CHUNK MFMA steps.

@@ -233,9 +233,9 @@ def test_images_of_a_wavefront(ps, n, B):
 
 # fc1's forward pass and input gradient on both sides of the lines between their forms.  Batches up to 64: 32 x 32, 32 x 64 and
 # 128 x 64 tiles; beyond: 32 x 32 tiles, 64 x 64, and 128 x 128 with either half of the forward sums side by side or one after the
-# other.  Whole tiles and remainders down to a column.
+# other, and 64 x 64 ones of the input gradient with wavefronts that only multiply.  Whole tiles and remainders down to a column.
 @pytest.mark.parametrize("n,B", [(1, 1), (6, 64), (7, 33), (9, 64), (17, 64), (64, 32), (64, 33), (63, 64), (107, 40),
-                                 (1, 65), (1, 512), (3, 193), (32, 100), (33, 97), (64, 128), (65, 90), (40, 257)])
+                                 (1, 65), (1, 512), (1, 640), (1, 641), (2, 130), (5, 128), (5, 129), (3, 193), (32, 100), (33, 97), (64, 128), (65, 90), (40, 257)])
 def test_fc1_forms(ps, n, B):
     """Activations and gradients of every image within what an fp32 sum may be off, and with the same bytes when their worker is
     alone.  The partial sums of K terms of size 1 are sqrt(k) large, each rounded by 2^-24 / sqrt(3) of that, and the result is
