@@ -80,7 +80,7 @@ def reduce_bytes_per_worker(batch):
 MIB = 1 << 20
 COUNTER_SUMMARY = os.path.join(ROOT, "profiles", "bench_outage_w256_b256_hbm_counters.txt")
 COUNTER_ROWS = {"conv1_fwd_kernel": "conv1_fwd_kernel<0>", "conv2_fwd_kernel": "conv2_fwd_kernel", "fc2_kernel": "::fc2_kernel",
-                "gemm_split<Fc1FwdEpi>": "gemm_split<ps::GemmCfg<true, true",
+                "gemm_split<Fc1FwdEpi>": "gemm_split_parts<ps::GemmCfg<true, true",
                 "gemm_split<Fc1DwEpi>": "gemm_split_edge<ps::GemmCfg<false, false",
                 "gemm_split<Fc1DxEpi>": "gemm_split_edge<ps::GemmCfg<false, true", "backward_kernel": "backward_kernel<ps::(anonymous namespace)::NoFc1",
                 "grad_reduce_kernel": "grad_reduce_kernel",
