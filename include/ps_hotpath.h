@@ -168,10 +168,10 @@ PS_API ps_status ps_drain_buffered_mitigated(ps_ctx* ctx, int32_t mode, const ps
  * arrival order.  Mode, policy and *lr_used_host (host, may be NULL) are those of
  * ps_drain_buffered_mitigated, and the same kernels run, on `hip_stream` (a hipStream_t, NULL for the
  * default stream), asynchronously.  The row list, the partial sums of the squared norms and the clip
- * factors, which the context-based call keeps in its workspace, live in a fixed array of 560,128 bytes
+ * factors, which the context-based call keeps in its workspace, live in a fixed array of 557,056 bytes
  * in the library's device image (each GPU the process uses holds one copy until the process ends); the
  * call allocates and frees nothing, on the host or on the device, and clears nothing (every element it
- * reads it has written first, but for counters that go on from call to call).  n_rows > PS_STATIC_DRAIN_MAX_ROWS gives PS_EINVAL and nothing runs;
+ * reads it has written first).  n_rows > PS_STATIC_DRAIN_MAX_ROWS gives PS_EINVAL and nothing runs;
  * n_rows = 0 changes nothing.  All calls on one GPU share that GPU's array: two calls whose kernels may
  * overlap (different streams, or threads) race.  The address of the array is looked up on the first call
  * on a device, or by ps_init on that device, whichever comes first; make one of them before a capture

@@ -52,7 +52,7 @@ struct Carve {
 };
 
 struct Layout {
-    uint64_t theta, ring, queue, ada_g2, ada_dx2, meta, idx, slotq, st_state, st_stamp, st_entry, st_ringver, st_log, st_range, st_idx, st_wid, hold, p1, am1, p2, am2, am2t, ht, z, pred, d3, dp2g, gscale, part, part1, fpart, normpart, scale, eval_loss, eval_ok, keep, total;
+    uint64_t theta, ring, queue, ada_g2, ada_dx2, meta, idx, slotq, st_state, st_stamp, st_entry, st_ringver, st_log, st_range, st_idx, st_wid, p1, am1, p2, am2, am2t, ht, z, pred, d3, dp2g, gscale, part, part1, fpart, normpart, scale, eval_loss, eval_ok, keep, total;
 };
 
 bool config_ok(const ps_config* c)
@@ -82,7 +82,6 @@ Layout make_layout(const ps_config& c)
     l.st_range = k.take(sizeof(StoreRange));
     l.st_idx = k.take(sizeof(int32_t) * c.queue_capacity);
     l.st_wid = k.take(sizeof(int32_t) * c.max_workers);
-    l.hold = k.take(sizeof(HoldState));
     l.p1 = k.take(n * P1_SIZE * 4);
     l.am1 = k.take(n * P1_SIZE);
     l.p2 = k.take(n * P2_SIZE * 4);
@@ -97,7 +96,7 @@ Layout make_layout(const ps_config& c)
     l.part = k.take((uint64_t)c.max_workers * conv2_part_slots(c.batch) * CONV2_PART * 4);
     l.part1 = k.take((uint64_t)c.max_workers * conv1_part_slots(c.batch) * OFF_W2 * 4);
     l.fpart = k.take((uint64_t)(512 + c.max_workers) * FC2_PART * 4);  // >= n * fc2_split(n) slots
-    l.normpart = k.take(norm_partials(c.queue_capacity) * 4);
+    l.normpart = k.take((uint64_t)c.queue_capacity * norm_slices() * 4);
     l.scale = k.take((uint64_t)c.queue_capacity * 4);
     l.eval_loss = k.take(n * 4);
     l.eval_ok = k.take(n * 4);
@@ -410,8 +409,7 @@ ps_status ps_init(ps_ctx** out, const ps_config* cfg, void* workspace_dev, uint6
     // the drain entry point that allocates nothing finds its scratch array resolved on this device
     if (e == hipSuccess) {
         unsigned char* unused = nullptr;
-        int units = 0;
-        e = static_scratch(&unused, &units);
+        e = static_scratch(&unused);
     }
     // Weights, ring, queue (padding included) and the index arrays start at zero.
     if (e == hipSuccess) e = hipMemsetAsync(c->ws, 0, lay.p1, c->stream);
@@ -611,7 +609,7 @@ ps_status ps_drain_buffered_mitigated(ps_ctx* c, int32_t mode, const ps_drain_po
         ps_status st = row_list(c, idx, &rows);
         if (st != PS_OK) return st;
         PS_HIP(c, launch_apply_clipped(c->theta(), c->at<float>(c->lay.queue), rows, (int)idx.size(), lr, mode, pol->clip_norm, c->at<float>(c->lay.normpart), c->at<float>(c->lay.scale),
-                                       c->compute_units >= HOLD_BLOCKS ? c->at<HoldState>(c->lay.hold) : nullptr, c->stream, c->prof));
+                                       c->stream, c->prof));
     } else {
         ps_status st = apply_entries(c, idx, lr, mode);
         if (st != PS_OK) return st;

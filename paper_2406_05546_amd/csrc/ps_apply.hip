@@ -11,9 +11,9 @@ static_assert(PS_ROW_FLOATS == ps::PSTRIDE, "header and kernels disagree on the 
 
 // Fixed scratch memory of the drain entry point that allocates nothing (ps_drain_rows_mitigated, at the
 // end of this file): row list int32 [rows] | clip factors float [rows] | partial sums of the squared norms
-// float [rows][32] | what a clipped drain in one launch keeps of its blocks (ps::HoldState).  Every GPU the process uses holds its
-// own copy at its own address; in host code this name is only a handle for hipGetSymbolAddress, never a device address.
-#define PS_STATIC_SCRATCH_BYTES ((size_t)PS_STATIC_DRAIN_MAX_ROWS * (4 + 4 + 4 * 32) + 3072)  /* 560,128 */
+// float [rows][32].  Every GPU the process uses holds its own copy at its own address; in host
+// code this name is only a handle for hipGetSymbolAddress, never a device address.
+#define PS_STATIC_SCRATCH_BYTES ((size_t)PS_STATIC_DRAIN_MAX_ROWS * (4 + 4 + 4 * 32))  /* 557,056 */
 static __device__ __align__(256) unsigned char scratch[PS_STATIC_SCRATCH_BYTES];
 
 namespace ps {
@@ -243,191 +243,6 @@ __global__ __launch_bounds__(256) void clip_scale_kernel(const float* __restrict
     scale[k] = norm > clip ? clip / norm : 1.f;
 }
 
-
-// Clipped drain in one launch that reads a row once as far as the chip can hold it: a factor needs the norm of the whole row, so
-// that two passes read everything twice, at the read rate both times.  A block to every compute unit has its share of the columns (a
-// float4 to a thread) of all rows: it forms its part of the rows' norms, keeps the first HOLD rows, in registers and in LDS,
-// waits until all blocks have published their parts, and applies; only the rows beyond HOLD are read again, the first of
-// them while it waits.  8 rows 21.7 -> 12.4 us, 27 35.6 -> 25, 64 67.8 -> 59.7, 100 106 -> 98.5, 112 115 -> 111.6; with 128 two passes are ahead.
-// Nothing has to be resident at the same time: a block whose wait comes to its end (other kernels hold compute units that blocks
-// still need) leaves its columns to clipped_rest_kernel, which follows and otherwise finds nothing to do.
-// `arrived` counts the blocks of all such launches and is never reset: before and after each, all its counters are the same
-// multiple of the blocks that use one (several, since 256 additions at one place take microseconds).
-// Parts and count are written and read past the caches (relaxed atomics of the whole GPU, a wait between a part and the arrival,
-// a barrier between the count and the others' parts).  Release and acquire in their place write back and invalidate an L2 for every
-// block: 50 us.
-constexpr int HOLD_WAVES = 13, HOLD_THREADS = 64 * HOLD_WAVES, HOLD_REGS = 18, HOLD_LDS = 11, HOLD_AHEAD = 6;
-constexpr int HOLD = HOLD_REGS + HOLD_LDS, HOLD_COLUMNS = (ROW4 + HOLD_BLOCKS - 1) / HOLD_BLOCKS;  // rows; columns of a block
-constexpr long long HOLD_WAIT = 5000;  // ticks of 10 ns
-static_assert(HOLD_COLUMNS <= HOLD_THREADS, "a column to a thread");
-
-struct HoldArgs {
-    float* partial;  // [K][HOLD_BLOCKS] sums of squares
-    HoldState* state;
-    int K;
-    float lr, clip;
-};
-
-// Sum over the wavefront: inside rows of 16 lanes by data-parallel primitives, then over the four rows.  (Through LDS, 64 rows'
-// sums were 15 us of the block's time.)
-__device__ __forceinline__ float wave_sum(float v)
-{
-    const auto add = [&](float x) { v += x; };
-    add(__int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, false)));   // quad_perm [1,0,3,2]
-    add(__int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xF, 0xF, false)));   // quad_perm [2,3,0,1]
-    add(__int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x141, 0xF, 0xF, false)));  // row_half_mirror
-    add(__int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x140, 0xF, 0xF, false)));  // row_mirror
-    const auto row = [&](int lane) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane)); };
-    return (row(0) + row(16)) + (row(32) + row(48));
-}
-__device__ __forceinline__ float square(const float4& g) { return fmaf(g.x, g.x, fmaf(g.y, g.y, fmaf(g.z, g.z, g.w * g.w))); }
-
-// scale[k] = min(1, clip / ||g_k||_2)  (1 for a zero gradient), by the wavefronts of a block.
-template <int WAVES>
-__device__ __forceinline__ void clip_scales(const HoldArgs& h, float* scale)
-{
-    const int lane = threadIdx.x & 63;
-    for (int k = threadIdx.x >> 6; k < h.K; k += WAVES) {
-        float sq = 0.f;
-#pragma unroll
-        for (int b = 0; b < HOLD_BLOCKS; b += 64)
-            sq += __hip_atomic_load(h.partial + k * HOLD_BLOCKS + b + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const float norm = sqrtf(wave_sum(sq));
-        if (lane == 0) scale[k] = norm > h.clip ? h.clip / norm : 1.f;
-    }
-}
-
-// One more gradient, scaled by c: an update of t, or of the sum.
-template <int MODE>
-__device__ __forceinline__ void take_row(const float4& g, float c, float lr, float4& t, float4& s)
-{
-    if (MODE == 0) {
-        s.x = fmaf(c, g.x, s.x); s.y = fmaf(c, g.y, s.y); s.z = fmaf(c, g.z, s.z); s.w = fmaf(c, g.w, s.w);
-    } else {
-        const float a = -lr * c;
-        t.x = fmaf(a, g.x, t.x); t.y = fmaf(a, g.y, t.y); t.z = fmaf(a, g.z, t.z); t.w = fmaf(a, g.w, t.w);
-    }
-}
-
-template <int MODE, bool LISTED>
-__global__ __launch_bounds__(HOLD_THREADS) void clipped_hold_kernel(float4* __restrict__ theta, const float4* __restrict__ queue, RowList rows, HoldArgs h)
-{
-    __shared__ float4 kept[HOLD_LDS][HOLD_THREADS];
-    __shared__ float waves[HOLD_MAX_ROWS][HOLD_WAVES];  // of a row: the wavefronts' sums, then [.][0] its factor
-    __shared__ int go_on;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, K = h.K;
-    const int i = blockIdx.x * HOLD_COLUMNS + tid;
-    const bool mine = tid < HOLD_COLUMNS && i < ROW4;
-    const float4* col = queue + (mine ? i : 0);
-    auto load = [&](int k) { return k < K ? ld_stream(col + row_of<LISTED>(rows, k)) : make_float4(0.f, 0.f, 0.f, 0.f); };
-    auto norm_part = [&](int k, const float4& g) {
-        if (k >= K) return;
-        const float sq = wave_sum(mine ? square(g) : 0.f);
-        if (lane == 0) waves[k][wave] = sq;
-    };
-    float4 held[HOLD_REGS];
-    {
-        float4 g[HOLD_LDS];
-#pragma unroll
-        for (int k = 0; k < HOLD_REGS; ++k) held[k] = load(k);
-#pragma unroll
-        for (int k = 0; k < HOLD_LDS; ++k) g[k] = load(HOLD_REGS + k);
-        __builtin_amdgcn_sched_barrier(0);  // all on their way
-#pragma unroll
-        for (int k = 0; k < HOLD_REGS; ++k) norm_part(k, held[k]);
-#pragma unroll
-        for (int k = 0; k < HOLD_LDS; ++k) {
-            norm_part(HOLD_REGS + k, g[k]);
-            kept[k][tid] = g[k];
-        }
-    }
-#pragma unroll 1
-    for (int k0 = HOLD; k0 < K; k0 += HOLD_AHEAD) {
-        float4 g[HOLD_AHEAD];
-#pragma unroll
-        for (int u = 0; u < HOLD_AHEAD; ++u) g[u] = load(k0 + u);
-#pragma unroll
-        for (int u = 0; u < HOLD_AHEAD; ++u) norm_part(k0 + u, g[u]);
-    }
-    __syncthreads();
-    if (tid < K) {
-        float sq = 0.f;
-#pragma unroll
-        for (int v = 0; v < HOLD_WAVES; ++v) sq += waves[tid][v];
-        __hip_atomic_store(h.partial + tid * HOLD_BLOCKS + blockIdx.x, sq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this block's parts are where all see them before its arrival
-    __syncthreads();
-    unsigned long long before = 0;
-    if (tid == 0) before = __hip_atomic_fetch_add(&h.state->arrived[blockIdx.x % HOLD_COUNTERS][0], 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    float4 g[HOLD_AHEAD];  // the first rows that are read again
-#pragma unroll
-    for (int u = 0; u < HOLD_AHEAD; ++u) g[u] = load(HOLD + u);
-    float4 t = mine ? theta[i] : make_float4(0.f, 0.f, 0.f, 0.f), s = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (wave == 0) {
-        constexpr int EACH = HOLD_BLOCKS / HOLD_COUNTERS;
-        const unsigned long long all = (__shfl(before, 0, 64) / EACH + 1) * EACH;
-        const long long start = wall_clock64();
-        bool there = false;
-        do {
-            there = __all(__hip_atomic_load(&h.state->arrived[lane % HOLD_COUNTERS][0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= all);
-        } while (!there && wall_clock64() - start < HOLD_WAIT);
-        if (lane == 0) {
-            go_on = there;
-            h.state->done[blockIdx.x] = there;
-        }
-    }
-    __syncthreads();
-    if (!go_on) return;
-    clip_scales<HOLD_WAVES>(h, &waves[0][0]);  // [k], in the place of the wavefronts' sums
-    __syncthreads();
-    const float* scale = &waves[0][0];
-#pragma unroll
-    for (int k = 0; k < HOLD_REGS; ++k)
-        if (k < K) take_row<MODE>(held[k], scale[k], h.lr, t, s);
-#pragma unroll
-    for (int k = 0; k < HOLD_LDS; ++k)
-        if (HOLD_REGS + k < K) take_row<MODE>(kept[k][tid], scale[HOLD_REGS + k], h.lr, t, s);
-#pragma unroll 1
-    for (int k0 = HOLD; k0 < K; k0 += HOLD_AHEAD) {
-        float4 now[HOLD_AHEAD];
-#pragma unroll
-        for (int u = 0; u < HOLD_AHEAD; ++u) now[u] = g[u];
-        if (k0 + HOLD_AHEAD < K) {
-#pragma unroll
-            for (int u = 0; u < HOLD_AHEAD; ++u) g[u] = load(k0 + HOLD_AHEAD + u);
-        }
-#pragma unroll
-        for (int u = 0; u < HOLD_AHEAD; ++u)
-            if (k0 + u < K) take_row<MODE>(now[u], scale[k0 + u], h.lr, t, s);
-    }
-    if (MODE == 0) take_row<1>(s, 1.f, h.lr, t, s);
-    if (mine) theta[i] = t;
-}
-
-// The columns of blocks whose wait came to its end.
-template <int MODE, bool LISTED>
-__global__ __launch_bounds__(256) void clipped_rest_kernel(float4* __restrict__ theta, const float4* __restrict__ queue, RowList rows, HoldArgs h)
-{
-    __shared__ float scale[HOLD_MAX_ROWS];
-    if (h.state->done[blockIdx.x]) return;
-    clip_scales<4>(h, scale);
-    __syncthreads();
-    for (int i = blockIdx.x * HOLD_COLUMNS + threadIdx.x; i < min(ROW4, (int)(blockIdx.x + 1) * HOLD_COLUMNS); i += 256) {
-        float4 t = theta[i], s = make_float4(0.f, 0.f, 0.f, 0.f);
-        for (int k0 = 0; k0 < h.K; k0 += UNROLL) {
-            float4 g[UNROLL];
-#pragma unroll
-            for (int u = 0; u < UNROLL; ++u) g[u] = ld_stream(queue + i + row_of<LISTED>(rows, min(k0 + u, h.K - 1)));
-#pragma unroll
-            for (int u = 0; u < UNROLL; ++u)
-                if (k0 + u < h.K) take_row<MODE>(g[u], scale[k0 + u], h.lr, t, s);
-        }
-        if (MODE == 0) take_row<1>(s, 1.f, h.lr, t, s);
-        theta[i] = t;
-    }
-}
-
 }  // namespace
 
 namespace {
@@ -476,31 +291,10 @@ hipError_t launch_apply(float* theta, const float* queue, const RowList& given, 
     return hipGetLastError();
 }
 
-namespace {
-
-template <int MODE, bool LISTED>
-void start_hold(float* theta, const float* queue, const RowList& rows, const HoldArgs& h, hipStream_t s)
-{
-    hipLaunchKernelGGL((clipped_hold_kernel<MODE, LISTED>), dim3(HOLD_BLOCKS), dim3(HOLD_THREADS), 0, s, (float4*)theta, (const float4*)queue, rows, h);
-    hipLaunchKernelGGL((clipped_rest_kernel<MODE, LISTED>), dim3(HOLD_BLOCKS), dim3(256), 0, s, (float4*)theta, (const float4*)queue, rows, h);
-}
-
-}  // namespace
-
 hipError_t launch_apply_clipped(float* theta, const float* queue, const RowList& given, int K, float lr, int mode, float clip,
-                                float* partial_dev, float* scale_dev, HoldState* state, hipStream_t s, Profiler& prof)
+                                float* partial_dev, float* scale_dev, hipStream_t s, Profiler& prof)
 {
     if (K <= 0) return hipSuccess;
-    if (state && K <= HOLD_MAX_ROWS) {
-        const HoldArgs h{partial_dev, state, K, lr, clip};
-        prof.begin(mode == 0 ? K_APPLY_SUM_CLIP : K_APPLY_SEQ_CLIP, s);
-        if (given.list)
-            mode == 0 ? start_hold<0, true>(theta, queue, given, h, s) : start_hold<1, true>(theta, queue, given, h, s);
-        else
-            mode == 0 ? start_hold<0, false>(theta, queue, given, h, s) : start_hold<1, false>(theta, queue, given, h, s);
-        prof.end(s);
-        return hipGetLastError();
-    }
     const RowList rows = listed(given, K, LISTED_ROWS, s);
     prof.begin(K_GRAD_SQNORM, s);
     hipLaunchKernelGGL(rows.list ? grad_sqnorm_kernel<true> : grad_sqnorm_kernel<false>, dim3(NORM_SLICES, K), dim3(256), 0, s,
@@ -555,7 +349,7 @@ hipError_t launch_elastic_average(float* theta, float* ring, const int32_t* slot
     return hipGetLastError();
 }
 
-uint64_t norm_partials(uint64_t rows) { return std::max(rows * NORM_SLICES, std::min<uint64_t>(rows, HOLD_MAX_ROWS) * HOLD_BLOCKS); }
+int norm_slices() { return NORM_SLICES; }
 
 // ---------------------------------------------------------------------------------------------
 // Drain for callers that cannot allocate.  What the context's workspace holds for the mitigated drain
@@ -567,13 +361,10 @@ constexpr int STATIC_MAX_ROWS = PS_STATIC_DRAIN_MAX_ROWS;
 constexpr size_t STATIC_IDX_OFF = 0;                                                   // int32 [rows]
 constexpr size_t STATIC_SCALE_OFF = STATIC_IDX_OFF + sizeof(int32_t) * STATIC_MAX_ROWS;  // float [rows]
 constexpr size_t STATIC_PART_OFF = STATIC_SCALE_OFF + sizeof(float) * STATIC_MAX_ROWS;   // float [rows][NORM_SLICES]
-constexpr size_t STATIC_HOLD_OFF = STATIC_PART_OFF + sizeof(float) * STATIC_MAX_ROWS * NORM_SLICES;  // HoldState, zero in the beginning
-static_assert(HOLD_MAX_ROWS * HOLD_BLOCKS <= STATIC_MAX_ROWS * NORM_SLICES && STATIC_HOLD_OFF % 256 == 0, "parts of the norms");
-static_assert(STATIC_HOLD_OFF + sizeof(HoldState) <= PS_STATIC_SCRATCH_BYTES, "scratch array size");
+static_assert(STATIC_PART_OFF + sizeof(float) * STATIC_MAX_ROWS * NORM_SLICES == PS_STATIC_SCRATCH_BYTES, "scratch array size");
 
 constexpr int MAX_DEVICES = 64;
 unsigned char* scratch_of_device[MAX_DEVICES] = {};  // device address of `scratch` on each GPU, once resolved
-int compute_units_of_device[MAX_DEVICES] = {};        // and how many compute units that GPU has
 
 thread_local char static_error[160] = "";
 
@@ -587,7 +378,7 @@ ps_status static_fail(ps_status st, const char* msg)
 
 // Device address of this GPU's copy of the array (the array's name is only a host-side handle), looked
 // up once per device with that device current.
-hipError_t static_scratch(unsigned char** out, int* compute_units)
+hipError_t static_scratch(unsigned char** out)
 {
     int dev = -1;
     hipError_t e = hipGetDevice(&dev);
@@ -598,12 +389,9 @@ hipError_t static_scratch(unsigned char** out, int* compute_units)
         e = hipGetSymbolAddress((void**)&ptr, HIP_SYMBOL(scratch));
         if (e != hipSuccess) return e;
         if (!ptr) return hipErrorInvalidSymbol;
-        e = hipDeviceGetAttribute(&compute_units_of_device[dev], hipDeviceAttributeMultiprocessorCount, dev);
-        if (e != hipSuccess) return e;
         scratch_of_device[dev] = ptr;
     }
     *out = scratch_of_device[dev];
-    *compute_units = compute_units_of_device[dev];
     return hipSuccess;
 }
 
@@ -627,18 +415,17 @@ extern "C" ps_status ps_drain_rows_mitigated(float* theta_dev, const float* grad
     if (!theta_dev || !grads_dev || (reinterpret_cast<uintptr_t>(theta_dev) & 15) || (reinterpret_cast<uintptr_t>(grads_dev) & 15))
         return static_fail(PS_EINVAL, "ps_drain_rows_mitigated: null or misaligned device pointer");
     unsigned char* base = nullptr;
-    int compute_units = 0;
-    if (static_scratch(&base, &compute_units) != hipSuccess)
+    if (static_scratch(&base) != hipSuccess)
         return static_fail(PS_EDEVICE, "ps_drain_rows_mitigated: the address of the static scratch array could not be resolved");
     float* scale = reinterpret_cast<float*>(base + STATIC_SCALE_OFF);
     float* partial = reinterpret_cast<float*>(base + STATIC_PART_OFF);
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     static Profiler no_timing;  // never enabled
-    // The row list, every partial sum and every clip factor of the rows in use are written before they are read.
-    HoldState* state = compute_units >= HOLD_BLOCKS ? reinterpret_cast<HoldState*>(base + STATIC_HOLD_OFF) : nullptr;
+    // Nothing in the array has to start at zero: the row list, every partial sum and every clip factor of the rows in
+    // use are written before they are read.
     const RowList rows{nullptr, 0, reinterpret_cast<int32_t*>(base + STATIC_IDX_OFF)};
     hipError_t e = pol->clip_norm > 0.f
-                       ? launch_apply_clipped(theta_dev, grads_dev, rows, n_rows, lr, mode, pol->clip_norm, partial, scale, state, s, no_timing)
+                       ? launch_apply_clipped(theta_dev, grads_dev, rows, n_rows, lr, mode, pol->clip_norm, partial, scale, s, no_timing)
                        : launch_apply(theta_dev, grads_dev, rows, n_rows, lr, mode, s, no_timing);
     if (e != hipSuccess) return static_fail(PS_EDEVICE, hipGetErrorString(e));
     return PS_OK;

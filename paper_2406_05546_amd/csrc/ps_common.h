@@ -183,19 +183,13 @@ hipError_t launch_apply(float* theta, const float* queue, const RowList& rows, i
                         const uint32_t* K_dev = nullptr);
 
 // Same with every gradient first scaled by min(1, clip / ||g||_2): a norm pass, then the apply pass.
-// With `state` (on a GPU of HOLD_BLOCKS compute units or more; zero in the beginning) up to HOLD_MAX_ROWS rows take one pass.
-constexpr int HOLD_BLOCKS = 256, HOLD_MAX_ROWS = 112, HOLD_COUNTERS = 16;
-struct HoldState {
-    unsigned long long arrived[HOLD_COUNTERS][16];  // [.][0]: blocks of all such launches so far, by their number mod HOLD_COUNTERS
-    int32_t done[HOLD_BLOCKS];                      // whether a block of the last one has applied its columns
-};
 hipError_t launch_apply_clipped(float* theta, const float* queue, const RowList& rows, int K, float lr, int mode, float clip,
-                                float* partial_dev, float* scale_dev, HoldState* state, hipStream_t s, Profiler& prof);
-uint64_t norm_partials(uint64_t rows);  // floats at partial_dev for up to this many rows
+                                float* partial_dev, float* scale_dev, hipStream_t s, Profiler& prof);
+int norm_slices();
 
 // Device address, on the current GPU, of the library's fixed scratch array (used by the drain entry point
-// that allocates nothing), and the GPU's number of compute units; resolved on first use per device.
-hipError_t static_scratch(unsigned char** out, int* compute_units);
+// that allocates nothing); resolved on first use per device.
+hipError_t static_scratch(unsigned char** out);
 const char* static_last_error();
 
 // ring[slot_j] -= lr * queue[q_j] for n (slot, q) pairs with distinct slots (pairs_dev: 2n int32).
