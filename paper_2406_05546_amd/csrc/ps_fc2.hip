@@ -217,8 +217,10 @@ __global__ __launch_bounds__(256, 2) void fc2_kernel(WorkerBuffers wb)
 }
 
 // Inference head (no dropout, no backward): logits, predicted class (lowest index on ties; 0 if its logit is NaN), per-image
-// cross-entropy and whether the prediction equals the label.  The logits of 16 images as above, operands straight from memory; then
-// wavefront v has image 4q + v of lane quarter q, a class to a lane.  A wavefront for an image, which read W4 again for each,
+// cross-entropy and whether the prediction equals the label.  The logits of 16 images as above, operands straight from memory, but
+// summed in eights (two matrix instructions) and those in a tree: off by 0.84e-7 of the root of the products' squares, where a chain
+// of 128 to a wavefront is off by 2.07e-7, in the same time.
+// Then wavefront v has image 4q + v of lane quarter q, a class to a lane.  A wavefront for an image, which read W4 again for each,
 // took 12.1 us for 8,192 images, four images to a wavefront with W4 in registers 11.3; their activations alone take 3.
 __global__ __launch_bounds__(256) void fc2_eval_kernel(WorkerBuffers wb, int groups, float* __restrict__ loss_i, int32_t* __restrict__ correct)
 {
@@ -236,17 +238,21 @@ __global__ __launch_bounds__(256) void fc2_eval_kernel(WorkerBuffers wb, int gro
     }
     const float b4 = theta[OFF_B4 + min(l16, NCLS - 1)];
     const int image = 4 * q + wave, label = wb.y[g0 + min(image, valid - 1)];
-    floatx4 zacc = {0.f, 0.f, 0.f, 0.f};
+    const floatx4 none = {0.f, 0.f, 0.f, 0.f};
+    const auto pair = [&](int j, int e) __attribute__((always_inline)) {
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(a[j][e + 1], wa[j][e + 1], __builtin_amdgcn_mfma_f32_16x16x4f32(a[j][e], wa[j][e], none, 0, 0, 0), 0, 0, 0);
+    };
+    floatx4 zsum[8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j)
+    for (int j = 0; j < 8; ++j) zsum[j] = pair(j, 0) + pair(j, 2);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) zacc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j][e], wa[j][e], zacc, 0, 0, 0);
-    *reinterpret_cast<floatx4*>(zpart + (wave * 64 + lane) * 4) = zacc;
+    for (int half = 4; half > 0; half /= 2)
+#pragma unroll
+        for (int j = 0; j < half; ++j) zsum[j] += zsum[j + half];
+    *reinterpret_cast<floatx4*>(zpart + (wave * 64 + lane) * 4) = zsum[0];
     __syncthreads();
-    float z = zpart[lane * 4 + wave];
-#pragma unroll
-    for (int v = 1; v < 4; ++v) z += zpart[(v * 64 + lane) * 4 + wave];
-    z += b4;
+    const auto part = [&](int v) { return zpart[(v * 64 + lane) * 4 + wave]; };
+    const float z = ((part(0) + part(1)) + (part(2) + part(3))) + b4;
     const auto sum = [](float x, float y) { return x + y; };
     const bool nan = row16_reduce(l16 == 0 && z != z ? 1.f : 0.f, sum) > 0.f;
     float zmax = row16_reduce(cls_ok ? z : -INFINITY, [](float x, float y) { return fmaxf(x, y); });

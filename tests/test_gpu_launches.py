@@ -66,6 +66,42 @@ def test_evaluation_of_odd_numbers_of_images(ps, n, B):
         ps.ps_destroy(ctx)
 
 
+def test_logits_of_an_evaluation(ps):
+    """A logit is 512 products, summed in eights and those in a tree: its error over a thousand draws is that of the same sums
+    formed here in 32 bits.  (Both are known to 1 part in 45; a chain of 128 to each wavefront has 2.4 times the error.)"""
+    import torch
+    N = 1000
+    rng = np.random.default_rng(3)
+    h = np.abs(rng.standard_normal((N, 512))).astype(np.float32)
+    w = (1000 * rng.uniform(-1, 1, (N, 512)) * (6 / 512) ** 0.5).astype(np.float32)
+    products = h.astype(np.float64) * w
+    w *= np.where(products.sum(1) < 0, -1, 1).astype(np.float32)[:, None]
+    exact, size = np.abs(products.sum(1)), np.sqrt((products ** 2).sum(1))
+    part = np.zeros((N, 64), np.float32)
+    for j in range(8):
+        part = (h[:, 64 * j:64 * j + 64].astype(np.float64) * w[:, 64 * j:64 * j + 64] + part).astype(np.float32)
+    while part.shape[1] > 1:
+        part = part[:, :part.shape[1] // 2] + part[:, part.shape[1] // 2:]
+    ctx = ps.ps_init(ps.make_config(1, 1, 1, 1, DROP_SEED, P_DROP))
+    try:
+        # fc1 without weights gives its biases, and the loss of class 1, whose logit is 0, is the logit of class 0
+        ps.ps_set_weights(ctx, np.zeros(ps.P, np.float32))
+        theta = ctx.workspace.view(torch.float32)[:ps.P]
+        x, y = torch.zeros(1, ps.IMAGE_PIXELS, device="cuda"), torch.ones(1, device="cuda", dtype=torch.int32)
+        hd, wd, got = torch.from_numpy(h).cuda(), torch.from_numpy(w).cuda(), np.empty(N)
+        for i in range(N):
+            theta[807616:808128] = hd[i]
+            theta[808128:808640] = wd[i]
+            got[i] = ps.ps_evaluate(ctx, -1, x, y)[0]
+    finally:
+        ps.ps_destroy(ctx)
+    sure = exact > 30  # or the other classes' exp does not vanish
+    assert sure.mean() > 0.95
+    off, bound = (float(np.sqrt((((v - exact) / size)[sure] ** 2).mean())) for v in (got, part[:, 0].astype(np.float64)))
+    print(f"error {off:.2e}, in 32 bits here {bound:.2e}")
+    assert off <= 1.1 * bound
+
+
 def test_evaluation_of_nan(ps):
     """Weights that are all NaN predict class 0, with a loss that is not a number."""
     import torch
