@@ -167,10 +167,12 @@ __device__ __forceinline__ floatx4 gemm_operand4(const float* __restrict__ base,
 }
 
 // The sums `which` of a 32x32 tile at (m0, n0), for which the split does not hold (ps_split.h), formed again with fp32 matrix
-// instructions, whose registers lie as those of the bf16 ones do.  Operands come straight from memory, 32 k ahead, so it takes
+// instructions, whose registers lie as those of the bf16 ones do.  Operands come straight from memory, so it takes
 // about four times as long as the tile did, unless the sums turn out NaN anyway: a network of NaN weights is not
 // slowed down by more than that first look.
-template <bool A_KC, bool B_KC, class Epi>
+// EARLY: 32 k ahead.  Tiny weights, forward of 2 x 32 66.2 -> 51.1 us, of 64 x 128 279 -> 267.  Not in gemm_block, whose launches
+// that have nothing to form again it slows down: input gradient of 8 x 176 29.0 -> 30.4 us, of the whole range 5 to 16 x 65 to 512 3-5 %.
+template <bool A_KC, bool B_KC, bool EARLY, class Epi>
 __device__ __forceinline__ void gemm_again(const GemmShape& sh, const Epi& epi, int z, int m0, int n0, int lane, uint32_t which, floatx16& sums)
 {
     lane = rarely(lane);
@@ -189,19 +191,25 @@ __device__ __forceinline__ void gemm_again(const GemmShape& sh, const Epi& epi, 
             b[i] = gemm_operand4<B_KC>(B, sh.ldb, col, k, sh.K);
         }
     };
-    load(0);
+    if (EARLY) load(0);
 #pragma unroll 1
     for (int k0 = 0; k0 < sh.K; k0 += 32) {
         floatx4 x[4], y[4];
+        if (EARLY) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            x[i] = a[i];
-            y[i] = b[i];
+            for (int i = 0; i < 4; ++i) {
+                x[i] = a[i];
+                y[i] = b[i];
+            }
+            load(k0 + 32);
         }
-        load(k0 + 32);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            if (k0 + 8 * i >= sh.K) break;
+            if (k0 + 8 * i >= sh.K) break;  // K is a multiple of 8, or the operands read as zero past it
+            if (!EARLY) {
+                x[i] = gemm_operand4<A_KC>(A, sh.lda, row, k0 + 8 * i + 4 * h, sh.K);
+                y[i] = gemm_operand4<B_KC>(B, sh.ldb, col, k0 + 8 * i + 4 * h, sh.K);
+            }
 #pragma unroll
             for (int j = 0; j < 4; ++j) again = __builtin_amdgcn_mfma_f32_32x32x2f32(x[i][j], y[i][j], again, 0, 0, 0);
         }
@@ -213,11 +221,11 @@ __device__ __forceinline__ void gemm_again(const GemmShape& sh, const Epi& epi, 
 }
 
 // Stores one 32x32 tile of sums at (m0, n0): register i of lane (h, l32) is row 8*(i/4) + 4*h + i%4, column l32.
-template <bool A_KC, bool B_KC, class Epi>
+template <bool A_KC, bool B_KC, bool EARLY, class Epi>
 __device__ __forceinline__ void gemm_finish(const GemmShape& sh, const Epi& epi, int z, int m0, int n0, int lane, floatx16 sums)
 {
     constexpr int G = A_KC || B_KC ? 4 : 16;  // as gemm_split_chunks looks at them, where that may have the same sums to form
-    if (any_lost<16, G>(sums)) gemm_again<A_KC, B_KC>(sh, epi, z, m0, n0, lane, lost_sums<16, G>(sums), sums);
+    if (any_lost<16, G>(sums)) gemm_again<A_KC, B_KC, EARLY>(sh, epi, z, m0, n0, lane, lost_sums<16, G>(sums), sums);
     const int n = n0 + (lane & 31);
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
@@ -351,7 +359,7 @@ __device__ __forceinline__ void gemm_block(const GemmShape& sh, const Epi& epi, 
     for (int a = 0; a < TM; ++a)
 #pragma unroll
         for (int b = 0; b < TN; ++b)
-            gemm_finish<Cfg::A_KC, Cfg::B_KC>(sh, epi, z, m0 + (wm * TM + a) * 32, n0 + (wn * TN + b) * 32, lane, CHUNK > 0 ? total[a][b] : acc[a][b].value());
+            gemm_finish<Cfg::A_KC, Cfg::B_KC, false>(sh, epi, z, m0 + (wm * TM + a) * 32, n0 + (wn * TN + b) * 32, lane, CHUNK > 0 ? total[a][b] : acc[a][b].value());
 }
 
 // One block's tile with eight wavefronts, two to a SIMD: four form the sum over the first half of the contraction, the others
@@ -475,7 +483,7 @@ __device__ __forceinline__ void gemm_sides_block(const GemmShape& sh, const Epi&
             floatx16 x = acc[a][b].value();
 #pragma unroll
             for (int i = 0; i < 16; ++i) x[i] += meet[half][wave][SHARED ? a % (TM / 2) : a][b][i][lane];
-            gemm_finish<Cfg::A_KC, Cfg::B_KC>(sh, epi, z, m0 + (wm * TM + a) * 32, n0 + (wn * TN + b) * 32, lane, x);
+            gemm_finish<Cfg::A_KC, Cfg::B_KC, true>(sh, epi, z, m0 + (wm * TM + a) * 32, n0 + (wn * TN + b) * 32, lane, x);
         }
 }
 
@@ -633,7 +641,7 @@ __global__ __launch_bounds__(64 * CHUNKS, NT == 1 ? 4 : CHUNKS == 4 ? 3 : 2) voi
 #pragma unroll
             for (int g = 0; g < 4; ++g) all |= which[j][g][lane] << (4 * g);
             floatx16 x;
-            gemm_again<A_KC, B_KC>(sh, epi, z, m0, n0 + 32 * j, lane, all, x);
+            gemm_again<A_KC, B_KC, true>(sh, epi, z, m0, n0 + 32 * j, lane, all, x);
 #pragma unroll
             for (int i = 0; i < 16; ++i) sums[j][i][lane] = x[i];
         }
@@ -786,7 +794,7 @@ __global__ __launch_bounds__(64 * PARTS * (T * T + roles_bring(T))) void gemm_sp
     for (int p = 1; p < PARTS; ++p)
 #pragma unroll
         for (int i = 0; i < 16; ++i) sums[i] += meet[p][i][lane];
-    gemm_finish<A_KC, B_KC>(sh, epi, z, m0 + 32 * mt, n0 + 32 * nt, lane, sums);
+    gemm_finish<A_KC, B_KC, true>(sh, epi, z, m0 + 32 * mt, n0 + 32 * nt, lane, sums);
 }
 
 // Whether a launch over this many 128 x 128 tiles leaves compute units idle.
@@ -900,7 +908,7 @@ __global__ __launch_bounds__(256, 2) void gemm_split_parts(GemmShape sh, Epi epi
 #pragma unroll
                 for (int k = 0; k < 4; ++k) x[4 * g + k] += first[k];
             }
-            gemm_finish<Cfg::A_KC, Cfg::B_KC>(sh, epi, z, m0 + (wm * TM + a) * 32, n0 + (wn * TN + b) * 32, lane, x);
+            gemm_finish<Cfg::A_KC, Cfg::B_KC, true>(sh, epi, z, m0 + (wm * TM + a) * 32, n0 + (wn * TN + b) * 32, lane, x);
         }
 }
 
