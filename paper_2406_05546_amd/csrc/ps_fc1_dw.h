@@ -58,14 +58,17 @@ typedef GemmCfg<false, false, 1, 1, 4, 1, 2> Fc1DwEdge;
 //
 // Alone, a wide tile of a short contraction is what it takes to bring the first stages and to store, and two blocks of a compute
 // unit leave much of that uncovered; of 64 x 128 tiles, which need two thirds of the registers, there are three.  Long
-// contractions pay for splitting operands more often, and many workers for stores in step, which edge blocks among the wide ones
-// put out of it (among the narrow ones they gain nothing: 64 of 128 95, 250 of 250 741).  The launch alone, us, events included;
-// 128 x 64 instead of 64 x 128 is up to 4 % behind:
-//   workers x images   43x40  250x3  250x16  250x64  64x96  250x96  250x100  64x128  100x128  160x128  200x128  64x192  80x200  43x250  250x250
-//   128 x 128           48.0  171.6   168.7   260.1   84.6   344.0    385.2   100.5    150.8    243.4    347.7   134.2   177.9   116.0    704.5
-//   64 x 128            42.5  149.8   149.5   235.6   77.0   345.5    395.8    94.7    146.8    239.0    354.2   129.5   181.0   118.5    742.0
+// contractions pay for splitting operands more often, and launches of many images for reading them more often, once their operands,
+// 8,320 bytes an image, outgrow the last-level cache (edge blocks among the narrow tiles gain nothing: 64 of 128 95, 250 of 250 741).  The
+// launch alone, us, events included; 128 x 64 instead of 64 x 128 is up to 4 % behind:
+//   workers x images   43x40  250x3  250x64  500x40  64x96  340x64  240x96  256x96  350x64  400x64  600x64  1000x24
+//   128 x 128           48.0  171.6   260.1   432.8   84.6   337.3   321.2   365.1   386.1   499.3   753.0    927.2
+//   64 x 128            42.5  149.8   235.6   387.4   77.0   310.9   319.5   366.3   387.1   521.4   799.0    984.8
+//   workers x images   64x128  100x128  160x128  176x128  200x112  225x100  250x100  190x128  200x128  64x192  80x200  43x250  250x250
+//   128 x 128           100.5    150.8    243.4    269.5    276.0    318.4    385.2    317.1    347.7   134.2   177.9   116.0    704.5
+//   64 x 128             94.7    146.8    239.0    260.6    259.8    302.7    395.8    319.1    354.2   129.5   181.0   118.5    742.0
 typedef GemmCfg<false, false, 1, 2, 2, 2, 2> Fc1DwShort;
-inline bool fc1_dw_short(const WorkerBuffers& wb) { return wb.B <= 96 || (wb.B <= 128 && FC1 / 128 * (FEAT_WIDE / 128) * wb.n <= 30 * wb.compute_units); }
+inline bool fc1_dw_short(const WorkerBuffers& wb) { return wb.B <= 128 && wb.n * wb.B <= 22500; }
 typedef GemmCfg<false, false, 2, 1, 2, 2, 2> Fc1DwFew;
 typedef Fc1DwMain Fc1DwSeveral;
 enum Fc1DwWhere { FC1_DW_FEW, FC1_DW_SEVERAL, FC1_DW_ALONE };

@@ -305,7 +305,8 @@ def test_fc1_weight_gradient_tiles(ps, n, B):
 
 
 # both sides of the lines between 64 x 128 and 128 x 128 tiles in a launch of their own; whole stages and a remainder
-@pytest.mark.parametrize("n,B", [(43, 1), (43, 17), (170, 96), (170, 97), (160, 97), (160, 128), (161, 128), (43, 128), (43, 129)])
+@pytest.mark.parametrize("n,B", [(43, 1), (43, 17), (170, 96), (170, 97), (160, 97), (160, 128), (161, 128), (43, 128), (43, 129),
+                                 (175, 128), (176, 128), (234, 96), (235, 96)])
 def test_fc1_weight_gradient_alone(ps, n, B):
     """A sum's order depends on the batch alone: the same bytes as next to conv2's gradients, in 128 x 64 tiles, which are held
     to 64 bits above."""
