@@ -70,15 +70,19 @@ static_assert(FWD_CHUNKS * FWD_CHUNK * GEMM_K == P2_SIZE && DX_CHUNKS * DX_CHUNK
 
 // forward: rows = 512 units (W3, k-contiguous), columns = the worker's samples (pool2, k-contiguous)
 // Beyond batches of 64, by how many tiles find a compute unit (the launch alone, us; all of K in one part: 1 x 256 23.7, 8 x 128
-// 39.8, 32 x 128 53.6, 48 x 128 74.3, 64 x 128 87.0):
-//   workers x images    1x256   8x128  16x128  16x200  24x80  32x128  24x200  40x128  48x128  56x128  64x128  72x128  256x256
-//   32 x 32, roles       18.0
-//   64 x 64, side by side        26.5    29.5    48.1   43.1    49.9    68.9    67.5    71.9    88.8
-//   128 x 128, side by side      59.2    59.4    59.5   59.1    60.3    62.3    61.0    64.3    69.5    75.6   128.1    587.9
-//   128 x 128, parts in turn                                                                            85.9   112.0    528.0
+// 39.8, 21 x 129 50.5, 32 x 128 53.6, 48 x 128 74.3, 64 x 128 87.0, 33 x 176 106.4).  64 x 64 tiles come two to a compute unit, and where there are
+// more 128 x 128 tiles than compute units, two rounds of them are ahead of those, whose second half of the batch may be empty:
+//   workers x images          1x256   8x128  16x128  21x129  24x80  32x128  22x129  24x200  40x128  56x128  64x128
+//   32 x 32, roles              18.0
+//   64 x 64, side by side               26.5    29.5    48.3   43.1    49.9    64.7    68.9    67.5    88.8
+//   128 x 128, side by side             59.2    59.4    64.8   59.1    60.3    65.3    62.3    61.0    69.5    75.6
+//   workers x images         33x129  33x176  25x320  42x160  43x192  72x128  256x256
+//   64 x 64, side by side      83.8    87.2    94.2    91.3   110.1
+//   128 x 128, side by side   121.7   125.8   128.2   124.1   128.1   128.1    587.9
+//   128 x 128, parts in turn  112.7   114.2   117.5   116.6   118.0   112.0    528.0
 void launch_fc1_fwd(const WorkerBuffers& wb, hipStream_t s)
 {
-    const int wide_tiles = FC1 / 128 * ((wb.B + 127) / 128) * wb.n;
+    const int wide_tiles = FC1 / 128 * ((wb.B + 127) / 128) * wb.n, square_tiles = FC1 / 64 * ((wb.B + 63) / 64) * wb.n;
     const Fc1FwdEpi epi{wb};
     if (wb.B <= CHUNKED_BATCH) {
         const int tiles = FC1 / 32 * wb.n;  // of a worker's samples 32 or 64 at a time
@@ -89,7 +93,7 @@ void launch_fc1_fwd(const WorkerBuffers& wb, hipStream_t s)
             gemm_launch<GemmCfg<true, true, 2, 1, 2, 2, 2>, FWD_CHUNK, 2>(FC1, wb.B, P2_SIZE, P2_SIZE, P2_SIZE, wb.n, epi, s);
     } else if (gemm_roles_fit<1>(FC1, wb.B, wb.n, wb.compute_units)) {
         gemm_launch_roles<true, true, 2, 1>(FC1, wb.B, P2_SIZE, P2_SIZE, P2_SIZE, wb.n, epi, s);
-    } else if (2 * wide_tiles <= wb.compute_units) {  // 64 x 64 tiles: two for a compute unit at most
+    } else if (square_tiles <= (wide_tiles > wb.compute_units ? 4 : 2) * wb.compute_units) {
         gemm_launch_sides<GemmCfg<true, true, 1, 1, 2, 2, 4>>(FC1, wb.B, P2_SIZE, P2_SIZE, P2_SIZE, wb.n, epi, s);
     } else if (wide_tiles <= wb.compute_units) {
         gemm_launch_sides<GemmCfg<true, true, 2, 2, 2, 2, 2>>(FC1, wb.B, P2_SIZE, P2_SIZE, P2_SIZE, wb.n, epi, s);

@@ -232,10 +232,11 @@ def test_images_of_a_wavefront(ps, n, B):
 
 
 # fc1's forward pass and input gradient on both sides of the lines between their forms.  Batches up to 64: 32 x 32, 32 x 64 and
-# 128 x 64 tiles; beyond: 32 x 32 tiles, 64 x 64, and 128 x 128 with either half of the forward sums side by side or one after the
+# 128 x 64 tiles; beyond: 32 x 32 tiles, 64 x 64 (up to 512, or up to 1,024 instead of more than 256 wide ones), and 128 x 128 with either half of the forward sums side by side or one after the
 # other, and 64 x 64 ones of the input gradient with wavefronts that only multiply.  Whole tiles and remainders down to a column.
 @pytest.mark.parametrize("n,B", [(1, 1), (6, 64), (7, 33), (9, 64), (17, 64), (64, 32), (64, 33), (63, 64), (107, 40),
-                                 (1, 65), (1, 512), (1, 640), (1, 641), (2, 130), (5, 128), (5, 129), (3, 193), (32, 100), (33, 97), (64, 128), (65, 90), (40, 257)])
+                                 (1, 65), (1, 512), (1, 640), (1, 641), (2, 130), (5, 128), (5, 129), (3, 193), (32, 100), (33, 97), (64, 128), (65, 90), (40, 257),
+                                 (21, 129), (22, 130), (33, 176), (43, 129)])
 def test_fc1_forms(ps, n, B):
     """Activations and gradients of every image within what an fp32 sum may be off, and with the same bytes when their worker is
     alone.  The partial sums of K terms of size 1 are sqrt(k) large, each rounded by 2^-24 / sqrt(3) of that, and the result is
@@ -274,6 +275,33 @@ def test_fc1_forms(ps, n, B):
                 np.testing.assert_array_equal(alone[k], seen[k])
     finally:
         ps.ps_destroy(ctx)
+
+
+def test_fc1_forward_of_a_ragged_batch(ps):
+    """Batches a little beyond 128 do not pay for an empty half of their tiles: 21 of 129, 504 tiles of 64 x 64, take no longer than
+    32 of 128, 512 (measured 48 and 50 us; in 128 x 128 tiles 60)."""
+    import torch
+    us = []
+    for n, B in ((21, 129), (32, 128)):
+        x = torch.rand(n, B, ps.IMAGE_PIXELS, device="cuda")
+        y = torch.zeros(n, B, device="cuda", dtype=torch.int32)
+        ctx = ps.ps_init(ps.make_config(n, B, 1, n, DROP_SEED, P_DROP))
+        try:
+            ps.ps_set_weights(ctx, synth.he_uniform_theta(5))
+            best = np.inf
+            for _ in range(6):
+                ps.ps_profile_enable(ctx, True)
+                for _ in range(10):
+                    ps.worker_grads_batched(ctx, range(n), [0] * n, [synth.minibatch_id(w, 0) for w in range(n)], x, y)
+                    ps.ps_drain_buffered(ctx, ps.DRAIN_SUM, 0.0)
+                ps.ps_sync(ctx)
+                ms, launches = ps.ps_profile_read(ctx)["gemm_split<Fc1FwdEpi>"]
+                best = min(best, 1e3 * ms / launches)
+            us.append(best)
+        finally:
+            ps.ps_destroy(ctx)
+    print(us)
+    assert us[0] <= 1.1 * us[1]
 
 
 # both sides of the lines between 128 x 64 and 128 x 128 tiles next to conv2's gradients, and between those and a launch of
