@@ -490,16 +490,18 @@ def _run(ps, theta, n, B, seed=17, labels=None, seen=None):
         ps.ps_sync(ctx)
         if seen is not None:
             seen.update(ps.ps_debug_last_activations(ctx, n - 1))
-        return _results(ps, ctx, n - 1, q[-1], theta, x[-1]), _results(ps, ctx, 0, q[0], synth.he_uniform_theta(5), x[0])
+        return _results(ps, ctx, n - 1, q[-1], theta, x[-1]), _results(ps, ctx, 0, q[0], synth.he_uniform_theta(5) if n > 1 else theta, x[0])
     finally:
         ps.ps_destroy(ctx)
 
 
 HUGE = np.float32(3.3999e38)  # finite, and infinite when rounded to 16 bits
 
-# launches of every form: images shared or not, fc1 in chunks, in one chain on tiles of every shape, its weight gradient
-# with conv2's (ragged or not) or by itself, conv2's weight gradient in shares or not
-FORMS = [(2, 16), (3, 33), (20, 40), (80, 40), (2, 130), (10, 130), (70, 130), (12, 65)]
+# launches of every form: images shared or not, fc1 in chunks on tiles of three shapes, its forward sums in halves and its input
+# gradient in one chain on tiles of every shape, its weight gradient with conv2's (ragged or not) or by itself, in wide tiles or
+# not, conv2's weight gradient in shares or not
+FORMS = [(2, 16), (3, 33), (20, 40), (80, 40), (2, 130), (10, 130), (70, 130), (12, 65), (1, 100), (12, 40), (107, 40), (5, 129), (40, 100),
+         (33, 176)]
 
 
 @pytest.mark.parametrize("n,B", FORMS)
@@ -591,12 +593,16 @@ def test_tiny_gradients_among_others(ps, n, B):
     _compare(broken, ("conv2 forward", "fc1 forward", "fc1 weight gradient", "conv2 input gradient", "conv2 weight gradient", "conv2 bias gradient"), 2.0 ** -100)
 
 
-@pytest.mark.parametrize("n,B", [(20, 40), (80, 40), (70, 130), (4, 256)])
+@pytest.mark.parametrize("n,B", [(20, 40), (80, 40), (70, 130), (4, 256), (12, 40), (107, 40), (5, 129), (40, 100), (33, 176)])
 @pytest.mark.parametrize("what", ["huge", "tiny", "some tiny"])
 def test_sums_formed_again_do_not_depend_on_the_launch(ps, n, B, what):
     """Which sums are lost, and what they are then, is decided by tiles that all forms of a launch share: conv1's, conv2's
-    and fc1's weight gradients of a worker have the same bytes alone and among n."""
+    and fc1's weight gradients, fc1's activations and input gradient of a worker have the same bytes alone and among n."""
     import torch
+
+    def layer(i):
+        return [v.copy().view(np.int32) for v in (ps.ps_debug_last_batch(ctx, i)["hdrop"], ps.ps_debug_last_activations(ctx, i)["dpool2"])]
+
     theta = synth.he_uniform_theta(5)
     g = torch.Generator(device="cuda")
     g.manual_seed(19)
@@ -616,9 +622,13 @@ def test_sums_formed_again_do_not_depend_on_the_launch(ps, n, B, what):
         ps.ps_set_weights(ctx, theta)
         mbs = [synth.minibatch_id(w, 7) for w in range(n)]
         entries = ps.worker_grads_batched(ctx, range(n), [0] * n, mbs, x, y)
+        ps.ps_sync(ctx)
+        layers = {i: layer(i) for i in (0, n - 1)}
         for i in (0, n - 1):
             (q,) = ps.worker_grads_batched(ctx, [i], [0], [mbs[i]], x[i:i + 1], y[i:i + 1])
             ps.ps_sync(ctx)
+            for a, b in zip(layers[i], layer(0)):
+                assert a.any() and np.array_equal(a, b)
             among, alone = ps.ps_get_grad(ctx, entries[i]), ps.ps_get_grad(ctx, q)
             assert among[:OFF_B3].any() and np.array_equal(among[:OFF_B3].view(np.int32), alone[:OFF_B3].view(np.int32))
             ps.ps_apply_async(ctx, q, 0.0)
