@@ -669,7 +669,7 @@ __global__ __launch_bounds__(64 * CHUNKS, NT == 1 ? 4 : CHUNKS == 4 ? 3 : 2) voi
 // waits 66 cycles for the one before, 330 to a step of 16, and up to 200 more where splits are issued on the same SIMD.
 // Forward of one worker of 256 images or four of 128: 64 x 64 tiles, whose wavefronts do everything, 38 us, in one part 24, in
 // two 18.  Input gradient, one part, of one of 100 15.4 -> 9.4 us, of two 15.4 -> 16.3.  T = 2, a multiplying wavefront on each
-// SIMD, input gradient of two of 100 to one of 512 16.6 -> 13.4 us (events included; with four that bring 15.2, and two such
+// SIMD, input gradient of two of 100 to one of 512 16.6 -> 13.4 us, of one of 640 and five of 128 17.3 -> 14.3 (events included; with four that bring 15.2, and two such
 // blocks to a compute unit, eight of 128, 25.6 against 21.3 in 64 x 64 tiles).  In two parts there is room for four of them to a part
 // only: forward of five to ten of 128 32.4 against 26.4 us side by side.
 constexpr int roles_bring(int T) { return 4 * T; }  // wavefronts of a part that bring operands; T * T multiply
@@ -690,7 +690,8 @@ __global__ __launch_bounds__(64 * PARTS * (T * T + roles_bring(T))) void gemm_sp
     if (v >= sh.gx * sh.gy * sh.gz) return;
     const int m0 = v % sh.gx * (32 * T), n0 = v / sh.gx % sh.gy * (32 * T), z = v / (sh.gx * sh.gy);
     const bool multiplies = wave < PARTS * MULT;
-    const int half = multiplies ? wave / MULT : (int)((uint32_t)(wave - PARTS * MULT) / BRING), bringer = (wave - PARTS * MULT) & (BRING - 1), t = (64 * bringer + lane) & (NT - 1);
+    const int half = multiplies ? wave / MULT : (int)((uint32_t)(wave - PARTS * MULT) / BRING);
+    const int bringer = (wave - PARTS * MULT) & (BRING - 1), t = (64 * bringer + lane) & (NT - 1);
     const int mt = wave & (T - 1), nt = wave / T & (T - 1);  // tile of a multiplying wavefront
     const int K = sh.K / PARTS, k_first = half * K, nk = (K + KS - 1) / KS, tail = (nk * KS - K) / GEMM_K;  // MFMA steps that the last stage repeats
 
@@ -818,8 +819,8 @@ __global__ __launch_bounds__(512, 2) void gemm_split_sides(GemmShape sh, Epi epi
 
 // The same sums for launches of many tiles: four wavefronts to a block, two blocks to a compute unit, which need not keep in
 // step, one half after the other.  The first half's sums, 64 a lane, wait in LDS (28) and in registers (36), for which loads run
-// one stage ahead instead of two.  256 workers of 256 images 558 us (all of K in one chain 557; 28, 20 and the rest in
-// the tile's own place in C 4 us more, all of them there 37 more; gemm_sides_block 38 more).
+// one stage ahead instead of two.  256 workers of 256 images 528 us (28, 20 and the rest in the tile's own place in C 4 us more, all
+// of them there 37 more; gemm_sides_block 60 more).
 template <class Cfg, class Epi>
 __global__ __launch_bounds__(256, 2) void gemm_split_parts(GemmShape sh, Epi epi)
 {
